@@ -102,7 +102,9 @@ int gp_kmv(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_
 /*
  * gp_kmv for callers that cannot allocate: code between hipStreamBeginCapture and
  * hipStreamEndCapture, serving loops that must never reach hipMalloc, harnesses that forbid it.
- * Same arguments, same kernels and bit-identical results as gp_kmv, but the scratch of the product
+ * Same arguments and kernels as gp_kmv, and bit-identical results as long as the partial images of gp_kmv's own
+ * column splits fit the scratch too (past that the column range is left whole, which only changes the order
+ * of the sums), but the scratch of the product
  * (column maxima, the packed images of V, column-split partial sums) is a file-scope device array
  * of GP_KMV_STATIC_SCRATCH_BYTES bytes that every GPU the library is used on holds until the
  * process ends, and the call reaches no hipMalloc, hipFree, stream synchronisation or memset

@@ -236,7 +236,7 @@ int gp_kmv_static(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut,
   int rc = kmv_check(ctx, "gp_kmv_static", dV, ldv, t, dOut, ldo);
   if (rc < 0) return rc;
   if (!ctx->static_scratch) return gp_fail(ctx, GP_ERR_HIP, "gp_kmv_static: the static scratch was not resolved on this device");
-  const size_t need = gp_kmv_scratch_bytes(ctx, t);
+  const size_t need = gp_kmv_least_scratch_bytes(ctx, t);
   if (need > (size_t)GP_KMV_STATIC_SCRATCH_BYTES)
     return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv_static: n = %lld, t = %d need %zu bytes of scratch, the static block holds %zu; use gp_kmv",
                    (long long)ctx->n, t, need, (size_t)GP_KMV_STATIC_SCRATCH_BYTES);

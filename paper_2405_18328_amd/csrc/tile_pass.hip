@@ -314,6 +314,13 @@ size_t gp_kmv_rect_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows) {
   return fp32_bytes > f16_bytes ? fp32_bytes : f16_bytes;
 }
 
+size_t gp_kmv_least_scratch_bytes(const gp_ctx* ctx, int t) {
+  KmvPlan pl = gp_plan_kmv(ctx, ctx->n);
+  const size_t fp32_bytes = pl.JS <= 1 ? 0 : (size_t)pl.JS * (size_t)ctx->n * (size_t)t * sizeof(float);
+  const size_t f16_bytes = gp_kmv_f16_least_scratch_bytes(ctx, t);
+  return fp32_bytes > f16_bytes ? fp32_bytes : f16_bytes;
+}
+
 size_t gp_kmv_scratch_bytes(const gp_ctx* ctx, int t) { return gp_kmv_rect_scratch_bytes(ctx, t, ctx->n); }
 
 // Scratch for a product over any column window of at most col_chunks chunks.  The number of column

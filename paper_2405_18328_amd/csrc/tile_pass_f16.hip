@@ -531,6 +531,13 @@ tileh_fn pick_h(int kind, int KH, int XP, int NT, int MI, int W) {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+struct KmvPlanH {
+  int MI;          // 32-row sub-tiles per wave
+  int W;           // wavefronts per workgroup
+  int row_blocks;
+  int JS, cps;     // column-range splits, chunks per split
+};
+
 struct ScratchH {
   size_t off_colmax, off_vy, off_vp, off_part, total;
 };
@@ -548,6 +555,36 @@ ScratchH scratch_layout(const gp_ctx* ctx, int t, int JS, int64_t rows) {
   return L;
 }
 
+// workgroups of four waves that share a compute unit: two (one wave per SIMD each), where their LDS rings fit
+int wgs_per_cu(int KH, int XP, int NT) {
+  const int G = XP * KH + 4 * NT, NS = G > 12 ? 3 : 4;
+  const size_t lds = (size_t)NS * (G * 64 + 8 * 4) * 16;
+  return 2 * align_up(lds, 1280) <= 160 * 1024 ? 2 : 1;
+}
+
+KmvPlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP) {
+  KmvPlanH pl;
+  const int64_t chunks = col_chunks > 0 ? col_chunks : (ctx->n + 31) / 32;
+  // two sub-tiles per wave halve the LDS operand traffic; past one k-step of distance operands the
+  // second sub-tile no longer fits the register file without spills
+  pl.MI = (ctx->KH == 1 && rows >= 8192) ? 2 : 1;
+  if (ctx->mi_forced) pl.MI = (ctx->mi_forced == 2 && ctx->KH <= 2) ? 2 : 1;   // tuning aid
+  pl.W = 4;   // 8-wave workgroups halve the L2-to-LDS traffic but measured no faster on MI355X
+  if (ctx->w_forced) pl.W = ctx->w_forced;                                      // tuning aid
+  const int rows_per_wg = 32 * pl.W * pl.MI;
+  pl.row_blocks = (int)((rows + rows_per_wg - 1) / rows_per_wg);
+  const int NT = (t > 1 && t % 32 == 1 ? t - 1 : t) > 32 ? 2 : 1;
+  const int slots = ctx->num_cu * (pl.W == 4 ? wgs_per_cu(ctx->KH, XP, NT) : 1);
+  // a partial image is written and read once, at about 4 TB/s; a chunk takes a workgroup about 1.2 us per sub-tile
+  const double image = (double)rows * t * sizeof(float);
+  int max_js = image * 3.0 > 2.0e9 ? (int)(2.0e9 / image) : 64;     // images past 2 GB would not pay for their memory
+  if (max_js < 1) max_js = 1;
+  if (max_js > 64) max_js = 64;
+  pl.JS = gp_column_splits(pl.row_blocks, chunks, slots, 2.0 * image / 4.0e12 / (1.2e-6 * pl.MI), max_js);
+  pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
+  return pl;
+}
+
 }  // namespace
 
 int gp_kh_bucket(int d, int kernel) {
@@ -560,28 +597,28 @@ int gp_kh_bucket(int d, int kernel) {
   return -1;
 }
 
-KmvPlan gp_plan_kmv_f16(const gp_ctx* ctx, int64_t rows, int64_t col_chunks) {
-  KmvPlan pl;
-  const int64_t chunks = col_chunks > 0 ? col_chunks : (ctx->n + 31) / 32;
-  // two sub-tiles per wave halve the LDS operand traffic; past one k-step of distance operands the
-  // second sub-tile no longer fits the register file without spills
-  pl.MI = (ctx->KH == 1 && rows >= 8192) ? 2 : 1;
-  if (ctx->mi_forced) pl.MI = (ctx->mi_forced == 2 && ctx->KH <= 2) ? 2 : 1;   // tuning aid
-  pl.W = 4;   // 8-wave workgroups halve the L2-to-LDS traffic but measured no faster on MI355X
-  if (ctx->w_forced) pl.W = ctx->w_forced;                                      // tuning aid
-  const int rows_per_wg = 32 * pl.W * pl.MI;
-  pl.row_blocks = (int)((rows + rows_per_wg - 1) / rows_per_wg);
-  const int target = 2 * ctx->num_cu;
-  int JS = 1;
-  if (pl.row_blocks < target) {
-    JS = (target + pl.row_blocks - 1) / pl.row_blocks;
-    const int64_t max_js = chunks / 4 > 0 ? chunks / 4 : 1;
-    if (JS > max_js) JS = (int)max_js;
-    if (JS > 64) JS = 64;
+// A launch runs in generations of `slots` workgroups, and a last generation of a few row blocks costs as much as a
+// full one: the time is about generations x (chunks per workgroup + what its prologue and flush cost), and
+// every further cut adds one partial image of the output to write and read (image_cost, in units of a
+// workgroup's chunk).  Measured on MI355X (n = 43945, d = 20, t = 17: 344 row blocks on 512 slots): two ranges
+// 946 us per product, SPLIT7.
+int gp_column_splits(int row_blocks, int64_t chunks, int slots, double image_cost, int max_splits) {
+  constexpr double FIXED = 4.0;       // prologue and flush of a workgroup, in chunks
+  constexpr int MIN_CHUNKS = 4;
+  int best = 1;
+  double best_cost = 1e300;
+  for (int js = 1; js <= max_splits; ++js) {
+    const int64_t cps = (chunks + js - 1) / js;
+    if (js > 1 && cps < MIN_CHUNKS) break;
+    const int parts = (int)((chunks + cps - 1) / cps);
+    const int64_t gens = ((int64_t)row_blocks * parts + slots - 1) / slots;
+    const double cost = (double)gens * ((double)cps + FIXED) + (parts > 1 ? image_cost * parts : 0.0);
+    if (cost < best_cost * (1.0 - 1e-9)) {
+      best_cost = cost;
+      best = parts;
+    }
   }
-  pl.cps = (int)((chunks + JS - 1) / JS);
-  pl.JS = (int)((chunks + pl.cps - 1) / pl.cps);
-  return pl;
+  return best;
 }
 
 int gp_launch_colmax(gp_ctx* ctx, const float* dV, int64_t ldv, int t, unsigned* cm, const float* dV2, int64_t ldv2,
@@ -601,16 +638,28 @@ int gp_launch_colmax(gp_ctx* ctx, const float* dV, int64_t ldv, int t, unsigned*
 }
 
 size_t gp_kmv_f16_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks) {
-  return scratch_layout(ctx, t, gp_plan_kmv_f16(ctx, rows, col_chunks).JS, rows).total;
+  size_t need = 0;
+  for (int XP = 2; XP <= 3; ++XP) {
+    const size_t b = scratch_layout(ctx, t, plan_h(ctx, rows, col_chunks, t, XP).JS, rows).total;
+    if (b > need) need = b;
+  }
+  return need;
 }
+
+size_t gp_kmv_f16_least_scratch_bytes(const gp_ctx* ctx, int t) { return scratch_layout(ctx, t, 1, ctx->n).total; }
 
 int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo, int add_noise,
                       void* scratch, size_t scratch_bytes, const unsigned* colmax_ready, const KmvRows* rows,
                       KmvDeferred* defer, const KmvWindow* win) {
   const int64_t nrows = rows ? rows->m : ctx->n;
   const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
-  const KmvPlan pl = gp_plan_kmv_f16(ctx, nrows, win ? win->nchunks : 0);
-  const ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
+  KmvPlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
+  ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
+  if (scratch_bytes < L.total) {    // no room for partial images (gp_kmv_static): the column range stays whole
+    pl.JS = 1;
+    pl.cps = win ? win->nchunks : (int)((ctx->n + 31) / 32);
+    L = scratch_layout(ctx, t, 1, nrows);
+  }
   if (scratch_bytes < L.total || !scratch)
     return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv: scratch %zu < %zu bytes", scratch_bytes, L.total);
   hipStream_t st = ctx->stream;
