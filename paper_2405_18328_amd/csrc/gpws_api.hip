@@ -84,9 +84,6 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
     else if (!strcmp(f, "f16x2")) ctx->path_forced = GP_PATH_F16X2;
     else if (!strcmp(f, "f16x3")) ctx->path_forced = GP_PATH_F16X3;
   }
-  // tuning aids of the tile pass, read once here and never in a launch path
-  if (const char* e = getenv("GPWS_MI")) ctx->mi_forced = atoi(e) == 2 ? 2 : 1;
-  if (const char* e = getenv("GPWS_W")) ctx->w_forced = atoi(e) == 8 ? 8 : 4;
   ctx->n_pad = (n + GP_ROW_ALIGN - 1) / GP_ROW_ALIGN * GP_ROW_ALIGN;
   ctx->stream = (hipStream_t)hip_stream;
   ctx->dX = dX;

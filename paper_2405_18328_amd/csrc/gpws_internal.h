@@ -65,8 +65,6 @@ struct gp_ctx {
   int XP;                 // pieces used per operand of the distance chain (2 or 3)
   int path;               // GP_PATH_* chosen by gp_set_theta
   int path_forced;        // -1, or a GP_PATH_* forced through the GPWS_PATH environment variable
-  int mi_forced;          // 0, or the sub-tiles per wave forced through GPWS_MI (tuning aid, read at gp_create)
-  int w_forced;           // 0, or the wavefronts per workgroup forced through GPWS_W (tuning aid, read at gp_create)
   bool f16_ok;            // false when d + 3 components do not fit the widest fp16 operand bucket (SE, d = 126)
   float max_norm;         // host copy of max_i |xs_i|^2
   double* dMean;          // d column means of X

@@ -72,23 +72,25 @@ __device__ __forceinline__ float minus_half(unsigned pk, float x) {
   return r;
 }
 
-// W wavefronts per workgroup: every workgroup streams all of V' and XA through its LDS, so the
-// L2-to-LDS traffic of a launch is inversely proportional to the rows a workgroup owns (32 MI W).
-template <int KIND, int KH, int XP, int NT, int MI, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void kmv_tile_f16_kernel(TileArgsH p) {
+// Two waves per SIMD with two software pipelines.  Four wavefronts per workgroup: every workgroup streams all
+// of V' and XA through its LDS, so the L2-to-LDS traffic of a launch is inversely proportional to the
+// rows a workgroup owns (128 MI; eight waves halve the traffic and measured no faster).
+template <int KIND, int KH, int XP, int NT, int MI, bool Y>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void kmv_tile_f16_kernel(TileArgsH p) {
   // One pipeline stage in LDS, in 16-byte units: G groups of 64 units (one wave-wide 16-byte load
   // each): XP*KH groups of XA pieces, then 4*NT groups of V' images; then one 8-unit y slot per wave.
+  constexpr int W = 4;
   constexpr int XA_G = XP * KH;
   constexpr int V_G = 4 * NT;
   constexpr int G = XA_G + V_G;
   constexpr int V_OFF = XA_G * 64;
   constexpr int V_U = V_G * 64;
   constexpr int VY_OFF = G * 64;
-  constexpr int STAGE = VY_OFF + 8 * W;
+  constexpr int STAGE = VY_OFF + (Y ? 8 * W : 0);
   constexpr int NS = G > 12 ? 3 : 4;               // stages: chunks up to ch + NS - 1 are in flight while ch is consumed
   constexpr int DEPTH = NS - 1;
   constexpr int LPW = (G + W - 1) / W;             // group loads per wave per chunk
-  constexpr int LPC = LPW + 1;                     // + the y slot
+  constexpr int LPC = LPW + (Y ? 1 : 0);           // + the y slot
   static_assert((DEPTH - 1) * LPC < 64, "vmcnt cannot express the pipeline depth");
   __shared__ u32x4 lds[NS][STAGE];
 
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const unsigned stage_off = (unsigned)((ch_target - c_begin) % NS) * (unsigned)(STAGE * 16);
 #pragma unroll
     for (int x = 0; x < LPW; ++x) dma16(g_src[x] + (int64_t)ch * g_stride[x], __builtin_amdgcn_readfirstlane(g_lds[x] + stage_off));
-    if (vy_lane) dma16(reinterpret_cast<const u32x4*>(p.VY + (int64_t)ch * 32) + lane, __builtin_amdgcn_readfirstlane(vy_lds + stage_off));
+    if (Y && vy_lane) dma16(reinterpret_cast<const u32x4*>(p.VY + (int64_t)ch * 32) + lane, __builtin_amdgcn_readfirstlane(vy_lds + stage_off));
   };
   // vmcnt <= (DEPTH-1)*LPC: everything but the newest DEPTH-1 chunks has landed (loads retire in order)
   constexpr int WAIT_N = (DEPTH - 1) * LPC;
@@ -237,10 +239,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         const float ex = __builtin_amdgcn_exp2f(fmaf(u, -LOG2E, (float)PHI_SHIFT));
         f[z] = fmaf(u, ex, ex);
       }
-      av = fmaf(f[z], vy[e >> 2][e & 3], av);
+      if (Y) av = fmaf(f[z], vy[e >> 2][e & 3], av);
     }
     // hi = f truncated to fp16 (both values in one conversion), lo = f - hi taken straight from the
-    // packed halves by the mixed-precision FMA, so the split costs two instructions per value
+    // packed halves by the mixed-precision FMA, so the split costs two instructions per value (its forms that
+    // write one fp16 half, one and a half instructions per value, measured 1 - 2 % slower)
     oh = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
     ol = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(minus_half<0>(oh, f[0]), minus_half<1>(oh, f[1])));
   };
@@ -260,7 +263,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(WAIT_N) : "memory");
     __syncthreads();
     distance(c_begin, S0);
-    load_vy(lds[0], 0, vy0);
+    if (Y) load_vy(lds[0], 0, vy0);
 #pragma unroll
     for (int e2 = 0; e2 < 4; ++e2) phi_pair(S0[0], 0, e2, vy0, accv[0], ph[e2], pl[e2]);
   };
@@ -283,9 +286,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         bl[mh][nt] = as_f16x8(s[V_OFF + ((mh * NT + nt) * 2 + 1) * 64 + lane]);
       }
     f32x4 vy1[2], vy0n[2];
-    load_vy(s, 1, vy1);
-    load_vy(s_next, 0, vy0n);
-    {   // past the last chunk the look-ahead group must not reach the y accumulator
+    if (Y) {
+      load_vy(s, 1, vy1);
+      load_vy(s_next, 0, vy0n);
+      // past the last chunk the look-ahead group must not reach the y accumulator
       const float keep = ch + 1 < c_end ? 1.0f : 0.0f;
       vy0n[0] *= keep;
       vy0n[1] *= keep;
@@ -320,8 +324,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         pl[e2] = nl[e2];
       }
     }
-    vy0[0] = vy0n[0];
-    vy0[1] = vy0n[1];
+    if (Y) {
+      vy0[0] = vy0n[0];
+      vy0[1] = vy0n[1];
+    }
   };
 
   // Writes what the accumulators hold to OUT (first: stores, adds the noise term once; later: adds to
@@ -357,7 +363,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
           acc[m][nt][r] = 0.0f;
         }
       }
-      if (p.vcol >= 0) {
+      if (Y) {
         const float tot = accv[m] + __shfl_xor(accv[m], 32);
         const int64_t i = ibase + li;
         if (h == 0 && i < p.n) {
@@ -380,6 +386,221 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     for (int ch = c_begin; ch < c_end; ch += 2) {
       chunk_body(ch, S0, S1);
       if (ch + 1 < c_end) chunk_body(ch + 1, S1, S0);
+    }
+    // no LDS write may be in flight, and no wave still reading, when the ring is refilled or released
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    flush(first);
+    first = false;
+    if (c_end >= r_end) break;
+    c_begin = c_end;
+    c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
+  }
+}
+
+// ---- four waves per SIMD ----------------------------------------------------------------------------
+// The same tile pass laid out for more waves instead of software pipelines: 128 registers hold one
+// sub-tile of 32 rows, and the other three waves of the SIMD are the pipeline.  Eight waves per workgroup
+// share a stage of two chunks in LDS, two stages deep, one barrier per two chunks.  NT = 0 is the product
+// with a single vector (the mean of a prediction): no contraction tiles at all, phi goes straight into one
+// FMA per pair, eight waves per SIMD.
+// What bounds it (SQ counters, n = 16384, d = 26, t = 65, Matern): the vector port 60 % and the matrix core
+// 48 % of the cycles; the stream of instructions alone, without LDS and barriers, 67 % and 54 %.
+// Measured against the two-wave kernel, same box: n = 16384 d = 26 t = 65 Matern 164 -> 160 us; n = 32768
+// d = 26 t = 65 SE 553 -> 516 us; one vector: n = 41157 d = 9 Matern 508 -> 409 us, n = 65536 d = 8 SE 892 -> 564 us.
+// With KH = 1 or NT = 1 the two-wave kernel with two sub-tiles per wave reads half the operands from LDS and stays ahead.
+constexpr int wide_waves(int KH, int XP, int NT) { return NT ? 4 : KH <= 2 ? 8 : XP * KH <= 16 ? 4 : 2; }   // per SIMD
+
+template <int KIND, int KH, int XP, int NT, bool Y>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(KH, XP, NT), wide_waves(KH, XP, NT)))) void kmv_tile_f16_wide_kernel(TileArgsH p) {
+  constexpr int W = 8;
+  constexpr int XA_G = XP * KH;                     // groups of 64 16-byte units per chunk
+  constexpr int V_G = 4 * NT;
+  constexpr int G = XA_G + V_G;
+  constexpr int V_OFF = XA_G * 64;                  // in units, inside a chunk
+  constexpr int CH_U = G * 64;                      // units per chunk
+  constexpr int VY_OFF = 2 * CH_U;                  // the two chunks' 32 y values each: 16 units
+  constexpr int STAGE = 2 * CH_U + (Y ? 16 : 0);
+  constexpr int LPW = (2 * G + W - 1) / W;          // group loads per wave and stage; surplus slots repeat the last group
+  __shared__ u32x4 lds[2][STAGE];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 5;
+  const int li = lane & 31;
+  const int js = blockIdx.x % p.JS;
+  const int rb = blockIdx.x / p.JS;
+  const int sub0 = rb * W + wave;
+  const int r_begin = js * p.cps;
+  const int r_end = min(p.nchunks, r_begin + p.cps);
+  int c_begin = r_begin;
+  int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
+
+  f16x8 xb[XP][KH];
+#pragma unroll
+  for (int pc = 0; pc < XP; ++pc)
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh) xb[pc][kh] = as_f16x8(p.XB[pc][((int64_t)sub0 * KH + kh) * 64 + lane]);
+
+  static_assert(NT > 0 || Y, "nothing to multiply");
+  f32x16 acc[NT > 0 ? NT : 1];
+  float accv[2] = {0.0f, 0.0f};
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[nt][r] = 0.0f;
+
+  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) void*)&lds[0][0];
+  const unsigned lane16 = lane * 16u;
+  // group g of a stage: chunk g / G, then XA pieces, then V' images; source = uniform base + 16 lane
+  auto dma16 = [](uint64_t base, unsigned off, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds_addr) : "memory", "m0");
+  };
+  auto issue_pair = [&](int ch0, int st) {
+#pragma unroll
+    for (int x = 0; x < LPW; ++x) {
+      const int g = min(wave + W * x, 2 * G - 1);
+      const int gc = g >= G ? g - G : g;
+      const int ch = min(g >= G ? ch0 + 1 : ch0, c_end - 1);     // past the end: harmless reload of the last chunk
+      const u32x4* src;
+      if (gc < XA_G) src = p.XA[gc / KH] + ((int64_t)ch * KH + gc % KH) * 64;
+      else src = p.VP + ((int64_t)ch * V_G + (gc - XA_G)) * 64;
+      dma16((uint64_t)src, lane16, lds_base + 16u * (unsigned)(st * STAGE + g * 64));
+    }
+    if (Y) {   // every wave fetches the same 256 bytes to the same place
+      const int ch = min(ch0 + (lane >> 3), c_end - 1);
+      if (lane < 16) dma16((uint64_t)p.VY, (unsigned)ch * 128u + (lane & 7) * 16u, lds_base + 16u * (unsigned)(st * STAGE + VY_OFF));
+    }
+  };
+
+  auto phi_pair = [&](float s0, float s1, const f32x4& vy, int q, unsigned& oh, unsigned& ol) {
+    float f[2];
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+      const float sv = z ? s1 : s0;
+      if (KIND == GP_SE_ARD) {
+        f[z] = __builtin_amdgcn_exp2f(sv);
+      } else {
+        const float u = __builtin_amdgcn_sqrtf(__builtin_fabsf(sv));
+        const float ex = __builtin_amdgcn_exp2f(fmaf(u, -LOG2E, (float)PHI_SHIFT));
+        f[z] = fmaf(u, ex, ex);
+      }
+      if (Y) accv[z] = fmaf(f[z], vy[q + z], accv[z]);
+    }
+    if constexpr (NT > 0) {
+      oh = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
+      ol = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(minus_half<0>(oh, f[0]), minus_half<1>(oh, f[1])));
+    }
+  };
+
+  auto chunk = [&](int ch, const u32x4* s, const u32x4* sy) {
+    f32x16 S;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) S[r] = 0.0f;
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh) {
+      f16x8 xa[XP];
+#pragma unroll
+      for (int pc = 0; pc < XP; ++pc) xa[pc] = as_f16x8(s[(pc * KH + kh) * 64 + lane]);
+      // smallest terms first
+      if constexpr (XP == 3) {
+        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[1], xb[1][kh], S, 0, 0, 0);
+        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[2], xb[0][kh], S, 0, 0, 0);
+        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[0], xb[XP - 1][kh], S, 0, 0, 0);
+      }
+      S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[1], xb[0][kh], S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[0], xb[1][kh], S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[0], xb[0][kh], S, 0, 0, 0);
+    }
+    if (p.diag && ch == sub0) {
+      asm volatile("" ::: "memory");
+      const float s0 = KIND == GP_SE_ARD ? (float)PHI_SHIFT : 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r >> 2) + 4 * h + (r & 3) == li) S[r] = s0;
+    }
+#pragma unroll
+    for (int mh = 0; mh < 2; ++mh) {
+      u32x4 ph, pl;
+      f32x4 vy[2];
+      if (Y) {
+#pragma unroll
+        for (int g2 = 0; g2 < 2; ++g2) vy[g2] = __builtin_bit_cast(f32x4, sy[2 * (2 * mh + g2) + h]);
+      }
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        unsigned oh = 0, ol = 0;
+        phi_pair(S[8 * mh + 2 * e2], S[8 * mh + 2 * e2 + 1], vy[e2 >> 1], 2 * (e2 & 1), oh, ol);
+        ph[e2] = oh;
+        pl[e2] = ol;
+      }
+      if constexpr (NT > 0) {
+      const f16x8 ah = as_f16x8(ph), al = as_f16x8(pl);
+      f16x8 bh[NT], bl[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        bh[nt] = as_f16x8(s[V_OFF + ((mh * NT + nt) * 2 + 0) * 64 + lane]);
+        bl[nt] = as_f16x8(s[V_OFF + ((mh * NT + nt) * 2 + 1) * 64 + lane]);
+      }
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[nt], acc[nt], 0, 0, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[nt], acc[nt], 0, 0, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[nt], acc[nt], 0, 0, 0);
+      }
+    }
+  };
+
+  float* out = p.OUT + (int64_t)js * p.split_stride;
+  auto flush = [&](bool first) {
+    const bool noise = first && p.add_noise && js == 0;
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    const int64_t ibase = (int64_t)sub0 * 32 + zero;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int c = li + 32 * nt;
+      const float oscale = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(c, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t i = ibase + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (i < p.n && c < p.ncols) {
+          float v = oscale * acc[nt][r];
+          if (noise) v = fmaf(p.sigma2, p.V[i * p.ldv + p.col0 + c], v);
+          if (!first) v += out[i * p.ldo + p.col0 + c];
+          out[i * p.ldo + p.col0 + c] = v;
+        }
+        acc[nt][r] = 0.0f;
+      }
+    }
+    if (Y) {
+      const float both = accv[0] + accv[1];
+      const float tot = both + __shfl_xor(both, 32);
+      const int64_t i = ibase + li;
+      if (h == 0 && i < p.n) {
+        float v = p.a2 * ldexpf(1.0f, -PHI_SHIFT) * tot;
+        if (noise) v = fmaf(p.sigma2, p.V[i * p.ldv + p.vcol], v);
+        if (!first) v += out[i * p.ldo + p.vcol];
+        out[i * p.ldo + p.vcol] = v;
+      }
+      accv[0] = accv[1] = 0.0f;
+    }
+  };
+
+  bool first = true;
+  for (;;) {
+    int st = 0;
+    issue_pair(c_begin, 0);
+    for (int ch = c_begin; ch < c_end; ch += 2) {
+      asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+      __syncthreads();              // this stage is complete in LDS, every wave is done with the other one
+      issue_pair(ch + 2, st ^ 1);
+      const u32x4* s = lds[st];
+      chunk(ch, s, s + VY_OFF);
+      if (ch + 1 < c_end) chunk(ch + 1, s + CH_U, s + VY_OFF + 8);
+      st ^= 1;
     }
     // no LDS write may be in flight, and no wave still reading, when the ring is refilled or released
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
@@ -501,42 +722,89 @@ __global__ void kmv_reduce_f16_kernel(const float* __restrict__ part, int64_t sp
 
 typedef void (*tileh_fn)(TileArgsH);
 
-template <int KIND, int KH, int XP>
-tileh_fn pick_h_nt_mi(int NT, int MI, int W) {
-  if constexpr (KH <= 2) {
-    if (MI == 2 && W == 8) return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, 8> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, 8>;
-    if (MI == 2) return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, 4> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, 4>;
+template <int KIND, int KH, int XP, bool Y>
+tileh_fn pick_h_nt_mi(int NT, int MI) {
+  if constexpr (KH == 1) {
+    if (MI == 2) return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, Y> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, Y>;
   }
-  if (W == 8) return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 1, 8> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 1, 8>;
-  return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 1, 4> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 1, 4>;
+  if constexpr (KH == 2) {
+    if (MI == 2 && NT == 1) return kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, Y>;
+  }
+  return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 1, Y> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 1, Y>;
 }
 
-template <int KIND, int XP>
-tileh_fn pick_h_kh(int KH, int NT, int MI, int W) {
+template <int KIND, int XP, bool Y>
+tileh_fn pick_h_kh(int KH, int NT, int MI) {
   switch (KH) {
-    case 1: return pick_h_nt_mi<KIND, 1, XP>(NT, MI, W);
-    case 2: return pick_h_nt_mi<KIND, 2, XP>(NT, MI, W);
-    case 3: return pick_h_nt_mi<KIND, 3, XP>(NT, MI, W);
-    case 4: return pick_h_nt_mi<KIND, 4, XP>(NT, MI, W);
-    case 6: return pick_h_nt_mi<KIND, 6, XP>(NT, MI, W);
-    case 8: return pick_h_nt_mi<KIND, 8, XP>(NT, MI, W);
+    case 1: return pick_h_nt_mi<KIND, 1, XP, Y>(NT, MI);
+    case 2: return pick_h_nt_mi<KIND, 2, XP, Y>(NT, MI);
+    case 3: return pick_h_nt_mi<KIND, 3, XP, Y>(NT, MI);
+    case 4: return pick_h_nt_mi<KIND, 4, XP, Y>(NT, MI);
+    case 6: return pick_h_nt_mi<KIND, 6, XP, Y>(NT, MI);
+    case 8: return pick_h_nt_mi<KIND, 8, XP, Y>(NT, MI);
   }
   return nullptr;
 }
 
-tileh_fn pick_h(int kind, int KH, int XP, int NT, int MI, int W) {
-  if (kind == GP_SE_ARD) return XP == 2 ? pick_h_kh<GP_SE_ARD, 2>(KH, NT, MI, W) : pick_h_kh<GP_SE_ARD, 3>(KH, NT, MI, W);
-  return XP == 2 ? pick_h_kh<GP_MATERN32_ARD, 2>(KH, NT, MI, W) : pick_h_kh<GP_MATERN32_ARD, 3>(KH, NT, MI, W);
+template <int KIND, int XP>
+tileh_fn pick_vec_kh(int KH) {
+  switch (KH) {
+    case 1: return kmv_tile_f16_wide_kernel<KIND, 1, XP, 0, true>;
+    case 2: return kmv_tile_f16_wide_kernel<KIND, 2, XP, 0, true>;
+    case 3: return kmv_tile_f16_wide_kernel<KIND, 3, XP, 0, true>;
+    case 4: return kmv_tile_f16_wide_kernel<KIND, 4, XP, 0, true>;
+    case 6: return kmv_tile_f16_wide_kernel<KIND, 6, XP, 0, true>;
+    case 8: return kmv_tile_f16_wide_kernel<KIND, 8, XP, 0, true>;
+  }
+  return nullptr;
 }
 
-inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+template <int KIND, int XP>
+tileh_fn pick_h(int KH, int NT, int MI, bool wide, bool y) {
+  if (NT == 0) return pick_vec_kh<KIND, XP>(KH);
+  if (wide) return y ? kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, true> : kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, false>;
+  return y ? pick_h_kh<KIND, XP, true>(KH, NT, MI) : pick_h_kh<KIND, XP, false>(KH, NT, MI);
+}
 
-struct KmvPlanH {
-  int MI;          // 32-row sub-tiles per wave
-  int W;           // wavefronts per workgroup
-  int row_blocks;
+// The kernel of one column pass of NT tiles (y: with the extra vector-ALU column).
+struct TileKernelH {
+  tileh_fn fn;
+  int rows_per_wg, threads;
+  int per_cu;              // workgroups that share a compute unit
+  double chunk_us;         // about what a chunk takes one of them
+};
+
+TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool y) {
+  TileKernelH k;
+  const int KH = ctx->KH;
+  // The wide kernel where it is ahead (see there) and has rows enough: it takes twice the waves to fill the chip, so
+  // below 32768 rows twice the column splits, whose images cost what it gains (n = 16384: 6 us against 4).  Two
+  // sub-tiles per wave halve the LDS operand traffic; past one k-step of distance operands (two with a
+  // single contraction tile) the second sub-tile no longer fits the register file without spills.
+  const bool wide = NT == 0 || (NT == 2 && KH == 2 && rows >= 32768);
+  const int MI = !wide && rows >= 8192 && (KH == 1 || (KH == 2 && NT == 1)) ? 2 : 1;
+  if (ctx->kernel == GP_SE_ARD) k.fn = XP == 2 ? pick_h<GP_SE_ARD, 2>(KH, NT, MI, wide, y) : pick_h<GP_SE_ARD, 3>(KH, NT, MI, wide, y);
+  else k.fn = XP == 2 ? pick_h<GP_MATERN32_ARD, 2>(KH, NT, MI, wide, y) : pick_h<GP_MATERN32_ARD, 3>(KH, NT, MI, wide, y);
+  k.rows_per_wg = wide ? 256 : 128 * MI;
+  k.threads = wide ? 512 : 256;
+  if (wide) {
+    k.per_cu = wide_waves(KH, XP, NT) / 2;
+    k.chunk_us = NT ? 2.5 : 0.3 * wide_waves(KH, XP, NT);
+  } else {
+    // two workgroups of one wave per SIMD, where their LDS rings fit
+    const int G = XP * KH + 4 * NT, NS = G > 12 ? 3 : 4;
+    const size_t lds = ((size_t)NS * (G * 64 + (y ? 8 * 4 : 0)) * 16 + 1279) / 1280 * 1280;
+    k.per_cu = 2 * lds <= 160 * 1024 ? 2 : 1;
+    k.chunk_us = 1.2 * MI;
+  }
+  return k;
+}
+
+struct PlanH {
   int JS, cps;     // column-range splits, chunks per split
 };
+
+inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct ScratchH {
   size_t off_colmax, off_vy, off_vp, off_part, total;
@@ -555,32 +823,23 @@ ScratchH scratch_layout(const gp_ctx* ctx, int t, int JS, int64_t rows) {
   return L;
 }
 
-// workgroups of four waves that share a compute unit: two (one wave per SIMD each), where their LDS rings fit
-int wgs_per_cu(int KH, int XP, int NT) {
-  const int G = XP * KH + 4 * NT, NS = G > 12 ? 3 : 4;
-  const size_t lds = (size_t)NS * (G * 64 + 8 * 4) * 16;
-  return 2 * align_up(lds, 1280) <= 160 * 1024 ? 2 : 1;
-}
+// tiles of the first (widest) column pass, and whether the vector-ALU column rides along with it: a lone
+// column past a multiple of 32 goes there, whose tile would be used for 1/32 of its width
+bool has_vec_column(int t) { return t % 32 == 1; }
+int pass_tiles(int rem) { return rem > 32 ? 2 : rem > 0 ? 1 : 0; }
 
-KmvPlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP) {
-  KmvPlanH pl;
+PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP) {
+  PlanH pl;
   const int64_t chunks = col_chunks > 0 ? col_chunks : (ctx->n + 31) / 32;
-  // two sub-tiles per wave halve the LDS operand traffic; past one k-step of distance operands the
-  // second sub-tile no longer fits the register file without spills
-  pl.MI = (ctx->KH == 1 && rows >= 8192) ? 2 : 1;
-  if (ctx->mi_forced) pl.MI = (ctx->mi_forced == 2 && ctx->KH <= 2) ? 2 : 1;   // tuning aid
-  pl.W = 4;   // 8-wave workgroups halve the L2-to-LDS traffic but measured no faster on MI355X
-  if (ctx->w_forced) pl.W = ctx->w_forced;                                      // tuning aid
-  const int rows_per_wg = 32 * pl.W * pl.MI;
-  pl.row_blocks = (int)((rows + rows_per_wg - 1) / rows_per_wg);
-  const int NT = (t > 1 && t % 32 == 1 ? t - 1 : t) > 32 ? 2 : 1;
-  const int slots = ctx->num_cu * (pl.W == 4 ? wgs_per_cu(ctx->KH, XP, NT) : 1);
-  // a partial image is written and read once, at about 4 TB/s; a chunk takes a workgroup about 1.2 us per sub-tile
+  const bool y = has_vec_column(t);
+  const TileKernelH k = tile_kernel_h(ctx, rows, XP, pass_tiles(y ? t - 1 : t), y);
+  const int row_blocks = (int)((rows + k.rows_per_wg - 1) / k.rows_per_wg);
+  // a partial image is written and read once, at about 4 TB/s
   const double image = (double)rows * t * sizeof(float);
   int max_js = image * 3.0 > 2.0e9 ? (int)(2.0e9 / image) : 64;     // images past 2 GB would not pay for their memory
   if (max_js < 1) max_js = 1;
   if (max_js > 64) max_js = 64;
-  pl.JS = gp_column_splits(pl.row_blocks, chunks, slots, 2.0 * image / 4.0e12 / (1.2e-6 * pl.MI), max_js);
+  pl.JS = gp_column_splits(row_blocks, chunks, k.per_cu * ctx->num_cu, 2.0 * image / 4.0e6 / k.chunk_us, max_js);
   pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
   return pl;
 }
@@ -653,7 +912,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
                       KmvDeferred* defer, const KmvWindow* win) {
   const int64_t nrows = rows ? rows->m : ctx->n;
   const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
-  KmvPlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
+  PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
   ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
   if (scratch_bytes < L.total) {    // no room for partial images (gp_kmv_static): the column range stays whole
     pl.JS = 1;
@@ -676,7 +935,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   if (win && !colmax_ready) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: a column window needs the column maxima");
   const float* dVw = dV + first * ldv;
 
-  if (!colmax_ready) {
+  if (!colmax_ready && t > 1) {   // a single vector is not scaled
     const int rc = gp_launch_colmax(ctx, dV, ldv, t, (unsigned*)(w + L.off_colmax));
     if (rc < 0) return rc;
   }
@@ -703,12 +962,11 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.sigma2 = (float)(ctx->sigma * ctx->sigma);
   a.add_noise = add_noise;
 
-  int vcol = (t > 1 && t % 32 == 1) ? 0 : -1;
+  int vcol = has_vec_column(t) ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;
-  const dim3 grid(pl.row_blocks * pl.JS), block(64 * pl.W);
-  while (c < t) {
+  do {
     const int rem = t - c;
-    const int NT = rem > 32 ? 2 : 1;
+    const int NT = pass_tiles(rem);
     a.col0 = c;
     a.ncols = rem < 32 * NT ? rem : 32 * NT;
     a.vcol = vcol;
@@ -720,14 +978,15 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
       GP_HIP(ctx, hipGetLastError());
     }
     vcol = -1;
-    tileh_fn fn = pick_h(ctx->kernel, ctx->KH, XP, NT, pl.MI, pl.W);
-    if (!fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
+    const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0);
+    if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
+    const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
     const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
-    hipLaunchKernelGGL(fn, grid, block, 0, st, a);
+    hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, st, a);
     GP_HIP(ctx, hipGetLastError());
     gp_prof_end(ctx, prof);
     c += a.ncols;
-  }
+  } while (c < t);
   if (defer) {
     defer->part = part;
     defer->stride = a.split_stride;

@@ -1,0 +1,64 @@
+"""The tile-pass kernels chosen by size and column count, at the edges of their ranges, against exact fp64 rows.
+
+  - one vector (t = 1): the kernel without contraction tiles, every bucket of distance steps, both
+    fp16 paths, single rows, tile edges, an odd chunk count, and the rectangular product with few rows;
+  - d <= 29, t > 32 and n at and past 32768: the kernel with four waves per SIMD, with and without the
+    vector-ALU column, and a second column pass on the other kernel;
+  - t <= 32 at n past 8192: two sub-tiles per wave for both short distance chains.
+"""
+import numpy as np
+import pytest
+
+from oracle import gp_oracle as orc
+from tests.gpu_util import Dev, relerr
+
+pytestmark = pytest.mark.gpu
+
+KMV_TOL = 1e-5
+
+
+def _case(n, d, kind, t, seed=5):
+    rng = np.random.default_rng(seed)
+    X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
+    V = rng.standard_normal((n, t)).astype(np.float32)
+    ell = np.full(d, 0.6 * np.sqrt(d)) * rng.uniform(0.8, 1.2, size=d)
+    return X, V, ell
+
+
+def _rows(n, k=96, seed=1):
+    """A sample of rows with the first, the last and both sides of the tile edges among them."""
+    edges = [i for i in (0, 31, 32, 127, 128, 255, 256, n - 257, n - 33, n - 1) if 0 <= i < n]
+    return np.unique(np.concatenate([edges, np.random.default_rng(seed).integers(0, n, size=k)]))
+
+
+@pytest.mark.parametrize("path", ["f16x2", "f16x3"])
+@pytest.mark.parametrize("kind", ["se", "matern32"])
+@pytest.mark.parametrize("n,d", [(1, 3), (31, 3), (33, 13), (97, 14), (257, 29), (1000, 30), (3001, 61), (515, 62), (770, 93), (901, 125)])
+def test_one_vector(monkeypatch, path, kind, n, d):
+    monkeypatch.setenv("GPWS_PATH", path)
+    X, V, ell = _case(n, d, kind, 1)
+    dv = Dev(X, kind, ell, 1.3, 0.4)
+    try:
+        assert relerr(dv.kmv(V, 1), orc.kmv_dense(X, ell, 1.3, kind, V, sigma=0.4)) <= KMV_TOL
+        rng = np.random.default_rng(9)
+        for m in (1, 300):
+            Xs = rng.uniform(-1.0, 1.0, size=(m, d)).astype(np.float32)
+            assert relerr(dv.predict(Xs, V), orc.cross_kmv(Xs, X, ell, 1.3, kind, V)) <= KMV_TOL
+    finally:
+        dv.close()
+
+
+@pytest.mark.parametrize("n,d,kind,t", [
+    (32767, 20, "matern32", 65), (32768, 26, "se", 65), (32801, 14, "matern32", 64), (33000, 29, "se", 97), (70001, 26, "matern32", 34),
+    (9001, 26, "matern32", 17), (9001, 12, "se", 33), (8191, 20, "se", 9), (40000, 8, "matern32", 1), (66001, 9, "se", 17)])
+@pytest.mark.parametrize("path", ["f16x2", "f16x3"])
+def test_kernel_choice_by_size(monkeypatch, path, n, d, kind, t):
+    monkeypatch.setenv("GPWS_PATH", path)
+    X, V, ell = _case(n, d, kind, t)
+    rows = _rows(n)
+    ref = orc.kmv_rows(X, ell, 0.9, kind, V, rows, sigma=0.5)
+    dv = Dev(X, kind, ell, 0.9, 0.5)
+    try:
+        assert relerr(dv.kmv(V, 1, ldv=t + 3, ldo=t + 1)[rows], ref) <= KMV_TOL
+    finally:
+        dv.close()
