@@ -430,14 +430,22 @@ CgLayout cg_layout(const gp_ctx* ctx, int t) {
 
 }  // namespace
 
-size_t gp_cg_workspace_bytes(const gp_ctx* ctx, int t) { return cg_layout(ctx, t).total; }
+// covers both forms of the solver: theta, and with it the product path, may change after the caller asked
+size_t gp_cg_workspace_bytes(const gp_ctx* ctx, int t) {
+  const size_t streams = cg_layout(ctx, t).total;
+  const size_t columns = gp_cg_by_columns(ctx) ? gp_cg_columns_workspace_bytes(ctx, t) : 0;
+  return streams > columns ? streams : columns;
+}
 
 int gp_cg_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
               const float* h_tol, int max_iters, void* dWork, size_t work_bytes, int* h_iters,
               int* h_kmv_count, float* h_relres) {
   const CgLayout L = cg_layout(ctx, t);
-  if (work_bytes < L.total) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_cg_solve: workspace %zu < %zu bytes", work_bytes, L.total);
+  const size_t need = gp_cg_workspace_bytes(ctx, t);
+  if (work_bytes < need) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_cg_solve: workspace %zu < %zu bytes", work_bytes, need);
   if ((uintptr_t)dWork % 256) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_cg_solve: workspace not 256-byte aligned");
+  if (gp_cg_by_columns(ctx) && ctx->path != GP_PATH_FP32)
+    return gp_cg_columns_run(ctx, dB, ldb, dX0, dV, ldv, t, h_tol, max_iters, dWork, h_iters, h_kmv_count, h_relres);
   hipStream_t st = ctx->stream;
   char* w = (char*)dWork;
   float* X = (float*)(w + L.off_X);

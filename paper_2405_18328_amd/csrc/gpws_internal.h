@@ -44,6 +44,12 @@ constexpr size_t GP_PIN_POST = 32768;     // flags the solvers' finalise kernels
 //   XB (row side i)   : g * [ -2 xs_i(0..d-1), 1, |xs_i|^2, 0.. ]
 // with xs = (x - mean)/ell and g = -log2(e)/2 (SE) or 3 (Matern-3/2), so that
 // XA_j . XB_i = g * r^2_ij comes straight out of the MFMA chain.
+// Column splits already worked out for a shape of product: a solver asks for the same few thousands of times.
+struct SplitMemo {
+  int64_t rows, chunks;
+  int t, XP, JS;
+};
+
 struct gp_ctx {
   int kernel;
   int64_t n;
@@ -90,6 +96,8 @@ struct gp_ctx {
   int prof_count;
   hipEvent_t* prof_ev;    // 2 * GP_PROF_MAX events, created on first enable
   unsigned char* prof_kind;   // kind of every recorded pair
+  SplitMemo split_memo[4];
+  int split_next;         // entry to overwrite next
   char err[256];
 };
 
@@ -184,6 +192,21 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
                       int add_noise, void* scratch, size_t scratch_bytes, const unsigned* colmax,
                       const KmvRows* rows, KmvDeferred* defer, const KmvWindow* win);
 
+// The tile passes alone, for solvers that keep their vectors column by column and pack operands themselves: the
+// sums of image k, column c lie at images[(k t + c) ld + i], a^2 included, no noise term; rows from n up to the next
+// multiple of 32 hold nothing of meaning.  f16 paths only.
+struct KmvPacked {
+  const void* VP;          // operands of every column pass, one after the other (gp_packed_units 16-byte units)
+  const float* VY;         // the vector-ALU column (column 0 when t = 32 q + 1), zero up to the next multiple of 32 rows
+  const unsigned* colmax;  // bit patterns of the column maxima the operands were scaled by
+  float* images;
+  int64_t ld;              // rows per column, a multiple of 32
+  const int* done;         // device flag that turns the launch into a no-op, or NULL
+};
+int64_t gp_packed_units(int t, int64_t nchunks);
+int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks = 0);   // most images such a product leaves
+int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const KmvRows* rows, const KmvWindow* win, int* images);
+
 // colmax[c] = bit pattern of max_i |V_ic| for c < t, stream-ordered; optionally the same for a second
 // n x t matrix in the same launch.  cleared = true: the caller has already zeroed the output words.
 int gp_launch_colmax(gp_ctx* ctx, const float* dV, int64_t ldv, int t, unsigned* colmax, const float* dV2 = nullptr,
@@ -206,6 +229,13 @@ int gp_cg_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float
               int t, const float* h_tol, int max_iters, void* dWork, size_t work_bytes,
               int* h_iters, int* h_kmv_count, float* h_relres);
 size_t gp_cg_workspace_bytes(const gp_ctx* ctx, int t);
+
+// ---- cg_columns.hip: the same solve for problems up to this size on the f16 product paths
+constexpr int64_t CG_COLUMNS_MAX_N = 65536;
+bool gp_cg_by_columns(const gp_ctx* ctx);
+size_t gp_cg_columns_workspace_bytes(const gp_ctx* ctx, int t);
+int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
+                      const float* h_tol, int max_iters, void* dWork, int* h_iters, int* h_kmv_count, float* h_relres);
 
 // ---- grad_pass.hip
 int gp_grad_run(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,

@@ -19,27 +19,12 @@
 #include <cstdlib>
 
 #include "gpws_internal.h"
+#include "split_f16.h"
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
-
-constexpr float LOG2E = 1.4426950408889634f;
-constexpr unsigned HI_MASK = 0xFFFFE000u;       // keeps sign, exponent and the top 10 mantissa bits
-constexpr int PHI_SHIFT = 15;                   // phi' = 2^15 phi <= 32768 stays inside fp16's range
-constexpr int V_TOP = 14;                       // max |V'_c| in [2^13, 2^14)
-
-// exponent e with max = f 2^e, f in [0.5, 1); 14 for an all-zero column (scale 1)
-__device__ __forceinline__ int column_exponent(unsigned max_bits) {
-  const float m = __uint_as_float(max_bits);
-  if (!(m > 0.0f)) return V_TOP;
-  int e;
-  (void)frexpf(m, &e);
-  return e < -60 ? -60 : e;
-}
 
 struct TileArgsH {
   const u32x4* XA[3];     // column-side pieces, 16-byte units [(chunk*KH + kh)*64 + lane]
@@ -59,6 +44,8 @@ struct TileArgsH {
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
+  int64_t cm_ld;           // > 0: images are column-major with this many rows per column (a multiple of 32)
+  const int* done;         // a non-zero value there turns the launch into a no-op; NULL: always runs
 };
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
@@ -70,6 +57,22 @@ __device__ __forceinline__ float minus_half(unsigned pk, float x) {
   if (H == 0) asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
   else asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
   return r;
+}
+
+// one lane's 16 accumulators of a column: four runs of four rows, eight rows apart, as 16-byte stores (a lane pair
+// covers 32 consecutive bytes); the accumulators are cleared
+__device__ __forceinline__ void store_column_quads(float* dst, bool ok, bool first, float scale, f32x16& acc) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    f32x4 v = scale * f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    if (ok) {
+      f32x4* d = reinterpret_cast<f32x4*>(dst + 8 * g);
+      if (!first) v += *d;
+      *d = v;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[4 * g + q] = 0.0f;
+  }
 }
 
 // Two waves per SIMD with two software pipelines.  Four wavefronts per workgroup: every workgroup streams all
@@ -94,6 +97,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert((DEPTH - 1) * LPC < 64, "vmcnt cannot express the pipeline depth");
   __shared__ u32x4 lds[NS][STAGE];
 
+  if (p.done && *p.done) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: lets the compiler branch on it
@@ -348,6 +352,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
       const int64_t ibase = (int64_t)(sub0 + m) * 32 + zero;
+      if (p.cm_ld) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int c = li + 32 * nt;
+          store_column_quads(out + (int64_t)(p.col0 + c) * p.cm_ld + ibase + 4 * h, c < p.ncols && ibase < p.cm_ld, first,
+                             oscale[nt], acc[m][nt]);
+        }
+        if (Y) {
+          const float tot = accv[m] + __shfl_xor(accv[m], 32);
+          if (h == 0 && ibase < p.cm_ld) {
+            float* o = out + (int64_t)p.vcol * p.cm_ld + ibase + li;
+            const float v = p.a2 * ldexpf(1.0f, -PHI_SHIFT) * tot;
+            *o = first ? v : *o + v;
+          }
+          accv[m] = 0.0f;
+        }
+        continue;
+      }
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const int c = li + 32 * nt;
@@ -424,6 +446,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   constexpr int LPW = (2 * G + W - 1) / W;          // group loads per wave and stage; surplus slots repeat the last group
   __shared__ u32x4 lds[2][STAGE];
 
+  if (p.done && *p.done) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -559,6 +582,28 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
     int zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
     const int64_t ibase = (int64_t)sub0 * 32 + zero;
+    if (p.cm_ld) {
+      if constexpr (NT > 0) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int c = li + 32 * nt;
+          const float oscale = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(c, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
+          store_column_quads(out + (int64_t)(p.col0 + c) * p.cm_ld + ibase + 4 * h, c < p.ncols && ibase < p.cm_ld, first,
+                             oscale, acc[nt]);
+        }
+      }
+      if (Y) {
+        const float both = accv[0] + accv[1];
+        const float tot = both + __shfl_xor(both, 32);
+        if (h == 0 && ibase < p.cm_ld) {
+          float* o = out + (int64_t)p.vcol * p.cm_ld + ibase + li;
+          const float v = p.a2 * ldexpf(1.0f, -PHI_SHIFT) * tot;
+          *o = first ? v : *o + v;
+        }
+        accv[0] = accv[1] = 0.0f;
+      }
+      return;
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int c = li + 32 * nt;
@@ -831,6 +876,12 @@ int pass_tiles(int rem) { return rem > 32 ? 2 : rem > 0 ? 1 : 0; }
 PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP) {
   PlanH pl;
   const int64_t chunks = col_chunks > 0 ? col_chunks : (ctx->n + 31) / 32;
+  for (const SplitMemo& m : ctx->split_memo)
+    if (m.JS && m.rows == rows && m.chunks == chunks && m.t == t && m.XP == XP) {
+      pl.JS = m.JS;
+      pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
+      return pl;
+    }
   const bool y = has_vec_column(t);
   const TileKernelH k = tile_kernel_h(ctx, rows, XP, pass_tiles(y ? t - 1 : t), y);
   const int row_blocks = (int)((rows + k.rows_per_wg - 1) / k.rows_per_wg);
@@ -841,6 +892,9 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
   if (max_js > 64) max_js = 64;
   pl.JS = gp_column_splits(row_blocks, chunks, k.per_cu * ctx->num_cu, 2.0 * image / 4.0e6 / k.chunk_us, max_js);
   pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
+  gp_ctx* memo = const_cast<gp_ctx*>(ctx);   // a context belongs to one host thread at a time
+  memo->split_memo[memo->split_next] = SplitMemo{rows, chunks, t, XP, pl.JS};
+  memo->split_next = (memo->split_next + 1) % 4;
   return pl;
 }
 
@@ -859,8 +913,8 @@ int gp_kh_bucket(int d, int kernel) {
 // A launch runs in generations of `slots` workgroups, and a last generation of a few row blocks costs as much as a
 // full one: the time is about generations x (chunks per workgroup + what its prologue and flush cost), and
 // every further cut adds one partial image of the output to write and read (image_cost, in units of a
-// workgroup's chunk).  Measured on MI355X (n = 43945, d = 20, t = 17: 344 row blocks on 512 slots): two ranges
-// 946 us per product, SPLIT7.
+// workgroup's chunk).  Measured on MI355X (gp_predict, n = 41157 and 4573 test points, t = 1: 36 row
+// blocks of 128 rows): 15 ranges, 540 workgroups, 149.8 us; 14 ranges, 504 workgroups, 121.9 us.
 int gp_column_splits(int row_blocks, int64_t chunks, int slots, double image_cost, int max_splits) {
   constexpr double FIXED = 4.0;       // prologue and flush of a workgroup, in chunks
   constexpr int MIN_CHUNKS = 4;
@@ -961,6 +1015,8 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.a2 = (float)(ctx->a * ctx->a);
   a.sigma2 = (float)(ctx->sigma * ctx->sigma);
   a.add_noise = add_noise;
+  a.cm_ld = 0;
+  a.done = nullptr;
 
   int vcol = has_vec_column(t) ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;
@@ -1000,5 +1056,74 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
                        nrows, t, dOut, ldo);
     GP_HIP(ctx, hipGetLastError());
   }
+  return GP_OK;
+}
+
+int64_t gp_packed_units(int t, int64_t nchunks) {
+  int64_t u = 0;
+  for (int c = has_vec_column(t) ? 1 : 0; c < t;) {
+    const int NT = pass_tiles(t - c);
+    u += nchunks * 4 * NT * 64;
+    c += 32 * NT;
+  }
+  return u;
+}
+
+int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks) {
+  int most = 1;
+  for (int XP = 2; XP <= 3; ++XP) {
+    const int js = plan_h(ctx, rows, col_chunks, t, XP).JS;
+    if (js > most) most = js;
+  }
+  return most;
+}
+
+int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const KmvRows* rows, const KmvWindow* win, int* images) {
+  const int64_t nrows = rows ? rows->m : ctx->n;
+  const PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, ctx->XP);
+  const int nchunks = win ? win->nchunks : (int)((ctx->n + 31) / 32);
+  TileArgsH a;
+  for (int pc = 0; pc < 3; ++pc) {
+    a.XA[pc] = (const u32x4*)ctx->dXAh[pc] + (win ? (int64_t)win->chunk0 * ctx->KH * 64 : 0);
+    a.XB[pc] = (const u32x4*)(rows ? rows->XBh[pc] : ctx->dXBh[pc]);
+  }
+  a.VY = pk.VY;
+  a.V = nullptr;
+  a.ldv = 0;
+  a.colmax = pk.colmax;
+  a.OUT = pk.images;
+  a.ldo = 0;
+  a.split_stride = pk.ld * (int64_t)t;
+  a.n = nrows;
+  a.diag = (rows || win) ? 0 : 1;
+  a.nchunks = nchunks;
+  a.JS = pl.JS;
+  a.cps = pl.cps;
+  a.a2 = (float)(ctx->a * ctx->a);
+  a.sigma2 = 0.0f;
+  a.add_noise = 0;
+  a.cm_ld = pk.ld;
+  a.done = pk.done;
+  const u32x4* VP = (const u32x4*)pk.VP;
+  int vcol = has_vec_column(t) ? 0 : -1;
+  int c = vcol >= 0 ? 1 : 0;
+  do {
+    const int rem = t - c, NT = pass_tiles(rem);
+    a.VP = VP;
+    a.col0 = c;
+    a.ncols = rem < 32 * NT ? rem : 32 * NT;
+    a.vcol = vcol;
+    vcol = -1;
+    const TileKernelH k = tile_kernel_h(ctx, nrows, ctx->XP, NT, a.vcol >= 0);
+    if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
+    const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
+    const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
+    hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, ctx->stream, a);
+    GP_HIP(ctx, hipGetLastError());
+    gp_prof_end(ctx, prof);
+    VP += (int64_t)nchunks * 4 * NT * 64;
+    c += a.ncols;
+  } while (c < t);
+  *images = pl.JS;
   return GP_OK;
 }
