@@ -35,41 +35,6 @@ struct CgCols {
   float sigma2;
 };
 
-// largest |.| of column c of A and its packed operands (the product with A that follows)
-__device__ __forceinline__ void pack_column(const CgCols& s, int c, const float* A, float mx, float* shf) {
-  const float m = column_max(mx, shf);
-  if (threadIdx.x == 0) s.colmax[c] = __float_as_uint(m);
-  const PackSpot spot = pack_spot(s.VP, s.t, s.ld / 32, c);
-  if (!spot.base) return;
-  const float scale = pack_scale(m);
-  const int nk = (int)(s.ld / 4);
-  for (int k0 = 0; k0 < nk; k0 += 4 * CT) {
-    f32x4 v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const f32x4*>(A + 4 * min(k0 + CT * j + (int)threadIdx.x, nk - 1));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = k0 + CT * j + (int)threadIdx.x;
-      if (k < nk) pack_quad(spot, k, v[j] * scale);
-    }
-  }
-}
-
-// warm start, ahead of the product H x0
-__global__ __launch_bounds__(CT) void cgc_pack_x_kernel(CgCols s) {
-  __shared__ float shf[16];
-  const int c = block_column(s.t);
-  if (c < 0) return;
-  const float* X = s.X + (int64_t)c * s.ld;
-  float mx = 0.0f;
-  for (int64_t k = threadIdx.x; k < s.ld / 4; k += CT) {
-    const f32x4 x = *reinterpret_cast<const f32x4*>(X + 4 * k);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(x[q]));
-  }
-  pack_column(s, c, X, mx, shf);
-}
-
 // R holds B: ||b||^2; warm: R -= H x0; P <- R, its operands; initial state of the column
 __global__ __launch_bounds__(CT) void cgc_start_kernel(CgCols s, int warm) {
   __shared__ double shd[16];
@@ -98,7 +63,7 @@ __global__ __launch_bounds__(CT) void cgc_start_kernel(CgCols s, int warm) {
   }
   const double bn2 = column_sum((double)bb, shd);
   const double rho = column_sum((double)rr, shd);
-  pack_column(s, c, s.P + col, mx, shf);
+  pack_column(s.VP, s.colmax, s.t, s.ld, c, s.P + col, mx, shf);
   if (threadIdx.x == 0) {
     const int zero = !(bn2 > 0.0);
     const double rel = zero ? 0.0 : sqrt(rho / bn2);
@@ -108,7 +73,7 @@ __global__ __launch_bounds__(CT) void cgc_start_kernel(CgCols s, int warm) {
     s.relres[c] = (float)rel;
     s.zero_rhs[c] = zero;
     s.frozen[c] = fr;
-    column_arrive(s.flags, s.post, s.t, !fr, false, false);
+    column_arrive(s.flags, s.post, s.t, !fr, 0, false);
   }
 }
 
@@ -243,7 +208,7 @@ __global__ __launch_bounds__(CT) void cgc_iter_kernel(CgCols s) {
       s.rho[c] = rho_new;
       s.relres[c] = (float)rel;
       s.frozen[c] = go ? 0 : 1;
-      column_arrive(s.flags, s.post, s.t, go, bad, true);   // nothing below is waited for by the others
+      column_arrive(s.flags, s.post, s.t, go, bad ? 1 : 0, true);   // nothing below is waited for by the others
     }
     if (go) {   // a column that has stopped needs no direction any more
       float mx = 0.0f;
@@ -279,11 +244,11 @@ __global__ __launch_bounds__(CT) void cgc_iter_kernel(CgCols s) {
           }
           *reinterpret_cast<f32x4*>(s.P + col + 4 * k) = pk;
         }
-        pack_column(s, c, s.P + col, mx, shf);
+        pack_column(s.VP, s.colmax, s.t, s.ld, c, s.P + col, mx, shf);
       }
     }
   } else if (tid == 0) {
-    column_arrive(s.flags, s.post, s.t, false, false, true);
+    column_arrive(s.flags, s.post, s.t, false, 0, true);
   }
 }
 
@@ -383,10 +348,10 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   GP_HIP(ctx, hipGetLastError());
   int kmv_count = 0;
   if (dX0) {
-    hipLaunchKernelGGL(cgc_pack_x_kernel, grid, block, 0, st, s);
+    hipLaunchKernelGGL(pack_columns_kernel, grid, block, 0, st, (const float*)s.X, s.VP, s.colmax, t, L.ld);
     pk.VY = s.X;
     pk.done = nullptr;
-    const int rc = gp_kmv_packed(ctx, t, pk, nullptr, nullptr, &s.JS);
+    const int rc = gp_kmv_packed(ctx, t, pk, nullptr, 0, nullptr, &s.JS);
     if (rc < 0) return drained(rc);
     ++kmv_count;
   }
@@ -414,7 +379,7 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   }
   for (int finished = 0, queued = 0; !done && finished < max_iters; ++finished) {
     for (; queued < max_iters && queued <= finished + ahead; ++queued) {
-      const int rc = gp_kmv_packed(ctx, t, pk, nullptr, nullptr, &s.JS);
+      const int rc = gp_kmv_packed(ctx, t, pk, nullptr, 0, nullptr, &s.JS);
       if (rc < 0) return drained(rc);
       if (long_columns) hipLaunchKernelGGL(cgc_sum_kernel, dim3((unsigned)((L.ld + CROWS - 1) / CROWS), t), dim3(256), 0, st, s);
       hipLaunchKernelGGL(iter, grid, block, 0, st, s);

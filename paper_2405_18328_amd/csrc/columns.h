@@ -94,6 +94,44 @@ __device__ __forceinline__ float column_max(float v, float* sh /* [16] */) {
   return m;
 }
 
+// largest |.| of column c of A (mx: this thread's part of it) and the column's operands for the next product
+__device__ __forceinline__ void pack_column(u32x4* VP, unsigned* colmax, int t, int64_t ld, int c, const float* A, float mx,
+                                            float* shf) {
+  const float m = column_max(mx, shf);
+  if (threadIdx.x == 0) colmax[c] = __float_as_uint(m);
+  const PackSpot spot = pack_spot(VP, t, ld / 32, c);
+  if (!spot.base) return;
+  const float scale = pack_scale(m);
+  const int nk = (int)(ld / 4);
+  for (int k0 = 0; k0 < nk; k0 += 4 * CT) {
+    f32x4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const f32x4*>(A + 4 * min(k0 + CT * j + (int)threadIdx.x, nk - 1));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = k0 + CT * j + (int)threadIdx.x;
+      if (k < nk) pack_quad(spot, k, v[j] * scale);
+    }
+  }
+}
+
+// maxima and operands of all columns of A
+__global__ __launch_bounds__(CT) void pack_columns_kernel(const float* __restrict__ A, u32x4* __restrict__ VP,
+                                                          unsigned* __restrict__ colmax, int t, int64_t ld) {
+  __shared__ float shf[16];
+  const int c = block_column(t);
+  if (c < 0) return;
+  const float* X = A + (int64_t)c * ld;
+  float mx = 0.0f;
+#pragma unroll 4
+  for (int64_t k = threadIdx.x; k < ld / 4; k += CT) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(X + 4 * k);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(x[q]));
+  }
+  pack_column(VP, colmax, t, ld, c, X, mx, shf);
+}
+
 // Sum over the images of a product at rows r .. r + 3 of a column, in order; rows from n on are 0.  Images are fetched
 // eight at a time, all loads of a batch in flight together (surplus ones repeat the last image).
 template <int BATCH = 8>
@@ -116,7 +154,7 @@ __device__ __forceinline__ f32x4 sum_images(const float* __restrict__ images, in
 
 // What a solver's device side tells the host loop, in one 8-byte store to pinned memory (nothing to order, so
 // no fence): steps finished in the low half, flags in the high half.
-constexpr unsigned COL_DONE = 1u, COL_BAD = 2u;
+constexpr unsigned COL_DONE = 1u;
 struct ColFlags {
   int all_done;
   int bad;
@@ -127,21 +165,21 @@ struct ColFlags {
 };
 
 // One thread per column, at its end: the column that arrives last raises the flags and posts the step.  The
-// ticket counts arrivals (bits 0-19), columns that go on (20-39) and failures (40-): one atomic says all, so
-// nothing else has to be visible to the last one.
-__device__ __forceinline__ void column_arrive(ColFlags* f, unsigned long long* post, int t, bool goes_on, bool bad, bool counts) {
-  const unsigned long long mine = 1ull | ((unsigned long long)goes_on << 20) | ((unsigned long long)bad << 40);
+// ticket counts arrivals (bits 0-15), columns that go on (16-31) and failures of kind 1 (32-47) and 2
+// (48-63; reported in preference): one atomic says all, so nothing else has to be visible to the last one.
+__device__ __forceinline__ void column_arrive(ColFlags* f, unsigned long long* post, int t, bool goes_on, int bad, bool counts) {
+  const unsigned long long mine = 1ull | ((unsigned long long)goes_on << 16) | (bad == 1 ? 1ull << 32 : bad == 2 ? 1ull << 48 : 0ull);
   const unsigned long long all = atomicAdd(&f->ticket, mine) + mine;
-  if ((int)(all & 0xFFFFFu) != t) return;
-  const bool any_bad = (all >> 40) != 0;
-  const bool done = any_bad || ((all >> 20) & 0xFFFFFu) == 0;
+  if ((int)(all & 0xFFFFu) != t) return;
+  const int any_bad = (all >> 48) ? 2 : (all >> 32) ? 1 : 0;
+  const bool done = any_bad || ((all >> 16) & 0xFFFFu) == 0;
   const int iters = f->iters + (counts ? 1 : 0);
   f->ticket = 0;
   f->iters = iters;
-  f->bad = any_bad ? 1 : 0;
+  f->bad = any_bad;
   f->all_done = done ? 1 : 0;
   const unsigned long long word = (unsigned long long)(unsigned)(iters + 1) |
-                                  ((unsigned long long)((done ? COL_DONE : 0u) | (any_bad ? COL_BAD : 0u)) << 32);
+                                  ((unsigned long long)(done ? COL_DONE : 0u) << 32);
   __hip_atomic_store(post, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 

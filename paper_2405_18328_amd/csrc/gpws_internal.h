@@ -205,7 +205,8 @@ struct KmvPacked {
 };
 int64_t gp_packed_units(int t, int64_t nchunks);
 int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks = 0);   // most images such a product leaves
-int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const KmvRows* rows, const KmvWindow* win, int* images);
+// gather: device, nrows indices of the context's points that are the rows of the product (NULL: all n, in order)
+int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvWindow* win, int* images);
 
 // colmax[c] = bit pattern of max_i |V_ic| for c < t, stream-ordered; optionally the same for a second
 // n x t matrix in the same launch.  cleared = true: the caller has already zeroed the output words.
@@ -223,6 +224,14 @@ size_t gp_sgd_workspace_bytes_impl(const gp_ctx* ctx, int t, int batch);
 int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
                const float* h_tol, const int* dBatches, int batch, int max_iters, double lr, double momentum,
                void* dWork, size_t work_bytes, int* h_iters, int* h_kmv_count, float* h_relres);
+
+// ---- sgd_columns.hip: the same solve for problems up to this size on the f16 product paths
+constexpr int64_t SGD_COLUMNS_MAX_N = 131072;
+bool gp_sgd_by_columns(const gp_ctx* ctx);
+size_t gp_sgd_columns_workspace_bytes(const gp_ctx* ctx, int t, int batch);
+int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
+                       const float* h_tol, const int* dBatches, int batch, int max_iters, double lr, double momentum,
+                       void* dWork, int* h_iters, int* h_kmv_count, float* h_relres);
 
 // ---- cg_kernels.hip
 int gp_cg_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv,

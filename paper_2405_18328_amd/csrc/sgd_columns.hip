@@ -1,0 +1,418 @@
+// Stochastic gradient descent with one workgroup per column, for n <= SGD_COLUMNS_MAX_N on the split-fp16 product
+// paths: the same step, stopping rule and freezing as the streaming kernels of sgd_kernels.hip, in three
+// launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
+// context's packed operands; the gradient on the mini-batch rows is spread over the chip; momentum, iterate,
+// the stopping test and the packing of the iterate for the next product are per column (columns.h).
+// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: 84 -> 43 us per step (product 19.5, gradient 10, the rest
+// 10.6 us).  Bound by memory latency and by the 64 partial images of the product (16.6 MB written and read).
+#include "columns.h"
+
+namespace {
+
+struct SgdCols {
+  ColFlags* flags;
+  unsigned long long* post;
+  double* rr;         // [t] squared norm of the residual estimate
+  double* bn2;        // [t]
+  float* tol;         // [t]
+  float* relres;      // [t]
+  int* frozen;        // [t]
+  int* zero_rhs;      // [t]
+  unsigned* colmax;   // [t]
+  float *B, *U, *M, *R;   // [t][ld]
+  float* G;           // [t][gld] step * gradient per mini-batch slot
+  double* deltas;     // [t][slices] change of the squared norm of the residual estimate
+  int* bad_index;     // raised by a mini-batch index outside [0, n)
+  u32x4* VP;
+  const float* images;
+  int JS;
+  int64_t stride;     // between images
+  int64_t n, ld, gld; // gld: rows per column of the product with the mini-batch rows
+  int t, batch;
+  float sigma2, step, rho;
+};
+
+// R holds B, U holds x0 (or 0): M <- 0; warm: R -= H x0; initial state of the column
+__global__ __launch_bounds__(CT) void sgdc_start_kernel(SgdCols s, int warm) {
+  __shared__ double shd[16];
+  const int c = block_column(s.t);
+  if (c < 0) return;
+  const int64_t col = (int64_t)c * s.ld;
+  float bb = 0.0f, rr = 0.0f;
+  for (int64_t k = threadIdx.x; k < s.ld / 4; k += CT) {
+    f32x4 r = *reinterpret_cast<const f32x4*>(s.B + col + 4 * k);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bb = fmaf(r[q], r[q], bb);
+    if (warm) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(s.U + col + 4 * k);
+      const f32x4 hx = sum_images(s.images, s.JS, s.stride, col + 4 * k, 4 * k, s.n);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) r[q] -= fmaf(s.sigma2, x[q], hx[q]);
+    }
+    *reinterpret_cast<f32x4*>(s.R + col + 4 * k) = r;
+    *reinterpret_cast<f32x4*>(s.M + col + 4 * k) = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rr = fmaf(r[q], r[q], rr);
+  }
+  const double bn2 = column_sum((double)bb, shd);
+  const double r2 = column_sum((double)rr, shd);
+  if (threadIdx.x == 0) {
+    const int zero = bn2 == 0.0;
+    const double rel = zero ? 0.0 : sqrt(r2 / bn2);
+    const int bad = !zero && (!(rel == rel) || rel > 3.0e38) ? 1 : 0;
+    const int fr = zero || (float)rel < s.tol[c];
+    s.bn2[c] = bn2;
+    s.rr[c] = r2;
+    s.relres[c] = (float)rel;
+    s.zero_rhs[c] = zero;
+    s.frozen[c] = fr;
+    if (!warm) s.colmax[c] = 0u;
+    column_arrive(s.flags, s.post, s.t, !fr, bad, false);
+  }
+}
+
+// The mini-batch rows I behind their product: G = (H U)[I] - B[I], R[I] <- -G, step * G kept per slot, and the change of
+// the residual estimate's squared norm per slice of slots.  Spread over the chip: a column's images (64 of them
+// for 1000 rows) would take one compute unit as long as everything else of a step.  Grid: slices x t.
+// HB images are fetched at a time, all loads in flight together.
+constexpr int GT = 256;
+template <int HB>
+__global__ __launch_bounds__(GT) void sgdc_grad_kernel(SgdCols s, const int* __restrict__ I) {
+  __shared__ double sh[GT / 64];
+  const int c = blockIdx.y;
+  const int64_t col = (int64_t)c * s.ld, gcol0 = (int64_t)c * s.gld;
+  const int slot = blockIdx.x * GT + threadIdx.x;
+  const bool mine = slot < s.batch;
+  int64_t i = I[mine ? slot : 0];
+  const int stopped = s.frozen[c], over = s.flags->all_done;
+  const bool outside = i < 0 || i >= s.n;
+  if (outside) i = 0;
+  const float ui = s.U[col + i], bi = s.B[col + i], old = s.R[col + i];
+  float hx = 0.0f;
+  for (int k = 0; k < s.JS; k += HB) {
+    float h[HB];
+#pragma unroll
+    for (int q = 0; q < HB; ++q) h[q] = s.images[(int64_t)min(k + q, s.JS - 1) * s.stride + gcol0 + (mine ? slot : 0)];
+#pragma unroll
+    for (int q = 0; q < HB; ++q)
+      if (k + q < s.JS) hx += h[q];
+  }
+  if (over) return;
+  if (outside) *s.bad_index = 1;
+  double acc = 0.0;
+  if (mine && !stopped) {
+    hx = fmaf(s.sigma2, ui, hx);
+    const float g = hx - bi;
+    s.R[col + i] = -g;
+    s.G[gcol0 + slot] = s.step * g;
+    acc = (double)g * (double)g - (double)old * (double)old;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) s.deltas[(int64_t)c * gridDim.x + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+// The rest of a step of one column: stopping test, momentum, iterate, the operands of the next product.
+// Q > 0: ld <= 4096 Q; momentum and iterate are in registers from the start, the gradient is scattered over the
+// column in LDS.  Q = 0: momentum and iterate are streamed, the mini-batch rows corrected afterwards and the iterate
+// read again to be packed (the column maximum is then an upper bound, all its scaling needs).
+template <int Q>
+__global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __restrict__ I, int slices) {
+  __shared__ float shf[16];
+  extern __shared__ float gcol[];     // [ld], Q > 0 only
+  const int c = block_column(s.t);
+  if (c < 0) return;
+  const int tid = threadIdx.x;
+  const int64_t col = (int64_t)c * s.ld, gcol0 = (int64_t)c * s.gld;
+  const int nk = (int)(s.ld / 4);
+  f32x4 u[Q ? Q : 1], m[Q ? Q : 1];
+  int64_t i0 = 0;
+  float g0 = 0.0f;
+  if constexpr (Q > 0) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int k = tid + CT * j;
+      u[j] = m[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (k < nk) {
+        u[j] = *reinterpret_cast<const f32x4*>(s.U + col + 4 * k);
+        m[j] = *reinterpret_cast<const f32x4*>(s.M + col + 4 * k);
+      }
+    }
+    i0 = I[min(tid, s.batch - 1)];
+    g0 = s.G[gcol0 + min(tid, s.batch - 1)];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int k = tid + CT * j;
+      if (k < nk) *reinterpret_cast<f32x4*>(gcol + 4 * k) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  bool go = !s.frozen[c];
+  const double rr0 = s.rr[c], bn2 = s.bn2[c];
+  const float tol = s.tol[c];
+  int bad = *s.bad_index ? 2 : 0;
+  double delta = 0.0;
+  for (int k = 0; k < slices; ++k) delta += s.deltas[(int64_t)c * slices + k];
+  if (s.flags->all_done) return;
+  if constexpr (Q > 0) {
+    if (go) {
+      __syncthreads();
+      if (tid < s.batch && i0 >= 0 && i0 < s.n) gcol[i0] = g0;
+      for (int slot = tid + CT; slot < s.batch; slot += CT) {
+        const int64_t i = I[slot];
+        if (i >= 0 && i < s.n) gcol[i] = s.G[gcol0 + slot];
+      }
+      __syncthreads();
+    }
+  }
+  if (go) {
+    double rr = rr0 + delta;
+    if (rr < 0.0) rr = 0.0;
+    const double rel = sqrt(rr / bn2);
+    if (!bad && (!(rel == rel) || rel > 3.0e38)) bad = 1;
+    if (tid == 0) {
+      const int fr = (float)rel < tol ? 1 : 0;
+      s.rr[c] = rr;
+      s.relres[c] = (float)rel;
+      s.frozen[c] = fr;
+      column_arrive(s.flags, s.post, s.t, !fr, bad, true);   // nothing below is waited for by the others
+    }
+    float mx = 0.0f;
+    if constexpr (Q > 0) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        const int k = tid + CT * j;
+        if (k < nk) {
+          const f32x4 g = *reinterpret_cast<const f32x4*>(gcol + 4 * k);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float mm = s.rho * m[j][q];
+            m[j][q] = mm - g[q];
+            u[j][q] = (u[j][q] + mm) - g[q];
+            mx = fmaxf(mx, fabsf(u[j][q]));
+          }
+          *reinterpret_cast<f32x4*>(s.M + col + 4 * k) = m[j];
+          *reinterpret_cast<f32x4*>(s.U + col + 4 * k) = u[j];
+        }
+      }
+      const float top = column_max(mx, shf);
+      if (tid == 0) s.colmax[c] = __float_as_uint(top);
+      const PackSpot spot = pack_spot(s.VP, s.t, s.ld / 32, c);
+      if (spot.base) {
+        const float scale = pack_scale(top);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+          const int k = tid + CT * j;
+          if (k < nk) pack_quad(spot, k, u[j] * scale);
+        }
+      }
+    } else {
+      for (int k0 = 0; k0 < nk; k0 += 4 * CT) {
+        f32x4 uu[4], mm[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int k = min(k0 + CT * j + tid, nk - 1);
+          uu[j] = *reinterpret_cast<const f32x4*>(s.U + col + 4 * k);
+          mm[j] = *reinterpret_cast<const f32x4*>(s.M + col + 4 * k);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int k = k0 + CT * j + tid;
+          if (k < nk) {
+            mm[j] *= s.rho;
+            uu[j] += mm[j];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(uu[j][q]));
+            *reinterpret_cast<f32x4*>(s.M + col + 4 * k) = mm[j];
+            *reinterpret_cast<f32x4*>(s.U + col + 4 * k) = uu[j];
+          }
+        }
+      }
+      __syncthreads();     // the streamed rows are in memory before the mini-batch rows are corrected
+      for (int slot = tid; slot < s.batch; slot += CT) {
+        int64_t i = I[slot];
+        if (i < 0 || i >= s.n) i = 0;
+        const float g = s.G[gcol0 + slot];
+        s.M[col + i] -= g;
+        const float v = s.U[col + i] - g;
+        s.U[col + i] = v;
+        mx = fmaxf(mx, fabsf(v));
+      }
+      __syncthreads();
+      pack_column(s.VP, s.colmax, s.t, s.ld, c, s.U + col, mx, shf);
+    }
+  } else if (tid == 0) {
+    column_arrive(s.flags, s.post, s.t, false, bad, true);
+  }
+}
+
+inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+
+struct Layout {
+  int64_t ld, gld, units;
+  size_t off_B, off_U, off_M, off_R, off_G, off_deltas, off_state, off_VP, off_images, total;
+};
+
+Layout layout(const gp_ctx* ctx, int t, int batch) {
+  Layout L;
+  L.ld = (ctx->n + 31) / 32 * 32;
+  L.gld = ((int64_t)batch + 31) / 32 * 32;
+  L.units = gp_packed_units(t, L.ld / 32);
+  const size_t arr = align_up((size_t)L.ld * t * sizeof(float), 256);
+  const size_t garr = align_up((size_t)L.gld * t * sizeof(float), 256);
+  size_t o = 0;
+  L.off_B = o; o += arr;
+  L.off_U = o; o += arr;
+  L.off_M = o; o += arr;
+  L.off_R = o; o += arr;
+  L.off_G = o; o += garr;
+  L.off_deltas = o; o += align_up((size_t)t * ((batch + GT - 1) / GT) * sizeof(double), 256);
+  L.off_state = o; o += align_up(sizeof(ColFlags) + 16 + (size_t)t * (2 * sizeof(double) + 2 * sizeof(float) + 3 * sizeof(int)), 256);
+  L.off_VP = o; o += align_up((size_t)L.units * 16, 256);
+  const size_t square = arr * (size_t)gp_packed_images(ctx, t, ctx->n);
+  const size_t rows = garr * (size_t)gp_packed_images(ctx, t, batch);
+  L.off_images = o; o += square > rows ? square : rows;
+  L.total = o;
+  return L;
+}
+
+typedef void (*step_fn)(SgdCols, const int*, int);
+
+}  // namespace
+
+bool gp_sgd_by_columns(const gp_ctx* ctx) { return ctx->n <= SGD_COLUMNS_MAX_N; }
+size_t gp_sgd_columns_workspace_bytes(const gp_ctx* ctx, int t, int batch) { return layout(ctx, t, batch).total; }
+
+int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
+                       const float* h_tol, const int* dBatches, int batch, int max_iters, double lr, double momentum,
+                       void* dWork, int* h_iters, int* h_kmv_count, float* h_relres) {
+  const Layout L = layout(ctx, t, batch);
+  hipStream_t st = ctx->stream;
+  char* w = (char*)dWork;
+  SgdCols s;
+  s.B = (float*)(w + L.off_B);
+  s.U = (float*)(w + L.off_U);
+  s.M = (float*)(w + L.off_M);
+  s.R = (float*)(w + L.off_R);
+  s.G = (float*)(w + L.off_G);
+  s.deltas = (double*)(w + L.off_deltas);
+  {
+    char* q = w + L.off_state;
+    s.flags = (ColFlags*)q; q += sizeof(ColFlags);
+    s.bad_index = (int*)q; q += 16;
+    s.rr = (double*)q; q += sizeof(double) * t;
+    s.bn2 = (double*)q; q += sizeof(double) * t;
+    s.tol = (float*)q; q += sizeof(float) * t;
+    s.relres = (float*)q; q += sizeof(float) * t;
+    s.frozen = (int*)q; q += sizeof(int) * t;
+    s.zero_rhs = (int*)q; q += sizeof(int) * t;
+    s.colmax = (unsigned*)q;
+  }
+  s.VP = (u32x4*)(w + L.off_VP);
+  s.images = (const float*)(w + L.off_images);
+  s.n = ctx->n;
+  s.ld = L.ld;
+  s.gld = L.gld;
+  s.t = t;
+  s.batch = batch;
+  s.sigma2 = (float)(ctx->sigma * ctx->sigma);
+  s.step = (float)(lr / (double)batch);
+  s.rho = (float)momentum;
+  s.JS = 1;
+  s.stride = L.ld * (int64_t)t;
+
+  // Pinned staging: tolerances in, flags and residuals out.  Written by the host only here; every solver
+  // synchronises the stream before it returns, so the copy a previous call queued from it has run.
+  if (sizeof(ColFlags) + sizeof(float) * t * 2 > GP_PIN_THETA)
+    return gp_fail(ctx, GP_ERR_ARG, "gp_sgd_solve: t too large for the pinned staging block");
+  ColFlags* hflags = (ColFlags*)((char*)ctx->hPinned + GP_PIN_SOLVER);
+  float* htol = (float*)(hflags + 1);
+  float* hrel = htol + t;
+  for (int c = 0; c < t; ++c) htol[c] = h_tol[c];
+  volatile unsigned long long* hpost = (volatile unsigned long long*)((char*)ctx->hPinned + GP_PIN_POST);
+  s.post = (unsigned long long*)((char*)ctx->dPinned + GP_PIN_POST);
+  *hpost = 0;
+
+  // an error return leaves nothing of this solve running: queued kernels would post into the next solve
+  auto drained = [&](int rc) -> int {
+    (void)hipStreamSynchronize(st);
+    return rc;
+  };
+
+  const dim3 grid(column_blocks(t)), block(CT);
+  KmvPacked pk;
+  pk.VP = s.VP;
+  pk.VY = s.U;
+  pk.colmax = s.colmax;
+  pk.images = (float*)(w + L.off_images);
+  pk.ld = L.ld;
+  pk.done = nullptr;
+  GP_HIP(ctx, hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(clear_units_kernel, dim3(1), dim3(256), 0, st, (u32x4*)s.flags, (int64_t)(sizeof(ColFlags) / 16 + 1));
+  if (!dX0 || t % 32 > 1) {   // U = 0, or columns that pad the last tile: operands nobody writes before the product reads them
+    int blocks = (int)((L.units + 255) / 256);
+    if (blocks > 4 * ctx->num_cu) blocks = 4 * ctx->num_cu;
+    if (blocks > 0) hipLaunchKernelGGL(clear_units_kernel, dim3(blocks), dim3(256), 0, st, s.VP, L.units);
+  }
+  hipLaunchKernelGGL(to_columns_kernel, transpose_grid(L.ld, t, 2), dim3(256), 0, st, dB, ldb, s.B, dX0, ldv, s.U, ctx->n, L.ld, t);
+  GP_HIP(ctx, hipGetLastError());
+  int kmv_count = 0;
+  if (dX0) {
+    hipLaunchKernelGGL(pack_columns_kernel, grid, block, 0, st, (const float*)s.U, s.VP, s.colmax, t, L.ld);
+    const int rc = gp_kmv_packed(ctx, t, pk, nullptr, 0, nullptr, &s.JS);
+    if (rc < 0) return drained(rc);
+    ++kmv_count;
+  }
+  hipLaunchKernelGGL(sgdc_start_kernel, grid, block, 0, st, s, dX0 ? 1 : 0);
+  GP_HIP(ctx, hipGetLastError());
+
+  pk.ld = L.gld;
+  pk.done = &s.flags->all_done;
+  s.stride = L.gld * (int64_t)t;
+  const step_fn step = L.ld <= CROWS ? sgdc_step_kernel<1> : L.ld <= 2 * CROWS ? sgdc_step_kernel<2> : L.ld <= 4 * CROWS ? sgdc_step_kernel<4>
+                                                                                                 : sgdc_step_kernel<0>;
+  const size_t lds = L.ld <= 4 * CROWS ? (size_t)L.ld * sizeof(float) : 0;
+  if (lds > 48 * 1024) GP_HIP(ctx, hipFuncSetAttribute((const void*)step, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  const int slices = (batch + GT - 1) / GT;
+  // Steps queued ahead of the flags the host has seen; kernels queued past the end return at once.
+  const int ahead = ctx->prof_mask ? 0 : 4;
+  unsigned long long seen = 0;
+  bool done = false;
+  auto wait_steps = [&](int steps) -> int {
+    const int rc = wait_post(ctx, "gp_sgd_solve", hpost, (unsigned)steps + 1, &seen);
+    done = ((seen >> 32) & COL_DONE) != 0;
+    return rc;
+  };
+  if (!ahead) {
+    const int rc = wait_steps(0);
+    if (rc < 0) return drained(rc);
+  }
+  for (int finished = 0, queued = 0; !done && finished < max_iters; ++finished) {
+    for (; queued < max_iters && queued <= finished + ahead; ++queued) {
+      const int* I = dBatches + (int64_t)queued * batch;
+      const int rc = gp_kmv_packed(ctx, t, pk, I, batch, nullptr, &s.JS);
+      if (rc < 0) return drained(rc);
+      auto* grad = s.JS <= 8 ? sgdc_grad_kernel<8> : s.JS <= 24 ? sgdc_grad_kernel<24> : sgdc_grad_kernel<64>;
+      hipLaunchKernelGGL(grad, dim3(slices, t), dim3(GT), 0, st, s, I);
+      hipLaunchKernelGGL(step, grid, block, lds, st, s, I, slices);
+      GP_HIP(ctx, hipGetLastError());
+    }
+    const int rc = wait_steps(finished + 1);
+    if (rc < 0) return drained(rc);
+  }
+
+  hipLaunchKernelGGL(from_columns_kernel, transpose_grid(L.ld, t, 1), dim3(256), 0, st, (const float*)s.U, L.ld, ctx->n, t,
+                     (const int*)s.zero_rhs, dV, ldv);
+  GP_HIP(ctx, hipGetLastError());
+  GP_HIP(ctx, hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st));
+  GP_HIP(ctx, hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st));
+  GP_HIP(ctx, hipStreamSynchronize(st));
+  if (h_iters) *h_iters = hflags->iters;
+  if (h_kmv_count) *h_kmv_count = kmv_count;
+  if (h_relres)
+    for (int c = 0; c < t; ++c) h_relres[c] = hrel[c];
+  if (hflags->bad == 2) return gp_fail(ctx, GP_ERR_ARG, "gp_sgd_solve: a mini-batch index is outside [0, n)");
+  if (hflags->bad) return gp_fail(ctx, GP_ERR_BREAKDOWN, "gp_sgd_solve: non-finite residual estimate at step %d (learning rate too large?)", hflags->iters);
+  return hflags->all_done ? GP_OK : GP_NOT_CONVERGED;
+}

@@ -44,9 +44,21 @@ struct TileArgsH {
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
+  const int* gather;       // row i of the output is the context's point gather[i] (an index outside [0, npoints) reads point 0); NULL: i
+  int64_t npoints;
   int64_t cm_ld;           // > 0: images are column-major with this many rows per column (a multiple of 32)
   const int* done;         // a non-zero value there turns the launch into a no-op; NULL: always runs
 };
+
+// where this lane's row operands of sub-tile `sub` start (units; + kh * 64 per distance step)
+template <int KH>
+__device__ __forceinline__ int64_t row_operand(const TileArgsH& p, int64_t sub, int lane) {
+  if (!p.gather) return sub * KH * 64 + lane;
+  const int64_t slot = sub * 32 + (lane & 31);
+  const int64_t v = p.gather[slot < p.n ? slot : 0];
+  const int64_t i = v >= 0 && v < p.npoints ? v : 0;
+  return (i >> 5) * KH * 64 + (lane & 32) + (i & 31);
+}
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
@@ -97,7 +109,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert((DEPTH - 1) * LPC < 64, "vmcnt cannot express the pipeline depth");
   __shared__ u32x4 lds[NS][STAGE];
 
-  if (p.done && *p.done) return;
+  const int over = p.done ? *p.done : 0;   // looked at only once the first loads are on their way
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: lets the compiler branch on it
@@ -116,12 +128,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // row-side operands: registers for the whole pass
   f16x8 xb[MI][XP][KH];
 #pragma unroll
-  for (int m = 0; m < MI; ++m)
+  for (int m = 0; m < MI; ++m) {
+    const int64_t at = row_operand<KH>(p, sub0 + m, lane);
 #pragma unroll
     for (int pc = 0; pc < XP; ++pc)
 #pragma unroll
-      for (int kh = 0; kh < KH; ++kh)
-        xb[m][pc][kh] = as_f16x8(p.XB[pc][((int64_t)(sub0 + m) * KH + kh) * 64 + lane]);
+      for (int kh = 0; kh < KH; ++kh) xb[m][pc][kh] = as_f16x8(p.XB[pc][at + kh * 64]);
+  }
 
   f32x16 acc[MI][NT];
   float accv[MI];
@@ -402,6 +415,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // Rounding error of an fp32 accumulator grows with the length of its chain of partial sums, so the
   // accumulators are added into OUT after every segment (the running sum then sees one addition per
   // segment).  The same threads read and write the same elements: no race, fixed order.
+  if (over) return;
   bool first = true;
   for (;;) {
     segment_prologue();
@@ -446,7 +460,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   constexpr int LPW = (2 * G + W - 1) / W;          // group loads per wave and stage; surplus slots repeat the last group
   __shared__ u32x4 lds[2][STAGE];
 
-  if (p.done && *p.done) return;
+  const int over = p.done ? *p.done : 0;   // looked at only once the first loads are on their way
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -461,10 +475,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
   f16x8 xb[XP][KH];
+  const int64_t row_at = row_operand<KH>(p, sub0, lane);
 #pragma unroll
   for (int pc = 0; pc < XP; ++pc)
 #pragma unroll
-    for (int kh = 0; kh < KH; ++kh) xb[pc][kh] = as_f16x8(p.XB[pc][((int64_t)sub0 * KH + kh) * 64 + lane]);
+    for (int kh = 0; kh < KH; ++kh) xb[pc][kh] = as_f16x8(p.XB[pc][row_at + kh * 64]);
 
   static_assert(NT > 0 || Y, "nothing to multiply");
   f32x16 acc[NT > 0 ? NT : 1];
@@ -634,6 +649,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
     }
   };
 
+  if (over) return;
   bool first = true;
   for (;;) {
     int st = 0;
@@ -1015,6 +1031,8 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.a2 = (float)(ctx->a * ctx->a);
   a.sigma2 = (float)(ctx->sigma * ctx->sigma);
   a.add_noise = add_noise;
+  a.gather = nullptr;
+  a.npoints = ctx->n;
   a.cm_ld = 0;
   a.done = nullptr;
 
@@ -1078,15 +1096,17 @@ int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks)
   return most;
 }
 
-int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const KmvRows* rows, const KmvWindow* win, int* images) {
-  const int64_t nrows = rows ? rows->m : ctx->n;
+int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvWindow* win, int* images) {
+  if (!gather) nrows = ctx->n;
   const PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, ctx->XP);
   const int nchunks = win ? win->nchunks : (int)((ctx->n + 31) / 32);
   TileArgsH a;
   for (int pc = 0; pc < 3; ++pc) {
     a.XA[pc] = (const u32x4*)ctx->dXAh[pc] + (win ? (int64_t)win->chunk0 * ctx->KH * 64 : 0);
-    a.XB[pc] = (const u32x4*)(rows ? rows->XBh[pc] : ctx->dXBh[pc]);
+    a.XB[pc] = (const u32x4*)ctx->dXBh[pc];
   }
+  a.gather = gather;
+  a.npoints = ctx->n;
   a.VY = pk.VY;
   a.V = nullptr;
   a.ldv = 0;
@@ -1095,7 +1115,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const KmvRows* rows, 
   a.ldo = 0;
   a.split_stride = pk.ld * (int64_t)t;
   a.n = nrows;
-  a.diag = (rows || win) ? 0 : 1;
+  a.diag = (gather || win) ? 0 : 1;
   a.nchunks = nchunks;
   a.JS = pl.JS;
   a.cps = pl.cps;
