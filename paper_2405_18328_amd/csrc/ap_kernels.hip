@@ -21,12 +21,13 @@
 #include <stdint.h>
 
 #include "gpws_internal.h"
+#include "ap_inverse.h"
 #include "col_streams.h"
 
 namespace {
 
-constexpr int TS = 64;              // tile edge of the factorisation kernels
-constexpr int AP_BATCH = 64;        // blocks factorised side by side (3 x 32 MiB of fp64 scratch each at block 2000)
+constexpr int TS = AP_TILE;         // tile edge of the factorisation kernels
+constexpr int AP_BATCH = AP_FACTOR_BATCH;   // blocks factorised side by side (3 x 32 MiB of fp64 scratch each at block 2000)
 
 typedef double fac_t;
 
@@ -524,10 +525,6 @@ __global__ __launch_bounds__(256) void ap_trinv_merge_kernel(const fac_t* __rest
 // ((r / 16) (BP / 4) + c / 4) 64 + (r % 16) 4 + c % 4.  What one wave of the block solve reads for its
 // row tile and 16 consecutive contraction indices (lane = (row, 4 of them), 16 bytes each) is then one
 // contiguous kilobyte, and the next 16 indices are the next kilobyte.
-__device__ __forceinline__ int64_t hinv_at(int r, int c, int BP) {
-  return ((int64_t)(r >> 4) * (BP >> 2) + (c >> 2)) * 64 + (r & 15) * 4 + (c & 3);
-}
-__device__ __forceinline__ constexpr int hinv_step() { return 64; }   // floats between c and c + 4 at fixed r
 // Workgroups are numbered by super-block (see sb_decode) and walk the contraction index downwards from
 // the same starting tile row, so that the 2 SB tile columns of X a super-block shares stay in its
 // XCD's L2 while they are in use.
@@ -1091,14 +1088,61 @@ ApLayout ap_layout(const gp_ctx* ctx, int t, int block) {
 
 }  // namespace
 
-size_t gp_ap_workspace_bytes_impl(const gp_ctx* ctx, int t, int block) { return ap_layout(ctx, t, block).total; }
+// blocks of a batch share the launches
+int gp_ap_inverses(gp_ctx* ctx, int block, int nb, int BP, int batch, float* Hinv, double* A, double* W, double* TT, double* DI,
+                   int* fac_breakdown) {
+  const int64_t n = ctx->n;
+  hipStream_t st = ctx->stream;
+  const int nt = BP / TS;
+  for (int blk0 = 0; blk0 < nb; blk0 += batch) {
+    const int cnt = nb - blk0 < batch ? nb - blk0 : batch;
+    hipLaunchKernelGGL(ap_build_kernel, dim3(nt, nt, cnt), dim3(256), 2 * TS * (ctx->d + 1) * sizeof(float), st, ctx->dX,
+                       ctx->d, n, (const double*)ctx->dTheta, ctx->kernel, block, BP, blk0, A);
+    for (int k0 = 0; k0 < nt; k0 += CHOL_ROUND) {
+      const int k1 = k0 + CHOL_ROUND < nt ? k0 + CHOL_ROUND : nt;
+      for (int c = k0; c < k1; ++c) {
+        // the round's earlier columns applied to column c (tiles (I, c), I >= c)
+        if (c > k0) hipLaunchKernelGGL(ap_chol_update_kernel, dim3(1, nt - c, cnt), dim3(256), 0, st, A, BP, k0, c - k0, c);
+        hipLaunchKernelGGL(ap_chol_diag_kernel, dim3(cnt), dim3(256), 0, st, A, BP, c, DI, W, fac_breakdown);
+        if (nt - c - 1 > 0)
+          hipLaunchKernelGGL(ap_chol_panel_kernel, dim3(nt - c - 1, cnt), dim3(256), 0, st, A, BP, c, (const fac_t*)DI);
+      }
+      // the whole round applied to everything past it
+      const int rest = nt - k1;
+      if (rest > 0) hipLaunchKernelGGL(ap_chol_update_kernel, dim3(rest, rest, cnt), dim3(256), 0, st, A, BP, k0, k1 - k0, k1);
+    }
+    for (int sz = 1; sz < nt; sz *= 2) {
+      const int pairs = (nt + 2 * sz - 1) / (2 * sz);
+      for (int step = 0; step < 2; ++step)
+        hipLaunchKernelGGL(ap_trinv_merge_kernel, dim3(sz, sz, pairs * cnt), dim3(256), 0, st, (const fac_t*)A, W, TT, BP, sz,
+                           pairs, step);
+    }
+    {
+      const int sbs = cnt * lauum_superblocks(nt);
+      hipLaunchKernelGGL(ap_lauum_kernel, dim3(sb_grid(sbs, SB)), dim3(256), 0, st,
+                         (const fac_t*)W, BP, cnt, Hinv + (size_t)blk0 * BP * BP);
+    }
+    GP_HIP(ctx, hipGetLastError());
+  }
+  return GP_OK;
+}
+
+// covers both forms of the solver: theta, and with it the product path, may change after the caller asked
+size_t gp_ap_workspace_bytes_impl(const gp_ctx* ctx, int t, int block) {
+  const size_t streams = ap_layout(ctx, t, block).total;
+  const size_t columns = gp_ap_by_columns(ctx, block) ? gp_ap_columns_workspace_bytes(ctx, t, block) : 0;
+  return streams > columns ? streams : columns;
+}
 
 int gp_ap_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
               const float* h_tol, int block, int max_iters, void* dWork, size_t work_bytes, int* h_iters,
               int* h_kmv_count, float* h_relres, int* h_picks) {
   const ApLayout L = ap_layout(ctx, t, block);
-  if (work_bytes < L.total) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_ap_solve: workspace %zu < %zu bytes", work_bytes, L.total);
+  const size_t need = gp_ap_workspace_bytes_impl(ctx, t, block);
+  if (work_bytes < need) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_ap_solve: workspace %zu < %zu bytes", work_bytes, need);
   if ((uintptr_t)dWork % 256) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_ap_solve: workspace not 256-byte aligned");
+  if (gp_ap_by_columns(ctx, block) && ctx->path != GP_PATH_FP32)
+    return gp_ap_columns_run(ctx, dB, ldb, dX0, dV, ldv, t, h_tol, block, max_iters, dWork, h_iters, h_kmv_count, h_relres, h_picks);
   hipStream_t st = ctx->stream;
   const int64_t n = ctx->n;
   char* w = (char*)dWork;
@@ -1162,38 +1206,11 @@ int gp_ap_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float
     return GP_OK;
   };
 
-  // ---- set-up: the inverse of every diagonal block, AP_BATCH blocks per round of launches
-  const int BP = L.BP, nt = BP / TS;
-  for (int blk0 = 0; blk0 < L.nb; blk0 += L.batch) {
-    const int cnt = L.nb - blk0 < L.batch ? L.nb - blk0 : L.batch;
-    hipLaunchKernelGGL(ap_build_kernel, dim3(nt, nt, cnt), dim3(256), 2 * TS * (ctx->d + 1) * sizeof(float), st, ctx->dX,
-                       ctx->d, n, (const double*)ctx->dTheta, ctx->kernel, block, BP, blk0, A);
-    for (int k0 = 0; k0 < nt; k0 += CHOL_ROUND) {
-      const int k1 = k0 + CHOL_ROUND < nt ? k0 + CHOL_ROUND : nt;
-      for (int c = k0; c < k1; ++c) {
-        // the round's earlier columns applied to column c (tiles (I, c), I >= c)
-        if (c > k0) hipLaunchKernelGGL(ap_chol_update_kernel, dim3(1, nt - c, cnt), dim3(256), 0, st, A, BP, k0, c - k0, c);
-        hipLaunchKernelGGL(ap_chol_diag_kernel, dim3(cnt), dim3(256), 0, st, A, BP, c, DI, W, fac_breakdown);
-        if (nt - c - 1 > 0)
-          hipLaunchKernelGGL(ap_chol_panel_kernel, dim3(nt - c - 1, cnt), dim3(256), 0, st, A, BP, c, (const fac_t*)DI);
-      }
-      // the whole round applied to everything past it
-      const int rest = nt - k1;
-      if (rest > 0) hipLaunchKernelGGL(ap_chol_update_kernel, dim3(rest, rest, cnt), dim3(256), 0, st, A, BP, k0, k1 - k0, k1);
-    }
-    for (int sz = 1; sz < nt; sz *= 2) {
-      const int pairs = (nt + 2 * sz - 1) / (2 * sz);
-      for (int step = 0; step < 2; ++step)
-        hipLaunchKernelGGL(ap_trinv_merge_kernel, dim3(sz, sz, pairs * cnt), dim3(256), 0, st, (const fac_t*)A, W, TT, BP, sz,
-                           pairs, step);
-    }
-    {
-      const int sbs = cnt * lauum_superblocks(nt);
-      hipLaunchKernelGGL(ap_lauum_kernel, dim3(sb_grid(sbs, SB)), dim3(256), 0, st,
-                         (const fac_t*)W, BP, cnt, Hinv + (size_t)blk0 * BP * BP);
-    }
-    GP_HIP(ctx, hipGetLastError());
+  {
+    const int rc = gp_ap_inverses(ctx, block, L.nb, L.BP, L.batch, Hinv, A, W, TT, DI, fac_breakdown);
+    if (rc < 0) return rc;
   }
+  const int BP = L.BP;
 
   // ---- initial residual
   int kmv_count = 0;

@@ -203,10 +203,18 @@ struct KmvPacked {
   int64_t ld;              // rows per column, a multiple of 32
   const int* done;         // device flag that turns the launch into a no-op, or NULL
 };
+// Contraction over the columns of one block of consecutive points, chosen on the device: points sel block ..
+// sel block + block - 1.  Operands and the vector-ALU column are counted from the chunk the block starts in, zero for
+// the points of its first and last chunk that are not the block's.
+struct KmvBlock {
+  const int* sel;
+  int block;
+  int nchunks;   // chunks a block can touch
+};
 int64_t gp_packed_units(int t, int64_t nchunks);
 int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks = 0);   // most images such a product leaves
 // gather: device, nrows indices of the context's points that are the rows of the product (NULL: all n, in order)
-int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvWindow* win, int* images);
+int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvBlock* win, int* images);
 
 // colmax[c] = bit pattern of max_i |V_ic| for c < t, stream-ordered; optionally the same for a second
 // n x t matrix in the same launch.  cleared = true: the caller has already zeroed the output words.
@@ -218,6 +226,20 @@ size_t gp_ap_workspace_bytes_impl(const gp_ctx* ctx, int t, int block);
 int gp_ap_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
               const float* h_tol, int block, int max_iters, void* dWork, size_t work_bytes, int* h_iters,
               int* h_kmv_count, float* h_relres, int* h_picks);
+
+// the inverse of every diagonal block of H (fp32, layout of ap_inverse.h), for the current theta; scratch: batch blocks of BP^2 doubles
+// (A, W, T) and batch BP 64 doubles (DI); *breakdown is raised when a block is not positive definite
+int gp_ap_inverses(gp_ctx* ctx, int block, int nb, int BP, int batch, float* Hinv, double* A, double* W, double* T, double* DI,
+                   int* breakdown);
+
+// ---- ap_columns.hip: the same solve for problems up to this size and this many blocks on the f16 product paths
+constexpr int64_t AP_COLUMNS_MAX_N = 65536;
+constexpr int AP_COLUMNS_MAX_BLOCKS = 256;
+bool gp_ap_by_columns(const gp_ctx* ctx, int block);
+size_t gp_ap_columns_workspace_bytes(const gp_ctx* ctx, int t, int block);
+int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
+                      const float* h_tol, int block, int max_iters, void* dWork, int* h_iters, int* h_kmv_count,
+                      float* h_relres, int* h_picks);
 
 // ---- sgd_kernels.hip
 size_t gp_sgd_workspace_bytes_impl(const gp_ctx* ctx, int t, int batch);

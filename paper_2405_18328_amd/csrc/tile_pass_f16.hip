@@ -44,6 +44,8 @@ struct TileArgsH {
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
+  const int* win_sel;      // contraction over the columns of block *win_sel (win_block points each): XA starts at that block's
+  int win_block;           // first chunk, and chunks past the last one are not there; NULL: XA as it is
   const int* gather;       // row i of the output is the context's point gather[i] (an index outside [0, npoints) reads point 0); NULL: i
   int64_t npoints;
   int64_t cm_ld;           // > 0: images are column-major with this many rows per column (a multiple of 32)
@@ -58,6 +60,11 @@ __device__ __forceinline__ int64_t row_operand(const TileArgsH& p, int64_t sub, 
   const int64_t v = p.gather[slot < p.n ? slot : 0];
   const int64_t i = v >= 0 && v < p.npoints ? v : 0;
   return (i >> 5) * KH * 64 + (lane & 32) + (i & 31);
+}
+
+// first chunk of the column side (0 unless the launch works on a block chosen on the device)
+__device__ __forceinline__ int64_t window_chunk(const TileArgsH& p) {
+  return p.win_sel ? ((int64_t)*p.win_sel * p.win_block) >> 5 : 0;
 }
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
@@ -120,8 +127,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int sub0 = (rb * W + wave) * MI;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
+  const int64_t chunk0 = window_chunk(p);
   const int r_begin = js * p.cps;
-  const int r_end = min(p.nchunks, r_begin + p.cps);
+  const int r_end = (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0);
   int c_begin = r_begin;
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
@@ -159,7 +167,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int x = 0; x < LPW; ++x) {
     const int g = min(wave + W * x, G - 1);
     if (g < XA_G) {
-      g_src[x] = p.XA[g / KH] + (g % KH) * 64 + lane;
+      g_src[x] = p.XA[g / KH] + (chunk0 * KH + g % KH) * 64 + lane;
       g_stride[x] = KH * 64;
     } else {
       g_src[x] = p.VP + (g - XA_G) * 64 + lane;
@@ -417,6 +425,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // segment).  The same threads read and write the same elements: no race, fixed order.
   if (over) return;
   bool first = true;
+  if (r_begin >= r_end) {   // a block at the end of the points is shorter than the launch
+    flush(true);
+    return;
+  }
   for (;;) {
     segment_prologue();
     for (int ch = c_begin; ch < c_end; ch += 2) {
@@ -469,8 +481,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   const int js = blockIdx.x % p.JS;
   const int rb = blockIdx.x / p.JS;
   const int sub0 = rb * W + wave;
+  const int64_t chunk0 = window_chunk(p);
   const int r_begin = js * p.cps;
-  const int r_end = min(p.nchunks, r_begin + p.cps);
+  const int r_end = (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0);
   int c_begin = r_begin;
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
@@ -502,7 +515,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
       const int gc = g >= G ? g - G : g;
       const int ch = min(g >= G ? ch0 + 1 : ch0, c_end - 1);     // past the end: harmless reload of the last chunk
       const u32x4* src;
-      if (gc < XA_G) src = p.XA[gc / KH] + ((int64_t)ch * KH + gc % KH) * 64;
+      if (gc < XA_G) src = p.XA[gc / KH] + ((chunk0 + ch) * KH + gc % KH) * 64;
       else src = p.VP + ((int64_t)ch * V_G + (gc - XA_G)) * 64;
       dma16((uint64_t)src, lane16, lds_base + 16u * (unsigned)(st * STAGE + g * 64));
     }
@@ -651,6 +664,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
 
   if (over) return;
   bool first = true;
+  if (r_begin >= r_end) {
+    flush(true);
+    return;
+  }
   for (;;) {
     int st = 0;
     issue_pair(c_begin, 0);
@@ -1031,8 +1048,10 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.a2 = (float)(ctx->a * ctx->a);
   a.sigma2 = (float)(ctx->sigma * ctx->sigma);
   a.add_noise = add_noise;
+  a.win_sel = nullptr;
+  a.win_block = 0;
   a.gather = nullptr;
-  a.npoints = ctx->n;
+  a.npoints = ctx->n - first;
   a.cm_ld = 0;
   a.done = nullptr;
 
@@ -1096,15 +1115,17 @@ int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks)
   return most;
 }
 
-int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvWindow* win, int* images) {
+int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvBlock* win, int* images) {
   if (!gather) nrows = ctx->n;
   const PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, ctx->XP);
   const int nchunks = win ? win->nchunks : (int)((ctx->n + 31) / 32);
   TileArgsH a;
   for (int pc = 0; pc < 3; ++pc) {
-    a.XA[pc] = (const u32x4*)ctx->dXAh[pc] + (win ? (int64_t)win->chunk0 * ctx->KH * 64 : 0);
+    a.XA[pc] = (const u32x4*)ctx->dXAh[pc];
     a.XB[pc] = (const u32x4*)ctx->dXBh[pc];
   }
+  a.win_sel = win ? win->sel : nullptr;
+  a.win_block = win ? win->block : 0;
   a.gather = gather;
   a.npoints = ctx->n;
   a.VY = pk.VY;
