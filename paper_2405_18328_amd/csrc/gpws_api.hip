@@ -111,6 +111,8 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
       GP_HIP(ctx, hipMalloc(&ctx->dXBh[pc], units * 16));
     }
   }
+  GP_HIP(ctx, hipMalloc((void**)&ctx->dColmax, sizeof(unsigned) * GP_MAX_T));
+  GP_HIP(ctx, hipMemsetAsync(ctx->dColmax, 0, sizeof(unsigned) * GP_MAX_T, ctx->stream));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dMean, sizeof(double) * d));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dTheta, sizeof(double) * (d + 2)));
   ctx->red_bytes = (size_t)1 << 22;
@@ -133,6 +135,7 @@ int gp_destroy(gp_ctx* ctx) {
     if (ctx->dXAh[pc]) (void)hipFree(ctx->dXAh[pc]);
     if (ctx->dXBh[pc]) (void)hipFree(ctx->dXBh[pc]);
   }
+  if (ctx->dColmax) (void)hipFree(ctx->dColmax);
   if (ctx->dMean) (void)hipFree(ctx->dMean);
   if (ctx->dTheta) (void)hipFree(ctx->dTheta);
   if (ctx->dRed) (void)hipFree(ctx->dRed);

@@ -44,6 +44,8 @@ struct TileArgsH {
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
+  unsigned* clear;         // column maxima in accumulation: everyone has read them, workgroup 0 zeroes them (clear_n words); NULL: none
+  int clear_n;
   const int* win_sel;      // contraction over the columns of block *win_sel (win_block points each): XA starts at that block's
   int win_block;           // first chunk, and chunks past the last one are not there; NULL: XA as it is
   const int* gather;       // row i of the output is the context's point gather[i] (an index outside [0, npoints) reads point 0); NULL: i
@@ -117,6 +119,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ u32x4 lds[NS][STAGE];
 
   const int over = p.done ? *p.done : 0;   // looked at only once the first loads are on their way
+  if (p.clear && blockIdx.x == 0)
+    for (int c = threadIdx.x; c < p.clear_n; c += blockDim.x) p.clear[c] = 0u;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: lets the compiler branch on it
@@ -473,6 +477,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   __shared__ u32x4 lds[2][STAGE];
 
   const int over = p.done ? *p.done : 0;   // looked at only once the first loads are on their way
+  if (p.clear && blockIdx.x == 0)
+    for (int c = threadIdx.x; c < p.clear_n; c += blockDim.x) p.clear[c] = 0u;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -748,7 +754,9 @@ __global__ __launch_bounds__(256) void clear_words_kernel(unsigned* __restrict__
 __global__ __launch_bounds__(256) void pack_v_kernel(const float* __restrict__ V, int64_t ldv, int64_t n, int nchunks,
                                                      int NT, int col0, int ncols, int vcol,
                                                      const unsigned* __restrict__ colmax, u32x4* __restrict__ VP,
-                                                     float* __restrict__ VY) {
+                                                     float* __restrict__ VY, unsigned* __restrict__ copy, int copy_n) {
+  if (copy && blockIdx.x == 0)      // the maxima as the tile kernel and later passes read them
+    for (int c = threadIdx.x; c < copy_n; c += 256) copy[c] = colmax[c];
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t total = (int64_t)nchunks * 2 * NT * 64;
   if (gid < total) {
@@ -786,15 +794,102 @@ __global__ __launch_bounds__(256) void pack_v_kernel(const float* __restrict__ V
   if (gid < npad) VY[gid] = (vcol >= 0 && gid < n) ? V[gid * ldv + vcol] : 0.0f;
 }
 
-__global__ void kmv_reduce_f16_kernel(const float* __restrict__ part, int64_t split_stride, int JS, int64_t n, int t,
-                                      float* __restrict__ out, int64_t ldo) {
+// Maxima and operands of all columns of a short V (n <= 8192, one column pass) in one launch: eight columns per
+// workgroup, a thread keeps up to NQ quads of rows of one column in registers between the two.  Instead of a pass over V
+// for the maxima, a second one for the operands, and the gap between them: gp_kmv at n = 2048, d = 8, t = 17 went
+// from 20.4 to 15.2 us.  Beyond 8192 rows a workgroup would hold too few loads in flight for the bytes it has to fetch.
+template <int NQ>
+__global__ __launch_bounds__(1024) void pack_small_kernel(const float* __restrict__ V, int64_t ldv, int n, int nchunks, int NT,
+                                                          int c0, int t, unsigned* __restrict__ colmax,
+                                                          u32x4* __restrict__ VP, float* __restrict__ VY) {
+  __shared__ float top[16][8];
+  const int tid = threadIdx.x, ql = tid >> 3;
+  const int c = 8 * blockIdx.x + (tid & 7);
+  const bool cok = c < t;
+  const int nk = 8 * nchunks;
+  f32x4 v[NQ];
+  float mx = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 4 * (ql + 128 * j) + q;
+      v[j][q] = (cok && i < n) ? V[(int64_t)i * ldv + c] : 0.0f;
+    }
+#pragma unroll
+  for (int j = 0; j < NQ; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[j][q]));
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if ((tid & 63) < 8) top[tid >> 6][tid & 7] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) mx = fmaxf(mx, top[w][tid & 7]);
+  if (tid < 8 && cok) colmax[c] = __float_as_uint(mx);
+  const int cc = c - c0;
+  if (cc >= 32 * NT) return;
+  const float scale = cc < 0 ? 1.0f : ldexpf(1.0f, V_TOP - column_exponent(__float_as_uint(mx)));
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    const int k = ql + 128 * j;
+    if (k >= nk) break;                  // whole groups of eight quads
+    const f32x4 w = v[j] * scale;
+    float h[4], l[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      h[q] = __uint_as_float(__float_as_uint(w[q]) & HI_MASK);
+      l[q] = w[q] - h[q];
+    }
+    const unsigned hi0 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[0], h[1]));
+    const unsigned hi1 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[2], h[3]));
+    const unsigned lo0 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[0], l[1]));
+    const unsigned lo1 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[2], l[3]));
+    const bool up = (k & 2) != 0;        // quads k and k + 2 (sixteen lanes on) make up one high and one low unit
+    const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi0 : lo0), 16);
+    const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi1 : lo1), 16);
+    if (cc < 0) {
+      *reinterpret_cast<f32x4*>(VY + 4 * k) = v[j];
+    } else {
+      const u32x4 unit = up ? u32x4{x0, x1, lo0, lo1} : u32x4{hi0, hi1, x0, x1};
+      VP[((int64_t)((k >> 2) * NT + (cc >> 5)) * 2 + (up ? 1 : 0)) * 64 + (cc & 31) + 32 * (k & 1)] = unit;
+    }
+  }
+}
+
+// OUT = sum of the partial images, in order.  A chain of dependent loads bounded it (one element per thread, one image
+// after the other); now four consecutive elements per thread, eight images fetched at a time.  With the clearing launch
+// of the column maxima gone, gp_predict n = 13500, m = 1500, t = 65: 79 -> 70 us; n = 41157, m = 4573, t = 1: 85 -> 78 us.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+__global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __restrict__ part, int64_t split_stride, int JS, int64_t n,
+                                                             int t, float* __restrict__ out, int64_t ldo) {
   const int64_t total = n * t;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / t;
-    const int c = (int)(e - i * t);
-    float s = 0.0f;
-    for (int k = 0; k < JS; ++k) s += part[(int64_t)k * split_stride + e];
-    out[i * ldo + c] = s;
+  for (int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; e < total; e += (int64_t)gridDim.x * 1024) {
+    const int64_t at = e + 4 <= total ? e : total - (total < 4 ? total : 4);   // the last thread's four overlap its neighbour's
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (total >= 4) {
+      for (int k = 0; k < JS; k += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f4u*>(part + (int64_t)min(k + u, JS - 1) * split_stride + at);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (k + u < JS) s += v[u];
+      }
+    } else {
+      for (int q = 0; q < (int)total; ++q)
+        for (int k = 0; k < JS; ++k) s[q] += part[(int64_t)k * split_stride + q];
+    }
+    int64_t i = at / t;
+    int c = (int)(at - i * t);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (at + q < total) out[i * ldo + c] = s[q];
+      if (++c == t) {
+        c = 0;
+        ++i;
+      }
+    }
   }
 }
 
@@ -1022,8 +1117,15 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   if (win && !colmax_ready) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: a column window needs the column maxima");
   const float* dVw = dV + first * ldv;
 
-  if (!colmax_ready && t > 1) {   // a single vector is not scaled
-    const int rc = gp_launch_colmax(ctx, dV, ldv, t, (unsigned*)(w + L.off_colmax));
+  // column maxima: the caller's; or taken while the operands are packed (short V, one pass); or accumulated in words of the
+  // context that are zero between calls, copied by the first packing and zeroed again by the first tile pass; on the static
+  // scratch in words of that scratch, cleared by a launch of their own: a captured gp_kmv_static may run beside other calls
+  const bool y = has_vec_column(t);
+  const bool small = !colmax_ready && !win && t > 1 && ctx->n <= 8192 && t - (y ? 1 : 0) <= 64;
+  const bool maxima = !colmax_ready && t > 1 && !small;       // a single vector is not scaled
+  const bool accumulate = maxima && scratch != ctx->static_scratch;
+  if (maxima) {
+    const int rc = gp_launch_colmax(ctx, dV, ldv, t, accumulate ? ctx->dColmax : (unsigned*)(w + L.off_colmax), nullptr, 0, nullptr, accumulate);
     if (rc < 0) return rc;
   }
 
@@ -1055,21 +1157,31 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.cm_ld = 0;
   a.done = nullptr;
 
-  int vcol = has_vec_column(t) ? 0 : -1;
+  int vcol = y ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;
+  bool first_pass = true;
   do {
     const int rem = t - c;
     const int NT = pass_tiles(rem);
     a.col0 = c;
     a.ncols = rem < 32 * NT ? rem : 32 * NT;
     a.vcol = vcol;
-    {
+    if (small) {
+      const int quads = (8 * nchunks + 127) / 128;
+      auto* pack = quads <= 2 ? pack_small_kernel<2> : quads <= 4 ? pack_small_kernel<4> : quads <= 8 ? pack_small_kernel<8> : pack_small_kernel<16>;
+      hipLaunchKernelGGL(pack, dim3((unsigned)((c + 32 * NT + 7) / 8)), dim3(1024), 0, st, dV, ldv, (int)ctx->n, nchunks, NT, c, t,
+                         (unsigned*)(w + L.off_colmax), VP, VY);
+    } else {
       const int64_t threads = (int64_t)nchunks * 2 * NT * 64;
       const int64_t need = threads > (int64_t)nchunks * 32 ? threads : (int64_t)nchunks * 32;
       hipLaunchKernelGGL(pack_v_kernel, dim3((unsigned)((need + 255) / 256)), dim3(256), 0, st, dVw, ldv, ncontr, nchunks, NT,
-                         a.col0, a.ncols, vcol, (const unsigned*)colmax, VP, VY);
-      GP_HIP(ctx, hipGetLastError());
+                         a.col0, a.ncols, vcol, accumulate && first_pass ? (const unsigned*)ctx->dColmax : colmax, VP, VY,
+                         accumulate && first_pass ? (unsigned*)(w + L.off_colmax) : nullptr, t);
     }
+    GP_HIP(ctx, hipGetLastError());
+    a.clear = accumulate && first_pass ? ctx->dColmax : nullptr;
+    a.clear_n = t;
+    first_pass = false;
     vcol = -1;
     const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
@@ -1087,8 +1199,8 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   }
   if (split && !defer) {
     const int64_t total = nrows * (int64_t)t;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 4 * ctx->num_cu) blocks = 4 * ctx->num_cu;
+    int blocks = (int)((total + 1023) / 1024);
+    if (blocks > 8 * ctx->num_cu) blocks = 8 * ctx->num_cu;
     hipLaunchKernelGGL(kmv_reduce_f16_kernel, dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, pl.JS,
                        nrows, t, dOut, ldo);
     GP_HIP(ctx, hipGetLastError());
@@ -1128,6 +1240,8 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
   a.win_block = win ? win->block : 0;
   a.gather = gather;
   a.npoints = ctx->n;
+  a.clear = nullptr;
+  a.clear_n = 0;
   a.VY = pk.VY;
   a.V = nullptr;
   a.ldv = 0;

@@ -4,7 +4,10 @@
     fp16 paths, single rows, tile edges, an odd chunk count, and the rectangular product with few rows;
   - d <= 29, t > 32 and n at and past 32768: the kernel with four waves per SIMD, with and without the
     vector-ALU column, and a second column pass on the other kernel;
-  - t <= 32 at n past 8192: two sub-tiles per wave for both short distance chains.
+  - t <= 32 at n past 8192: two sub-tiles per wave for both short distance chains;
+  - n <= 8192, one column pass: operands packed in one launch, at the edges of its rows per thread and
+    of its groups of eight columns; and repeated calls of different widths around it, since the column
+    maxima of longer products are accumulated in words that every call has to leave clear.
 """
 import numpy as np
 import pytest
@@ -60,5 +63,21 @@ def test_kernel_choice_by_size(monkeypatch, path, n, d, kind, t):
     dv = Dev(X, kind, ell, 0.9, 0.5)
     try:
         assert relerr(dv.kmv(V, 1, ldv=t + 3, ldo=t + 1)[rows], ref) <= KMV_TOL
+    finally:
+        dv.close()
+
+
+@pytest.mark.parametrize("n", [1, 33, 1024, 1025, 2049, 4096, 4097, 8192, 8193])
+def test_short_pack_and_column_maxima(n):
+    X, V, ell = _case(n, 7, "matern32", 97)
+    V *= np.exp2(np.random.default_rng(2).integers(-9, 10, size=97)).astype(np.float32)    # columns of very different size
+    rows = _rows(n, 32)
+    ref = orc.kmv_rows(X, ell, 1.1, "matern32", V, rows, sigma=0.3)
+    dv = Dev(X, "matern32", ell, 1.1, 0.3)
+    try:
+        for c0, t in [(0, 97), (40, 2), (0, 64), (8, 65), (31, 66), (60, 9), (0, 33), (5, 8), (64, 31)]:
+            got = dv.kmv(np.ascontiguousarray(V[:, c0:c0 + t]), 1)[rows]
+            for c in range(t):
+                assert relerr(got[:, c], ref[:, c0 + c]) <= KMV_TOL, (t, c)
     finally:
         dv.close()
