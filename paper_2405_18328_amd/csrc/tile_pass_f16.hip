@@ -99,7 +99,10 @@ __device__ __forceinline__ void store_column_quads(float* dst, bool ok, bool fir
 // Two waves per SIMD with two software pipelines.  Four wavefronts per workgroup: every workgroup streams all
 // of V' and XA through its LDS, so the L2-to-LDS traffic of a launch is inversely proportional to the
 // rows a workgroup owns (128 MI; eight waves halve the traffic and measured no faster).
-template <int KIND, int KH, int XP, int NT, int MI, bool Y>
+// CM: compiled with what the column solvers ask for (row gather, column window, column-major images, early return).  The
+// widest shape (KH = 1, NT = 2, MI = 2) has no registers for it: with that code in it spilled 65 instead of 27
+// registers and gp_kmv at n = 2000000 d = 11 t = 65 took 1.93 s instead of 1.61 s, so it is built both ways.
+template <int KIND, int KH, int XP, int NT, int MI, bool Y, bool CM = true>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void kmv_tile_f16_kernel(TileArgsH p) {
   // One pipeline stage in LDS, in 16-byte units: G groups of 64 units (one wave-wide 16-byte load
   // each): XP*KH groups of XA pieces, then 4*NT groups of V' images; then one 8-unit y slot per wave.
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert((DEPTH - 1) * LPC < 64, "vmcnt cannot express the pipeline depth");
   __shared__ u32x4 lds[NS][STAGE];
 
-  const int over = p.done ? *p.done : 0;   // looked at only once the first loads are on their way
+  const int over = CM && p.done ? *p.done : 0;   // looked at only once the first loads are on their way
   if (p.clear && blockIdx.x == 0)
     for (int c = threadIdx.x; c < p.clear_n; c += blockDim.x) p.clear[c] = 0u;
   const int tid = threadIdx.x;
@@ -131,9 +134,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int sub0 = (rb * W + wave) * MI;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
-  const int64_t chunk0 = window_chunk(p);
+  const int64_t chunk0 = CM ? window_chunk(p) : 0;
   const int r_begin = js * p.cps;
-  const int r_end = (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0);
+  const int r_end = CM ? (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0) : min(p.nchunks, r_begin + p.cps);
   int c_begin = r_begin;
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   f16x8 xb[MI][XP][KH];
 #pragma unroll
   for (int m = 0; m < MI; ++m) {
-    const int64_t at = row_operand<KH>(p, sub0 + m, lane);
+    const int64_t at = CM ? row_operand<KH>(p, sub0 + m, lane) : (int64_t)(sub0 + m) * KH * 64 + lane;
 #pragma unroll
     for (int pc = 0; pc < XP; ++pc)
 #pragma unroll
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
       const int64_t ibase = (int64_t)(sub0 + m) * 32 + zero;
-      if (p.cm_ld) {
+      if (CM && p.cm_ld) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const int c = li + 32 * nt;
@@ -429,7 +432,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // segment).  The same threads read and write the same elements: no race, fixed order.
   if (over) return;
   bool first = true;
-  if (r_begin >= r_end) {   // a block at the end of the points is shorter than the launch
+  if (CM && r_begin >= r_end) {   // a block at the end of the points is shorter than the launch
     flush(true);
     return;
   }
@@ -896,8 +899,9 @@ __global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __rest
 typedef void (*tileh_fn)(TileArgsH);
 
 template <int KIND, int KH, int XP, bool Y>
-tileh_fn pick_h_nt_mi(int NT, int MI) {
+tileh_fn pick_h_nt_mi(int NT, int MI, bool cm) {
   if constexpr (KH == 1) {
+    if (MI == 2 && NT == 2 && !cm) return kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, Y, false>;
     if (MI == 2) return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, Y> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, Y>;
   }
   if constexpr (KH == 2) {
@@ -907,14 +911,14 @@ tileh_fn pick_h_nt_mi(int NT, int MI) {
 }
 
 template <int KIND, int XP, bool Y>
-tileh_fn pick_h_kh(int KH, int NT, int MI) {
+tileh_fn pick_h_kh(int KH, int NT, int MI, bool cm) {
   switch (KH) {
-    case 1: return pick_h_nt_mi<KIND, 1, XP, Y>(NT, MI);
-    case 2: return pick_h_nt_mi<KIND, 2, XP, Y>(NT, MI);
-    case 3: return pick_h_nt_mi<KIND, 3, XP, Y>(NT, MI);
-    case 4: return pick_h_nt_mi<KIND, 4, XP, Y>(NT, MI);
-    case 6: return pick_h_nt_mi<KIND, 6, XP, Y>(NT, MI);
-    case 8: return pick_h_nt_mi<KIND, 8, XP, Y>(NT, MI);
+    case 1: return pick_h_nt_mi<KIND, 1, XP, Y>(NT, MI, cm);
+    case 2: return pick_h_nt_mi<KIND, 2, XP, Y>(NT, MI, cm);
+    case 3: return pick_h_nt_mi<KIND, 3, XP, Y>(NT, MI, cm);
+    case 4: return pick_h_nt_mi<KIND, 4, XP, Y>(NT, MI, cm);
+    case 6: return pick_h_nt_mi<KIND, 6, XP, Y>(NT, MI, cm);
+    case 8: return pick_h_nt_mi<KIND, 8, XP, Y>(NT, MI, cm);
   }
   return nullptr;
 }
@@ -933,10 +937,10 @@ tileh_fn pick_vec_kh(int KH) {
 }
 
 template <int KIND, int XP>
-tileh_fn pick_h(int KH, int NT, int MI, bool wide, bool y) {
+tileh_fn pick_h(int KH, int NT, int MI, bool wide, bool y, bool cm) {
   if (NT == 0) return pick_vec_kh<KIND, XP>(KH);
   if (wide) return y ? kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, true> : kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, false>;
-  return y ? pick_h_kh<KIND, XP, true>(KH, NT, MI) : pick_h_kh<KIND, XP, false>(KH, NT, MI);
+  return y ? pick_h_kh<KIND, XP, true>(KH, NT, MI, cm) : pick_h_kh<KIND, XP, false>(KH, NT, MI, cm);
 }
 
 // The kernel of one column pass of NT tiles (y: with the extra vector-ALU column).
@@ -947,7 +951,8 @@ struct TileKernelH {
   double chunk_us;         // about what a chunk takes one of them
 };
 
-TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool y) {
+// cm: the launch sets any of done, win_sel, gather and cm_ld (the shape does not depend on it)
+TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool y, bool cm) {
   TileKernelH k;
   const int KH = ctx->KH;
   // The wide kernel where it is ahead (see there) and has rows enough: it takes twice the waves to fill the chip, so
@@ -956,8 +961,8 @@ TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool 
   // single contraction tile) the second sub-tile no longer fits the register file without spills.
   const bool wide = NT == 0 || (NT == 2 && KH == 2 && rows >= 32768);
   const int MI = !wide && rows >= 8192 && (KH == 1 || (KH == 2 && NT == 1)) ? 2 : 1;
-  if (ctx->kernel == GP_SE_ARD) k.fn = XP == 2 ? pick_h<GP_SE_ARD, 2>(KH, NT, MI, wide, y) : pick_h<GP_SE_ARD, 3>(KH, NT, MI, wide, y);
-  else k.fn = XP == 2 ? pick_h<GP_MATERN32_ARD, 2>(KH, NT, MI, wide, y) : pick_h<GP_MATERN32_ARD, 3>(KH, NT, MI, wide, y);
+  if (ctx->kernel == GP_SE_ARD) k.fn = XP == 2 ? pick_h<GP_SE_ARD, 2>(KH, NT, MI, wide, y, cm) : pick_h<GP_SE_ARD, 3>(KH, NT, MI, wide, y, cm);
+  else k.fn = XP == 2 ? pick_h<GP_MATERN32_ARD, 2>(KH, NT, MI, wide, y, cm) : pick_h<GP_MATERN32_ARD, 3>(KH, NT, MI, wide, y, cm);
   k.rows_per_wg = wide ? 256 : 128 * MI;
   k.threads = wide ? 512 : 256;
   if (wide) {
@@ -1011,7 +1016,7 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
       return pl;
     }
   const bool y = has_vec_column(t);
-  const TileKernelH k = tile_kernel_h(ctx, rows, XP, pass_tiles(y ? t - 1 : t), y);
+  const TileKernelH k = tile_kernel_h(ctx, rows, XP, pass_tiles(y ? t - 1 : t), y, false);
   const int row_blocks = (int)((rows + k.rows_per_wg - 1) / k.rows_per_wg);
   // a partial image is written and read once, at about 4 TB/s
   const double image = (double)rows * t * sizeof(float);
@@ -1183,7 +1188,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     a.clear_n = t;
     first_pass = false;
     vcol = -1;
-    const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0);
+    const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0, false);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
     const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
     const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
@@ -1269,7 +1274,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
     a.ncols = rem < 32 * NT ? rem : 32 * NT;
     a.vcol = vcol;
     vcol = -1;
-    const TileKernelH k = tile_kernel_h(ctx, nrows, ctx->XP, NT, a.vcol >= 0);
+    const TileKernelH k = tile_kernel_h(ctx, nrows, ctx->XP, NT, a.vcol >= 0, true);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
     const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
     const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
