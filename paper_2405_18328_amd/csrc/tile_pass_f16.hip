@@ -1051,6 +1051,10 @@ int gp_kh_bucket(int d, int kernel) {
 int gp_column_splits(int row_blocks, int64_t chunks, int slots, double image_cost, int max_splits) {
   constexpr double FIXED = 4.0;       // prologue and flush of a workgroup, in chunks
   constexpr int MIN_CHUNKS = 4;
+  // Past four generations the workgroups have drifted apart, which fills the last one by itself, and column ranges only
+  // cost locality: 3.1 generations (n = 400000 d = 3 t = 65) split 450 -> 424 ms a CG step; 7.6 (n = 500000 d = 90) 221 ->
+  // 225 ms, 15.3 (n = 2000000 d = 11) 1590 -> 1690 ms a product.
+  if (row_blocks > 4 * slots) return 1;
   int best = 1;
   double best_cost = 1e300;
   for (int js = 1; js <= max_splits; ++js) {
