@@ -167,6 +167,8 @@ struct ColFlags {
 // One thread per column, at its end: the column that arrives last raises the flags and posts the step.  The
 // ticket counts arrivals (bits 0-15), columns that go on (16-31) and failures of kind 1 (32-47) and 2
 // (48-63; reported in preference): one atomic says all, so nothing else has to be visible to the last one.
+// The caller has a barrier between it and every read of all_done and of the column's own state by the workgroup's other
+// waves: the last arrival raises all_done at once, and a wave that read it late would leave the running step.
 __device__ __forceinline__ void column_arrive(ColFlags* f, unsigned long long* post, int t, bool goes_on, int bad, bool counts) {
   const unsigned long long mine = 1ull | ((unsigned long long)goes_on << 16) | (bad == 1 ? 1ull << 32 : bad == 2 ? 1ull << 48 : 0ull);
   const unsigned long long all = atomicAdd(&f->ticket, mine) + mine;

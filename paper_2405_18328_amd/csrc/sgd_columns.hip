@@ -167,6 +167,9 @@ __global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __r
     }
   }
   if (go) {
+    // Thread 0 publishes below what every thread reads above (the column's stop, and through the last arrival all_done):
+    // not before all waves have read it.  The register forms have a barrier around the scatter into LDS.
+    if constexpr (Q == 0) __syncthreads();
     double rr = rr0 + delta;
     if (rr < 0.0) rr = 0.0;
     const double rel = sqrt(rr / bn2);

@@ -50,3 +50,63 @@ def test_iterates_follow_the_step(n, t, batch, kind):
         assert bool((V1 == V2).all())
     finally:
         dv.close()
+
+
+def _stopping_run(X, ell, a, sigma, kind, B, batches, lr, momentum, stop):
+    """Column c of the step above stops behind step stop[c] (0: at the start, -1: a zero right-hand side, stops there too;
+    past the last batch: never).  Returns the iterates, the final residual estimates and tolerances that the
+    estimates first pass at those steps, half-way between the smallest before and the one that passes."""
+    B = B.astype(np.float64)
+    U, M, R = np.zeros_like(B), np.zeros_like(B), B.copy()
+    norm = np.where(stop < 0, 1.0, np.linalg.norm(B, axis=0))
+    live = stop > 0
+    est = np.where(stop < 0, 0.0, 1.0)
+    tol = np.where(stop <= 0, 2.0, 1e-7)
+    for k, I in enumerate(batches, 1):
+        if not live.any():
+            break
+        G = orc.kmv_rows(X, ell, a, kind, U, I, sigma=sigma) - B[I]
+        M *= momentum
+        M[I] -= lr / len(I) * G
+        U[:, live] += M[:, live]
+        R[np.ix_(I, live)] = -G[:, live]
+        now = np.linalg.norm(R, axis=0) / norm
+        ends = live & (stop == k)
+        assert (now[ends] < 0.999 * est[ends]).all()      # the estimates of the live columns fall
+        tol[ends] = 0.5 * (now[ends] + est[ends])
+        est = np.where(live, now, est)
+        live &= ~ends
+    return U, est, tol
+
+
+@pytest.mark.parametrize("n,t,batch,d", [
+    (16384, 9, 2500, 2),        # the register form, for comparison
+    (16385, 1, 2500, 3), (17000, 9, 2501, 2), (20003, 34, 3000, 2)])
+def test_columns_stop_at_their_own_steps(n, t, batch, d):
+    """Columns that stop at every step of the solve, the last one ending it: a stopping column has its whole update, every
+    row of it, although its stop (and the end of the solve) is published while the workgroup is still at work."""
+    rng = np.random.default_rng(n + t)
+    X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
+    steps = 6
+    stop = 3 + rng.permutation(t) % (steps - 2)           # the estimates need two steps to move
+    if t > 2:
+        stop[1], stop[t - 1] = 0, -1
+    B = np.cos(X.astype(np.float64) @ rng.uniform(-2.0, 2.0, size=(d, t)) + rng.uniform(0.0, 3.0, size=t)).astype(np.float32)
+    B[:, stop < 0] = 0.0
+    batches = np.stack([rng.permutation(n)[:batch] for _ in range(steps)]).astype(np.int32)
+    ell, lr = np.full(d, 0.5), 0.5
+    ref, est, tol = _stopping_run(X, ell, 0.9, 0.8, "se", B, batches, lr, 0.9, stop)
+    dv = Dev(X, "se", ell, 0.9, 0.8)
+    try:
+        for limit in (steps, int(stop.max()) - 1):        # to the end of the solve, and one step short of it
+            print(f"[sgd columns] stops n={n} t={t} batch={batch} limit={limit}", flush=True)
+            rc, iters, kmv, relres, Vd = dv.sgd_solve(B, tol, batches, lr, 0.9, max_iters=limit)
+            assert (rc, iters, kmv) == ((0, stop.max(), 0) if limit == steps else (1, limit, 0))
+            V = Vd.cpu().numpy().astype(np.float64)
+            done = (stop > 0) & (stop <= limit)
+            err = np.linalg.norm(V - ref, axis=0)[done] / np.linalg.norm(ref, axis=0)[done]
+            assert err.max(initial=0.0) <= 1e-4, err.max()           # as above; one wave's rows left out of one step are 1e-2
+            assert np.abs(relres[done] / est[done] - 1.0).max(initial=0.0) <= 1e-4
+            assert not V[:, stop <= 0].any()
+    finally:
+        dv.close()
