@@ -54,6 +54,21 @@ struct TileArgsH {
   const int* done;         // a non-zero value there turns the launch into a no-op; NULL: always runs
 };
 
+// What a tile kernel is compiled for, besides the row-major product of gp_kmv and gp_predict (FORM_PLAIN).  The shapes
+// that fill the register file are built once per form: with all options in one kernel, KH = 1 NT = 2 MI = 2
+// kept 65 registers in scratch memory (now 2; FORM_PLAIN 27) and the wide kernel 15 (9).  Measured before -> after:
+// a CG iteration, d = 11, t = 65, n = 16384 201 -> 161 us, n = 65536 2428 -> 2105 us; a block update of alternating
+// projections, n = 16384 d = 5 t = 65, block 2000, 97 -> 71 us.
+enum {
+  FORM_PLAIN,
+  FORM_COLUMNS,   // the solvers' products: column-major images, early return
+  FORM_GATHER,    // and rows gathered from the context's points
+  FORM_WINDOW,    // and a column window chosen on the device
+  FORM_ANY        // all of it, chosen by the arguments
+};
+constexpr bool has_gather(int form) { return form == FORM_GATHER || form == FORM_ANY; }
+constexpr bool has_window(int form) { return form == FORM_WINDOW || form == FORM_ANY; }
+
 // where this lane's row operands of sub-tile `sub` start (units; + kh * 64 per distance step)
 template <int KH>
 __device__ __forceinline__ int64_t row_operand(const TileArgsH& p, int64_t sub, int lane) {
@@ -99,10 +114,7 @@ __device__ __forceinline__ void store_column_quads(float* dst, bool ok, bool fir
 // Two waves per SIMD with two software pipelines.  Four wavefronts per workgroup: every workgroup streams all
 // of V' and XA through its LDS, so the L2-to-LDS traffic of a launch is inversely proportional to the
 // rows a workgroup owns (128 MI; eight waves halve the traffic and measured no faster).
-// CM: compiled with what the column solvers ask for (row gather, column window, column-major images, early return).  The
-// widest shape (KH = 1, NT = 2, MI = 2) has no registers for it: with that code in it spilled 65 instead of 27
-// registers and gp_kmv at n = 2000000 d = 11 t = 65 took 1.93 s instead of 1.61 s, so it is built both ways.
-template <int KIND, int KH, int XP, int NT, int MI, bool Y, bool CM = true>
+template <int KIND, int KH, int XP, int NT, int MI, bool Y, int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void kmv_tile_f16_kernel(TileArgsH p) {
   // One pipeline stage in LDS, in 16-byte units: G groups of 64 units (one wave-wide 16-byte load
   // each): XP*KH groups of XA pieces, then 4*NT groups of V' images; then one 8-unit y slot per wave.
@@ -121,6 +133,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert((DEPTH - 1) * LPC < 64, "vmcnt cannot express the pipeline depth");
   __shared__ u32x4 lds[NS][STAGE];
 
+  constexpr bool CM = FORM != FORM_PLAIN;
   const int over = CM && p.done ? *p.done : 0;   // looked at only once the first loads are on their way
   if (p.clear && blockIdx.x == 0)
     for (int c = threadIdx.x; c < p.clear_n; c += blockDim.x) p.clear[c] = 0u;
@@ -134,9 +147,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int sub0 = (rb * W + wave) * MI;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
-  const int64_t chunk0 = CM ? window_chunk(p) : 0;
+  const int64_t chunk0 = has_window(FORM) ? window_chunk(p) : 0;
   const int r_begin = js * p.cps;
-  const int r_end = CM ? (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0) : min(p.nchunks, r_begin + p.cps);
+  const int r_end = has_window(FORM) ? (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0) : min(p.nchunks, r_begin + p.cps);
   int c_begin = r_begin;
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
@@ -144,7 +157,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   f16x8 xb[MI][XP][KH];
 #pragma unroll
   for (int m = 0; m < MI; ++m) {
-    const int64_t at = CM ? row_operand<KH>(p, sub0 + m, lane) : (int64_t)(sub0 + m) * KH * 64 + lane;
+    const int64_t at = has_gather(FORM) ? row_operand<KH>(p, sub0 + m, lane) : (int64_t)(sub0 + m) * KH * 64 + lane;
 #pragma unroll
     for (int pc = 0; pc < XP; ++pc)
 #pragma unroll
@@ -380,7 +393,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
       const int64_t ibase = (int64_t)(sub0 + m) * 32 + zero;
-      if (CM && p.cm_ld) {
+      if (FORM == FORM_ANY ? p.cm_ld != 0 : CM) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const int c = li + 32 * nt;
@@ -432,7 +445,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // segment).  The same threads read and write the same elements: no race, fixed order.
   if (over) return;
   bool first = true;
-  if (CM && r_begin >= r_end) {   // a block at the end of the points is shorter than the launch
+  if (has_window(FORM) && r_begin >= r_end) {   // a block at the end of the points is shorter than the launch
     flush(true);
     return;
   }
@@ -466,7 +479,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // With KH = 1 or NT = 1 the two-wave kernel with two sub-tiles per wave reads half the operands from LDS and stays ahead.
 constexpr int wide_waves(int KH, int XP, int NT) { return NT ? 4 : KH <= 2 ? 8 : XP * KH <= 16 ? 4 : 2; }   // per SIMD
 
-template <int KIND, int KH, int XP, int NT, bool Y>
+template <int KIND, int KH, int XP, int NT, bool Y, int FORM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(KH, XP, NT), wide_waves(KH, XP, NT)))) void kmv_tile_f16_wide_kernel(TileArgsH p) {
   constexpr int W = 8;
   constexpr int XA_G = XP * KH;                     // groups of 64 16-byte units per chunk
@@ -479,7 +492,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   constexpr int LPW = (2 * G + W - 1) / W;          // group loads per wave and stage; surplus slots repeat the last group
   __shared__ u32x4 lds[2][STAGE];
 
-  const int over = p.done ? *p.done : 0;   // looked at only once the first loads are on their way
+  constexpr bool CM = FORM != FORM_PLAIN;
+  const int over = CM && p.done ? *p.done : 0;   // looked at only once the first loads are on their way
   if (p.clear && blockIdx.x == 0)
     for (int c = threadIdx.x; c < p.clear_n; c += blockDim.x) p.clear[c] = 0u;
   const int tid = threadIdx.x;
@@ -490,14 +504,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   const int js = blockIdx.x % p.JS;
   const int rb = blockIdx.x / p.JS;
   const int sub0 = rb * W + wave;
-  const int64_t chunk0 = window_chunk(p);
+  const int64_t chunk0 = has_window(FORM) ? window_chunk(p) : 0;
   const int r_begin = js * p.cps;
-  const int r_end = (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0);
+  const int r_end = has_window(FORM) ? (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0) : min(p.nchunks, r_begin + p.cps);
   int c_begin = r_begin;
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
   f16x8 xb[XP][KH];
-  const int64_t row_at = row_operand<KH>(p, sub0, lane);
+  const int64_t row_at = has_gather(FORM) ? row_operand<KH>(p, sub0, lane) : (int64_t)sub0 * KH * 64 + lane;
 #pragma unroll
   for (int pc = 0; pc < XP; ++pc)
 #pragma unroll
@@ -619,7 +633,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
     int zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
     const int64_t ibase = (int64_t)sub0 * 32 + zero;
-    if (p.cm_ld) {
+    if (FORM == FORM_ANY ? p.cm_ld != 0 : CM) {
       if constexpr (NT > 0) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -673,7 +687,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
 
   if (over) return;
   bool first = true;
-  if (r_begin >= r_end) {
+  if (has_window(FORM) && r_begin >= r_end) {
     flush(true);
     return;
   }
@@ -898,27 +912,46 @@ __global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __rest
 
 typedef void (*tileh_fn)(TileArgsH);
 
-template <int KIND, int KH, int XP, bool Y>
-tileh_fn pick_h_nt_mi(int NT, int MI, bool cm) {
-  if constexpr (KH == 1) {
-    if (MI == 2 && NT == 2 && !cm) return kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, Y, false>;
-    if (MI == 2) return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, Y> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 2, Y>;
+template <int KIND, int KH, int XP, int NT, int MI, bool Y>
+tileh_fn pick_form(int form) {
+  switch (form) {
+    case FORM_PLAIN: return kmv_tile_f16_kernel<KIND, KH, XP, NT, MI, Y, FORM_PLAIN>;
+    case FORM_COLUMNS: return kmv_tile_f16_kernel<KIND, KH, XP, NT, MI, Y, FORM_COLUMNS>;
+    case FORM_GATHER: return kmv_tile_f16_kernel<KIND, KH, XP, NT, MI, Y, FORM_GATHER>;
   }
-  if constexpr (KH == 2) {
-    if (MI == 2 && NT == 1) return kmv_tile_f16_kernel<KIND, KH, XP, 1, 2, Y>;
-  }
-  return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 1, Y> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 1, Y>;
+  return kmv_tile_f16_kernel<KIND, KH, XP, NT, MI, Y, FORM_WINDOW>;
 }
 
 template <int KIND, int XP, bool Y>
-tileh_fn pick_h_kh(int KH, int NT, int MI, bool cm) {
+tileh_fn pick_wide_form(int form) {
+  switch (form) {
+    case FORM_PLAIN: return kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, Y, FORM_PLAIN>;
+    case FORM_COLUMNS: return kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, Y, FORM_COLUMNS>;
+    case FORM_GATHER: return kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, Y, FORM_GATHER>;
+  }
+  return kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, Y, FORM_WINDOW>;
+}
+
+template <int KIND, int KH, int XP, bool Y>
+tileh_fn pick_h_nt_mi(int NT, int MI, int form) {
+  if constexpr (KH == 1) {
+    if (MI == 2) return NT == 1 ? pick_form<KIND, KH, XP, 1, 2, Y>(form) : pick_form<KIND, KH, XP, 2, 2, Y>(form);
+  }
+  if constexpr (KH == 2) {
+    if (MI == 2 && NT == 1) return pick_form<KIND, KH, XP, 1, 2, Y>(form);
+  }
+  return NT == 1 ? kmv_tile_f16_kernel<KIND, KH, XP, 1, 1, Y, FORM_ANY> : kmv_tile_f16_kernel<KIND, KH, XP, 2, 1, Y, FORM_ANY>;
+}
+
+template <int KIND, int XP, bool Y>
+tileh_fn pick_h_kh(int KH, int NT, int MI, int form) {
   switch (KH) {
-    case 1: return pick_h_nt_mi<KIND, 1, XP, Y>(NT, MI, cm);
-    case 2: return pick_h_nt_mi<KIND, 2, XP, Y>(NT, MI, cm);
-    case 3: return pick_h_nt_mi<KIND, 3, XP, Y>(NT, MI, cm);
-    case 4: return pick_h_nt_mi<KIND, 4, XP, Y>(NT, MI, cm);
-    case 6: return pick_h_nt_mi<KIND, 6, XP, Y>(NT, MI, cm);
-    case 8: return pick_h_nt_mi<KIND, 8, XP, Y>(NT, MI, cm);
+    case 1: return pick_h_nt_mi<KIND, 1, XP, Y>(NT, MI, form);
+    case 2: return pick_h_nt_mi<KIND, 2, XP, Y>(NT, MI, form);
+    case 3: return pick_h_nt_mi<KIND, 3, XP, Y>(NT, MI, form);
+    case 4: return pick_h_nt_mi<KIND, 4, XP, Y>(NT, MI, form);
+    case 6: return pick_h_nt_mi<KIND, 6, XP, Y>(NT, MI, form);
+    case 8: return pick_h_nt_mi<KIND, 8, XP, Y>(NT, MI, form);
   }
   return nullptr;
 }
@@ -926,21 +959,21 @@ tileh_fn pick_h_kh(int KH, int NT, int MI, bool cm) {
 template <int KIND, int XP>
 tileh_fn pick_vec_kh(int KH) {
   switch (KH) {
-    case 1: return kmv_tile_f16_wide_kernel<KIND, 1, XP, 0, true>;
-    case 2: return kmv_tile_f16_wide_kernel<KIND, 2, XP, 0, true>;
-    case 3: return kmv_tile_f16_wide_kernel<KIND, 3, XP, 0, true>;
-    case 4: return kmv_tile_f16_wide_kernel<KIND, 4, XP, 0, true>;
-    case 6: return kmv_tile_f16_wide_kernel<KIND, 6, XP, 0, true>;
-    case 8: return kmv_tile_f16_wide_kernel<KIND, 8, XP, 0, true>;
+    case 1: return kmv_tile_f16_wide_kernel<KIND, 1, XP, 0, true, FORM_ANY>;
+    case 2: return kmv_tile_f16_wide_kernel<KIND, 2, XP, 0, true, FORM_ANY>;
+    case 3: return kmv_tile_f16_wide_kernel<KIND, 3, XP, 0, true, FORM_ANY>;
+    case 4: return kmv_tile_f16_wide_kernel<KIND, 4, XP, 0, true, FORM_ANY>;
+    case 6: return kmv_tile_f16_wide_kernel<KIND, 6, XP, 0, true, FORM_ANY>;
+    case 8: return kmv_tile_f16_wide_kernel<KIND, 8, XP, 0, true, FORM_ANY>;
   }
   return nullptr;
 }
 
 template <int KIND, int XP>
-tileh_fn pick_h(int KH, int NT, int MI, bool wide, bool y, bool cm) {
+tileh_fn pick_h(int KH, int NT, int MI, bool wide, bool y, int form) {
   if (NT == 0) return pick_vec_kh<KIND, XP>(KH);
-  if (wide) return y ? kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, true> : kmv_tile_f16_wide_kernel<KIND, 2, XP, 2, false>;
-  return y ? pick_h_kh<KIND, XP, true>(KH, NT, MI, cm) : pick_h_kh<KIND, XP, false>(KH, NT, MI, cm);
+  if (wide) return y ? pick_wide_form<KIND, XP, true>(form) : pick_wide_form<KIND, XP, false>(form);
+  return y ? pick_h_kh<KIND, XP, true>(KH, NT, MI, form) : pick_h_kh<KIND, XP, false>(KH, NT, MI, form);
 }
 
 // The kernel of one column pass of NT tiles (y: with the extra vector-ALU column).
@@ -951,18 +984,19 @@ struct TileKernelH {
   double chunk_us;         // about what a chunk takes one of them
 };
 
-// cm: the launch sets any of done, win_sel, gather and cm_ld (the shape does not depend on it)
-TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool y, bool cm) {
+// form: FORM_PLAIN .. FORM_WINDOW (the shape does not depend on it)
+TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool y, int form) {
   TileKernelH k;
   const int KH = ctx->KH;
   // The wide kernel where it is ahead (see there) and has rows enough: it takes twice the waves to fill the chip, so
   // below 32768 rows twice the column splits, whose images cost what it gains (n = 16384: 6 us against 4).  Two
   // sub-tiles per wave halve the LDS operand traffic; past one k-step of distance operands (two with a
-  // single contraction tile) the second sub-tile no longer fits the register file without spills.
+  // single contraction tile) the second sub-tile no longer fits the register file.  Registers kept in scratch memory
+  // with two: KH = 1 NT = 2 27 - 39 row-major, 2 - 8 column-major; KH = 2 NT = 1 none, 12 - 15 row-major on three pieces.
   const bool wide = NT == 0 || (NT == 2 && KH == 2 && rows >= 32768);
   const int MI = !wide && rows >= 8192 && (KH == 1 || (KH == 2 && NT == 1)) ? 2 : 1;
-  if (ctx->kernel == GP_SE_ARD) k.fn = XP == 2 ? pick_h<GP_SE_ARD, 2>(KH, NT, MI, wide, y, cm) : pick_h<GP_SE_ARD, 3>(KH, NT, MI, wide, y, cm);
-  else k.fn = XP == 2 ? pick_h<GP_MATERN32_ARD, 2>(KH, NT, MI, wide, y, cm) : pick_h<GP_MATERN32_ARD, 3>(KH, NT, MI, wide, y, cm);
+  if (ctx->kernel == GP_SE_ARD) k.fn = XP == 2 ? pick_h<GP_SE_ARD, 2>(KH, NT, MI, wide, y, form) : pick_h<GP_SE_ARD, 3>(KH, NT, MI, wide, y, form);
+  else k.fn = XP == 2 ? pick_h<GP_MATERN32_ARD, 2>(KH, NT, MI, wide, y, form) : pick_h<GP_MATERN32_ARD, 3>(KH, NT, MI, wide, y, form);
   k.rows_per_wg = wide ? 256 : 128 * MI;
   k.threads = wide ? 512 : 256;
   if (wide) {
@@ -1016,7 +1050,7 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
       return pl;
     }
   const bool y = has_vec_column(t);
-  const TileKernelH k = tile_kernel_h(ctx, rows, XP, pass_tiles(y ? t - 1 : t), y, false);
+  const TileKernelH k = tile_kernel_h(ctx, rows, XP, pass_tiles(y ? t - 1 : t), y, FORM_PLAIN);
   const int row_blocks = (int)((rows + k.rows_per_wg - 1) / k.rows_per_wg);
   // a partial image is written and read once, at about 4 TB/s
   const double image = (double)rows * t * sizeof(float);
@@ -1192,7 +1226,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     a.clear_n = t;
     first_pass = false;
     vcol = -1;
-    const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0, false);
+    const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0, FORM_PLAIN);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
     const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
     const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
@@ -1278,7 +1312,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
     a.ncols = rem < 32 * NT ? rem : 32 * NT;
     a.vcol = vcol;
     vcol = -1;
-    const TileKernelH k = tile_kernel_h(ctx, nrows, ctx->XP, NT, a.vcol >= 0, true);
+    const TileKernelH k = tile_kernel_h(ctx, nrows, ctx->XP, NT, a.vcol >= 0, gather ? FORM_GATHER : win ? FORM_WINDOW : FORM_COLUMNS);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
     const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
     const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
