@@ -102,15 +102,13 @@ int gp_kmv(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_
 /*
  * gp_kmv for callers that cannot allocate: code between hipStreamBeginCapture and
  * hipStreamEndCapture, serving loops that must never reach hipMalloc, harnesses that forbid it.
- * Same arguments and kernels as gp_kmv, and bit-identical results as long as the partial images of gp_kmv's own
- * column splits fit the scratch too (past that the column range is left whole, which only changes the order
- * of the sums), but the scratch of the product
+ * Same arguments, same kernels and bit-identical results as gp_kmv, but the scratch of the product
  * (column maxima, the packed images of V, column-split partial sums) is a file-scope device array
  * of GP_KMV_STATIC_SCRATCH_BYTES bytes that every GPU the library is used on holds until the
  * process ends, and the call reaches no hipMalloc, hipFree, stream synchronisation or memset
- * command.  A product whose scratch does not fit (256 bytes per row for the packed images of V,
- * plus n t floats per column split, of which there are up to 64 when n is small: n = 16384, t = 65
- * needs 39 MB, n = 200000 needs 52 MB, n = 300000 does not fit) is refused with GP_ERR_WORKSPACE
+ * command.  Partial sums that do not fit are made and added up for one panel of rows after the other.
+ * A product whose packed images of V do not fit (260 bytes per row: n = 250000 fits, n = 300000 does
+ * not; in fp32 arithmetic, n t floats per column split) is refused with GP_ERR_WORKSPACE
  * and nothing is launched: use gp_kmv for it.
  * All calls on one GPU, from any context, share that GPU's array: two such calls must not be in
  * flight on one GPU at the same time (calls on one stream are ordered and safe; calls on different

@@ -171,7 +171,7 @@ struct KmvPlan {
 };
 KmvPlan gp_plan_kmv(const gp_ctx* ctx, int64_t rows, int64_t col_chunks = 0);   // col_chunks = 0: all of the context's
 size_t gp_kmv_scratch_bytes(const gp_ctx* ctx, int t);   // square product, worst case over the paths gp_set_theta may choose
-size_t gp_kmv_least_scratch_bytes(const gp_ctx* ctx, int t);   // the least the square product can run with
+size_t gp_kmv_least_scratch_bytes(const gp_ctx* ctx, int t);   // the least the square product can run with (its rows in panels)
 size_t gp_kmv_rect_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows);
 size_t gp_kmv_window_scratch_bytes(const gp_ctx* ctx, int t, int col_chunks);   // product over any column window of at most that many chunks
 // OUT = K V (+ sigma^2 V).  colmax: optional device array of t bit patterns of max_i |V_ic| that the
@@ -188,7 +188,7 @@ int gp_kh_bucket(int d, int kernel);
 // side by side (see the definition): every row block is cut alike, so all rows share one summation tree.
 int gp_column_splits(int row_blocks, int64_t chunks, int slots, double image_cost, int max_splits);
 size_t gp_kmv_f16_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks = 0);
-size_t gp_kmv_f16_least_scratch_bytes(const gp_ctx* ctx, int t);   // square product with the column range left whole
+size_t gp_kmv_f16_least_scratch_bytes(const gp_ctx* ctx, int t);   // square product with its rows in panels
 int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo,
                       int add_noise, void* scratch, size_t scratch_bytes, const unsigned* colmax,
                       const KmvRows* rows, KmvDeferred* defer, const KmvWindow* win);

@@ -44,6 +44,7 @@ struct TileArgsH {
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
+  int rb0;                 // first row block of the launch (FORM_PLAIN, FORM_ANY)
   unsigned* clear;         // column maxima in accumulation: everyone has read them, workgroup 0 zeroes them (clear_n words); NULL: none
   int clear_n;
   const int* win_sel;      // contraction over the columns of block *win_sel (win_block points each): XA starts at that block's
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int h = lane >> 5;
   const int li = lane & 31;
   const int js = blockIdx.x % p.JS;
-  const int rb = blockIdx.x / p.JS;
+  const int rb = blockIdx.x / p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.rb0 : 0);
   const int sub0 = (rb * W + wave) * MI;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   const int h = lane >> 5;
   const int li = lane & 31;
   const int js = blockIdx.x % p.JS;
-  const int rb = blockIdx.x / p.JS;
+  const int rb = blockIdx.x / p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.rb0 : 0);
   const int sub0 = rb * W + wave;
   const int64_t chunk0 = has_window(FORM) ? window_chunk(p) : 0;
   const int r_begin = js * p.cps;
@@ -1040,6 +1041,11 @@ ScratchH scratch_layout(const gp_ctx* ctx, int t, int JS, int64_t rows) {
 bool has_vec_column(int t) { return t % 32 == 1; }
 int pass_tiles(int rem) { return rem > 32 ? 2 : rem > 0 ? 1 : 0; }
 
+// Where the scratch does not hold the partial images of all rows, they are made and summed for one panel of rows after the
+// other: every row keeps its column cuts and the order of its sums.
+constexpr int PANEL_ROWS = 256;        // a panel is a multiple of this, and this of every kernel's rows per workgroup
+size_t panel_image_bytes(int t) { return (size_t)(t < 65 ? t : 65) * sizeof(float); }   // per row: the columns of one pass
+
 PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP) {
   PlanH pl;
   const int64_t chunks = col_chunks > 0 ? col_chunks : (ctx->n + 31) / 32;
@@ -1057,6 +1063,14 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
   int max_js = image * 3.0 > 2.0e9 ? (int)(2.0e9 / image) : 64;     // images past 2 GB would not pay for their memory
   if (max_js < 1) max_js = 1;
   if (max_js > 64) max_js = 64;
+  if (rows == ctx->n && chunks == (ctx->n + 31) / 32) {
+    // gp_kmv_static makes the same cuts on a fixed block, where one panel of PANEL_ROWS rows has to fit beside the operands
+    const size_t least = scratch_layout(ctx, t, 1, rows).total;
+    if (least <= (size_t)GP_KMV_STATIC_SCRATCH_BYTES) {
+      const int64_t fit = (int64_t)(((size_t)GP_KMV_STATIC_SCRATCH_BYTES - least) / (panel_image_bytes(t) * PANEL_ROWS));
+      if (fit < max_js) max_js = fit < 1 ? 1 : (int)fit;
+    }
+  }
   pl.JS = gp_column_splits(row_blocks, chunks, k.per_cu * ctx->num_cu, 2.0 * image / 4.0e6 / k.chunk_us, max_js);
   pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
   gp_ctx* memo = const_cast<gp_ctx*>(ctx);   // a context belongs to one host thread at a time
@@ -1139,10 +1153,14 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
   PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
   ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
-  if (scratch_bytes < L.total) {    // no room for partial images (gp_kmv_static): the column range stays whole
-    pl.JS = 1;
-    pl.cps = win ? win->nchunks : (int)((ctx->n + 31) / 32);
-    L = scratch_layout(ctx, t, 1, nrows);
+  int64_t panel = nrows;
+  if (scratch_bytes < L.total && pl.JS > 1 && !defer && scratch_bytes > L.off_part) {   // gp_kmv_static: panels of rows
+    panel = (int64_t)((scratch_bytes - L.off_part) / (pl.JS * panel_image_bytes(t))) / PANEL_ROWS * PANEL_ROWS;
+    if (panel > 0) {
+      const int64_t panels = (nrows + panel - 1) / panel;          // of one size
+      panel = ((nrows + panels - 1) / panels + PANEL_ROWS - 1) / PANEL_ROWS * PANEL_ROWS;
+      L.total = L.off_part + (size_t)panel * pl.JS * panel_image_bytes(t);
+    }
   }
   if (scratch_bytes < L.total || !scratch)
     return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv: scratch %zu < %zu bytes", scratch_bytes, L.total);
@@ -1152,7 +1170,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   float* VY = (float*)(w + L.off_vy);
   u32x4* VP = (u32x4*)(w + L.off_vp);
   float* part = (float*)(w + L.off_part);
-  const bool split = pl.JS > 1;
+  const bool split = pl.JS > 1, panels = split && panel < nrows;
   // a column window is handed to the kernels as a point set of its own that starts at chunk 0
   const int nchunks = win ? win->nchunks : (int)((ctx->n + 31) / 32);
   const int64_t first = win ? (int64_t)win->chunk0 * 32 : 0;
@@ -1199,7 +1217,13 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.npoints = ctx->n - first;
   a.cm_ld = 0;
   a.done = nullptr;
+  a.rb0 = 0;
 
+  auto sum_images_of = [&](int64_t m, int width, float* out) {     // out = the sum of the images of m rows
+    int blocks = (int)((m * width + 1023) / 1024);
+    if (blocks > 8 * ctx->num_cu) blocks = 8 * ctx->num_cu;
+    hipLaunchKernelGGL(kmv_reduce_f16_kernel, dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, pl.JS, m, width, out, ldo);
+  };
   int vcol = y ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;
   bool first_pass = true;
@@ -1228,11 +1252,23 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     vcol = -1;
     const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0, FORM_PLAIN);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
-    const dim3 grid((unsigned)((nrows + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
-    const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
-    hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, st, a);
-    GP_HIP(ctx, hipGetLastError());
-    gp_prof_end(ctx, prof);
+    const int col = a.vcol >= 0 ? a.vcol : a.col0, width = a.ncols + (a.vcol >= 0 ? 1 : 0);   // the pass's columns
+    for (int64_t r0 = 0; r0 < nrows; r0 += panel) {
+      const int64_t m = nrows - r0 < panel ? nrows - r0 : panel;
+      if (panels) {
+        a.OUT = part - (r0 * width + col);     // images of this panel and these columns, addressed by row and column as ever
+        a.ldo = width;
+        a.split_stride = m * width;
+        a.n = r0 + m;
+        a.rb0 = (int)(r0 / k.rows_per_wg);
+      }
+      const dim3 grid((unsigned)((m + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
+      const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
+      hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, st, a);
+      GP_HIP(ctx, hipGetLastError());
+      gp_prof_end(ctx, prof);
+      if (panels) sum_images_of(m, width, dOut + r0 * ldo + col);
+    }
     c += a.ncols;
   } while (c < t);
   if (defer) {
@@ -1240,14 +1276,8 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     defer->stride = a.split_stride;
     defer->JS = pl.JS;
   }
-  if (split && !defer) {
-    const int64_t total = nrows * (int64_t)t;
-    int blocks = (int)((total + 1023) / 1024);
-    if (blocks > 8 * ctx->num_cu) blocks = 8 * ctx->num_cu;
-    hipLaunchKernelGGL(kmv_reduce_f16_kernel, dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, pl.JS,
-                       nrows, t, dOut, ldo);
-    GP_HIP(ctx, hipGetLastError());
-  }
+  if (split && !defer && !panels) sum_images_of(nrows, t, dOut);
+  GP_HIP(ctx, hipGetLastError());
   return GP_OK;
 }
 
@@ -1302,6 +1332,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
   a.add_noise = 0;
   a.cm_ld = pk.ld;
   a.done = pk.done;
+  a.rb0 = 0;
   const u32x4* VP = (const u32x4*)pk.VP;
   int vcol = has_vec_column(t) ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;

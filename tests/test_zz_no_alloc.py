@@ -91,3 +91,36 @@ def test_static_scratch_product_refuses_what_does_not_fit_and_bad_arguments():
         assert e.value.code == gp.GP_ERR_ARG
     finally:
         gp.gp_destroy(ctx)
+
+
+@pytest.mark.parametrize("n,d,kind,t", [
+    (131073, 26, "matern32", 97),     # two column passes, the second without the vector-ALU column, on two kernels
+    (70001, 26, "matern32", 34),      # wide kernel, a ragged last panel
+    (131073, 12, "se", 65),           # one row past a full generation of workgroups
+    (150000, 3, "se", 65), (240001, 2, "matern32", 66)])
+def test_static_scratch_product_whose_partial_images_do_not_fit(n, d, kind, t):
+    """Sizes whose column splits leave more partial images than the static scratch holds: row panels, the same bits."""
+    rng = np.random.default_rng(n)
+    X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
+    V = rng.standard_normal((n, t)).astype(np.float32)
+    dv = Dev(X, kind, np.full(d, 0.6 * np.sqrt(d)), 0.9, 0.5)
+    try:
+        Vd = dv.to(V)
+        outs, launches = [], []
+        for fn in (gp.gp_kmv_static, gp.gp_kmv):
+            out = torch.full((n, t + 1), -777.0, device=dv.dev)
+            print(f"[no-alloc] {fn.__name__} n={n} d={d} t={t}", flush=True)
+            gp.gp_profile(dv.ctx, 1 << gp.GP_PROF_TILE)
+            fn(dv.ctx, Vd, t, t, out, t + 1, 1)
+            launches.append(gp.gp_profile_read(dv.ctx)[0])
+            gp.gp_profile(dv.ctx, 0)
+            outs.append(out)
+        assert launches[0] > launches[1], launches         # the panels were taken
+        assert torch.equal(outs[0], outs[1]), "gp_kmv_static differs from gp_kmv"
+        got = outs[0].cpu().numpy()
+        assert (got[:, t:] == -777.0).all()
+        rows = np.unique(np.r_[0, 255, 256, n - 1, rng.integers(0, n, 60)])
+        ref = orc.kmv_rows(X, np.full(d, 0.6 * np.sqrt(d)), 0.9, kind, V, rows, sigma=0.5)
+        assert relerr(got[rows, :t], ref) <= KMV_TOL
+    finally:
+        dv.close()
