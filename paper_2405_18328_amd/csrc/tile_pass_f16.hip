@@ -44,7 +44,7 @@ struct TileArgsH {
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
-  int rb0;                 // first row block of the launch (FORM_PLAIN, FORM_ANY)
+  int rb0, js0;            // first row block and first column range of the launch (FORM_PLAIN, FORM_ANY)
   unsigned* clear;         // column maxima in accumulation: everyone has read them, workgroup 0 zeroes them (clear_n words); NULL: none
   int clear_n;
   const int* win_sel;      // contraction over the columns of block *win_sel (win_block points each): XA starts at that block's
@@ -57,7 +57,7 @@ struct TileArgsH {
 
 // What a tile kernel is compiled for, besides the row-major product of gp_kmv and gp_predict (FORM_PLAIN).  The shapes
 // that fill the register file are built once per form: with all options in one kernel, KH = 1 NT = 2 MI = 2
-// kept 65 registers in scratch memory (now 2; FORM_PLAIN 27) and the wide kernel 15 (9).  Measured before -> after:
+// kept 65 registers in scratch memory (now 2; FORM_PLAIN 27) and the wide kernel 15 (none; FORM_PLAIN 9).  Before -> after:
 // a CG iteration, d = 11, t = 65, n = 16384 201 -> 161 us, n = 65536 2428 -> 2105 us; a block update of alternating
 // projections, n = 16384 d = 5 t = 65, block 2000, 97 -> 71 us.
 enum {
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: lets the compiler branch on it
   const int h = lane >> 5;
   const int li = lane & 31;
-  const int js = blockIdx.x % p.JS;
+  const int js = blockIdx.x % p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.js0 : 0);
   const int rb = blockIdx.x / p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.rb0 : 0);
   const int sub0 = (rb * W + wave) * MI;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5;
   const int li = lane & 31;
-  const int js = blockIdx.x % p.JS;
+  const int js = blockIdx.x % p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.js0 : 0);
   const int rb = blockIdx.x / p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.rb0 : 0);
   const int sub0 = rb * W + wave;
   const int64_t chunk0 = has_window(FORM) ? window_chunk(p) : 0;
@@ -875,16 +875,29 @@ __global__ __launch_bounds__(1024) void pack_small_kernel(const float* __restric
   }
 }
 
-// OUT = sum of the partial images, in order.  A chain of dependent loads bounded it (one element per thread, one image
+// OUT = (add: OUT +) sum of the partial images, in order.  A chain of dependent loads bounded it (one element per thread, one image
 // after the other); now four consecutive elements per thread, eight images fetched at a time.  With the clearing launch
 // of the column maxima gone, gp_predict n = 13500, m = 1500, t = 65: 79 -> 70 us; n = 41157, m = 4573, t = 1: 85 -> 78 us.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __restrict__ part, int64_t split_stride, int JS, int64_t n,
-                                                             int t, float* __restrict__ out, int64_t ldo) {
+                                                             int t, int add, float* __restrict__ out, int64_t ldo) {
   const int64_t total = n * t;
   for (int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; e < total; e += (int64_t)gridDim.x * 1024) {
-    const int64_t at = e + 4 <= total ? e : total - (total < 4 ? total : 4);   // the last thread's four overlap its neighbour's
     f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int64_t at = e + 4 <= total || total < 4 ? e : total - 4;     // the last thread loads its neighbour's too
+    auto each = [&](auto f) {       // this thread's elements
+      int64_t i = at / t;
+      int c = (int)(at - i * t);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (at + q >= e && at + q < total) f(q, out + i * ldo + c);
+        if (++c == t) {
+          c = 0;
+          ++i;
+        }
+      }
+    };
+    if (add) each([&](int q, const float* o) { s[q] = *o; });
     if (total >= 4) {
       for (int k = 0; k < JS; k += 8) {
         f32x4 v[8];
@@ -898,16 +911,7 @@ __global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __rest
       for (int q = 0; q < (int)total; ++q)
         for (int k = 0; k < JS; ++k) s[q] += part[(int64_t)k * split_stride + q];
     }
-    int64_t i = at / t;
-    int c = (int)(at - i * t);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (at + q < total) out[i * ldo + c] = s[q];
-      if (++c == t) {
-        c = 0;
-        ++i;
-      }
-    }
+    each([&](int q, float* o) { *o = s[q]; });
   }
 }
 
@@ -1041,11 +1045,6 @@ ScratchH scratch_layout(const gp_ctx* ctx, int t, int JS, int64_t rows) {
 bool has_vec_column(int t) { return t % 32 == 1; }
 int pass_tiles(int rem) { return rem > 32 ? 2 : rem > 0 ? 1 : 0; }
 
-// Where the scratch does not hold the partial images of all rows, they are made and summed for one panel of rows after the
-// other: every row keeps its column cuts and the order of its sums.
-constexpr int PANEL_ROWS = 256;        // a panel is a multiple of this, and this of every kernel's rows per workgroup
-size_t panel_image_bytes(int t) { return (size_t)(t < 65 ? t : 65) * sizeof(float); }   // per row: the columns of one pass
-
 PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP) {
   PlanH pl;
   const int64_t chunks = col_chunks > 0 ? col_chunks : (ctx->n + 31) / 32;
@@ -1063,20 +1062,57 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
   int max_js = image * 3.0 > 2.0e9 ? (int)(2.0e9 / image) : 64;     // images past 2 GB would not pay for their memory
   if (max_js < 1) max_js = 1;
   if (max_js > 64) max_js = 64;
-  if (rows == ctx->n && chunks == (ctx->n + 31) / 32) {
-    // gp_kmv_static makes the same cuts on a fixed block, where one panel of PANEL_ROWS rows has to fit beside the operands
-    const size_t least = scratch_layout(ctx, t, 1, rows).total;
-    if (least <= (size_t)GP_KMV_STATIC_SCRATCH_BYTES) {
-      const int64_t fit = (int64_t)(((size_t)GP_KMV_STATIC_SCRATCH_BYTES - least) / (panel_image_bytes(t) * PANEL_ROWS));
-      if (fit < max_js) max_js = fit < 1 ? 1 : (int)fit;
-    }
-  }
   pl.JS = gp_column_splits(row_blocks, chunks, k.per_cu * ctx->num_cu, 2.0 * image / 4.0e6 / k.chunk_us, max_js);
   pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
   gp_ctx* memo = const_cast<gp_ctx*>(ctx);   // a context belongs to one host thread at a time
   memo->split_memo[memo->split_next] = SplitMemo{rows, chunks, t, XP, pl.JS};
   memo->split_next = (memo->split_next + 1) % 4;
   return pl;
+}
+
+// Where the scratch does not hold the partial images of all rows (gp_kmv_static), they are made and summed for one panel of
+// rows and one group of column ranges after the other, a group's operands packed for it: every row keeps its column
+// ranges and the order of its sums, so the result is the same bit for bit.
+struct PanelsH {
+  int64_t rows;    // per panel, a multiple of PANEL_ROWS; 0: no panels
+  int group;       // column ranges at a time
+};
+constexpr int PANEL_ROWS = 256;     // a multiple of every kernel's rows per workgroup
+
+size_t panel_images_at(const ScratchH& L, int group, const PlanH& pl) {
+  return L.off_vp + align_up((size_t)group * pl.cps * 2 * 2 * 2 * 64 * 16, 256);
+}
+
+// Smaller groups leave room for larger panels.  A launch takes about one unit of time per generation of workgroups, 0.55 where
+// there is at most one per compute unit.  gp_kmv_static, Matern-3/2, t = 65, every row's column range in one image -> panels
+// (gp_kmv, all images at once): n = 70001 d = 26 4.29 -> 2.86 ms (2.76), n = 150000 d = 5 14.0 -> 11.8 ms (10.6),
+// n = 200000 d = 5 24.2 -> 20.7 ms (19.6), n = 240000 d = 5 28.4 -> 29.8 ms (26.8).
+PanelsH plan_panels(const gp_ctx* ctx, int64_t nrows, int t, int XP, const PlanH& pl, const ScratchH& L, size_t scratch_bytes) {
+  const bool y = has_vec_column(t);
+  const TileKernelH k = tile_kernel_h(ctx, nrows, XP, pass_tiles(y ? t - 1 : t), y, FORM_PLAIN);
+  const int64_t unit = PANEL_ROWS / k.rows_per_wg, slots = (int64_t)k.per_cu * ctx->num_cu;
+  const int64_t units = (nrows + PANEL_ROWS - 1) / PANEL_ROWS;
+  const size_t per_unit = (size_t)(t < 65 ? t : 65) * sizeof(float) * PANEL_ROWS;     // images of the columns of one pass
+  PanelsH best{0, pl.JS};
+  double best_cost = 1e300;
+  for (int group = pl.JS; group >= 1; --group) {
+    const size_t at = panel_images_at(L, group, pl);
+    if (at >= scratch_bytes) continue;
+    const int64_t fit = min((int64_t)((scratch_bytes - at) / (per_unit * group)), units);
+    const int64_t wgs = fit * unit * group;
+    const int64_t full = wgs >= slots ? wgs / slots * slots : wgs > ctx->num_cu ? ctx->num_cu : wgs;    // whole generations
+    for (int64_t p : {fit, full / (unit * group)}) {
+      if (p < 1) continue;
+      const int64_t w = p * unit * group;
+      const double gens = w <= ctx->num_cu ? 0.55 : (double)((w + slots - 1) / slots);
+      const double cost = gens * (double)((units + p - 1) / p) * ((pl.JS + group - 1) / group);
+      if (cost < best_cost * (1.0 - 1e-9)) {
+        best_cost = cost;
+        best = PanelsH{p * PANEL_ROWS, group};
+      }
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -1153,15 +1189,8 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
   PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
   ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
-  int64_t panel = nrows;
-  if (scratch_bytes < L.total && pl.JS > 1 && !defer && scratch_bytes > L.off_part) {   // gp_kmv_static: panels of rows
-    panel = (int64_t)((scratch_bytes - L.off_part) / (pl.JS * panel_image_bytes(t))) / PANEL_ROWS * PANEL_ROWS;
-    if (panel > 0) {
-      const int64_t panels = (nrows + panel - 1) / panel;          // of one size
-      panel = ((nrows + panels - 1) / panels + PANEL_ROWS - 1) / PANEL_ROWS * PANEL_ROWS;
-      L.total = L.off_part + (size_t)panel * pl.JS * panel_image_bytes(t);
-    }
-  }
+  const PanelsH pn = scratch_bytes < L.total && pl.JS > 1 && !defer && !win ? plan_panels(ctx, nrows, t, XP, pl, L, scratch_bytes) : PanelsH{0, pl.JS};
+  if (pn.rows) L = scratch_layout(ctx, t, 1, nrows), L.off_part = panel_images_at(L, pn.group, pl), L.total = scratch_bytes;
   if (scratch_bytes < L.total || !scratch)
     return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv: scratch %zu < %zu bytes", scratch_bytes, L.total);
   hipStream_t st = ctx->stream;
@@ -1170,7 +1199,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   float* VY = (float*)(w + L.off_vy);
   u32x4* VP = (u32x4*)(w + L.off_vp);
   float* part = (float*)(w + L.off_part);
-  const bool split = pl.JS > 1, panels = split && panel < nrows;
+  const bool split = pl.JS > 1;
   // a column window is handed to the kernels as a point set of its own that starts at chunk 0
   const int nchunks = win ? win->nchunks : (int)((ctx->n + 31) / 32);
   const int64_t first = win ? (int64_t)win->chunk0 * 32 : 0;
@@ -1218,11 +1247,13 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.cm_ld = 0;
   a.done = nullptr;
   a.rb0 = 0;
+  a.js0 = 0;
 
-  auto sum_images_of = [&](int64_t m, int width, float* out) {     // out = the sum of the images of m rows
+  auto sum_images_of = [&](int64_t m, int width, bool add, float* out) {     // out = the sum of the images of m rows
     int blocks = (int)((m * width + 1023) / 1024);
     if (blocks > 8 * ctx->num_cu) blocks = 8 * ctx->num_cu;
-    hipLaunchKernelGGL(kmv_reduce_f16_kernel, dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, pl.JS, m, width, out, ldo);
+    hipLaunchKernelGGL(kmv_reduce_f16_kernel, dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, a.JS, m, width, add ? 1 : 0,
+                       out, ldo);
   };
   int vcol = y ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;
@@ -1233,41 +1264,56 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     a.col0 = c;
     a.ncols = rem < 32 * NT ? rem : 32 * NT;
     a.vcol = vcol;
+    const int vc = vcol;
+    vcol = -1;
+    auto pack = [&](int c0, int chunks) {      // operands of chunks c0 .. c0 + chunks - 1
+      const int64_t threads = (int64_t)chunks * 2 * NT * 64;
+      const int64_t need = threads > (int64_t)chunks * 32 ? threads : (int64_t)chunks * 32;
+      const int64_t r0 = (int64_t)c0 * 32;
+      hipLaunchKernelGGL(pack_v_kernel, dim3((unsigned)((need + 255) / 256)), dim3(256), 0, st, dVw + r0 * ldv, ldv, ncontr - r0, chunks, NT,
+                         a.col0, a.ncols, vc, accumulate && first_pass ? (const unsigned*)ctx->dColmax : colmax, VP, VY + r0,
+                         accumulate && first_pass ? (unsigned*)(w + L.off_colmax) : nullptr, t);
+    };
     if (small) {
       const int quads = (8 * nchunks + 127) / 128;
-      auto* pack = quads <= 2 ? pack_small_kernel<2> : quads <= 4 ? pack_small_kernel<4> : quads <= 8 ? pack_small_kernel<8> : pack_small_kernel<16>;
-      hipLaunchKernelGGL(pack, dim3((unsigned)((c + 32 * NT + 7) / 8)), dim3(1024), 0, st, dV, ldv, (int)ctx->n, nchunks, NT, c, t,
+      auto* pack_small = quads <= 2 ? pack_small_kernel<2> : quads <= 4 ? pack_small_kernel<4> : quads <= 8 ? pack_small_kernel<8> : pack_small_kernel<16>;
+      hipLaunchKernelGGL(pack_small, dim3((unsigned)((c + 32 * NT + 7) / 8)), dim3(1024), 0, st, dV, ldv, (int)ctx->n, nchunks, NT, c, t,
                          (unsigned*)(w + L.off_colmax), VP, VY);
-    } else {
-      const int64_t threads = (int64_t)nchunks * 2 * NT * 64;
-      const int64_t need = threads > (int64_t)nchunks * 32 ? threads : (int64_t)nchunks * 32;
-      hipLaunchKernelGGL(pack_v_kernel, dim3((unsigned)((need + 255) / 256)), dim3(256), 0, st, dVw, ldv, ncontr, nchunks, NT,
-                         a.col0, a.ncols, vcol, accumulate && first_pass ? (const unsigned*)ctx->dColmax : colmax, VP, VY,
-                         accumulate && first_pass ? (unsigned*)(w + L.off_colmax) : nullptr, t);
+    } else if (pn.group == pl.JS) {
+      pack(0, nchunks);
     }
     GP_HIP(ctx, hipGetLastError());
     a.clear = accumulate && first_pass ? ctx->dColmax : nullptr;
     a.clear_n = t;
     first_pass = false;
-    vcol = -1;
     const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0, FORM_PLAIN);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
     const int col = a.vcol >= 0 ? a.vcol : a.col0, width = a.ncols + (a.vcol >= 0 ? 1 : 0);   // the pass's columns
+    const int64_t panel = pn.rows ? pn.rows : nrows;
     for (int64_t r0 = 0; r0 < nrows; r0 += panel) {
       const int64_t m = nrows - r0 < panel ? nrows - r0 : panel;
-      if (panels) {
-        a.OUT = part - (r0 * width + col);     // images of this panel and these columns, addressed by row and column as ever
-        a.ldo = width;
-        a.split_stride = m * width;
-        a.n = r0 + m;
-        a.rb0 = (int)(r0 / k.rows_per_wg);
+      for (int j0 = 0; j0 < pl.JS; j0 += pn.group) {
+        if (pn.rows) {     // images of this panel, these column ranges and columns, addressed by row, range and column as ever
+          a.JS = min(pn.group, pl.JS - j0);
+          a.js0 = j0;
+          a.rb0 = (int)(r0 / k.rows_per_wg);
+          a.n = r0 + m;
+          a.ldo = width;
+          a.split_stride = m * width;
+          a.OUT = part - (j0 * a.split_stride + r0 * width + col);
+        }
+        if (pn.group < pl.JS) {
+          const int c0 = j0 * pl.cps;
+          pack(c0, min(a.JS * pl.cps, nchunks - c0));
+          a.VP = VP - (int64_t)c0 * 4 * NT * 64;
+        }
+        const dim3 grid((unsigned)((m + k.rows_per_wg - 1) / k.rows_per_wg) * a.JS);
+        const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
+        hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, st, a);
+        GP_HIP(ctx, hipGetLastError());
+        gp_prof_end(ctx, prof);
+        if (pn.rows) sum_images_of(m, width, j0 > 0, dOut + r0 * ldo + col);
       }
-      const dim3 grid((unsigned)((m + k.rows_per_wg - 1) / k.rows_per_wg) * pl.JS);
-      const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
-      hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, st, a);
-      GP_HIP(ctx, hipGetLastError());
-      gp_prof_end(ctx, prof);
-      if (panels) sum_images_of(m, width, dOut + r0 * ldo + col);
     }
     c += a.ncols;
   } while (c < t);
@@ -1276,7 +1322,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     defer->stride = a.split_stride;
     defer->JS = pl.JS;
   }
-  if (split && !defer && !panels) sum_images_of(nrows, t, dOut);
+  if (split && !defer && !pn.rows) sum_images_of(nrows, t, false, dOut);
   GP_HIP(ctx, hipGetLastError());
   return GP_OK;
 }
@@ -1333,6 +1379,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
   a.cm_ld = pk.ld;
   a.done = pk.done;
   a.rb0 = 0;
+  a.js0 = 0;
   const u32x4* VP = (const u32x4*)pk.VP;
   int vcol = has_vec_column(t) ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;

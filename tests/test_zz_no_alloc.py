@@ -97,7 +97,7 @@ def test_static_scratch_product_refuses_what_does_not_fit_and_bad_arguments():
     (131073, 26, "matern32", 97),     # two column passes, the second without the vector-ALU column, on two kernels
     (70001, 26, "matern32", 34),      # wide kernel, a ragged last panel
     (131073, 12, "se", 65),           # one row past a full generation of workgroups
-    (150000, 3, "se", 65), (240001, 2, "matern32", 66)])
+    (150000, 3, "se", 65), (230000, 26, "se", 17), (240001, 2, "matern32", 66)])
 def test_static_scratch_product_whose_partial_images_do_not_fit(n, d, kind, t):
     """Sizes whose column splits leave more partial images than the static scratch holds: row panels, the same bits."""
     rng = np.random.default_rng(n)
