@@ -250,7 +250,8 @@ int gp_predict(gp_ctx* ctx, const float* dXstar, int64_t m, const float* dV, int
  */
 enum {
   GP_PROF_TILE = 0,      /* K V tile pass (either arithmetic path) */
-  /* the three vector kernels of gp_cg_solve past n = 65536 or on the fp32 path (below that one kernel, not bracketed) */
+  /* the vector kernels of gp_cg_solve; up to n = 65536 on the fp16 paths one kernel does all of an iteration, counted as
+     GP_PROF_CG_XR, behind one that counts as GP_PROF_CG_DOT where n is past 16384: the sum of the three is the vector work */
   GP_PROF_CG_DOT = 1,    /* gp_cg_solve: p^T (H p) */
   GP_PROF_CG_XR = 2,     /* gp_cg_solve: x += alpha p, r -= alpha H p, r^T r */
   GP_PROF_CG_P = 3,      /* gp_cg_solve: p = r + beta p */

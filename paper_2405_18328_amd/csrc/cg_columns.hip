@@ -381,8 +381,14 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
     for (; queued < max_iters && queued <= finished + ahead; ++queued) {
       const int rc = gp_kmv_packed(ctx, t, pk, nullptr, 0, nullptr, &s.JS);
       if (rc < 0) return drained(rc);
-      if (long_columns) hipLaunchKernelGGL(cgc_sum_kernel, dim3((unsigned)((L.ld + CROWS - 1) / CROWS), t), dim3(256), 0, st, s);
+      if (long_columns) {
+        const bool pr = gp_prof_begin(ctx, GP_PROF_CG_DOT);
+        hipLaunchKernelGGL(cgc_sum_kernel, dim3((unsigned)((L.ld + CROWS - 1) / CROWS), t), dim3(256), 0, st, s);
+        gp_prof_end(ctx, pr);
+      }
+      const bool pr = gp_prof_begin(ctx, GP_PROF_CG_XR);
       hipLaunchKernelGGL(iter, grid, block, 0, st, s);
+      gp_prof_end(ctx, pr);
       GP_HIP(ctx, hipGetLastError());
     }
     const int rc = wait_steps(finished + 1);

@@ -58,3 +58,25 @@ def test_iterates_follow_the_textbook_recurrence(n, d, kind, t):
         assert torch.equal(V3, Vd)
     finally:
         dv.close()
+
+
+@pytest.mark.parametrize("n,kinds", [(2000, ("CG_XR",)), (16384, ("CG_XR",)), (16385, ("CG_DOT", "CG_XR")),
+                                     (65537, ("CG_DOT", "CG_XR", "CG_P"))])
+def test_profile_counts_the_vector_kernels(n, kinds):
+    """gp_profile times the vector work of every iteration, whichever kernels do it."""
+    rng = np.random.default_rng(n)
+    X = rng.uniform(-1.0, 1.0, size=(n, 3)).astype(np.float32)
+    B = rng.standard_normal((n, 5)).astype(np.float32)
+    dv = Dev(X, "se", np.full(3, 0.5), 0.9, 1.1)
+    try:
+        print(f"[cg columns] profile n={n}", flush=True)
+        dv.gp.gp_profile(dv.ctx, (1 << dv.gp.GP_PROF_KINDS) - 1)
+        _, iters, _, _, _ = dv.solve(B, 1e-7, max_iters=4)
+        read = {k: dv.gp.gp_profile_read_kind(dv.ctx, getattr(dv.gp, "GP_PROF_" + k)) for k in ("TILE", "CG_DOT", "CG_XR", "CG_P")}
+        dv.gp.gp_profile(dv.ctx, 0)
+        assert iters == 4
+        for k, (launches, ms) in read.items():
+            assert launches == (iters if k == "TILE" or k in kinds else 0), read
+            assert ms > 0.0 or not launches
+    finally:
+        dv.close()
