@@ -475,9 +475,13 @@ int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
     (void)hipStreamSynchronize(st);
     return rc;
   };
+  auto failed = [&](hipError_t e) -> bool {
+    if (e != hipSuccess) (void)drained(gp_fail(ctx, GP_ERR_HIP, "gp_ap_solve: %s", hipGetErrorString(e)));
+    return e != hipSuccess;
+  };
 
   const dim3 grid(column_blocks(t)), cblock(CT);
-  GP_HIP(ctx, hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st));
+  if (failed(hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st))) return GP_ERR_HIP;
   auto clear = [&](void* p, size_t bytes) {
     const int64_t units = (int64_t)(bytes / 16);
     int blocks = (int)((units + 255) / 256);
@@ -488,7 +492,7 @@ int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   clear(s.VP, (size_t)L.units * 16);   // columns that pad the last tile, and stopped columns, are never written
   clear(s.D, L.off_bnorm - L.off_D);   // D and VY
   hipLaunchKernelGGL(to_columns_kernel, transpose_grid(L.ld, t, 2), dim3(256), 0, st, dB, ldb, s.R, dX0, ldv, s.V, ctx->n, L.ld, t);
-  GP_HIP(ctx, hipGetLastError());
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
   int rc = gp_ap_inverses(ctx, block, L.nb, L.BP, L.batch, (float*)(w + L.off_hinv), (double*)(w + L.off_A), (double*)(w + L.off_W),
                           (double*)(w + L.off_T), (double*)(w + L.off_DI), fac_breakdown);
   if (rc < 0) return drained(rc);
@@ -511,7 +515,7 @@ int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   const bool small = (int64_t)((L.nb + L.parts - 1) / L.parts) * block <= 2 * CROWS;   // rows of a part
   hipLaunchKernelGGL((small ? apc_update_kernel<2, true> : apc_update_kernel<4, true>), ugrid, cblock, 0, st, s, dX0 ? 1 : 0);
   if (dX0 && t % 32 > 1) clear(s.VP, (size_t)L.units * 16);   // the windows' operands are laid out anew
-  GP_HIP(ctx, hipGetLastError());
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
 
   const KmvBlock win = {&s.flags->pad, block, L.win_chunks};
   pk.VY = s.VY;
@@ -541,7 +545,7 @@ int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
       rc = gp_kmv_packed(ctx, t, pk, nullptr, 0, &win, &s.JS);
       if (rc < 0) return drained(rc);
       hipLaunchKernelGGL(update, ugrid, cblock, 0, st, s, 0);
-      GP_HIP(ctx, hipGetLastError());
+      if (failed(hipGetLastError())) return GP_ERR_HIP;
     }
     if (h_picks) h_picks[finished] = sel;
     rc = wait_steps(finished + 1);
@@ -550,10 +554,10 @@ int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
 
   hipLaunchKernelGGL(from_columns_kernel, transpose_grid(L.ld, t, 1), dim3(256), 0, st, (const float*)s.V, L.ld, ctx->n, t,
                      (const int*)s.zero_rhs, dV, ldv);
-  GP_HIP(ctx, hipGetLastError());
-  GP_HIP(ctx, hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipStreamSynchronize(st));
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
+  if (failed(hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st))) return GP_ERR_HIP;
+  if (failed(hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st))) return GP_ERR_HIP;
+  if (failed(hipStreamSynchronize(st))) return GP_ERR_HIP;
   if (h_iters) *h_iters = hflags->iters;
   if (h_kmv_count) *h_kmv_count = kmv_count;
   if (h_relres)

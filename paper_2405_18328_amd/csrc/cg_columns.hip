@@ -330,6 +330,10 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
     (void)hipStreamSynchronize(st);
     return rc;
   };
+  auto failed = [&](hipError_t e) -> bool {
+    if (e != hipSuccess) (void)drained(gp_fail(ctx, GP_ERR_HIP, "gp_cg_solve: %s", hipGetErrorString(e)));
+    return e != hipSuccess;
+  };
 
   const dim3 grid(column_blocks(t)), block(CT);
   KmvPacked pk;
@@ -337,7 +341,7 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   pk.colmax = s.colmax;
   pk.images = (float*)(w + L.off_images);
   pk.ld = L.ld;
-  GP_HIP(ctx, hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st));
+  if (failed(hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st))) return GP_ERR_HIP;
   hipLaunchKernelGGL(clear_units_kernel, dim3(1), dim3(256), 0, st, (u32x4*)s.flags, (int64_t)(sizeof(ColFlags) / 16));
   if (t % 32 > 1) {   // the columns that pad the last tile are never written
     int blocks = (int)((L.units + 255) / 256);
@@ -345,7 +349,7 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
     hipLaunchKernelGGL(clear_units_kernel, dim3(blocks), dim3(256), 0, st, s.VP, L.units);
   }
   hipLaunchKernelGGL(to_columns_kernel, transpose_grid(L.ld, t, 2), dim3(256), 0, st, dB, ldb, s.R, dX0, ldv, s.X, ctx->n, L.ld, t);
-  GP_HIP(ctx, hipGetLastError());
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
   int kmv_count = 0;
   if (dX0) {
     hipLaunchKernelGGL(pack_columns_kernel, grid, block, 0, st, (const float*)s.X, s.VP, s.colmax, t, L.ld);
@@ -356,7 +360,7 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
     ++kmv_count;
   }
   hipLaunchKernelGGL(cgc_start_kernel, grid, block, 0, st, s, dX0 ? 1 : 0);
-  GP_HIP(ctx, hipGetLastError());
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
 
   pk.VY = s.P;
   pk.done = &s.flags->all_done;
@@ -389,7 +393,7 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
       const bool pr = gp_prof_begin(ctx, GP_PROF_CG_XR);
       hipLaunchKernelGGL(iter, grid, block, 0, st, s);
       gp_prof_end(ctx, pr);
-      GP_HIP(ctx, hipGetLastError());
+      if (failed(hipGetLastError())) return GP_ERR_HIP;
     }
     const int rc = wait_steps(finished + 1);
     if (rc < 0) return drained(rc);
@@ -397,10 +401,10 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
 
   hipLaunchKernelGGL(from_columns_kernel, transpose_grid(L.ld, t, 1), dim3(256), 0, st, (const float*)s.X, L.ld, ctx->n, t,
                      (const int*)s.zero_rhs, dV, ldv);
-  GP_HIP(ctx, hipGetLastError());
-  GP_HIP(ctx, hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipStreamSynchronize(st));
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
+  if (failed(hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st))) return GP_ERR_HIP;
+  if (failed(hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st))) return GP_ERR_HIP;
+  if (failed(hipStreamSynchronize(st))) return GP_ERR_HIP;
   if (h_iters) *h_iters = hflags->iters;
   if (h_kmv_count) *h_kmv_count = kmv_count + hflags->iters;
   if (h_relres)

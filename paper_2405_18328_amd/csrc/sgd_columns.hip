@@ -342,6 +342,10 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
     (void)hipStreamSynchronize(st);
     return rc;
   };
+  auto failed = [&](hipError_t e) -> bool {
+    if (e != hipSuccess) (void)drained(gp_fail(ctx, GP_ERR_HIP, "gp_sgd_solve: %s", hipGetErrorString(e)));
+    return e != hipSuccess;
+  };
 
   const dim3 grid(column_blocks(t)), block(CT);
   KmvPacked pk;
@@ -351,7 +355,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
   pk.images = (float*)(w + L.off_images);
   pk.ld = L.ld;
   pk.done = nullptr;
-  GP_HIP(ctx, hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st));
+  if (failed(hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st))) return GP_ERR_HIP;
   hipLaunchKernelGGL(clear_units_kernel, dim3(1), dim3(256), 0, st, (u32x4*)s.flags, (int64_t)(sizeof(ColFlags) / 16 + 1));
   if (!dX0 || t % 32 > 1) {   // U = 0, or columns that pad the last tile: operands nobody writes before the product reads them
     int blocks = (int)((L.units + 255) / 256);
@@ -359,7 +363,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
     if (blocks > 0) hipLaunchKernelGGL(clear_units_kernel, dim3(blocks), dim3(256), 0, st, s.VP, L.units);
   }
   hipLaunchKernelGGL(to_columns_kernel, transpose_grid(L.ld, t, 2), dim3(256), 0, st, dB, ldb, s.B, dX0, ldv, s.U, ctx->n, L.ld, t);
-  GP_HIP(ctx, hipGetLastError());
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
   int kmv_count = 0;
   if (dX0) {
     hipLaunchKernelGGL(pack_columns_kernel, grid, block, 0, st, (const float*)s.U, s.VP, s.colmax, t, L.ld);
@@ -368,7 +372,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
     ++kmv_count;
   }
   hipLaunchKernelGGL(sgdc_start_kernel, grid, block, 0, st, s, dX0 ? 1 : 0);
-  GP_HIP(ctx, hipGetLastError());
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
 
   pk.ld = L.gld;
   pk.done = &s.flags->all_done;
@@ -376,7 +380,8 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
   const step_fn step = L.ld <= CROWS ? sgdc_step_kernel<1> : L.ld <= 2 * CROWS ? sgdc_step_kernel<2> : L.ld <= 4 * CROWS ? sgdc_step_kernel<4>
                                                                                                  : sgdc_step_kernel<0>;
   const size_t lds = L.ld <= 4 * CROWS ? (size_t)L.ld * sizeof(float) : 0;
-  if (lds > 48 * 1024) GP_HIP(ctx, hipFuncSetAttribute((const void*)step, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  if (lds > 48 * 1024 && failed(hipFuncSetAttribute((const void*)step, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
+    return GP_ERR_HIP;
   const int slices = (batch + GT - 1) / GT;
   // Steps queued ahead of the flags the host has seen; kernels queued past the end return at once.
   const int ahead = ctx->prof_mask ? 0 : 4;
@@ -399,7 +404,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
       auto* grad = s.JS <= 8 ? sgdc_grad_kernel<8> : s.JS <= 24 ? sgdc_grad_kernel<24> : sgdc_grad_kernel<64>;
       hipLaunchKernelGGL(grad, dim3(slices, t), dim3(GT), 0, st, s, I);
       hipLaunchKernelGGL(step, grid, block, lds, st, s, I, slices);
-      GP_HIP(ctx, hipGetLastError());
+      if (failed(hipGetLastError())) return GP_ERR_HIP;
     }
     const int rc = wait_steps(finished + 1);
     if (rc < 0) return drained(rc);
@@ -407,10 +412,10 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
 
   hipLaunchKernelGGL(from_columns_kernel, transpose_grid(L.ld, t, 1), dim3(256), 0, st, (const float*)s.U, L.ld, ctx->n, t,
                      (const int*)s.zero_rhs, dV, ldv);
-  GP_HIP(ctx, hipGetLastError());
-  GP_HIP(ctx, hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipStreamSynchronize(st));
+  if (failed(hipGetLastError())) return GP_ERR_HIP;
+  if (failed(hipMemcpyAsync(hrel, s.relres, sizeof(float) * t, hipMemcpyDeviceToHost, st))) return GP_ERR_HIP;
+  if (failed(hipMemcpyAsync(hflags, s.flags, sizeof(ColFlags), hipMemcpyDeviceToHost, st))) return GP_ERR_HIP;
+  if (failed(hipStreamSynchronize(st))) return GP_ERR_HIP;
   if (h_iters) *h_iters = hflags->iters;
   if (h_kmv_count) *h_kmv_count = kmv_count;
   if (h_relres)
