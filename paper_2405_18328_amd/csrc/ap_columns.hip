@@ -236,7 +236,7 @@ __global__ __launch_bounds__(CT) void apc_update_kernel(ApCols s, int warm) {
   }
   if (go) {
     for (int k = tid; k < k1 - k0; k += CT) bn[k] = 0.0;
-    float bb = 0.0f;
+    double bb = 0.0;
     for (int base = (int)(r0 / 4); base < q_end; base += CT * Q) {
       if (base > (int)(r0 / 4)) fetch(base);
       __syncthreads();     // bn is cleared, and the squares of the stretch before have been read
@@ -245,9 +245,11 @@ __global__ __launch_bounds__(CT) void apc_update_kernel(ApCols s, int warm) {
         const int k = base + CT * j + tid;
         if (k < q_end) {
           if (START) {
+            f32x4 own = r[j];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-              if (4 * k + q >= r0 && 4 * k + q < r1) bb = fmaf(r[j][q], r[j][q], bb);
+              if (4 * k + q < r0 || 4 * k + q >= r1) own[q] = 0.0f;
+            bb += dot4(own, own);
             if (warm) {
               const f32x4 x = *reinterpret_cast<const f32x4*>(s.V + col + 4 * k);
 #pragma unroll
@@ -278,7 +280,7 @@ __global__ __launch_bounds__(CT) void apc_update_kernel(ApCols s, int warm) {
       block_norms(sq, 4 * (int64_t)base, max(4 * (int64_t)base, r0), min(4 * (int64_t)(base + CT * Q), r1), s, k0, bn);
     }
     if (START) {
-      const double b2 = column_sum((double)bb, shd);
+      const double b2 = column_sum(bb, shd);
       if (tid == 0) put(&s.bpart[(int64_t)c * parts + blockIdx.x], b2);
     }
     __syncthreads();

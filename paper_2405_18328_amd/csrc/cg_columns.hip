@@ -42,11 +42,11 @@ __global__ __launch_bounds__(CT) void cgc_start_kernel(CgCols s, int warm) {
   const int c = block_column(s.t);
   if (c < 0) return;
   const int64_t col = (int64_t)c * s.ld;
-  float bb = 0.0f, rr = 0.0f, mx = 0.0f;
+  double bb = 0.0, rr = 0.0;
+  float mx = 0.0f;
   for (int64_t k = threadIdx.x; k < s.ld / 4; k += CT) {
     f32x4 r = *reinterpret_cast<const f32x4*>(s.R + col + 4 * k);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bb = fmaf(r[q], r[q], bb);
+    bb += dot4(r, r);
     if (warm) {
       const f32x4 x = *reinterpret_cast<const f32x4*>(s.X + col + 4 * k);
       const f32x4 hx = sum_images(s.images, s.JS, s.stride, col + 4 * k, 4 * k, s.n);
@@ -55,14 +55,12 @@ __global__ __launch_bounds__(CT) void cgc_start_kernel(CgCols s, int warm) {
       *reinterpret_cast<f32x4*>(s.R + col + 4 * k) = r;
     }
     *reinterpret_cast<f32x4*>(s.P + col + 4 * k) = r;
+    rr += dot4(r, r);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      rr = fmaf(r[q], r[q], rr);
-      mx = fmaxf(mx, fabsf(r[q]));
-    }
+    for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(r[q]));
   }
-  const double bn2 = column_sum((double)bb, shd);
-  const double rho = column_sum((double)rr, shd);
+  const double bn2 = column_sum(bb, shd);
+  const double rho = column_sum(rr, shd);
   pack_column(s.VP, s.colmax, s.t, s.ld, c, s.P + col, mx, shf);
   if (threadIdx.x == 0) {
     const int zero = !(bn2 > 0.0);
@@ -85,7 +83,7 @@ __global__ __launch_bounds__(256) void cgc_sum_kernel(CgCols s) {
   const int c = blockIdx.y;
   const int64_t col = (int64_t)c * s.ld;
   const int nk = (int)(s.ld / 4);
-  float acc = 0.0f;
+  double v = 0.0;
   f32x4 p[4], h[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -101,14 +99,11 @@ __global__ __launch_bounds__(256) void cgc_sum_kernel(CgCols s) {
     const int k = blockIdx.x * CT + threadIdx.x + 256 * j;
     if (k < nk) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        h[j][q] = fmaf(s.sigma2, p[j][q], h[j][q]);
-        acc = fmaf(p[j][q], h[j][q], acc);
-      }
+      for (int q = 0; q < 4; ++q) h[j][q] = fmaf(s.sigma2, p[j][q], h[j][q]);
+      v += dot4(p[j], h[j]);
       *reinterpret_cast<f32x4*>(s.HP + col + 4 * k) = h[j];
     }
   }
-  double v = (double)acc;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
@@ -147,17 +142,16 @@ __global__ __launch_bounds__(CT) void cgc_iter_kernel(CgCols s) {
   bool go = !s.frozen[c], bad = false;
   if (s.flags->all_done) return;
   if (go) {
-    float acc = 0.0f;
+    double acc = 0.0;
     double gamma;
     if constexpr (Q > 0) {
 #pragma unroll
-      for (int j = 0; j < Q; ++j)
+      for (int j = 0; j < Q; ++j) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          hp[j][q] = fmaf(s.sigma2, p[j][q], hp[j][q]);
-          acc = fmaf(p[j][q], hp[j][q], acc);
-        }
-      gamma = column_sum((double)acc, shd);
+        for (int q = 0; q < 4; ++q) hp[j][q] = fmaf(s.sigma2, p[j][q], hp[j][q]);
+        acc += dot4(p[j], hp[j]);
+      }
+      gamma = column_sum(acc, shd);
     } else {
       gamma = 0.0;
       const int slices = (nk + CT - 1) / CT;
@@ -166,7 +160,7 @@ __global__ __launch_bounds__(CT) void cgc_iter_kernel(CgCols s) {
     float al = 0.0f;
     if (!(gamma > 0.0) || !isfinite(gamma)) bad = true;
     else al = (float)(rho / gamma);
-    acc = 0.0f;
+    acc = 0.0;
     if constexpr (Q > 0) {
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
@@ -175,8 +169,8 @@ __global__ __launch_bounds__(CT) void cgc_iter_kernel(CgCols s) {
         for (int q = 0; q < 4; ++q) {
           x[j][q] = fmaf(al, p[j][q], x[j][q]);
           r[j][q] = fmaf(-al, hp[j][q], r[j][q]);
-          acc = fmaf(r[j][q], r[j][q], acc);
         }
+        acc += dot4(r[j], r[j]);
         if (k < nk) {
           *reinterpret_cast<f32x4*>(s.X + col + 4 * k) = x[j];
           *reinterpret_cast<f32x4*>(s.R + col + 4 * k) = r[j];
@@ -193,13 +187,13 @@ __global__ __launch_bounds__(CT) void cgc_iter_kernel(CgCols s) {
         for (int q = 0; q < 4; ++q) {
           xk[q] = fmaf(al, pk[q], xk[q]);
           rk[q] = fmaf(-al, h[q], rk[q]);
-          acc = fmaf(rk[q], rk[q], acc);
         }
+        acc += dot4(rk, rk);
         *reinterpret_cast<f32x4*>(s.X + col + 4 * k) = xk;
         *reinterpret_cast<f32x4*>(s.R + col + 4 * k) = rk;
       }
     }
-    const double rho_new = column_sum((double)acc, shd);
+    const double rho_new = column_sum(acc, shd);
     const double rel = sqrt(rho_new / bn2);
     if (!isfinite(rho_new)) bad = true;
     const float be = (float)(rho_new / rho);

@@ -70,6 +70,11 @@ __device__ __forceinline__ float pack_scale(float max_abs) {
   return ldexpf(1.0f, V_TOP - column_exponent(__float_as_uint(max_abs)));
 }
 
+// x . y of four rows; handed to an fp64 sum at once, since a longer fp32 chain loses small terms behind large ones
+__device__ __forceinline__ double dot4(f32x4 x, f32x4 y) {
+  return (double)fmaf(x[3], y[3], fmaf(x[2], y[2], fmaf(x[1], y[1], x[0] * y[0])));
+}
+
 // sum / max over the workgroup, in a fixed order, known to every thread afterwards
 __device__ __forceinline__ double column_sum(double v, double* sh /* [16] */) {
 #pragma unroll

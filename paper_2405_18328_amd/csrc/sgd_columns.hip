@@ -38,11 +38,10 @@ __global__ __launch_bounds__(CT) void sgdc_start_kernel(SgdCols s, int warm) {
   const int c = block_column(s.t);
   if (c < 0) return;
   const int64_t col = (int64_t)c * s.ld;
-  float bb = 0.0f, rr = 0.0f;
+  double bb = 0.0, rr = 0.0;
   for (int64_t k = threadIdx.x; k < s.ld / 4; k += CT) {
     f32x4 r = *reinterpret_cast<const f32x4*>(s.B + col + 4 * k);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bb = fmaf(r[q], r[q], bb);
+    bb += dot4(r, r);
     if (warm) {
       const f32x4 x = *reinterpret_cast<const f32x4*>(s.U + col + 4 * k);
       const f32x4 hx = sum_images(s.images, s.JS, s.stride, col + 4 * k, 4 * k, s.n);
@@ -51,11 +50,10 @@ __global__ __launch_bounds__(CT) void sgdc_start_kernel(SgdCols s, int warm) {
     }
     *reinterpret_cast<f32x4*>(s.R + col + 4 * k) = r;
     *reinterpret_cast<f32x4*>(s.M + col + 4 * k) = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) rr = fmaf(r[q], r[q], rr);
+    rr += dot4(r, r);
   }
-  const double bn2 = column_sum((double)bb, shd);
-  const double r2 = column_sum((double)rr, shd);
+  const double bn2 = column_sum(bb, shd);
+  const double r2 = column_sum(rr, shd);
   if (threadIdx.x == 0) {
     const int zero = bn2 == 0.0;
     const double rel = zero ? 0.0 : sqrt(r2 / bn2);
