@@ -3,7 +3,10 @@
 The library runs on a stand-in for the HIP runtime, on the CPU: kernels do nothing, device memory is host memory, and
 every query of the stream reports one more finished step in the place the solvers' kernels post to.  The stand-in fails
 one runtime call after the other, through a whole solve; whatever was queued before has to be waited for, since a
-kernel left over would write to the caller's workspace and post into the next solve."""
+kernel left over would write to the caller's workspace and post into the next solve.
+
+On the way: the kernels with 1024 threads, of which a compute unit runs one workgroup at a time, are not launched with
+a few workgroups more than there are compute units."""
 import os
 import subprocess
 import sys
@@ -17,11 +20,12 @@ RUNTIME = r"""
 #include <cstdlib>
 #include <cstring>
 static char* pinned;
-static int queued, until_failure;
+static int queued, until_failure, wide;
 static unsigned steps;
 static hipError_t fallible() { return until_failure > 0 && --until_failure == 0 ? hipErrorUnknown : hipSuccess; }
 extern "C" {
 int fake_queued() { return queued; }
+int fake_wide() { return wide; }      // most workgroups of a launch with 1024 threads each
 int fake_fail(int k) { const int left = until_failure; until_failure = k; steps = 0; queued = 0; return left; }
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
 void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
@@ -31,7 +35,11 @@ hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return 
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* m, hipStream_t* s) {
   *g = *b = dim3(1); *m = 0; *s = nullptr; return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { ++queued; return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3 g, dim3 b, void**, size_t, hipStream_t) {
+  ++queued;
+  if (b.x == 1024 && (int)(g.x * g.y) > wide) wide = g.x * g.y;
+  return hipSuccess;
+}
 hipError_t hipGetLastError() { return fallible(); }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return fallible(); }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
@@ -92,6 +100,7 @@ def solve():
     if solver == "ap": return lib.gp_ap_solve(*head, batch, 6, *tail, None)
     return lib.gp_sgd_solve(*head, I, batch, 6, C.c_double(1e-3), C.c_double(0.9), *tail)
 assert fake.fake_fail(0) == 0 and solve() == 1, lib.gp_last_error(ctx)     # not converged after 6 steps
+assert 0 < fake.fake_wide() <= 256, "%d workgroups of a launch on 256 compute units" % fake.fake_wide()
 k = 0
 while True:
     k += 1
