@@ -42,6 +42,7 @@ struct ApCols {
 };
 
 constexpr int POSTS = 16;
+constexpr int AP_FEW_BLOCKS = 40;    // up to here one wave per block ends a step, beyond it a thread per block (see there)
 
 // d = H[I,I]^-1 R[I,:] for the block the last step chose.  One workgroup per 32 rows, 16 NTL columns and one of SOLVE_KS
 // ranges of the contraction index, whose sums apc_pack adds (v_mfma_f32_16x16x4_f32: A operand lane l holds A[l % 16][l / 16],
@@ -296,54 +297,113 @@ __global__ __launch_bounds__(CT) void apc_update_kernel(ApCols s, int warm) {
   __syncthreads();
   if (!last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  // Everything the tail needs is requested at once: the block norms into LDS, where they fit, the columns' state into
-  // the thread that judges the column.
-  double* norms = reinterpret_cast<double*>(sq);
-  constexpr int NORMS = CROWS * Q / 2;
-  const int total = s.t * s.nb;
-  const bool staged = total <= NORMS;
-  if (staged)
-    for (int e = tid; e < total; e += CT) norms[e] = get(&s.bnorm[e]);
-  if (START)
-    for (int k = 0; k < parts; ++k) bn2 += get(&s.bpart[(int64_t)q0 * parts + k]);
-  __syncthreads();
-  if (tid < s.t) {
-    double v = 0.0;
+  // Judges a column by the sum of its block norms; by the thread of the column's number.
+  auto judge = [&](double v) {
+    bool goes_on = false;
     if (!stopped0) {
-      if (staged) {
-        for (int k = 0; k < s.nb; ++k) v += norms[tid * s.nb + k];
-      } else {
-#pragma unroll 8
-        for (int k = 0; k < s.nb; ++k) v += get(&s.bnorm[(int64_t)tid * s.nb + k]);
-      }
       const int zero = bn2 == 0.0;
       const double rel = zero ? 0.0 : sqrt(v / bn2);
-      const bool goes_on = !(zero || (float)rel < tol);
+      goes_on = !(zero || (float)rel < tol);
       if (START) {
         s.bn2[tid] = bn2;
         s.zero_rhs[tid] = zero;
       }
       s.relres[tid] = (float)rel;
       s.frozen[tid] = goes_on ? 0 : 1;
-      live[tid] = goes_on ? 1 : 0;
       if (goes_on) any_live = 1;
       if (!zero && (!(rel == rel) || rel > 3.0e38)) any_bad = 1;
-    } else {
-      live[tid] = 0;
     }
-  }
-  __syncthreads();
+    live[tid] = goes_on ? 1 : 0;
+  };
+  // The block norms are staged in LDS, as many columns at a time as fit: all loads of a thread in flight together, those of the
+  // next columns ahead of the work on these.
+  double* norms = reinterpret_cast<double*>(sq);
+  constexpr int NORMS = CROWS * Q / 2, PER = NORMS / CT;
+  const int cols = min(min(s.t, AP_COLUMNS_MAX_BLOCKS), NORMS / s.nb);    // their sums go to bn
+  double next[PER];
+  auto request = [&](int c0) {
+    const int count = min(cols, s.t - c0) * s.nb;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (tid + CT * u < count) next[u] = get(&s.bnorm[(int64_t)c0 * s.nb + tid + CT * u]);
+  };
+  auto stage = [&](int c0) {
+    const int count = min(cols, s.t - c0) * s.nb;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (tid + CT * u < count) norms[tid + CT * u] = next[u];
+    __syncthreads();
+  };
+  request(0);
+  if (START && tid < s.t)
+    for (int k = 0; k < parts; ++k) bn2 += get(&s.bpart[(int64_t)tid * parts + k]);
+  stage(0);
   double best = -1.0;
   int at = 0x7fffffff;
-  for (int k = wave; k < s.nb; k += CT / 64) {
-    double v = 0.0;
-    for (int q = lane; q < s.t; q += 64)
-      if (live[q]) v += staged ? norms[q * s.nb + k] : get(&s.bnorm[(int64_t)q * s.nb + k]);
+  if (cols == s.t && s.nb <= AP_FEW_BLOCKS) {
+    // few blocks: a thread per column, then a wave per block
+    if (tid < s.t) {
+      double v = 0.0;
+      for (int k = 0; k < s.nb; ++k) v += norms[tid * s.nb + k];
+      judge(v);
+    }
+    __syncthreads();
+    for (int k = wave; k < s.nb; k += CT / 64) {
+      double v = 0.0;
+      for (int q = lane; q < s.t; q += 64)
+        if (live[q]) v += norms[q * s.nb + k];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (v > best) {
-      best = v;
-      at = k;
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+      if (v > best) {
+        best = v;
+        at = k;
+      }
+    }
+  } else {
+    // 16 lanes add up a column; a thread per block, in `groups` groups of columns, adds up the block over the columns that go on.
+    // Per block update: n = 65536 block 256 t = 65 (three stages; the thread of a column read its norms one after the other)
+    // 87 -> 70 us; n = 16384 t = 17, a wave per block -> a thread per block: 128 blocks 41.7 -> 36.2 us, 41 blocks 36.5 -> 36.2,
+    // 17 blocks (n = 8192) 36.1 -> 36.9.
+    const int log_nb = s.nb <= 64 ? 6 : s.nb <= 128 ? 7 : 8;
+    const int mine = tid & ((1 << log_nb) - 1), group = tid >> log_nb, groups = CT >> log_nb;
+    double score = 0.0;
+    for (int c0 = 0; c0 < s.t; c0 += cols) {
+      const int nc = min(cols, s.t - c0);
+      if (c0 + cols < s.t) request(c0 + cols);
+      for (int q = tid >> 4; q < nc; q += CT / 16) {
+        double v = 0.0;
+        for (int k = tid & 15; k < s.nb; k += 16) v += norms[q * s.nb + k];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if ((tid & 15) == 0) bn[q] = v;
+      }
+      __syncthreads();
+      if (tid >= c0 && tid < c0 + nc) judge(bn[tid - c0]);
+      __syncthreads();
+      if (mine < s.nb)
+        for (int q = group; q < nc; q += groups)
+          if (live[c0 + q]) score += norms[q * s.nb + mine];
+      __syncthreads();     // the next columns take the place of these
+      if (c0 + cols < s.t) stage(c0 + cols);
+    }
+    norms[tid] = score;
+    __syncthreads();
+    if (tid < s.nb) {
+      double v = 0.0;
+      for (int g = 0; g < groups; ++g) v += norms[(g << log_nb) + tid];
+      if (v > best) {
+        best = v;
+        at = tid;
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {     // the largest, the lowest block on a tie
+      const double v = __shfl_xor(best, off);
+      const int k = __shfl_xor(at, off);
+      if (v > best || (v == best && k < at)) {
+        best = v;
+        at = k;
+      }
     }
   }
   if (lane == 0) {
