@@ -31,9 +31,10 @@ void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
 void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 void __hipUnregisterFatBinary(void**) {}
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+static dim3 grid, block;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t) { grid = g; block = b; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* m, hipStream_t* s) {
-  *g = *b = dim3(1); *m = 0; *s = nullptr; return hipSuccess;
+  *g = grid; *b = block; *m = 0; *s = nullptr; return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void*, dim3 g, dim3 b, void**, size_t, hipStream_t) {
   ++queued;
