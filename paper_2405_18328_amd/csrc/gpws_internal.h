@@ -249,8 +249,14 @@ int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, floa
                void* dWork, size_t work_bytes, int* h_iters, int* h_kmv_count, float* h_relres);
 
 // ---- sgd_columns.hip: the same solve for problems up to this size on the f16 product paths
-constexpr int64_t SGD_COLUMNS_MAX_N = 131072;
-bool gp_sgd_by_columns(const gp_ctx* ctx);
+// Its vector work takes one compute unit per column, a time that grows with n but not with t up to 256, the streaming
+// kernels' with n t.  Per step with batches of 1000, Matern-3/2, d = 26, streaming -> columns:
+//   n = 65536   t = 1  83 -> 50 us, t = 17  76 -> 72, t = 33  84 -> 79, t = 65  116 -> 97
+//   n = 81920   t = 1  92 -> 59,    t = 17  84 -> 84, t = 33  94 -> 94, t = 48 109 -> 103
+//   n = 131072  t = 1 114 -> 83,    t = 17 109 -> 126, t = 48 142 -> 153, t = 65 170 -> 164, t = 97 267 -> 255
+// (for a single column the streaming kernels have too few workgroups).
+constexpr int64_t SGD_COLUMNS_MAX_N = 131072, SGD_COLUMNS_FEW_N = 81920;
+bool gp_sgd_by_columns(const gp_ctx* ctx, int t);
 size_t gp_sgd_columns_workspace_bytes(const gp_ctx* ctx, int t, int batch);
 int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,
                        const float* h_tol, const int* dBatches, int batch, int max_iters, double lr, double momentum,

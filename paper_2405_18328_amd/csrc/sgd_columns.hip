@@ -1,5 +1,5 @@
-// Stochastic gradient descent with one workgroup per column, for n <= SGD_COLUMNS_MAX_N on the split-fp16 product
-// paths: the same step, stopping rule and freezing as the streaming kernels of sgd_kernels.hip, in three
+// Stochastic gradient descent with one workgroup per column, for n <= SGD_COLUMNS_FEW_N (SGD_COLUMNS_MAX_N with one or
+// more than 64 columns) on the split-fp16 product paths: the same step, stopping rule and freezing as the streaming kernels of sgd_kernels.hip, in three
 // launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
 // context's packed operands; the gradient on the mini-batch rows is spread over the chip; momentum, iterate,
 // the stopping test and the packing of the iterate for the next product are per column (columns.h).
@@ -282,7 +282,9 @@ typedef void (*step_fn)(SgdCols, const int*, int);
 
 }  // namespace
 
-bool gp_sgd_by_columns(const gp_ctx* ctx) { return ctx->n <= SGD_COLUMNS_MAX_N; }
+bool gp_sgd_by_columns(const gp_ctx* ctx, int t) {
+  return ctx->n <= (t == 1 || t > 64 ? SGD_COLUMNS_MAX_N : SGD_COLUMNS_FEW_N);
+}
 size_t gp_sgd_columns_workspace_bytes(const gp_ctx* ctx, int t, int batch) { return layout(ctx, t, batch).total; }
 
 int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, float* dV, int64_t ldv, int t,

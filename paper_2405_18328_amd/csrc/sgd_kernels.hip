@@ -400,7 +400,7 @@ SgdLayout sgd_layout(const gp_ctx* ctx, int t, int batch) {
 // covers both forms of the solver: theta, and with it the product path, may change after the caller asked
 size_t gp_sgd_workspace_bytes_impl(const gp_ctx* ctx, int t, int batch) {
   const size_t streams = sgd_layout(ctx, t, batch).total;
-  const size_t columns = gp_sgd_by_columns(ctx) ? gp_sgd_columns_workspace_bytes(ctx, t, batch) : 0;
+  const size_t columns = gp_sgd_by_columns(ctx, t) ? gp_sgd_columns_workspace_bytes(ctx, t, batch) : 0;
   return streams > columns ? streams : columns;
 }
 
@@ -411,7 +411,7 @@ int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, floa
   const size_t need = gp_sgd_workspace_bytes_impl(ctx, t, batch);
   if (work_bytes < need) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_sgd_solve: workspace %zu < %zu bytes", work_bytes, need);
   if ((uintptr_t)dWork % 256) return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_sgd_solve: workspace not 256-byte aligned");
-  if (gp_sgd_by_columns(ctx) && ctx->path != GP_PATH_FP32)
+  if (gp_sgd_by_columns(ctx, t) && ctx->path != GP_PATH_FP32)
     return gp_sgd_columns_run(ctx, dB, ldb, dX0, dV, ldv, t, h_tol, dBatches, batch, max_iters, lr, momentum, dWork, h_iters,
                               h_kmv_count, h_relres);
   hipStream_t st = ctx->stream;

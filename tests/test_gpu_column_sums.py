@@ -16,7 +16,7 @@ from tests.gpu_util import Dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("solver,n,t", [("cg", 65536, 2), ("cg", 16384, 3), ("sgd", 131072, 2), ("sgd", 65536, 3), ("ap", 65536, 130)])
+@pytest.mark.parametrize("solver,n,t", [("cg", 65536, 2), ("cg", 16384, 3), ("sgd", 131072, 1), ("sgd", 65536, 3), ("ap", 65536, 130)])
 def test_start_residual(solver, n, t):
     rng = np.random.default_rng(n)
     X = rng.uniform(-1.0, 1.0, size=(n, 2)).astype(np.float32)

@@ -1,5 +1,5 @@
-"""gp_sgd_solve with one workgroup per column (n <= 131072 on the fp16 product paths) at the edges of the column lengths
-and batch sizes its kernels are built for: the oracle's step run on exact rows of the same problem."""
+"""gp_sgd_solve with one workgroup per column (on the fp16 product paths, n <= 81920, or 131072 with one or more than 64
+columns) at the edges of the column lengths and batch sizes its kernels are built for, and just past them: the oracle's step run on exact rows of the same problem."""
 import numpy as np
 import pytest
 
@@ -23,7 +23,8 @@ def _reference(X, ell, a, sigma, kind, B, batches, X0, lr, momentum):
 
 
 @pytest.mark.parametrize("n,t,batch", [(1, 1, 1), (33, 2, 7), (4096, 17, 257), (4097, 33, 1000), (8193, 66, 31), (16384, 65, 1000),
-                                       (16385, 9, 1025), (20003, 1, 64), (40001, 17, 1500), (131072, 2, 100), (131073, 2, 100)])
+                                       (16385, 9, 1025), (20003, 1, 64), (40001, 17, 1500), (131072, 2, 100), (131073, 2, 100),
+                                       (81920, 2, 100), (81921, 64, 50), (131072, 1, 100), (131072, 65, 40)])
 @pytest.mark.parametrize("kind", ["se", "matern32"])
 def test_iterates_follow_the_step(n, t, batch, kind):
     rng = np.random.default_rng(n + t)
