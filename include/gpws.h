@@ -95,7 +95,8 @@ int gp_set_theta(gp_ctx* ctx, const double* h_lengthscale, double signal_scale, 
  * (GP_ERR_ARG otherwise).  1 <= t <= GP_MAX_T.
  * Asynchronous on the context's stream, except that the first call, and any call
  * that needs more scratch than an earlier one (larger t), waits for the stream
- * and reallocates the context's scratch block with hipMalloc.
+ * and reallocates the context's scratch block with hipMalloc.  It holds 260 bytes per
+ * row and, where the columns are split to fill the chip, up to 2 GB of partial sums.
  */
 int gp_kmv(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo, int add_noise);
 

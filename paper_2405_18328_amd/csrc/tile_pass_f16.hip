@@ -1059,9 +1059,9 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
   const int row_blocks = (int)((rows + k.rows_per_wg - 1) / k.rows_per_wg);
   // a partial image is written and read once, at about 4 TB/s
   const double image = (double)rows * t * sizeof(float);
-  int max_js = image * 3.0 > 2.0e9 ? (int)(2.0e9 / image) : 64;     // images past 2 GB would not pay for their memory
+  // images of more than 2 GB in all would not pay for their memory
+  int max_js = image * 64.0 > 2.0e9 ? (int)(2.0e9 / image) : 64;
   if (max_js < 1) max_js = 1;
-  if (max_js > 64) max_js = 64;
   pl.JS = gp_column_splits(row_blocks, chunks, k.per_cu * ctx->num_cu, 2.0 * image / 4.0e6 / k.chunk_us, max_js);
   pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
   gp_ctx* memo = const_cast<gp_ctx*>(ctx);   // a context belongs to one host thread at a time

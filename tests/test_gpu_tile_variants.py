@@ -81,3 +81,19 @@ def test_short_pack_and_column_maxima(n):
                 assert relerr(got[:, c], ref[:, c0 + c]) <= KMV_TOL, (t, c)
     finally:
         dv.close()
+
+
+@pytest.mark.parametrize("n,d,t", [(400000, 3, 65), (400000, 26, 129), (510000, 3, 257), (200000, 26, 1024), (2000000, 3, 65)])
+def test_partial_images_are_bounded(n, d, t):
+    """Column splits leave at most 2 GB of partial images, whatever the sizes: the CG workspace is eight arrays of n x t at
+    most, the packed operands and those images."""
+    import torch
+    from paper_2405_18328_amd import binding as gp
+    X = torch.rand(n, d, device="cuda:0")
+    ctx = gp.gp_create(gp.GP_MATERN32_ARD, n, d, X, torch.cuda.current_stream().cuda_stream)
+    try:
+        size = gp.gp_workspace_bytes(ctx, t)
+        print(f"[scratch] n={n} t={t}: {size / 1e9:.2f} GB", flush=True)
+        assert 0 < size <= 8 * 4 * n * t + 264 * n + 2.0e9 + 1e8
+    finally:
+        gp.gp_destroy(ctx)
