@@ -9,7 +9,8 @@
 // Bound by memory latency: 65 workgroups pull 450 KB each at n = 16384 (about 15 us).  One marginal-likelihood step on
 // MI355X, before -> after: n = 2048 d = 8 t = 17 (88 iterations) 4.38 -> 1.56 ms; n = 16384 d = 26 t = 65 (7 iterations)
 // 1.82 -> 1.65 ms; n = 43945 d = 20 t = 17 (21 iterations; with cgc_sum_kernel) 18.2 -> 17.0 ms.
-// Past CG_COLUMNS_MAX_N a product takes 2 ms and more and the streaming kernels, spread over the whole chip, are ahead.
+// CG_COLUMNS_MAX_N is where the two forms meet at the least favourable shape: per iteration, streaming -> columns, n = 65536,
+// d = 11 t = 65 2092 -> 2105 us, d = 5 t = 33 1598 -> 1591; ahead by 5 - 40 % at other d and t there, and more below.
 #include "columns.h"
 
 namespace {

@@ -39,12 +39,12 @@ struct TileArgsH {
   int64_t split_stride;
   int64_t n;               // rows of the output (the context's n, or m for a rectangular product)
   int diag;                // square product: the pair (i, i) gets r^2 = 0 exactly
+  int diag_shift;          // chunk of the first row minus the first chunk of the contraction
   int nchunks;             // column chunks (always the context's points)
   int col0, ncols, vcol;
   int JS, cps;             // column-range splits inside this launch, chunks per split
   float a2, sigma2;
   int add_noise;
-  int rb0, js0;            // first row block and first column range of the launch (FORM_PLAIN, FORM_ANY)
   unsigned* clear;         // column maxima in accumulation: everyone has read them, workgroup 0 zeroes them (clear_n words); NULL: none
   int clear_n;
   const int* win_sel;      // contraction over the columns of block *win_sel (win_block points each): XA starts at that block's
@@ -143,9 +143,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: lets the compiler branch on it
   const int h = lane >> 5;
   const int li = lane & 31;
-  const int js = blockIdx.x % p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.js0 : 0);
-  const int rb = blockIdx.x / p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.rb0 : 0);
+  const int js = blockIdx.x % p.JS;
+  const int rb = blockIdx.x / p.JS;
   const int sub0 = (rb * W + wave) * MI;
+  const int diag_at = p.diag ? sub0 + p.diag_shift : -MI;     // the chunk that holds the first sub-tile's own points
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
   const int64_t chunk0 = has_window(FORM) ? window_chunk(p) : 0;
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
-      if (p.diag && ch == sub0 + m) {
+      if (ch == diag_at + m) {
         // one chunk in thousands: an opaque statement keeps this a real (wave-uniform) branch instead of
         // sixteen selects executed on every chunk
         asm volatile("" ::: "memory");
@@ -473,8 +474,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // share a stage of two chunks in LDS, two stages deep, one barrier per two chunks.  NT = 0 is the product
 // with a single vector (the mean of a prediction): no contraction tiles at all, phi goes straight into one
 // FMA per pair, eight waves per SIMD.
-// What bounds it (SQ counters, n = 16384, d = 26, t = 65, Matern): the vector port 60 % and the matrix core
-// 48 % of the cycles; the stream of instructions alone, without LDS and barriers, 67 % and 54 %.
+// What bounds it (SQ counters, n = 32768, d = 26, t = 65, Matern): the vector port in use 69 % and the matrix core 60 % of
+// the cycles; the two-wave kernel at n = 16384: 62 % and 49 %.
 // Measured against the two-wave kernel, same box: n = 16384 d = 26 t = 65 Matern 164 -> 160 us; n = 32768
 // d = 26 t = 65 SE 553 -> 516 us; one vector: n = 41157 d = 9 Matern 508 -> 409 us, n = 65536 d = 8 SE 892 -> 564 us.
 // With KH = 1 or NT = 1 the two-wave kernel with two sub-tiles per wave reads half the operands from LDS and stays ahead.
@@ -502,9 +503,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5;
   const int li = lane & 31;
-  const int js = blockIdx.x % p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.js0 : 0);
-  const int rb = blockIdx.x / p.JS + (FORM == FORM_PLAIN || FORM == FORM_ANY ? p.rb0 : 0);
+  const int js = blockIdx.x % p.JS;
+  const int rb = blockIdx.x / p.JS;
   const int sub0 = rb * W + wave;
+  const int diag_at = p.diag ? sub0 + p.diag_shift : -1;
   const int64_t chunk0 = has_window(FORM) ? window_chunk(p) : 0;
   const int r_begin = js * p.cps;
   const int r_end = has_window(FORM) ? (int)min((int64_t)min(p.nchunks, r_begin + p.cps), (p.npoints + 31) / 32 - chunk0) : min(p.nchunks, r_begin + p.cps);
@@ -588,7 +590,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
       S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[0], xb[1][kh], S, 0, 0, 0);
       S = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[0], xb[0][kh], S, 0, 0, 0);
     }
-    if (p.diag && ch == sub0) {
+    if (ch == diag_at) {
       asm volatile("" ::: "memory");
       const float s0 = KIND == GP_SE_ARD ? (float)PHI_SHIFT : 0.0f;
 #pragma unroll
@@ -1189,7 +1191,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
   PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
   ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
-  const PanelsH pn = scratch_bytes < L.total && pl.JS > 1 && !defer && !win ? plan_panels(ctx, nrows, t, XP, pl, L, scratch_bytes) : PanelsH{0, pl.JS};
+  const PanelsH pn = scratch_bytes < L.total && pl.JS > 1 && !defer && !win && !rows ? plan_panels(ctx, nrows, t, XP, pl, L, scratch_bytes) : PanelsH{0, pl.JS};
   if (pn.rows) L = scratch_layout(ctx, t, 1, nrows), L.off_part = panel_images_at(L, pn.group, pl), L.total = scratch_bytes;
   if (scratch_bytes < L.total || !scratch)
     return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv: scratch %zu < %zu bytes", scratch_bytes, L.total);
@@ -1246,8 +1248,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.npoints = ctx->n - first;
   a.cm_ld = 0;
   a.done = nullptr;
-  a.rb0 = 0;
-  a.js0 = 0;
+  a.diag_shift = 0;
 
   auto sum_images_of = [&](int64_t m, int width, bool add, float* out) {     // out = the sum of the images of m rows
     int blocks = (int)((m * width + 1023) / 1024);
@@ -1293,19 +1294,25 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     for (int64_t r0 = 0; r0 < nrows; r0 += panel) {
       const int64_t m = nrows - r0 < panel ? nrows - r0 : panel;
       for (int j0 = 0; j0 < pl.JS; j0 += pn.group) {
-        if (pn.rows) {     // images of this panel, these column ranges and columns, addressed by row, range and column as ever
+        if (pn.rows) {     // a panel is a set of rows of its own, a group of column ranges a point set of its own
+          const int c0 = j0 * pl.cps;
           a.JS = min(pn.group, pl.JS - j0);
-          a.js0 = j0;
-          a.rb0 = (int)(r0 / k.rows_per_wg);
-          a.n = r0 + m;
+          a.nchunks = min(a.JS * pl.cps, nchunks - c0);
+          a.npoints = ctx->n - (int64_t)c0 * 32;
+          a.n = m;
+          a.diag_shift = (int)(r0 / 32) - c0;
+          a.add_noise = add_noise && j0 == 0;
+          a.V = dV + r0 * ldv;
+          a.VY = VY + (int64_t)c0 * 32;
+          a.VP = VP + (pn.group < pl.JS ? 0 : (int64_t)c0 * 4 * NT * 64);
+          for (int pc = 0; pc < 3; ++pc) {
+            a.XA[pc] = (const u32x4*)ctx->dXAh[pc] + (int64_t)c0 * ctx->KH * 64;
+            a.XB[pc] = (const u32x4*)ctx->dXBh[pc] + (r0 / 32) * ctx->KH * 64;
+          }
           a.ldo = width;
           a.split_stride = m * width;
-          a.OUT = part - (j0 * a.split_stride + r0 * width + col);
-        }
-        if (pn.group < pl.JS) {
-          const int c0 = j0 * pl.cps;
-          pack(c0, min(a.JS * pl.cps, nchunks - c0));
-          a.VP = VP - (int64_t)c0 * 4 * NT * 64;
+          a.OUT = part - col;
+          if (pn.group < pl.JS) pack(c0, a.nchunks);
         }
         const dim3 grid((unsigned)((m + k.rows_per_wg - 1) / k.rows_per_wg) * a.JS);
         const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
@@ -1378,8 +1385,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
   a.add_noise = 0;
   a.cm_ld = pk.ld;
   a.done = pk.done;
-  a.rb0 = 0;
-  a.js0 = 0;
+  a.diag_shift = 0;
   const u32x4* VP = (const u32x4*)pk.VP;
   int vcol = has_vec_column(t) ? 0 : -1;
   int c = vcol >= 0 ? 1 : 0;

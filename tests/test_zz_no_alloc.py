@@ -124,3 +124,40 @@ def test_static_scratch_product_whose_partial_images_do_not_fit(n, d, kind, t):
         assert relerr(got[rows, :t], ref) <= KMV_TOL
     finally:
         dv.close()
+
+
+@pytest.mark.parametrize("n,d,t", [(3000, 26, 65), (20000, 3, 17), (131073, 3, 66)])
+def test_static_scratch_product_in_a_captured_graph(n, d, t):
+    """Recorded once and replayed on changing vectors, with eager products on the same scratch between the replays; the last
+    size works in panels of rows."""
+    rng = np.random.default_rng(n)
+    X = torch.from_numpy(rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)).to("cuda:0")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ctx = gp.gp_create(gp.GP_SE_ARD, n, d, X, stream.cuda_stream)
+        try:
+            gp.gp_set_theta(ctx, np.full(d, 0.6 * np.sqrt(d)), 0.9, 0.5)
+            V = torch.randn(n, t, device="cuda:0")
+            out, want = torch.empty_like(V), torch.empty_like(V)
+            gp.gp_kmv_static(ctx, V, t, t, out, t, 1)
+            gp.gp_kmv(ctx, V, t, t, want, t, 1)
+            torch.cuda.synchronize()
+            print(f"[no-alloc] capture n={n} d={d} t={t}", flush=True)
+            graph = torch.cuda.CUDAGraph()
+            graph.capture_begin()
+            gp.gp_kmv_static(ctx, V, t, t, out, t, 1)
+            graph.capture_end()
+            for _ in range(3):
+                V.copy_(torch.randn(n, t, device="cuda:0"))
+                out.fill_(float("nan"))
+                gp.gp_kmv_static(ctx, V, t, t, want, t, 0)      # another product over the shared scratch
+                gp.gp_kmv(ctx, V, t, t, want, t, 1)
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(out, want)
+            del graph
+        finally:
+            torch.cuda.synchronize()
+            gp.gp_destroy(ctx)
