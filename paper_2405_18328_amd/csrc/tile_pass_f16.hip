@@ -1217,6 +1217,13 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   const bool maxima = !colmax_ready && t > 1 && !small;       // a single vector is not scaled
   const bool accumulate = maxima && scratch != ctx->static_scratch;
   if (maxima) {
+    if (accumulate) {
+      if (ctx->colmax_dirty) {
+        hipLaunchKernelGGL(clear_words_kernel, dim3((ctx->colmax_dirty + 255) / 256), dim3(256), 0, st, ctx->dColmax, nullptr, ctx->colmax_dirty);
+        GP_HIP(ctx, hipGetLastError());
+      }
+      if (ctx->colmax_dirty < t) ctx->colmax_dirty = t;     // until the launch that clears them is on the stream
+    }
     const int rc = gp_launch_colmax(ctx, dV, ldv, t, accumulate ? ctx->dColmax : (unsigned*)(w + L.off_colmax), nullptr, 0, nullptr, accumulate);
     if (rc < 0) return rc;
   }
@@ -1319,6 +1326,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
         hipLaunchKernelGGL(k.fn, grid, dim3(k.threads), 0, st, a);
         GP_HIP(ctx, hipGetLastError());
         gp_prof_end(ctx, prof);
+        if (a.clear) ctx->colmax_dirty = 0;
         if (pn.rows) sum_images_of(m, width, j0 > 0, dOut + r0 * ldo + col);
       }
     }

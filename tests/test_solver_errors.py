@@ -131,3 +131,39 @@ def test_an_error_return_leaves_nothing_queued(runtime, solver, n, warm):
     r = subprocess.run([sys.executable, "-c", CHILD, runtime, LIB, solver, str(n), str(warm)], capture_output=True, text=True,
                        timeout=300, env=dict(os.environ, OMP_NUM_THREADS="1"))
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+PRODUCTS = r"""
+import ctypes as C, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+lib = C.CDLL(sys.argv[2])
+lib.gp_last_error.restype = C.c_char_p
+n, i64, p = 9000, C.c_int64, C.c_void_p
+X, V, O = (C.c_float * (n * 3))(), (C.c_float * (n * 40))(), (C.c_float * (n * 40))()
+ctx = p()
+assert lib.gp_create(C.byref(ctx), 0, i64(n), 3, X, None) == 0
+assert lib.gp_set_theta(ctx, (C.c_double * 3)(1, 1, 1), C.c_double(1), C.c_double(0.5)) == 0
+def launches(t, fail=0):
+    fake.fake_fail(fail)
+    rc = lib.gp_kmv(ctx, V, i64(t), t, O, i64(t), 1)
+    return rc, fake.fake_queued(), fake.fake_fail(0)
+assert launches(40)[0] == 0
+plain = launches(9)[1], launches(40)[1]
+for k in range(1, 20):
+    rc, _, left = launches(40, k)
+    if left > 0: break
+    assert rc == -2
+    # the failed product has taken its maxima (after its first launch) but may not have cleared them
+    again = launches(9)
+    assert again[0] == 0 and again[1] in (plain[0], plain[0] + 1), (k, again, plain)
+    if k <= 3: assert again[1] == plain[0] + 1, (k, again, plain)
+    assert launches(9)[1] == plain[0] and launches(40)[1] == plain[1]
+assert k > 3, k
+"""
+
+
+def test_a_product_behind_a_failed_one_starts_from_clear_maxima(runtime):
+    """gp_kmv accumulates its column maxima in words that its tile pass clears: where a call ends between the two, the next
+    one clears them first, or it would scale its columns by the other call's maxima."""
+    r = subprocess.run([sys.executable, "-c", PRODUCTS, runtime, LIB], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
