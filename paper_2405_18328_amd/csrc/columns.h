@@ -49,20 +49,12 @@ __device__ __forceinline__ PackSpot pack_spot(u32x4* VP, int t, int64_t nchunks,
 // so lanes two apart exchange theirs and every lane writes one whole unit.  The lanes of a group of eight must
 // call it together.
 __device__ __forceinline__ void pack_quad(const PackSpot& s, int k, f32x4 v) {
-  float h[4], l[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    h[q] = __uint_as_float(__float_as_uint(v[q]) & HI_MASK);
-    l[q] = v[q] - h[q];
-  }
-  const unsigned hi0 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[0], h[1]));
-  const unsigned hi1 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[2], h[3]));
-  const unsigned lo0 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[0], l[1]));
-  const unsigned lo1 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[2], l[3]));
+  unsigned hi[2], lo[2];
+  split_quad(v, hi, lo);
   const bool up = (k & 2) != 0;          // this lane writes the low part
-  const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi0 : lo0), 2);
-  const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi1 : lo1), 2);
-  const u32x4 unit = up ? u32x4{x0, x1, lo0, lo1} : u32x4{hi0, hi1, x0, x1};
+  const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi[0] : lo[0]), 2);
+  const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi[1] : lo[1]), 2);
+  const u32x4 unit = up ? u32x4{x0, x1, lo[0], lo[1]} : u32x4{hi[0], hi[1], x0, x1};
   const int64_t g = (int64_t)(k >> 2) * s.NT + s.nt;   // (chunk*2 + mh)*NT + nt
   s.base[(g * 2 + (up ? 1 : 0)) * 64 + s.lane + 32 * (k & 1)] = unit;
 }

@@ -24,6 +24,21 @@ __device__ __forceinline__ int column_exponent(unsigned max_bits) {
   return e < -60 ? -60 : e;
 }
 
+// four scaled values as fp16 halves, packed in pairs: hi is truncated to 11 significant bits, lo is what is left
+__device__ __forceinline__ void split_quad(f32x4 v, unsigned (&hi)[2], unsigned (&lo)[2]) {
+  float h[4], l[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    h[q] = __uint_as_float(__float_as_uint(v[q]) & HI_MASK);
+    l[q] = v[q] - h[q];
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    hi[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[2 * k], h[2 * k + 1]));
+    lo[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[2 * k], l[2 * k + 1]));
+  }
+}
+
 }  // namespace
 
 #endif

@@ -854,24 +854,15 @@ __global__ __launch_bounds__(1024) void pack_small_kernel(const float* __restric
   for (int j = 0; j < NQ; ++j) {
     const int k = ql + 128 * j;
     if (k >= nk) break;                  // whole groups of eight quads
-    const f32x4 w = v[j] * scale;
-    float h[4], l[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      h[q] = __uint_as_float(__float_as_uint(w[q]) & HI_MASK);
-      l[q] = w[q] - h[q];
-    }
-    const unsigned hi0 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[0], h[1]));
-    const unsigned hi1 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[2], h[3]));
-    const unsigned lo0 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[0], l[1]));
-    const unsigned lo1 = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[2], l[3]));
+    unsigned hi[2], lo[2];
+    split_quad(v[j] * scale, hi, lo);
     const bool up = (k & 2) != 0;        // quads k and k + 2 (sixteen lanes on) make up one high and one low unit
-    const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi0 : lo0), 16);
-    const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi1 : lo1), 16);
+    const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi[0] : lo[0]), 16);
+    const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi[1] : lo[1]), 16);
     if (cc < 0) {
       *reinterpret_cast<f32x4*>(VY + 4 * k) = v[j];
     } else {
-      const u32x4 unit = up ? u32x4{x0, x1, lo0, lo1} : u32x4{hi0, hi1, x0, x1};
+      const u32x4 unit = up ? u32x4{x0, x1, lo[0], lo[1]} : u32x4{hi[0], hi[1], x0, x1};
       VP[((int64_t)((k >> 2) * NT + (cc >> 5)) * 2 + (up ? 1 : 0)) * 64 + (cc & 31) + 32 * (k & 1)] = unit;
     }
   }
