@@ -280,10 +280,12 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
 int gp_grad_run(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,
                 double* h_grad);
 // fp64 reduction of one right-hand-side block's tile-pass output OUT[JS][n][nq] into acc[d + 2]
-// (part: G x (d + 2) workgroup partials); first_block adds the sigma component sum_i w_ii
+// (part: G x (d + 2) workgroup partials); first_block adds the sigma component sum_i w_ii.  tri_rows > 0: only the tiles on
+// and above the diagonal were worked on, the columns of a row block of that many rows in pieces of at most tri_cps chunks,
+// one image of OUT each
 int gp_grad_reduce_launch(gp_ctx* ctx, const float* OUT, int64_t split_stride, int JS, int nq, const float* dV,
                           int64_t ldv, const float* dB, int64_t ldb, int t, float half_w, float probe_w,
-                          int first_block, double* part, int G, double* acc);
+                          int first_block, double* part, int G, double* acc, int tri_rows = 0, int tri_cps = 0);
 
 // ---- grad_pass_f16.hip
 int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,

@@ -234,7 +234,8 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restric
                                                           int64_t n, int d, const float* __restrict__ V,
                                                           int64_t ldv, const float* __restrict__ B, int64_t ldb,
                                                           int t, float half_w, float probe_w, int first_block,
-                                                          double* __restrict__ part /* [grid][d+2] */) {
+                                                          double* __restrict__ part /* [grid][d+2] */,
+                                                          int tri_rows, int tri_cps, int chunks) {
   extern __shared__ double sh[];   // [256]
   const int nq = 2 * d + 2;
   // thread <-> (row, component): consecutive threads take consecutive components of a row;
@@ -249,6 +250,10 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restric
     double s = 0.0;
     if (rsub < rows_per_step) {
       for (int64_t i = (int64_t)blockIdx.x * rows_per_step + rsub; i < n; i += (int64_t)gridDim.x * rows_per_step) {
+        if (tri_rows) {
+          const int len = chunks - (int)(i / tri_rows) * (tri_rows / 32);
+          JS = (len + tri_cps - 1) / tri_cps;
+        }
         if (comp < d) {
           float y = 0.f, t2 = 0.f, t1 = 0.f;
 #pragma unroll 4
@@ -351,11 +356,11 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 int gp_grad_reduce_launch(gp_ctx* ctx, const float* OUT, int64_t split_stride, int JS, int nq, const float* dV,
                           int64_t ldv, const float* dB, int64_t ldb, int t, float half_w, float probe_w,
-                          int first_block, double* part, int G, double* acc) {
+                          int first_block, double* part, int G, double* acc, int tri_rows, int tri_cps) {
   const int d = ctx->d;
   hipLaunchKernelGGL(grad_reduce_kernel, dim3(G), dim3(256), 256 * sizeof(double), ctx->stream, OUT, split_stride, JS,
                      (int64_t)nq, (const float*)ctx->dXs, ctx->n, d, dV, ldv, dB, ldb, t, half_w, probe_w, first_block,
-                     part);
+                     part, tri_rows, tri_cps, (int)((ctx->n + 31) / 32));
   hipLaunchKernelGGL(grad_finalize_kernel, dim3(d + 2), dim3(256), 0, ctx->stream, (const double*)part, G, d + 2, acc);
   GP_HIP(ctx, hipGetLastError());
   return GP_OK;

@@ -2,29 +2,41 @@
 // trace estimator), split-fp16 matrix-core tile pass.  Same mathematics as the fp32 pass:
 //   g_k = sum_ij w_ij (dH/dtheta_k)_ij,  w_ij = A_i . C_j,  G = w .* psi,  row sums of G Q with
 //   Q = [xs, xs^2, 1], plus one vector-ALU column sum_j w_ij K_ij / a^2 for the amplitude.
+// dH/dtheta_k is symmetric, so only the tiles on and above the diagonal are worked on, with the weights of both
+// halves: u_ij = w_ij + w_ji.  The y column's term is symmetric by itself (v_i v_j, one FMA per pair on the vector
+// ALU); a probe's becomes two, a_i z_j + z_i a_j with a = -v / (2s).  A square expanded as
+// (xs_i - xs_j)^2 = xs_i^2 + xs_j^2 - 2 xs_i xs_j needs the sums over j of one row only, never those of a column, so
+// half a matrix of pairs is all there is to it.
 // All three contractions of a 32x32 tile of pairs run on v_mfma_f32_32x32x16_f16 with operands split
-// into two fp16 pieces (three products per fp32 product, fp32 accumulation):
+// into two fp16 pieces rounded to nearest (three products per fp32 product, fp32 accumulation):
 //   1. S[j][i]  = XA_j . XB_i        the distance chain of the K V pass (same packed operands)
-//   2. W'[j][i] = C'_j . A'_i        C' = C scaled per column to max in [2^6, 2^7), A' carries the
-//                                    inverse column scales and a global power of two alpha chosen so
-//                                    that |W' psi| < 2^15 (from sum_c max|A_c| max|C_c| >= |w_ij|)
-//   3. OUT_i   += G'[i][j] Q'_j      G' = W' psi split on the VALU, Q' = 2^qshift Q pre-split
-// The epilogue removes alpha and 2^qshift.  K and w are never stored.
+//   2. U'[j][i] = C'_j . A'_i        the probes' part of u; every column-side component is scaled to max in [2^6, 2^7),
+//                                    the row side carries the inverse scales and a global power of two alpha chosen so
+//                                    that |U' psi| < 2^15 (from the sum over the components of max|row| max|column| >= |u_ij|)
+//   3. OUT_i   += G'[i][j] Q'_j      G' = U' psi split on the VALU, Q' = 2^qshift Q pre-split
+// The epilogue removes alpha and 2^qshift.  K and u are never stored.
+// Matrix instructions per pair of mirrored tiles, d = 26, t = 65: 42 instead of 66 (6 + 24 + 12 against twice 6 + 15 + 12), and half
+// the vector work; the matrix core and the vector port together bound it (48 % and 53 % of the cycles at n = 43945, d = 20, t = 17, at 1.86 GHz).
+// A gradient, all pairs -> half: n = 16384, d = 26, t = 65 (Matern) 327 -> 252 us; n = 43945, d = 20, t = 17 1491 -> 888 us;
+// n = 131072, d = 3, t = 65 (SE) 10.5 -> 7.9 ms; n = 20000, d = 60, t = 33 1065 -> 568 us.  Error against 64 bits, V a solution:
+// n = 8192, d = 26, t = 65 1.05e-6 -> 2.3e-7; n = 8000, d = 9, t = 33 1.8e-6 -> 3.3e-7.
 #include <cstdlib>
 
 #include "gpws_internal.h"
+#include "split_f16.h"
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-constexpr float LOG2E = 1.4426950408889634f;
 constexpr int C_TOP = 7;                    // max |C'_c| in [2^6, 2^7)
-constexpr int W_TOP = 13;                   // alpha sum_c max|A_c| max|C_c| <= 2^13, so |W' psi| <= 3 2^13 < 2^15
-constexpr int GRAD_TBLOCK_H = 80;           // right-hand-side columns per tile pass (5 k-steps of 16)
+constexpr int U_TOP = 13;                   // alpha |u_ij| <= 2^13, so |U' psi| <= 3 2^13 < 2^15
+constexpr int PROBE_BLOCK = 64;             // probe columns per tile pass (two times 4 k-steps of 16)
+// A workgroup's waves, 32 rows each.  Two workgroups of four run past each other's barriers; from six k-steps of probes on a chunk's
+// operands are so many that eight waves should share them.  n = 16384, d = 26: t = 65 (8 k-steps) 254 us a gradient with four
+// waves, 239 with eight; n = 43945, d = 20, t = 17 (2 k-steps) 839 and 915.
+constexpr int grad_waves(int KT) { return KT >= 6 ? 8 : 4; }
 
 struct GradArgsH {
   const u32x4* XA[3];     // column-side distance pieces [(chunk*KH + kh)*64 + lane]
@@ -32,44 +44,46 @@ struct GradArgsH {
   const u32x4* CA;        // C' images, column side: [((chunk*2 + part)*KT + kt)*64 + lane]
   const u32x4* AB;        // A' images, row side, same indexing by sub-tile
   const u32x4* QP;        // Q' images of this column pass: [(((chunk*2 + mh)*NT + nt)*2 + part)*64 + lane]
+  const float* VY;        // the y column, zero from n up to the end of its chunk; all zero in later blocks of probes
   const int* scales;      // [0] = exponent of alpha
-  float* OUT;             // [JS][n][ldo]
+  float* OUT;             // [pieces of a row][n][ldo]
   int64_t ldo;
   int64_t split_stride;
   int64_t n;
   int nchunks;
   int col0, ncols;        // Q columns of this pass
-  int vcol;               // output column of sum_j w_ij K_ij / a^2, or -1
-  int JS, cps;
+  int vcol;               // output column of sum_j u_ij K_ij / a^2, or -1
+  int cps;                // most chunks one workgroup takes of its rows' columns
   int qshift;             // Q' = 2^qshift Q
   int slot_kh, slot_h, slot_e;   // where the row-side operand carries the SE exponent shift, or -1
 };
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
-// x - (float)half H of pk, one v_fma_mix_f32 (source 0 read as the fp16 half, sources 1 and 2 as fp32)
-template <int H>
-__device__ __forceinline__ float minus_half(unsigned pk, float x) {
-  float r;
-  if (H == 0) asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
-  else asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
-  return r;
+// row blocks (the first ones) whose columns have more than js pieces: row block rb has nchunks - rb W chunks
+__host__ __device__ inline int grad_rows_with_piece(int js, int nchunks, int cps, int W) {
+  return (nchunks - js * cps + W - 1) / W;
 }
 
+// A workgroup takes piece js of the columns of row block rb, from the row block's first chunk on.  Only pieces that are there
+// have a workgroup: with the others returning at once, as many pieces as compute units did not run side by side, the hardware
+// dealing workgroups to the eight dies in turn (n = 16384, d = 26, t = 65: compute units busy 46 % of the launch).
 template <int KIND, int KH, int XP, int KT, int NT>
-__global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
-  constexpr int W = 4;
+__global__ __launch_bounds__(64 * grad_waves(KT)) void grad_tile_f16_kernel(GradArgsH p) {
+  constexpr int W = grad_waves(KT);
   constexpr int XA_G = XP * KH;          // groups of 64 16-byte units per stage
   constexpr int C_G = 2 * KT;
   constexpr int Q_G = 4 * NT;
   constexpr int G = XA_G + C_G + Q_G;
   constexpr int C_OFF = XA_G * 64;
   constexpr int Q_OFF = (XA_G + C_G) * 64;
-  constexpr int STAGE = G * 64;
-  constexpr int NS = G > 24 ? 2 : 3;     // LDS ring: chunks up to ch + NS - 1 in flight while ch is consumed
+  constexpr int Y_OFF = G * 64;          // then the chunk's 32 y values: 8 units
+  constexpr int STAGE = G * 64 + 8;
+  constexpr int NS = 3 * STAGE <= 5120 ? 3 : 2;    // LDS ring (two workgroups share 160 KB): chunks up to ch + NS - 1 in flight while ch is consumed
   constexpr int DEPTH = NS - 1;
   constexpr int LPW = (G + W - 1) / W;   // group loads per wave per chunk
-  static_assert((DEPTH - 1) * LPW < 64, "vmcnt cannot express the pipeline depth");
+  constexpr int LPC = LPW + 1;           // + the y values (every wave fetches the same 128 bytes to the same place)
+  static_assert(DEPTH * LPC < 64, "vmcnt cannot express the pipeline depth");
   __shared__ u32x4 lds[NS][STAGE];
 
   const int tid = threadIdx.x;
@@ -77,13 +91,16 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: lets the compiler branch on it
   const int h = lane >> 5;
   const int li = lane & 31;
-  const int js = blockIdx.x % p.JS;
-  const int rb = blockIdx.x / p.JS;
+  int js = 0, rb = blockIdx.x;
+  for (int rows; rb >= (rows = grad_rows_with_piece(js, p.nchunks, p.cps, W)); ++js) rb -= rows;
   const int sub0 = rb * W + wave;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
-  const int r_begin = js * p.cps;
-  const int r_end = min(p.nchunks, r_begin + p.cps);
+  const int len = p.nchunks - rb * W;
+  const int pieces = (len + p.cps - 1) / p.cps;
+  const int per = (len + pieces - 1) / pieces;
+  const int r_begin = rb * W + js * per;
+  const int r_end = min(p.nchunks, r_begin + per);
   int c_begin = r_begin;
   int c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
 
@@ -136,8 +153,9 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
     }
     g_lds[x] = __builtin_amdgcn_readfirstlane(lds_base + 16u * (unsigned)(g * 64));
   }
+  const unsigned vy_lds = lds_base + 16u * (unsigned)Y_OFF;
   // inline assembly keeps the ordering explicit (s_waitcnt vmcnt(N) + barrier) instead of the
-  // compiler's conservative drain of all LDS-DMA loads at every barrier; m0 is restored
+  // compiler's conservative drain of all LDS-DMA loads at every barrier
   auto dma16 = [](const u32x4* src, unsigned lds_addr) {
     // m0 carries the LDS address of the load; it is declared clobbered, so the compiler keeps nothing in it
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds_addr) : "memory", "m0");
@@ -147,8 +165,9 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
     const unsigned stage_off = (unsigned)((ch_target - c_begin) % NS) * (unsigned)(STAGE * 16);
 #pragma unroll
     for (int x = 0; x < LPW; ++x) dma16(g_src[x] + (int64_t)ch * g_stride[x], __builtin_amdgcn_readfirstlane(g_lds[x] + stage_off));
+    if (lane < 8) dma16(reinterpret_cast<const u32x4*>(p.VY + (int64_t)ch * 32) + lane, __builtin_amdgcn_readfirstlane(vy_lds + stage_off));
   };
-  constexpr int WAIT_N = (DEPTH - 1) * LPW;   // all but the newest DEPTH - 1 chunks have landed
+  constexpr int WAIT_N = (DEPTH - 1) * LPC;   // all but the newest DEPTH - 1 chunks have landed
 
   // Writes the accumulators to OUT (first: stores; later: adds to what is there) without alpha and
   // 2^qshift, and clears them.  Doing so after every segment keeps the chains of fp32 partial sums
@@ -158,8 +177,9 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
   // then enters the sums over rows with alternating sign instead of adding up.
   const int alpha_exp = p.scales[0];
   const float row_sign = (sub0 & 1) ? -1.0f : 1.0f;
-  const float oscale = row_sign * ldexpf(1.0f, -alpha_exp - p.qshift);
+  const float oscale = row_sign * (KIND == GP_SE_ARD ? 1.0f : 3.0f) * ldexpf(1.0f, -alpha_exp - p.qshift);   // psi = 3 exp(-u) for Matern: the 3 is applied here
   const float vscale = row_sign * ldexpf(1.0f, -alpha_exp);
+  const float yi = row_sign * ldexpf(sub0 < p.nchunks ? p.VY[(int64_t)sub0 * 32 + li] : 0.0f, alpha_exp);
   float* out = p.OUT + (int64_t)js * p.split_stride;
   auto flush = [&](bool first) {
     // an opaque zero keeps the address arithmetic of the flush inside it: hoisted out of the segment
@@ -192,20 +212,11 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
       accv = 0.0f;
     }
   };
-  bool first = true;
 
-  for (;;) {
+  auto chunk = [&](int ch, const u32x4* s) {
+    f32x16 S, U;
 #pragma unroll
-  for (int d0 = 0; d0 < DEPTH; ++d0) issue_chunk(c_begin + d0);
-  for (int ch = c_begin; ch < c_end; ++ch) {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(WAIT_N) : "memory");
-    __syncthreads();              // chunk ch is complete in LDS; every wave is done with chunk ch - 1
-    issue_chunk(ch + DEPTH);      // refills the stage chunk ch - 1 occupied
-    const u32x4* s = lds[(ch - c_begin) % NS];
-
-    f32x16 S, Wc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { S[r] = 0.0f; Wc[r] = 0.0f; }
+    for (int r = 0; r < 16; ++r) { S[r] = 0.0f; U[r] = 0.0f; }
 #pragma unroll
     for (int kh = 0; kh < KH; ++kh) {
       f16x8 xa[XP];
@@ -225,21 +236,29 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
     // its accumulator input is the largest addend, but an accumulator input smaller than the products is
     // cut off below half a unit in the last place of the result toward minus infinity (measured on
     // MI355X).  Small cross terms summed first and the hi*hi products added on top of them would give
-    // every w_ij a bias of about -2^-25 |w_ij| of one sign, which the sum over all pairs does not average
+    // every weight a bias of about -2^-25 of its size of one sign, which the sum over all pairs does not average
     // out while the terms themselves cancel (V nearly orthogonal to K's large eigenvectors, as after a solve).
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
       const f16x8 ch_ = as_f16x8(s[C_OFF + (0 * KT + kt) * 64 + lane]);
       const f16x8 cl_ = as_f16x8(s[C_OFF + (1 * KT + kt) * 64 + lane]);
-      Wc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ch_, abh[kt], Wc, 0, 0, 0);
-      Wc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ch_, abl[kt], Wc, 0, 0, 0);
-      Wc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cl_, abh[kt], Wc, 0, 0, 0);
+      U = __builtin_amdgcn_mfma_f32_32x32x16_f16(ch_, abh[kt], U, 0, 0, 0);
+      U = __builtin_amdgcn_mfma_f32_32x32x16_f16(ch_, abl[kt], U, 0, 0, 0);
+      U = __builtin_amdgcn_mfma_f32_32x32x16_f16(cl_, abh[kt], U, 0, 0, 0);
     }
-    if (ch == sub0) {   // the pair (i, i): r^2 = 0 exactly
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 yj = __builtin_bit_cast(f32x4, s[Y_OFF + 2 * q + h]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) U[4 * q + e] = fmaf(yi, yj[e], U[4 * q + e]);
+    }
+    if (ch == sub0) {   // the tile on the diagonal holds both halves already; the pair (i, i): r^2 = 0 exactly
       asm volatile("" ::: "memory");   // keeps this a real (wave-uniform) branch instead of selects on every chunk
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
+      for (int r = 0; r < 16; ++r) {
+        U[r] *= 0.5f;
         if (8 * (r >> 2) + 4 * h + (r & 3) == li) S[r] = 0.0f;
+      }
     }
 
 #pragma unroll
@@ -258,16 +277,16 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
           } else {
             // S = 3 r^2; rounding-level negatives are mirrored (free source modifier), (i, i) is exactly 0
             const float u = __builtin_amdgcn_sqrtf(__builtin_fabsf(S[r]));
-            const float e = __builtin_amdgcn_exp2f(-LOG2E * u);
-            psi = 3.0f * e;
-            kval = fmaf(u, e, e);
+            psi = __builtin_amdgcn_exp2f(-LOG2E * u);
+            kval = fmaf(u, psi, psi);
           }
-          g[z] = Wc[r] * psi;
-          accv = fmaf(Wc[r], kval, accv);
+          g[z] = U[r] * psi;
+          accv = fmaf(U[r], kval, accv);
         }
-        // hi = g truncated to fp16, lo = g - hi read from the packed halves by the mixed-precision FMA
-        gh[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(g[0], g[1]));
-        gl[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(minus_half<0>(gh[e2], g[0]), minus_half<1>(gh[e2], g[1])));
+        unsigned hi, lo;
+        split_pair(g[0], g[1], hi, lo);
+        gh[e2] = hi;
+        gl[e2] = lo;
       }
       const f16x8 ah = as_f16x8(gh), al = as_f16x8(gl);
 #pragma unroll
@@ -279,15 +298,29 @@ __global__ __launch_bounds__(256) void grad_tile_f16_kernel(GradArgsH p) {
         acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[nt], 0, 0, 0);
       }
     }
-  }
-  // no LDS write may be in flight, and no wave still reading, when the ring is refilled or released
-  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-  __syncthreads();
-  flush(first);
-  first = false;
-  if (c_end >= r_end) break;
-  c_begin = c_end;
-  c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
+  };
+
+  // The row operands are waited for here, where the compiler sees it: it would otherwise wait for them at their first use,
+  // inside the loop, and there drain the ring's loads too, chunk after chunk.
+  __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+  bool first = true;
+  for (;;) {
+#pragma unroll
+    for (int d0 = 0; d0 < DEPTH; ++d0) issue_chunk(c_begin + d0);
+    for (int ch = c_begin; ch < c_end; ++ch) {
+      asm volatile("s_waitcnt vmcnt(%0)" : : "n"(WAIT_N) : "memory");
+      __syncthreads();              // chunk ch is complete in LDS; every wave is done with chunk ch - 1
+      issue_chunk(ch + DEPTH);      // refills the stage chunk ch - 1 occupied
+      if (ch >= sub0) chunk(ch, lds[(ch - c_begin) % NS]);     // the first chunks of a row block lie below the diagonal for its later waves
+    }
+    // no LDS write may be in flight, and no wave still reading, when the ring is refilled or released
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    __syncthreads();
+    flush(first);
+    first = false;
+    if (c_end >= r_end) break;
+    c_begin = c_end;
+    c_end = min(r_end, c_begin + GP_FLUSH_CHUNKS);
   }
 }
 
@@ -299,81 +332,88 @@ __device__ __forceinline__ int exponent_of(float m, int dflt) {
   return e < -100 ? -100 : (e > 100 ? 100 : e);
 }
 
-// scales of one block of right-hand-side columns [t0, t0 + tb): scales[0] = exponent of alpha,
-// scales[1 + m] = exponent e_m with max |C_m| in [2^(e_m - 1), 2^e_m).  One workgroup, fixed-order sum.
-__global__ __launch_bounds__(128) void grad_scales_kernel(const unsigned* __restrict__ cmV, const unsigned* __restrict__ cmB,
-                                                          int t0, int tb, float half_w, float probe_w,
-                                                          int* __restrict__ scales) {
-  __shared__ float bound[128];
+// scales of one block of probe columns [c0, c0 + sb): scales[0] = exponent of alpha, scales[1 + m] = exponent e of
+// max |z_m| in [2^(e - 1), 2^e), scales[1 + PROBE_BLOCK + m] = the same of the weighted solutions a_m = probe_w v_m.
+// with_y: the y column's weights are in the bound too.  One workgroup, fixed-order sum.
+__global__ __launch_bounds__(PROBE_BLOCK) void grad_scales_kernel(const unsigned* __restrict__ cmV, const unsigned* __restrict__ cmB,
+                                                                  int c0, int sb, int with_y, float half_w, float probe_w,
+                                                                  int* __restrict__ scales) {
+  __shared__ float bound[PROBE_BLOCK];
   const int m = threadIdx.x;
   float b = 0.0f;
-  if (m < tb) {
-    const int col = t0 + m;
-    const float maxV = __uint_as_float(cmV[col]);
-    const float maxC = col == 0 ? maxV : __uint_as_float(cmB[col]);
-    const float maxA = fabsf(col == 0 ? half_w : probe_w) * maxV;
-    scales[1 + m] = exponent_of(maxC, C_TOP);
-    b = maxA * maxC;
+  if (m < sb) {
+    const float maxA = fabsf(probe_w) * __uint_as_float(cmV[c0 + m]);
+    const float maxZ = __uint_as_float(cmB[c0 + m]);
+    scales[1 + m] = exponent_of(maxZ, C_TOP);
+    scales[1 + PROBE_BLOCK + m] = exponent_of(maxA, C_TOP);
+    b = 2.0f * maxA * maxZ;
   }
   bound[m] = b;
   __syncthreads();
   if (m == 0) {
-    float wb = 0.0f;
-    for (int k = 0; k < tb; ++k) wb += bound[k];
-    // |w_ij| <= wb <= 2^e, so alpha = 2^(W_TOP - e) keeps alpha |w_ij| <= 2^W_TOP
-    scales[0] = (wb > 0.0f && wb < 3.0e38f) ? W_TOP - exponent_of(wb, W_TOP) : 0;
+    const float maxY = __uint_as_float(cmV[0]);
+    float ub = with_y ? 2.0f * half_w * maxY * maxY : 0.0f;
+    for (int k = 0; k < sb; ++k) ub += bound[k];
+    // |u_ij| <= ub <= 2^e, so alpha = 2^(U_TOP - e) keeps alpha |u_ij| <= 2^U_TOP
+    scales[0] = (ub > 0.0f && ub < 3.0e38f) ? U_TOP - exponent_of(ub, U_TOP) : 0;
   }
 }
 
-__device__ __forceinline__ void split2(float v, float& hi, float& lo) {
-  // hi is what fp16 truncation really stores (also for subnormal results), lo the exact remainder
-  const auto pk = __builtin_amdgcn_cvt_pkrtz(v, 0.0f);
-  hi = (float)pk[0];
-  lo = v - hi;
-}
-
-// C' (column side) and A' (row side) images of columns [t0, t0 + tb); one thread per (chunk, kt, lane)
+// C' (column side) and A' (row side) images of probe columns [c0, c0 + sb), one thread per (chunk, k-step of 16 probes,
+// lane): k-step kt holds z on the column side and a on the row side, k-step KTH + kt the other way round.
+// VY: the y column (with_y) or zeros.
 __global__ __launch_bounds__(256) void grad_pack_ac_f16_kernel(const float* __restrict__ V, int64_t ldv,
                                                                const float* __restrict__ B, int64_t ldb, int64_t n,
-                                                               int64_t nchunks_pad, int t0, int tb, int KT, float half_w,
+                                                               int64_t nchunks_pad, int c0, int sb, int KTH, int with_y,
                                                                float probe_w, const int* __restrict__ scales,
-                                                               u32x4* __restrict__ CA, u32x4* __restrict__ AB) {
+                                                               u32x4* __restrict__ CA, u32x4* __restrict__ AB,
+                                                               float* __restrict__ VY) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= nchunks_pad * KT * 64) return;
+  if (gid < nchunks_pad * 32) VY[gid] = with_y && gid < n ? V[gid * ldv] : 0.0f;
+  if (gid >= nchunks_pad * KTH * 64) return;
   const int lane = (int)(gid & 63);
-  const int kt = (int)((gid >> 6) % KT);
-  const int64_t chunk = (gid >> 6) / KT;
+  const int kt = (int)((gid >> 6) % KTH);
+  const int64_t chunk = (gid >> 6) / KTH;
   const int64_t row = chunk * 32 + (lane & 31);
   const int alpha_exp = scales[0];
-  u32x4 ch, cl, ah, al;
+  u32x4 im[8];     // z and a as column side, a and z as row side: high and low pieces
 #pragma unroll
   for (int e2 = 0; e2 < 4; ++e2) {
-    float c_hi[2], c_lo[2], a_hi[2], a_lo[2];
+    float x[4][2];
 #pragma unroll
-    for (int z = 0; z < 2; ++z) {
-      const int m = 16 * kt + 8 * (lane >> 5) + 2 * e2 + z;
-      float c = 0.0f, a = 0.0f;
-      if (row < n && m < tb) {
-        const int col = t0 + m;
-        const int ec = scales[1 + m];
-        const float v = V[row * ldv + col];
-        const float cv = col == 0 ? v : B[row * ldb + col];
-        c = ldexpf(cv, C_TOP - ec);
-        a = ldexpf((col == 0 ? half_w : probe_w) * v, alpha_exp + ec - C_TOP);
-        if (chunk & 1) a = -a;   // undone by the tile kernel's epilogue (row_sign)
+    for (int q = 0; q < 2; ++q) {
+      const int m = 16 * kt + 8 * (lane >> 5) + 2 * e2 + q;
+      for (int k = 0; k < 4; ++k) x[k][q] = 0.0f;
+      if (row < n && m < sb) {
+        const int ez = scales[1 + m], ea = scales[1 + PROBE_BLOCK + m];
+        const float a = probe_w * V[row * ldv + c0 + m], z = B[row * ldb + c0 + m];
+        x[0][q] = ldexpf(z, C_TOP - ez);
+        x[1][q] = ldexpf(a, C_TOP - ea);
+        x[2][q] = ldexpf(a, alpha_exp + ez - C_TOP);
+        x[3][q] = ldexpf(z, alpha_exp + ea - C_TOP);
+        if (chunk & 1) {   // undone by the tile kernel's epilogue (row_sign)
+          x[2][q] = -x[2][q];
+          x[3][q] = -x[3][q];
+        }
       }
-      split2(c, c_hi[z], c_lo[z]);
-      split2(a, a_hi[z], a_lo[z]);
     }
-    ch[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(c_hi[0], c_hi[1]));
-    cl[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(c_lo[0], c_lo[1]));
-    ah[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(a_hi[0], a_hi[1]));
-    al[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(a_lo[0], a_lo[1]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      unsigned hi, lo;
+      split_pair(x[k][0], x[k][1], hi, lo);
+      im[2 * k][e2] = hi;
+      im[2 * k + 1][e2] = lo;
+    }
   }
-  const int64_t u_hi = ((chunk * 2 + 0) * KT + kt) * 64 + lane;
-  const int64_t u_lo = ((chunk * 2 + 1) * KT + kt) * 64 + lane;
-  CA[u_hi] = ch; CA[u_lo] = cl;
-  AB[u_hi] = ah; AB[u_lo] = al;
+  const int KT = 2 * KTH;
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    const int64_t u = ((chunk * 2 + part) * KT + kt) * 64 + lane;
+    CA[u] = im[part];
+    CA[u + KTH * 64] = im[2 + part];
+    AB[u] = im[4 + part];
+    AB[u + KTH * 64] = im[6 + part];
+  }
 }
 
 // Q' images of Q columns [col0, col0 + ncols), Q = [xs (d), xs^2 (d), 1]; one thread per (chunk, mh, nt, lane).
@@ -396,7 +436,7 @@ __global__ __launch_bounds__(256) void grad_pack_q_f16_kernel(const float* __res
   u32x4 hi, lo;
 #pragma unroll
   for (int e2 = 0; e2 < 4; ++e2) {
-    float fh[2], fl[2];
+    float f[2];
 #pragma unroll
     for (int z = 0; z < 2; ++z) {
       const int e = 2 * e2 + z;
@@ -408,10 +448,12 @@ __global__ __launch_bounds__(256) void grad_pack_q_f16_kernel(const float* __res
         else v = 1.0f;
         v = ldexpf(v, qshift);
       }
-      split2(v, fh[z], fl[z]);
+      f[z] = v;
     }
-    hi[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(fh[0], fh[1]));
-    lo[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(fl[0], fl[1]));
+    unsigned fh, fl;
+    split_pair(f[0], f[1], fh, fl);
+    hi[e2] = fh;
+    lo[e2] = fl;
   }
   u32x4* dst = QP + ((chunk * 2 + mh) * NT + nt) * 2 * 64;
   dst[lane] = hi;
@@ -422,8 +464,12 @@ typedef void (*gradh_fn)(GradArgsH);
 
 template <int KIND, int KH, int XP>
 gradh_fn pick_kt_nt(int KT, int NT) {
-  if (KT == 2) return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 2, 1> : grad_tile_f16_kernel<KIND, KH, XP, 2, 2>;
-  return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 5, 1> : grad_tile_f16_kernel<KIND, KH, XP, 5, 2>;
+  switch (KT) {
+    case 2: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 2, 1> : grad_tile_f16_kernel<KIND, KH, XP, 2, 2>;
+    case 4: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 4, 1> : grad_tile_f16_kernel<KIND, KH, XP, 4, 2>;
+    case 6: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 6, 1> : grad_tile_f16_kernel<KIND, KH, XP, 6, 2>;
+  }
+  return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 8, 1> : grad_tile_f16_kernel<KIND, KH, XP, 8, 2>;
 }
 
 template <int KIND, int XP>
@@ -446,6 +492,49 @@ gradh_fn pick_gradh(int kind, int KH, int XP, int KT, int NT) {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+int grad_probe_steps(int s) { return s > 16 ? (s + 15) / 16 : 1; }
+
+// The work of one block of probes: workgroups of W waves, most chunks one of them takes, pieces of the longest rows (the first
+// ones), all workgroups.  `slots` workgroups run side by side.
+struct GradPlan {
+  int W, cps, pieces, workgroups;
+};
+GradPlan grad_plan(int KT, int chunks, int cus) {
+  GradPlan pl;
+  pl.W = grad_waves(KT);
+  const int slots = cus * 8 / pl.W, row_blocks = (chunks + pl.W - 1) / pl.W;
+  // Rows from long to short fill two generations and more by themselves; fewer are cut into pieces, each an image to write
+  // and sum.  Pieces are of about one length, so beyond one generation the time lies between what a slot has to do on the
+  // average and whole generations.
+  constexpr double FIXED = 6.0;       // prologue and flush of a workgroup, in chunks
+  double best = 1e300;
+  for (int pieces = 1; pieces <= (row_blocks >= 2 * slots ? 1 : 64); ++pieces) {
+    const int cps = (chunks + pieces - 1) / pieces;
+    if (pieces > 1 && cps < 4) break;
+    int64_t all = 0, work = 0;
+    for (int rb = 0; rb < row_blocks; ++rb) {
+      const int len = chunks - rb * pl.W;
+      all += (len + cps - 1) / cps;
+      work += len;
+    }
+    double cost = cps + FIXED;
+    if (all > slots) {
+      const double mean = ((double)work + FIXED * all) / slots, gens = (double)((all + slots - 1) / slots);
+      const double c = 0.5 * (mean + 0.5 * cps) + 0.5 * gens * ((double)work / all + FIXED);
+      if (c > cost) cost = c;
+    }
+    cost += 0.25 * pieces;
+    if (cost < best) {
+      best = cost;
+      pl.cps = cps;
+    }
+  }
+  pl.pieces = (chunks + pl.cps - 1) / pl.cps;
+  pl.workgroups = 0;
+  for (int js = 0; js < pl.pieces; ++js) pl.workgroups += grad_rows_with_piece(js, chunks, pl.cps, pl.W);
+  return pl;
+}
+
 }  // namespace
 
 int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,
@@ -458,22 +547,13 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
   const float half_w = 0.5f;
   const float probe_w = s > 0 ? (float)(-0.5 / (double)s) : 0.0f;
 
-  // plan: one 32-row sub-tile per wave; the column range is split over workgroups until the chip is
-  // full (the kernel itself flushes its accumulators at intervals, so long column ranges need no split)
   const int64_t chunks = (n + 31) / 32;
   const int64_t chunks_pad = ctx->n_pad / 32;
-  const int row_blocks = (int)((n + 127) / 128);
-  int JS = 1;
-  const int target = 2 * ctx->num_cu;
-  if (row_blocks < target) {
-    JS = (target + row_blocks - 1) / row_blocks;
-    const int64_t max_js = chunks / 4 > 0 ? chunks / 4 : 1;
-    if (JS > max_js) JS = (int)max_js;
-    if (JS > 64) JS = 64;
-  }
-  const int cps = (int)((chunks + JS - 1) / JS);
-  JS = (int)((chunks + cps - 1) / cps);
-  const int KTmax = t <= 32 ? 2 : 5;
+  // blocks of PROBE_BLOCK probes, the last one with what is left
+  const int first_block = s < PROBE_BLOCK ? s : PROBE_BLOCK, last_block = s > PROBE_BLOCK ? (s - 1) % PROBE_BLOCK + 1 : first_block;
+  const int KTmax = 2 * grad_probe_steps(first_block);
+  const GradPlan first_plan = grad_plan(KTmax, (int)chunks, ctx->num_cu), last_plan = grad_plan(2 * grad_probe_steps(last_block), (int)chunks, ctx->num_cu);
+  const int JS = first_plan.pieces > last_plan.pieces ? first_plan.pieces : last_plan.pieces;
   // workgroups of the fp64 reduction: one step of 256 / (d + 2) rows each when n allows, so that
   // enough loads are in flight (the kernel is latency-bound at small n)
   int G;
@@ -489,8 +569,9 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
   const size_t part_bytes = align_up((size_t)G * (d + 2) * sizeof(double), 256);
   const size_t acc_bytes = align_up((size_t)(d + 2) * sizeof(double), 256);
   const size_t cm_bytes = align_up((size_t)t * sizeof(unsigned), 256);
-  const size_t sc_bytes = align_up((size_t)(1 + GRAD_TBLOCK_H) * sizeof(int), 256);
-  int rc = gp_ensure_scratch(ctx, 2 * op_bytes + q_bytes + out_bytes + part_bytes + acc_bytes + 2 * cm_bytes + sc_bytes);
+  const size_t sc_bytes = align_up((size_t)(1 + 2 * PROBE_BLOCK) * sizeof(int), 256);
+  const size_t vy_bytes = align_up((size_t)chunks_pad * 32 * sizeof(float), 256);
+  int rc = gp_ensure_scratch(ctx, 2 * op_bytes + q_bytes + out_bytes + part_bytes + acc_bytes + 2 * cm_bytes + sc_bytes + vy_bytes);
   if (rc < 0) return rc;
   char* w = (char*)ctx->dScratch;
   u32x4* CA = (u32x4*)w; w += op_bytes;
@@ -501,7 +582,8 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
   double* acc = (double*)w; w += acc_bytes;
   unsigned* cmV = (unsigned*)w; w += cm_bytes;
   unsigned* cmB = (unsigned*)w; w += cm_bytes;
-  int* scales = (int*)w;
+  int* scales = (int*)w; w += sc_bytes;
+  float* VY = (float*)w;
   hipStream_t st = ctx->stream;
 
   GP_HIP(ctx, hipMemsetAsync(acc, 0, acc_bytes + 2 * cm_bytes, st));   // acc, cmV, cmB lie back to back
@@ -525,14 +607,13 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
   a.CA = CA;
   a.AB = AB;
   a.QP = QP;
+  a.VY = VY;
   a.scales = scales;
   a.OUT = OUT;
   a.ldo = nq;
   a.split_stride = n * (int64_t)nq;
   a.n = n;
   a.nchunks = (int)chunks;
-  a.JS = JS;
-  a.cps = cps;
   a.qshift = qshift;
   a.slot_kh = a.slot_h = a.slot_e = -1;
   if (ctx->kernel == GP_SE_ARD) {
@@ -541,18 +622,18 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
     a.slot_h = (k % 16) / 8;
     a.slot_e = k % 8;
   }
-  const dim3 grid(row_blocks * JS), block(256);
-
-  for (int t0 = 0; t0 < t; t0 += GRAD_TBLOCK_H) {
-    const int tb = t - t0 < GRAD_TBLOCK_H ? t - t0 : GRAD_TBLOCK_H;
-    const int KT = tb <= 32 ? 2 : 5;
-    hipLaunchKernelGGL(grad_scales_kernel, dim3(1), dim3(128), 0, st, (const unsigned*)cmV, (const unsigned*)cmB, t0, tb,
+  for (int c0 = 1; c0 == 1 || c0 < t; c0 += PROBE_BLOCK) {
+    const int sb = t - c0 < PROBE_BLOCK ? t - c0 : PROBE_BLOCK;       // 0 when y is the only column
+    const int KTH = grad_probe_steps(sb), KT = 2 * KTH, with_y = c0 == 1;
+    const GradPlan& pl = sb == first_block ? first_plan : last_plan;
+    a.cps = pl.cps;
+    hipLaunchKernelGGL(grad_scales_kernel, dim3(1), dim3(PROBE_BLOCK), 0, st, (const unsigned*)cmV, (const unsigned*)cmB, c0, sb, with_y,
                        half_w, probe_w, scales);
     GP_HIP(ctx, hipGetLastError());
     {
-      const int64_t units = chunks_pad * KT * 64;
+      const int64_t units = chunks_pad * KTH * 64;
       hipLaunchKernelGGL(grad_pack_ac_f16_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, st, dV, ldv, dB, ldb,
-                         n, chunks_pad, t0, tb, KT, half_w, probe_w, (const int*)scales, CA, AB);
+                         n, chunks_pad, c0, sb, KTH, with_y, probe_w, (const int*)scales, CA, AB, VY);
       GP_HIP(ctx, hipGetLastError());
     }
     int vcol = nq - 1;
@@ -572,13 +653,13 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
       gradh_fn fn = pick_gradh(ctx->kernel, ctx->KH, ctx->XP, KT, NT);
       if (!fn) return gp_fail(ctx, GP_ERR_ARG, "gp_mll_grad: no fp16 kernel for KH=%d", ctx->KH);
       const bool pr = gp_prof_begin(ctx, GP_PROF_GRAD_TILE);
-      hipLaunchKernelGGL(fn, grid, block, 0, st, a);
+      hipLaunchKernelGGL(fn, dim3(pl.workgroups), dim3(64 * pl.W), 0, st, a);
       gp_prof_end(ctx, pr);
       GP_HIP(ctx, hipGetLastError());
       c += a.ncols;
     }
-    rc = gp_grad_reduce_launch(ctx, OUT, a.split_stride, JS, nq, dV, ldv, dB, ldb, t, half_w, probe_w, t0 == 0 ? 1 : 0,
-                               part, G, acc);
+    rc = gp_grad_reduce_launch(ctx, OUT, a.split_stride, pl.pieces, nq, dV, ldv, dB, ldb, t, half_w, probe_w, with_y, part, G, acc,
+                               32 * pl.W, pl.cps);
     if (rc < 0) return rc;
   }
 

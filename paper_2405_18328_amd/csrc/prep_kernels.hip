@@ -5,6 +5,7 @@
 #include <cstring>
 
 #include "gpws_internal.h"
+#include "split_f16.h"
 
 namespace {
 
@@ -84,16 +85,14 @@ __global__ void pack_kernel(const float* __restrict__ X, int64_t n, int64_t n_pa
   }
 }
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// x = hi + mid + lo with hi, mid truncated to 11 significant bits (exact in fp16), lo rounded
+// x = hi + mid + lo, each rounded to nearest: with truncated pieces every product would come out a little too small, and with it
+// every distance, of one sign
 __device__ __forceinline__ void split3(float x, float& hi, float& mid, float& lo) {
-  hi = __uint_as_float(__float_as_uint(x) & 0xFFFFE000u);
+  hi = (float)(_Float16)x;
   const float r1 = x - hi;
-  mid = __uint_as_float(__float_as_uint(r1) & 0xFFFFE000u);
+  mid = (float)(_Float16)r1;
   lo = r1 - mid;
 }
-
 // split-fp16 operands of the matrix-core path; one thread per (chunk, kh, lane)
 __global__ void pack_f16_kernel(const float* __restrict__ Xs, const float* __restrict__ norm, int64_t n,
                                 int64_t n_pad, int d, int KH, int is_se, float gamma, u32x4* __restrict__ A0,
@@ -129,8 +128,8 @@ __global__ void pack_f16_kernel(const float* __restrict__ Xs, const float* __res
     }
 #pragma unroll
     for (int pc = 0; pc < 3; ++pc) {
-      a[pc][e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(pa[pc][0], pa[pc][1]));
-      b[pc][e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(pb[pc][0], pb[pc][1]));
+      a[pc][e2] = pack_f16(pa[pc][0], pa[pc][1]);
+      b[pc][e2] = pack_f16(pb[pc][0], pb[pc][1]);
     }
   }
   A0[gid] = a[0]; A1[gid] = a[1]; A2[gid] = a[2];

@@ -11,7 +11,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr unsigned HI_MASK = 0xFFFFE000u;       // keeps sign, exponent and the top 10 mantissa bits
 constexpr int PHI_SHIFT = 15;                   // phi' = 2^15 phi <= 32768 stays inside fp16's range
 constexpr int V_TOP = 14;                       // max |V'_c| in [2^13, 2^14)
 
@@ -24,19 +23,34 @@ __device__ __forceinline__ int column_exponent(unsigned max_bits) {
   return e < -60 ? -60 : e;
 }
 
-// four scaled values as fp16 halves, packed in pairs: hi is truncated to 11 significant bits, lo is what is left
+// two values as fp16 halves of a word, rounded to nearest
+__device__ __forceinline__ unsigned pack_f16(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), f16x2));
+}
+
+// x - (float)half H of pk, one v_fma_mix_f32 (source 0 read as the fp16 half, sources 1 and 2 as fp32)
+template <int H>
+__device__ __forceinline__ float minus_half(unsigned pk, float x) {
+  float r;
+  if (H == 0) asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
+  else asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
+  return r;
+}
+
+// Two values split into fp16 pieces, hi + lo, packed in pairs, two instructions per value.  Both pieces are rounded to nearest: with
+// truncated ones every product comes out a little too small, by about 2^-22 of its size, and sums that cancel do not
+// average that out.
+__device__ __forceinline__ void split_pair(float a, float b, unsigned& hi, unsigned& lo) {
+  hi = pack_f16(a, b);
+  lo = pack_f16(minus_half<0>(hi, a), minus_half<1>(hi, b));
+}
+
+// four scaled values as fp16 halves, packed in pairs
 __device__ __forceinline__ void split_quad(f32x4 v, unsigned (&hi)[2], unsigned (&lo)[2]) {
-  float h[4], l[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    h[q] = __uint_as_float(__float_as_uint(v[q]) & HI_MASK);
-    l[q] = v[q] - h[q];
-  }
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    hi[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(h[2 * k], h[2 * k + 1]));
-    lo[k] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(l[2 * k], l[2 * k + 1]));
-  }
+  for (int k = 0; k < 2; ++k) split_pair(v[2 * k], v[2 * k + 1], hi[k], lo[k]);
 }
 
 }  // namespace

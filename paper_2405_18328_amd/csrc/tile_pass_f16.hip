@@ -4,13 +4,13 @@
 // fp32-MFMA time instead of hiding under it), while the fp16 MFMA runs on the matrix cores at 16x the
 // rate and overlaps with VALU work.  This path therefore evaluates both contractions of the tile pass
 // with v_mfma_f32_32x32x16_f16 on operands split into fp16 pieces, fp32 accumulation:
-//   x = hi + mid (+ lo), each piece an 11-bit fp16 mantissa, hi and mid obtained by truncation, so
+//   x = hi + mid (+ lo), each piece an 11-bit fp16 mantissa rounded to nearest, so
 //   a.b ~ ah.bh + ah.bm + am.bh (+ ah.bl + al.bh + am.bm): relative error 2^-22 (2^-33), i.e. fp32-class.
 // The VALU keeps what needs fp32: the kernel function (exp2 / sqrt) and the split of phi.
 //
 // Per 32x32 tile of pairs (j, i), one wavefront:
 //   1. S[j][i] = XA_j . XB_i     3 (or 6) MFMAs per 16 components      (= g r^2_ij [+ 15 for SE])
-//   2. phi' = 2^15 phi(S)        VALU; hi = phi' truncated to fp16, lo = phi' - hi; packed to fp16 pairs
+//   2. phi' = 2^15 phi(S)        VALU; hi = phi' rounded to fp16, lo = phi' - hi; packed to fp16 pairs
 //   3. OUT_i += phi'[i][j] V'_j  2 k-steps x NT x 3 MFMAs; V' = V scaled per column by a power of two
 //                                so that max |V'_c| is in [2^13, 2^14), pre-split and pre-packed
 // The accumulator layout of step 1 (lane = i, register r <-> j = 8(r/4) + 4(lane/32) + r%4) gives each lane
@@ -86,15 +86,6 @@ __device__ __forceinline__ int64_t window_chunk(const TileArgsH& p) {
 }
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
-
-// x - (float)half H of pk, one v_fma_mix_f32 (source 0 read as the fp16 half, sources 1 and 2 as fp32)
-template <int H>
-__device__ __forceinline__ float minus_half(unsigned pk, float x) {
-  float r;
-  if (H == 0) asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
-  else asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(pk), "v"(x));
-  return r;
-}
 
 // one lane's 16 accumulators of a column: four runs of four rows, eight rows apart, as 16-byte stores (a lane pair
 // covers 32 consecutive bytes); the accumulators are cleared
@@ -288,11 +279,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
       if (Y) av = fmaf(f[z], vy[e >> 2][e & 3], av);
     }
-    // hi = f truncated to fp16 (both values in one conversion), lo = f - hi taken straight from the
-    // packed halves by the mixed-precision FMA, so the split costs two instructions per value (its forms that
-    // write one fp16 half, one and a half instructions per value, measured 1 - 2 % slower)
-    oh = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
-    ol = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(minus_half<0>(oh, f[0]), minus_half<1>(oh, f[1])));
+    split_pair(f[0], f[1], oh, ol);
   };
   auto load_vy = [&](const u32x4* s, int mh, f32x4 (&vy)[2]) {
 #pragma unroll
@@ -566,8 +553,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
       if (Y) accv[z] = fmaf(f[z], vy[q + z], accv[z]);
     }
     if constexpr (NT > 0) {
-      oh = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
-      ol = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(minus_half<0>(oh, f[0]), minus_half<1>(oh, f[1])));
+      split_pair(f[0], f[1], oh, ol);
     }
   };
 
@@ -793,17 +779,17 @@ __global__ __launch_bounds__(256) void pack_v_kernel(const float* __restrict__ V
     u32x4 hi, lo;
 #pragma unroll
     for (int e2 = 0; e2 < 4; ++e2) {
-      float fh[2], fl[2];
+      float f[2];
 #pragma unroll
       for (int z = 0; z < 2; ++z) {
         const int e = 2 * e2 + z;
         const int64_t j = chunk * 32 + 16 * mh + 8 * (e >> 2) + 4 * hh + (e & 3);
-        const float v = (cok && j < n) ? V[j * ldv + col] * scale : 0.0f;
-        fh[z] = __uint_as_float(__float_as_uint(v) & HI_MASK);
-        fl[z] = v - fh[z];
+        f[z] = (cok && j < n) ? V[j * ldv + col] * scale : 0.0f;
       }
-      hi[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(fh[0], fh[1]));
-      lo[e2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(fl[0], fl[1]));
+      unsigned fh, fl;
+      split_pair(f[0], f[1], fh, fl);
+      hi[e2] = fh;
+      lo[e2] = fl;
     }
     u32x4* dst = VP + ((chunk * 2 + mh) * NT + nt) * 2 * 64;
     dst[lane] = hi;

@@ -1,0 +1,69 @@
+"""The gradient's tile pass over one half of the pairs, at the sizes where its rows, pieces and blocks of probes end.
+
+Rows: tiles of 32, workgroups of 4 or 8 of them (more than 32 probes: 8).  Columns: pieces of at least 4 tiles, several per row
+from n = 300 on.  Probes: 16 per step, 64 per pass, one step at least.  Bound, per component: the sum over all pairs of the
+terms' sizes times
+
+    2^-22 (3 + 2 max |x|^2 + 2)   products of two split factors and G Q (three times 2^-22 at most, each piece being rounded to
+                                  nearest), r^2 (2^-22 of the two squared norms), exp and sqrt (1 ulp each)
+
+and the result's own rounding, which that covers."""
+import numpy as np
+import pytest
+
+from oracle import gp_oracle as orc
+from tests.gpu_util import Dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(n, d, t, kind, seed):
+    rng = np.random.default_rng(seed)
+    X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
+    V = rng.standard_normal((n, t)).astype(np.float32) * np.exp(rng.uniform(-3, 3, t)).astype(np.float32)
+    B = rng.standard_normal((n, t)).astype(np.float32) * np.exp(rng.uniform(-3, 3, t)).astype(np.float32)
+    ell, a, sigma = rng.uniform(0.7, 1.3, d) * np.sqrt(d / 3.0), 1.2, 0.4
+    V64, B64 = V.astype(np.float64), B.astype(np.float64)
+    s = t - 1
+    A, C = V64.copy(), B64.copy()
+    A[:, 0] *= 0.5
+    C[:, 0] = V64[:, 0]
+    if s:
+        A[:, 1:] *= -0.5 / s
+    W = np.abs(A) @ np.abs(C).T        # sizes of the terms of w_ij
+    xs = (X.astype(np.float64) - X.astype(np.float64).mean(0)) / ell
+    unit = 2.0 ** -22 * (5.0 + 2.0 * (xs ** 2).sum(1).max())
+    dv = Dev(X, kind, ell, a, sigma)
+    try:
+        got = np.array(dv.grad(dv.to(V), dv.to(B)))
+        again = np.array(dv.grad(dv.to(V), dv.to(B)))
+    finally:
+        dv.close()
+    assert (got == again).all()
+    ref = orc.mll_grad_hutchinson(X, ell, a, sigma, kind, B64, V=V64)
+    for k, dH in enumerate(orc.dH_list(X.astype(np.float64), ell, a, sigma, kind)):
+        # an expanded square has terms the size of both squared coordinates, where dH has their difference
+        size = (W * np.abs(dH)).sum()
+        if k < d:
+            psi = np.exp(-0.5 * orc.scaled_sqdist(X, X, ell)) if kind == "se" else 3.0 * np.exp(-np.sqrt(3.0 * orc.scaled_sqdist(X, X, ell)))
+            size = a * a / ell[k] * (W * psi * 2.0 * (xs[:, k][:, None] ** 2 + xs[:, k][None, :] ** 2)).sum()
+        assert abs(got[k] - ref[k]) <= unit * size, (k, got[k], ref[k], unit * size)
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 127, 128, 129, 255, 256, 257, 300, 511, 513, 1031])
+@pytest.mark.parametrize("t", [3, 66])
+def test_rows(n, t):
+    print(f"[grad half] n={n} t={t}", flush=True)
+    _check(n, 4, t, "matern32" if n % 2 else "se", n + t)
+
+
+@pytest.mark.parametrize("t", [1, 2, 16, 17, 18, 33, 34, 49, 50, 65, 66, 81, 97, 129, 130])
+def test_probes(t):
+    print(f"[grad half] t={t}", flush=True)
+    _check(413, 5, t, "se" if t % 2 else "matern32", t)
+
+
+@pytest.mark.parametrize("d,t", [(13, 20), (14, 70), (15, 40), (31, 20), (32, 70), (46, 33), (63, 65), (96, 66), (125, 65)])
+def test_dimensions(d, t):
+    print(f"[grad half] d={d} t={t}", flush=True)
+    _check(290, d, t, "matern32", d)
