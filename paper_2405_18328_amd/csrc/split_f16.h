@@ -47,6 +47,14 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& hi, unsig
   lo = pack_f16(minus_half<0>(hi, a), minus_half<1>(hi, b));
 }
 
+// Two values >= 0 split with hi rounded towards zero, so that lo is not negative either; lo is rounded to nearest.  For the
+// tile pass of a product, where this saves power, not instructions: with lo of either sign the matrix cores' operands change
+// more from one product to the next, and at n = 500000, d = 90, t = 65 a product takes 227 ms instead of 216.
+__device__ __forceinline__ void split_pair_positive(float a, float b, unsigned& hi, unsigned& lo) {
+  hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(a, b));
+  lo = pack_f16(minus_half<0>(hi, a), minus_half<1>(hi, b));
+}
+
 // four scaled values as fp16 halves, packed in pairs
 __device__ __forceinline__ void split_quad(f32x4 v, unsigned (&hi)[2], unsigned (&lo)[2]) {
 #pragma unroll

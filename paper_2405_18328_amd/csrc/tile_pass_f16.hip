@@ -4,13 +4,13 @@
 // fp32-MFMA time instead of hiding under it), while the fp16 MFMA runs on the matrix cores at 16x the
 // rate and overlaps with VALU work.  This path therefore evaluates both contractions of the tile pass
 // with v_mfma_f32_32x32x16_f16 on operands split into fp16 pieces, fp32 accumulation:
-//   x = hi + mid (+ lo), each piece an 11-bit fp16 mantissa rounded to nearest, so
+//   x = hi + mid (+ lo), each piece an 11-bit fp16 mantissa, so
 //   a.b ~ ah.bh + ah.bm + am.bh (+ ah.bl + al.bh + am.bm): relative error 2^-22 (2^-33), i.e. fp32-class.
 // The VALU keeps what needs fp32: the kernel function (exp2 / sqrt) and the split of phi.
 //
 // Per 32x32 tile of pairs (j, i), one wavefront:
 //   1. S[j][i] = XA_j . XB_i     3 (or 6) MFMAs per 16 components      (= g r^2_ij [+ 15 for SE])
-//   2. phi' = 2^15 phi(S)        VALU; hi = phi' rounded to fp16, lo = phi' - hi; packed to fp16 pairs
+//   2. phi' = 2^15 phi(S)        VALU; hi = phi' cut to fp16, lo = phi' - hi rounded; packed to fp16 pairs
 //   3. OUT_i += phi'[i][j] V'_j  2 k-steps x NT x 3 MFMAs; V' = V scaled per column by a power of two
 //                                so that max |V'_c| is in [2^13, 2^14), pre-split and pre-packed
 // The accumulator layout of step 1 (lane = i, register r <-> j = 8(r/4) + 4(lane/32) + r%4) gives each lane
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
       if (Y) av = fmaf(f[z], vy[e >> 2][e & 3], av);
     }
-    split_pair(f[0], f[1], oh, ol);
+    split_pair_positive(f[0], f[1], oh, ol);
   };
   auto load_vy = [&](const u32x4* s, int mh, f32x4 (&vy)[2]) {
 #pragma unroll
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
       if (Y) accv[z] = fmaf(f[z], vy[q + z], accv[z]);
     }
     if constexpr (NT > 0) {
-      split_pair(f[0], f[1], oh, ol);
+      split_pair_positive(f[0], f[1], oh, ol);
     }
   };
 
