@@ -102,8 +102,8 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
   GP_HIP(ctx, hipMalloc((void**)&ctx->dXA, packed));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dXB, packed));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dXs, (size_t)n * d * sizeof(float)));
-  GP_HIP(ctx, hipMalloc((void**)&ctx->dNorm, (size_t)ctx->n_pad * sizeof(float)));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dMaxNorm, 256));
+  GP_HIP(ctx, hipMemsetAsync(ctx->dMaxNorm, 0, 256, ctx->stream));
   {
     const size_t units = (size_t)(ctx->n_pad / GP_CHUNK) * ctx->KH * 64;
     for (int pc = 0; pc < 3; ++pc) {
@@ -120,6 +120,7 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
   ctx->pinned_bytes = (size_t)1 << 16;
   GP_HIP(ctx, hipHostMalloc(&ctx->hPinned, ctx->pinned_bytes, hipHostMallocDefault));
   GP_HIP(ctx, hipHostGetDevicePointer(&ctx->dPinned, ctx->hPinned, 0));
+  memset(ctx->hPinned, 0, ctx->pinned_bytes);
   return gp_launch_column_means(ctx);
 }
 
@@ -129,7 +130,6 @@ int gp_destroy(gp_ctx* ctx) {
   if (ctx->dXA) (void)hipFree(ctx->dXA);
   if (ctx->dXB) (void)hipFree(ctx->dXB);
   if (ctx->dXs) (void)hipFree(ctx->dXs);
-  if (ctx->dNorm) (void)hipFree(ctx->dNorm);
   if (ctx->dMaxNorm) (void)hipFree(ctx->dMaxNorm);
   for (int pc = 0; pc < 3; ++pc) {
     if (ctx->dXAh[pc]) (void)hipFree(ctx->dXAh[pc]);
@@ -173,23 +173,17 @@ int gp_set_theta(gp_ctx* ctx, const double* h_lengthscale, double signal_scale, 
   ctx->a = signal_scale;
   ctx->sigma = noise_scale;
   GP_HIP(ctx, hipMemcpyAsync(ctx->dTheta, stage, sizeof(double) * (ctx->d + 2), hipMemcpyHostToDevice, ctx->stream));
-  GP_HIP(ctx, hipMemsetAsync(ctx->dMaxNorm, 0, sizeof(unsigned), ctx->stream));
-  int rc = gp_launch_pack(ctx);
-  if (rc < 0) return rc;
   // The largest scaled squared norm decides which product path holds the error budget.  The host-side
   // bound sum_k (xabs_k / ell_k)^2 >= max_i |xs_i|^2 settles the common case (two fp16 pieces) without a
   // read-back; otherwise the exact maximum found by the packing kernel is fetched.
   double bound = 0.0;
   for (int k = 0; k < ctx->d; ++k) bound += (ctx->xabs[k] / ctx->ell[k]) * (ctx->xabs[k] / ctx->ell[k]);
   bound *= 1.0 + 1e-5;   // fp32 rounding of the scaled inputs
-  if (bound <= (double)GP_NORM_X2_MAX && ctx->path_forced < 0) {
-    ctx->max_norm = (float)bound;
-  } else {
-    float* hmax = (float*)((char*)ctx->hPinned + GP_PIN_NORM);
-    GP_HIP(ctx, hipMemcpyAsync(hmax, ctx->dMaxNorm, sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
-    GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    ctx->max_norm = *hmax;
-  }
+  const bool settled = bound <= (double)GP_NORM_X2_MAX && ctx->path_forced < 0;
+  ctx->max_norm = (float)bound;
+  int rc = gp_launch_pack(ctx, !settled);
+  if (rc < 0) return rc;
+  if (!settled && (rc = gp_wait_norm(ctx, "gp_set_theta", &ctx->max_norm)) < 0) return rc;
   if (!std::isfinite(ctx->max_norm))
     return gp_fail(ctx, GP_ERR_ARG, "gp_set_theta: inputs scaled by the lengthscales are not finite");
   int path = ctx->max_norm <= GP_NORM_X2_MAX ? GP_PATH_F16X2

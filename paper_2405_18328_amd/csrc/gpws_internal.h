@@ -21,7 +21,7 @@ constexpr int GP_VEC_PAD = 4;         // solver arrays are padded to a multiple 
 constexpr float GP_PAD_NORM = 1.0e30f; // squared norm given to padding rows of XA (phi underflows to 0)
 constexpr int GP_PACK_SLACK = 256;    // floats allocated past the packed arrays: staging loads overrun by < 256
 constexpr float GP_PAD_NORM_H = 60000.0f;  // same for the fp16 operands (must fit fp16)
-enum { GP_PATH_FP32 = 0, GP_PATH_F16X2 = 1, GP_PATH_F16X3 = 2 };
+enum { GP_PATH_PENDING = -1, GP_PATH_FP32 = 0, GP_PATH_F16X2 = 1, GP_PATH_F16X3 = 2 };
 // fp16 distance pieces: two pieces carry 22 bits, so r^2 has an absolute error ~2^-22 (|xs_i|^2+|xs_j|^2);
 // past this squared norm three pieces (33 bits) are used, and past fp16's range the fp32 MFMA path
 constexpr float GP_NORM_X2_MAX = 64.0f;
@@ -61,8 +61,8 @@ struct gp_ctx {
   float* dXA;             // packed, n_pad/32 * KS * 64
   float* dXB;
   float* dXs;             // scaled centred inputs, row-major n x d (gradient pass)
-  float* dNorm;           // |xs_i|^2, n_pad entries
-  unsigned* dMaxNorm;     // bit pattern of max_i |xs_i|^2 (device), refreshed by gp_set_theta
+  unsigned long long* dMaxNorm;   // a tag and below it the bit pattern of the largest |xs_i|^2 packed under it (device)
+  unsigned norm_seq;      // the latest tag
   // split-fp16 operands of the matrix-core path: three pieces (hi, mid, lo) per side, 16-byte units
   // [(chunk*KH + kh)*64 + lane], element e of a unit = component 16 kh + 8 (lane/32) + e
   void* dXAh[3];
@@ -109,7 +109,7 @@ struct KmvRows {
   int64_t m;
   const float* XB;        // fp32 packed row operands, [m_pad/32][KS][64]
   const void* XBh[3];     // fp16 pieces, [m_pad/32][KH][64] 16-byte units
-  int path;               // GP_PATH_* to use (covers the norms of both point sets)
+  int path;               // GP_PATH_* to use (covers the norms of both point sets); GP_PATH_PENDING: gp_rows_path will tell
 };
 
 // Column-split partial results of a product whose final sum the caller takes over (the CG dot-product
@@ -156,12 +156,15 @@ int gp_ensure_scratch(gp_ctx* ctx, size_t bytes);
 
 // ---- prep_kernels.hip
 int gp_launch_column_means(gp_ctx* ctx);
-int gp_launch_pack(gp_ctx* ctx);
+int gp_launch_pack(gp_ctx* ctx, bool want_norm);
+// waits for the largest scaled squared norm of the latest packing that was asked for it
+int gp_wait_norm(gp_ctx* ctx, const char* who, float* norm);
 // packs m other points (device, row-major m x d) against the context's centring and theta into
-// caller-provided buffers sized by gp_pack_rows_bytes; fills rows (path from the larger of the two
-// sets' scaled norms; synchronises the stream to read that norm back)
+// caller-provided buffers sized by gp_pack_rows_bytes; fills rows.  The path follows from the larger of the two sets' scaled
+// norms: it stays pending until gp_rows_path waits for that norm, so that launches which do not depend on it go first
 size_t gp_pack_rows_bytes(const gp_ctx* ctx, int64_t m);
 int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows);
+int gp_rows_path(gp_ctx* ctx, KmvRows* rows);
 
 // ---- tile_pass.hip
 struct KmvPlan {
@@ -181,7 +184,7 @@ size_t gp_kmv_window_scratch_bytes(const gp_ctx* ctx, int t, int col_chunks);   
 // defer: NULL, or where to report column-split partials instead of summing them into OUT.
 int gp_kmv_launch(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo,
                   int add_noise, void* scratch, size_t scratch_bytes, const unsigned* colmax,
-                  const KmvRows* rows = nullptr, KmvDeferred* defer = nullptr, const KmvWindow* win = nullptr);
+                  KmvRows* rows = nullptr, KmvDeferred* defer = nullptr, const KmvWindow* win = nullptr);
 
 // ---- tile_pass_f16.hip
 int gp_kh_bucket(int d, int kernel);
@@ -190,9 +193,11 @@ int gp_kh_bucket(int d, int kernel);
 int gp_column_splits(int row_blocks, int64_t chunks, int slots, double image_cost, int max_splits);
 size_t gp_kmv_f16_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks = 0);
 size_t gp_kmv_f16_least_scratch_bytes(const gp_ctx* ctx, int t);   // square product with its rows in panels
+// GP_OK, an error, or GP_TO_FP32: the rows' path was pending and turned out to be the fp32 one (nothing is in OUT yet)
+constexpr int GP_TO_FP32 = 1000;
 int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo,
                       int add_noise, void* scratch, size_t scratch_bytes, const unsigned* colmax,
-                      const KmvRows* rows, KmvDeferred* defer, const KmvWindow* win);
+                      KmvRows* rows, KmvDeferred* defer, const KmvWindow* win);
 
 // The tile passes alone, for solvers that keep their vectors column by column and pack operands themselves: the
 // sums of image k, column c lie at images[(k t + c) ld + i], a^2 included, no noise term; rows from n up to the next

@@ -339,14 +339,16 @@ size_t gp_kmv_window_scratch_bytes(const gp_ctx* ctx, int t, int col_chunks) {
 }
 
 int gp_kmv_launch(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo,
-                  int add_noise, void* scratch, size_t scratch_bytes, const unsigned* colmax, const KmvRows* rows,
+                  int add_noise, void* scratch, size_t scratch_bytes, const unsigned* colmax, KmvRows* rows,
                   KmvDeferred* defer, const KmvWindow* win) {
   if (rows && add_noise) return gp_fail(ctx, GP_ERR_ARG, "rectangular product with a noise term");
   const int64_t all_chunks = (ctx->n + 31) / 32;
   if (win && (add_noise || rows || win->chunk0 < 0 || win->nchunks < 1 || (int64_t)win->chunk0 + win->nchunks > all_chunks))
     return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: bad column window");
-  if ((rows ? rows->path : ctx->path) != GP_PATH_FP32)
-    return gp_kmv_launch_f16(ctx, dV, ldv, t, dOut, ldo, add_noise, scratch, scratch_bytes, colmax, rows, defer, win);
+  if ((rows ? rows->path : ctx->path) != GP_PATH_FP32) {
+    const int rc = gp_kmv_launch_f16(ctx, dV, ldv, t, dOut, ldo, add_noise, scratch, scratch_bytes, colmax, rows, defer, win);
+    if (rc != GP_TO_FP32) return rc;
+  }
   const int64_t nrows = rows ? rows->m : ctx->n;
   const KmvPlan pl = gp_plan_kmv(ctx, nrows, win ? win->nchunks : 0);
   const bool split = pl.JS > 1;

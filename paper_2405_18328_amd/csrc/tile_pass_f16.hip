@@ -1162,14 +1162,10 @@ size_t gp_kmv_f16_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows, int64_t 
 size_t gp_kmv_f16_least_scratch_bytes(const gp_ctx* ctx, int t) { return scratch_layout(ctx, t, 1, ctx->n).total; }
 
 int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut, int64_t ldo, int add_noise,
-                      void* scratch, size_t scratch_bytes, const unsigned* colmax_ready, const KmvRows* rows,
+                      void* scratch, size_t scratch_bytes, const unsigned* colmax_ready, KmvRows* rows,
                       KmvDeferred* defer, const KmvWindow* win) {
   const int64_t nrows = rows ? rows->m : ctx->n;
-  const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
-  PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
-  ScratchH L = scratch_layout(ctx, t, pl.JS, nrows);
-  const PanelsH pn = scratch_bytes < L.total && pl.JS > 1 && !defer && !win && !rows ? plan_panels(ctx, nrows, t, XP, pl, L, scratch_bytes) : PanelsH{0, pl.JS};
-  if (pn.rows) L = scratch_layout(ctx, t, 1, nrows), L.off_part = panel_images_at(L, pn.group, pl), L.total = scratch_bytes;
+  ScratchH L = scratch_layout(ctx, t, 1, nrows);     // where the operands lie does not depend on the splits
   if (scratch_bytes < L.total || !scratch)
     return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv: scratch %zu < %zu bytes", scratch_bytes, L.total);
   hipStream_t st = ctx->stream;
@@ -1177,8 +1173,6 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   const unsigned* colmax = colmax_ready ? colmax_ready : (const unsigned*)(w + L.off_colmax);
   float* VY = (float*)(w + L.off_vy);
   u32x4* VP = (u32x4*)(w + L.off_vp);
-  float* part = (float*)(w + L.off_part);
-  const bool split = pl.JS > 1;
   // a column window is handed to the kernels as a point set of its own that starts at chunk 0
   const int nchunks = win ? win->nchunks : (int)((ctx->n + 31) / 32);
   const int64_t first = win ? (int64_t)win->chunk0 * 32 : 0;
@@ -1204,6 +1198,49 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     const int rc = gp_launch_colmax(ctx, dV, ldv, t, accumulate ? ctx->dColmax : (unsigned*)(w + L.off_colmax), nullptr, 0, nullptr, accumulate);
     if (rc < 0) return rc;
   }
+
+  // operands of one column pass, chunks c0 .. c0 + chunks - 1
+  auto pack = [&](int c0, int chunks, int NT, int col0, int ncols, int vc, bool first_pass) {
+    const int64_t threads = (int64_t)chunks * 2 * NT * 64;
+    const int64_t need = threads > (int64_t)chunks * 32 ? threads : (int64_t)chunks * 32;
+    const int64_t r0 = (int64_t)c0 * 32;
+    hipLaunchKernelGGL(pack_v_kernel, dim3((unsigned)((need + 255) / 256)), dim3(256), 0, st, dVw + r0 * ldv, ldv, ncontr - r0, chunks, NT,
+                       col0, ncols, vc, accumulate && first_pass ? (const unsigned*)ctx->dColmax : colmax, VP, VY + r0,
+                       accumulate && first_pass ? (unsigned*)(w + L.off_colmax) : nullptr, t);
+  };
+  auto pack_pass = [&](int NT, int col0, int ncols, int vc, bool first_pass) -> int {      // all of them
+    if (small) {
+      const int quads = (8 * nchunks + 127) / 128;
+      auto* pack_small = quads <= 2 ? pack_small_kernel<2> : quads <= 4 ? pack_small_kernel<4> : quads <= 8 ? pack_small_kernel<8> : pack_small_kernel<16>;
+      hipLaunchKernelGGL(pack_small, dim3((unsigned)((col0 + 32 * NT + 7) / 8)), dim3(1024), 0, st, dV, ldv, (int)ctx->n, nchunks, NT, col0, t,
+                         (unsigned*)(w + L.off_colmax), VP, VY);
+    } else {
+      pack(0, nchunks, NT, col0, ncols, vc, first_pass);
+    }
+    GP_HIP(ctx, hipGetLastError());
+    return GP_OK;
+  };
+  // Where the path still depends on the norms of the rows being packed, the first pass's operands are packed before they are
+  // waited for: the host's wait is hidden behind them.  With the packing in one kernel, gp_predict n = 41157, m = 4573, t = 1
+  // 78 -> 64 us; n = 13500, m = 1500, t = 65 73 -> 52 us.
+  bool packed = false;
+  if (rows && rows->path == GP_PATH_PENDING) {
+    const int c = y ? 1 : 0, NT = pass_tiles(t - c);
+    int rc = pack_pass(NT, c, t - c < 32 * NT ? t - c : 32 * NT, y ? 0 : -1, true);
+    if (rc < 0 || (rc = gp_rows_path(ctx, rows)) < 0) return rc;
+    if (rows->path == GP_PATH_FP32) return GP_TO_FP32;
+    packed = true;
+  }
+
+  const int XP = rows ? (rows->path == GP_PATH_F16X3 ? 3 : 2) : ctx->XP;
+  PlanH pl = plan_h(ctx, nrows, win ? win->nchunks : 0, t, XP);
+  L = scratch_layout(ctx, t, pl.JS, nrows);
+  const PanelsH pn = scratch_bytes < L.total && pl.JS > 1 && !defer && !win && !rows ? plan_panels(ctx, nrows, t, XP, pl, L, scratch_bytes) : PanelsH{0, pl.JS};
+  if (pn.rows) L = scratch_layout(ctx, t, 1, nrows), L.off_part = panel_images_at(L, pn.group, pl), L.total = scratch_bytes;
+  if (scratch_bytes < L.total)
+    return gp_fail(ctx, GP_ERR_WORKSPACE, "gp_kmv: scratch %zu < %zu bytes", scratch_bytes, L.total);
+  float* part = (float*)(w + L.off_part);
+  const bool split = pl.JS > 1;
 
   TileArgsH a;
   for (int pc = 0; pc < 3; ++pc) {
@@ -1251,26 +1288,13 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     a.vcol = vcol;
     const int vc = vcol;
     vcol = -1;
-    auto pack = [&](int c0, int chunks) {      // operands of chunks c0 .. c0 + chunks - 1
-      const int64_t threads = (int64_t)chunks * 2 * NT * 64;
-      const int64_t need = threads > (int64_t)chunks * 32 ? threads : (int64_t)chunks * 32;
-      const int64_t r0 = (int64_t)c0 * 32;
-      hipLaunchKernelGGL(pack_v_kernel, dim3((unsigned)((need + 255) / 256)), dim3(256), 0, st, dVw + r0 * ldv, ldv, ncontr - r0, chunks, NT,
-                         a.col0, a.ncols, vc, accumulate && first_pass ? (const unsigned*)ctx->dColmax : colmax, VP, VY + r0,
-                         accumulate && first_pass ? (unsigned*)(w + L.off_colmax) : nullptr, t);
-    };
-    if (small) {
-      const int quads = (8 * nchunks + 127) / 128;
-      auto* pack_small = quads <= 2 ? pack_small_kernel<2> : quads <= 4 ? pack_small_kernel<4> : quads <= 8 ? pack_small_kernel<8> : pack_small_kernel<16>;
-      hipLaunchKernelGGL(pack_small, dim3((unsigned)((c + 32 * NT + 7) / 8)), dim3(1024), 0, st, dV, ldv, (int)ctx->n, nchunks, NT, c, t,
-                         (unsigned*)(w + L.off_colmax), VP, VY);
-    } else if (pn.group == pl.JS) {
-      pack(0, nchunks);
+    if (!packed && pn.group == pl.JS) {
+      const int rc = pack_pass(NT, a.col0, a.ncols, vc, first_pass);
+      if (rc < 0) return rc;
     }
-    GP_HIP(ctx, hipGetLastError());
+    packed = false;
     a.clear = accumulate && first_pass ? ctx->dColmax : nullptr;
     a.clear_n = t;
-    first_pass = false;
     const TileKernelH k = tile_kernel_h(ctx, nrows, XP, NT, a.vcol >= 0, FORM_PLAIN);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for KH=%d", ctx->KH);
     const int col = a.vcol >= 0 ? a.vcol : a.col0, width = a.ncols + (a.vcol >= 0 ? 1 : 0);   // the pass's columns
@@ -1296,7 +1320,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
           a.ldo = width;
           a.split_stride = m * width;
           a.OUT = part - col;
-          if (pn.group < pl.JS) pack(c0, a.nchunks);
+          if (pn.group < pl.JS) pack(c0, a.nchunks, NT, a.col0, a.ncols, vc, first_pass);
         }
         const dim3 grid((unsigned)((m + k.rows_per_wg - 1) / k.rows_per_wg) * a.JS);
         const bool prof = gp_prof_begin(ctx, GP_PROF_TILE);
@@ -1307,6 +1331,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
         if (pn.rows) sum_images_of(m, width, j0 > 0, dOut + r0 * ldo + col);
       }
     }
+    first_pass = false;
     c += a.ncols;
   } while (c < t);
   if (defer) {

@@ -1,0 +1,75 @@
+"""Packing of points (32 rows to a workgroup, eight threads to a norm) and the norm that a prediction waits for.
+
+Row counts around a chunk of 32 and the packed arrays' 512 rows, dimensions around a thread's eight components and a k-step's 16,
+and up to the largest.  Bound: products of two split factors (3 2^-22) and r^2 from two pieces per coordinate (2^-22 of the two
+squared norms, taken four times for the steps of the chain that meet in it), against the sum of the terms' sizes."""
+import numpy as np
+import pytest
+
+from oracle import gp_oracle as orc
+from tests.gpu_util import Dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _unit(X, Xs, ell):
+    mean = X.astype(np.float64).mean(0)
+    top = max((((P - mean) / ell) ** 2).sum(1).max() for P in (X.astype(np.float64), Xs.astype(np.float64)))
+    return 2.0 ** -22 * (5.0 + 8.0 * top)
+
+
+def _check(dv, X, Xs, ell, a, kind, V):
+    got = dv.predict(Xs, V)
+    ref = orc.cross_kmv(Xs, X, ell, a, kind, V)
+    size = a * a * np.abs(V.astype(np.float64)).sum(0)
+    assert (np.abs(got - ref) <= _unit(X, Xs, ell) * size).all(), (np.abs(got - ref) / size).max()
+
+
+@pytest.mark.parametrize("m", [1, 31, 32, 33, 511, 512, 513])
+@pytest.mark.parametrize("n,t", [(65, 1), (1025, 34)])
+def test_rows(m, n, t):
+    print(f"[pack points] m={m} n={n} t={t}", flush=True)
+    rng = np.random.default_rng(m + n)
+    d, kind = 5, "se" if m % 2 else "matern32"
+    X, Xs = rng.uniform(-1, 1, (n, d)).astype(np.float32), rng.uniform(-1, 1, (m, d)).astype(np.float32)
+    V = rng.standard_normal((n, t)).astype(np.float32)
+    ell = rng.uniform(0.8, 1.2, d)
+    dv = Dev(X, kind, ell, 1.1, 0.3)
+    try:
+        _check(dv, X, Xs, ell, 1.1, kind, V)
+    finally:
+        dv.close()
+
+
+@pytest.mark.parametrize("d", [1, 2, 7, 8, 9, 13, 14, 15, 31, 62, 93, 126])
+@pytest.mark.parametrize("kind", ["se", "matern32"])
+def test_dimensions(d, kind):
+    print(f"[pack points] d={d} {kind}", flush=True)
+    rng = np.random.default_rng(d)
+    X, Xs = rng.uniform(-1, 1, (323, d)).astype(np.float32), rng.uniform(-1, 1, (70, d)).astype(np.float32)
+    V = rng.standard_normal((323, 3)).astype(np.float32)
+    ell = rng.uniform(0.8, 1.2, d) * np.sqrt(d)
+    dv = Dev(X, kind, ell, 0.9, 0.3)
+    try:
+        _check(dv, X, Xs, ell, 0.9, kind, V)
+    finally:
+        dv.close()
+
+
+def test_a_far_prediction_leaves_nothing_for_the_next():
+    """Near points, then points whose norm asks for three pieces, then for fp32, then near ones again: the first call's bits."""
+    rng = np.random.default_rng(3)
+    X, Xs = rng.uniform(-1, 1, (300, 4)).astype(np.float32), rng.uniform(-1, 1, (40, 4)).astype(np.float32)
+    V = rng.standard_normal((300, 33)).astype(np.float32)
+    ell = np.full(4, 1.0)
+    dv = Dev(X, "matern32", ell, 1.0, 0.3)
+    try:
+        first = dv.predict(Xs, V)
+        for far in (30.0, 300.0):
+            dv.predict(far * Xs, V)
+            assert (dv.predict(Xs, V) == first).all()
+            kmv = dv.kmv(V, 1)
+            assert (dv.kmv(V, 1) == kmv).all()
+        _check(dv, X, Xs, ell, 1.0, "matern32", V)
+    finally:
+        dv.close()
