@@ -3,7 +3,7 @@
 // launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
 // context's packed operands; the gradient on the mini-batch rows is spread over the chip; momentum, iterate,
 // the stopping test and the packing of the iterate for the next product are per column (columns.h).
-// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: 78 -> 45 us per step (product 20.2, gradient 10.1, the rest
+// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: 78 -> 43 us per step (product 20.2, gradient 8.6, the rest
 // 10.7 us).  Bound by memory latency and by the 64 partial images of the product (16.6 MB written and read).
 #include "columns.h"
 
@@ -70,46 +70,59 @@ __global__ __launch_bounds__(CT) void sgdc_start_kernel(SgdCols s, int warm) {
 }
 
 // The mini-batch rows I behind their product: G = (H U)[I] - B[I], R[I] <- -G, step * G kept per slot, and the change of
-// the residual estimate's squared norm per slice of slots.  Spread over the chip: a column's images (64 of them
-// for 1000 rows) would take one compute unit as long as everything else of a step.  Grid: slices x t.
-// HB images are fetched at a time, all loads in flight together.
-constexpr int GT = 256;
-template <int HB>
-__global__ __launch_bounds__(GT) void sgdc_grad_kernel(SgdCols s, const int* __restrict__ I) {
-  __shared__ double sh[GT / 64];
-  const int c = blockIdx.y;
+// the residual estimate's squared norm per slice of slots.  Bound by the latency of the images (64 of them for 1000 rows,
+// 16.6 MB at t = 65): a workgroup takes 64 slots, 16 groups of threads share the images between them, 16 bytes a load.  With one
+// slot and all images to a thread there were too few workgroups to hide it: 9.8 -> 8.6 us a step at n = 16384, t = 65.  Grid: slices x t.
+constexpr int GS = 64;      // slots per workgroup
+constexpr int GG = 16;      // groups of images; group g sums images g, g + GG, ..
+__global__ __launch_bounds__(GS / 4 * GG) void sgdc_grad_kernel(SgdCols s, const int* __restrict__ I) {
+  __shared__ f32x4 part[GG][GS / 4];
+  const int c = blockIdx.y, tid = threadIdx.x;
   const int64_t col = (int64_t)c * s.ld, gcol0 = (int64_t)c * s.gld;
-  const int slot = blockIdx.x * GT + threadIdx.x;
-  const bool mine = slot < s.batch;
-  int64_t i = I[mine ? slot : 0];
-  const int stopped = s.frozen[c], over = s.flags->all_done;
-  const bool outside = i < 0 || i >= s.n;
-  if (outside) i = 0;
-  const float ui = s.U[col + i], bi = s.B[col + i], old = s.R[col + i];
-  float hx = 0.0f;
-  for (int k = 0; k < s.JS; k += HB) {
-    float h[HB];
-#pragma unroll
-    for (int q = 0; q < HB; ++q) h[q] = s.images[(int64_t)min(k + q, s.JS - 1) * s.stride + gcol0 + (mine ? slot : 0)];
-#pragma unroll
-    for (int q = 0; q < HB; ++q)
-      if (k + q < s.JS) hx += h[q];
+  const int slot = blockIdx.x * GS + tid;
+  const bool mine = tid < GS && slot < s.batch;
+  int64_t i = 0;
+  float ui = 0.0f, bi = 0.0f, old = 0.0f;
+  bool outside = false;
+  if (mine) {
+    i = I[slot];
+    outside = i < 0 || i >= s.n;
+    if (outside) i = 0;
+    ui = s.U[col + i];
+    bi = s.B[col + i];
+    old = s.R[col + i];
   }
+  const int stopped = s.frozen[c], over = s.flags->all_done;
+  const int quad = tid % (GS / 4), g = tid / (GS / 4);
+  const float* at = s.images + gcol0 + min((int)blockIdx.x * GS + 4 * quad, (int)s.gld - 4);
+  f32x4 h = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k = g; k < s.JS; k += 4 * GG) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(at + (int64_t)min(k + GG * u, s.JS - 1) * s.stride);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (k + GG * u < s.JS) h += v[u];
+  }
+  part[g][quad] = h;
   if (over) return;
+  __syncthreads();
+  if (tid >= GS) return;      // one wave of slots
   if (outside) *s.bad_index = 1;
   double acc = 0.0;
   if (mine && !stopped) {
+    float hx = 0.0f;
+#pragma unroll
+    for (int k = 0; k < GG; ++k) hx += part[k][tid / 4][tid % 4];
     hx = fmaf(s.sigma2, ui, hx);
-    const float g = hx - bi;
-    s.R[col + i] = -g;
-    s.G[gcol0 + slot] = s.step * g;
-    acc = (double)g * (double)g - (double)old * (double)old;
+    const float gr = hx - bi;
+    s.R[col + i] = -gr;
+    s.G[gcol0 + slot] = s.step * gr;
+    acc = (double)gr * (double)gr - (double)old * (double)old;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-  __syncthreads();
-  if (threadIdx.x == 0) s.deltas[(int64_t)c * gridDim.x + blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  if (tid == 0) s.deltas[(int64_t)c * gridDim.x + blockIdx.x] = acc;
 }
 
 // The rest of a step of one column: stopping test, momentum, iterate, the operands of the next product.
@@ -150,9 +163,11 @@ __global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __r
   const double rr0 = s.rr[c], bn2 = s.bn2[c];
   const float tol = s.tol[c];
   int bad = *s.bad_index ? 2 : 0;
-  double delta = 0.0;
-  for (int k = 0; k < slices; ++k) delta += s.deltas[(int64_t)c * slices + k];
+  double delta = 0.0;      // every wave adds up all slices
+  for (int k = tid & 63; k < slices; k += 64) delta += s.deltas[(int64_t)c * slices + k];
   if (s.flags->all_done) return;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) delta += __shfl_xor(delta, off);
   if constexpr (Q > 0) {
     if (go) {
       __syncthreads();
@@ -268,7 +283,7 @@ Layout layout(const gp_ctx* ctx, int t, int batch) {
   L.off_M = o; o += arr;
   L.off_R = o; o += arr;
   L.off_G = o; o += garr;
-  L.off_deltas = o; o += align_up((size_t)t * ((batch + GT - 1) / GT) * sizeof(double), 256);
+  L.off_deltas = o; o += align_up((size_t)t * ((batch + GS - 1) / GS) * sizeof(double), 256);
   L.off_state = o; o += align_up(sizeof(ColFlags) + 16 + (size_t)t * (2 * sizeof(double) + 2 * sizeof(float) + 3 * sizeof(int)), 256);
   L.off_VP = o; o += align_up((size_t)L.units * 16, 256);
   const size_t square = arr * (size_t)gp_packed_images(ctx, t, ctx->n);
@@ -382,7 +397,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
   const size_t lds = L.ld <= 4 * CROWS ? (size_t)L.ld * sizeof(float) : 0;
   if (lds > 48 * 1024 && failed(hipFuncSetAttribute((const void*)step, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
     return GP_ERR_HIP;
-  const int slices = (batch + GT - 1) / GT;
+  const int slices = (batch + GS - 1) / GS;
   // Steps queued ahead of the flags the host has seen; kernels queued past the end return at once.
   const int ahead = ctx->prof_mask ? 0 : 4;
   unsigned long long seen = 0;
@@ -401,8 +416,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
       const int* I = dBatches + (int64_t)queued * batch;
       const int rc = gp_kmv_packed(ctx, t, pk, I, batch, nullptr, &s.JS);
       if (rc < 0) return drained(rc);
-      auto* grad = s.JS <= 8 ? sgdc_grad_kernel<8> : s.JS <= 24 ? sgdc_grad_kernel<24> : sgdc_grad_kernel<64>;
-      hipLaunchKernelGGL(grad, dim3(slices, t), dim3(GT), 0, st, s, I);
+      hipLaunchKernelGGL(sgdc_grad_kernel, dim3(slices, t), dim3(GS / 4 * GG), 0, st, s, I);
       hipLaunchKernelGGL(step, grid, block, lds, st, s, I, slices);
       if (failed(hipGetLastError())) return GP_ERR_HIP;
     }
