@@ -57,7 +57,7 @@ struct TileArgsH {
 
 // What a tile kernel is compiled for, besides the row-major product of gp_kmv and gp_predict (FORM_PLAIN).  The shapes
 // that fill the register file are built once per form: with all options in one kernel, KH = 1 NT = 2 MI = 2
-// kept 65 registers in scratch memory (now 2; FORM_PLAIN 27) and the wide kernel 15 (none; FORM_PLAIN 9).  Before -> after:
+// kept 65 registers in scratch memory (now 2) and the wide kernel 15 (none; FORM_PLAIN 7).  Before -> after:
 // a CG iteration, d = 11, t = 65, n = 16384 201 -> 161 us, n = 65536 2428 -> 2105 us; a block update of alternating
 // projections, n = 16384 d = 5 t = 65, block 2000, 97 -> 71 us.
 enum {
@@ -101,6 +101,40 @@ __device__ __forceinline__ void store_column_quads(float* dst, bool ok, bool fir
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[4 * g + q] = 0.0f;
   }
+}
+
+// One lane's 16 accumulators of a column into a row-major output: first stores, later adds to what is there; noise adds
+// sigma^2 V.  All loads go out before the first value is used, with clamped indices instead of a branch around each, behind which they
+// were waited for one by one; the branches also kept 27 registers of the KH = 1, NT = 2, MI = 2 kernel in scratch memory (now 2).
+// gp_kmv n = 16384, d = 11, t = 65 (SE) 149 -> 139 us; d = 26 (Matern) 187 -> 186 us.
+__device__ __forceinline__ void store_row_elements(const TileArgsH& p, float* out, int64_t ibase, int h, int c, bool first, bool noise,
+                                                   float scale, f32x16& acc) {
+  const bool cok = c < p.ncols;
+  const int64_t col = p.col0 + (cok ? c : 0);
+  auto row = [&](int r) { return ibase + 8 * (r >> 2) + 4 * h + (r & 3); };
+  float v[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    v[r] = scale * acc[r];
+    acc[r] = 0.0f;
+  }
+  if (noise) {
+    float w[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) w[r] = p.V[min(row(r), p.n - 1) * p.ldv + col];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = fmaf(p.sigma2, w[r], v[r]);
+  }
+  if (!first) {
+    float w[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) w[r] = out[min(row(r), p.n - 1) * p.ldo + col];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] += w[r];
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (cok && row(r) < p.n) out[row(r) * p.ldo + col] = v[r];
 }
 
 // Two waves per SIMD with two software pipelines.  Four wavefronts per workgroup: every workgroup streams all
@@ -401,20 +435,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         continue;
       }
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int c = li + 32 * nt;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t i = ibase + 8 * (r >> 2) + 4 * h + (r & 3);
-          if (i < p.n && c < p.ncols) {
-            float v = oscale[nt] * acc[m][nt][r];
-            if (noise) v = fmaf(p.sigma2, p.V[i * p.ldv + p.col0 + c], v);
-            if (!first) v += out[i * p.ldo + p.col0 + c];
-            out[i * p.ldo + p.col0 + c] = v;
-          }
-          acc[m][nt][r] = 0.0f;
-        }
-      }
+      for (int nt = 0; nt < NT; ++nt) store_row_elements(p, out, ibase, h, li + 32 * nt, first, noise, oscale[nt], acc[m][nt]);
       if (Y) {
         const float tot = accv[m] + __shfl_xor(accv[m], 32);
         const int64_t i = ibase + li;
@@ -648,17 +669,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
     for (int nt = 0; nt < NT; ++nt) {
       const int c = li + 32 * nt;
       const float oscale = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(c, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t i = ibase + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (i < p.n && c < p.ncols) {
-          float v = oscale * acc[nt][r];
-          if (noise) v = fmaf(p.sigma2, p.V[i * p.ldv + p.col0 + c], v);
-          if (!first) v += out[i * p.ldo + p.col0 + c];
-          out[i * p.ldo + p.col0 + c] = v;
-        }
-        acc[nt][r] = 0.0f;
-      }
+      store_row_elements(p, out, ibase, h, c, first, noise, oscale, acc[nt]);
     }
     if (Y) {
       const float both = accv[0] + accv[1];
@@ -675,6 +686,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(wide_waves(
   };
 
   if (over) return;
+  // The row operands are waited for here, where the compiler sees it: it would otherwise wait for them at their first use,
+  // inside the loop, and there drain the stage in flight too, every two chunks.  With the stores above, gp_kmv
+  // n = 40000, d = 20, t = 65 (SE) 808 -> 790 us.
+  __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
   bool first = true;
   if (has_window(FORM) && r_begin >= r_end) {
     flush(true);
@@ -976,7 +991,7 @@ TileKernelH tile_kernel_h(const gp_ctx* ctx, int64_t rows, int XP, int NT, bool 
   // below 32768 rows twice the column splits, whose images cost what it gains (n = 16384: 6 us against 4).  Two
   // sub-tiles per wave halve the LDS operand traffic; past one k-step of distance operands (two with a
   // single contraction tile) the second sub-tile no longer fits the register file.  Registers kept in scratch memory
-  // with two: KH = 1 NT = 2 27 - 39 row-major, 2 - 8 column-major; KH = 2 NT = 1 none, 12 - 15 row-major on three pieces.
+  // with two: KH = 1 NT = 2 2 on two pieces, 8 on three; KH = 2 NT = 1 none.
   const bool wide = NT == 0 || (NT == 2 && KH == 2 && rows >= 32768);
   const int MI = !wide && rows >= 8192 && (KH == 1 || (KH == 2 && NT == 1)) ? 2 : 1;
   if (ctx->kernel == GP_SE_ARD) k.fn = XP == 2 ? pick_h<GP_SE_ARD, 2>(KH, NT, MI, wide, y, form) : pick_h<GP_SE_ARD, 3>(KH, NT, MI, wide, y, form);
