@@ -502,21 +502,20 @@ struct GradPlan {
 GradPlan grad_plan(int KT, int chunks, int cus) {
   GradPlan pl;
   pl.W = grad_waves(KT);
-  const int slots = cus * 8 / pl.W, row_blocks = (chunks + pl.W - 1) / pl.W;
+  const int slots = cus * 8 / pl.W, row_blocks = (chunks + pl.W - 1) / pl.W, shift = pl.W == 8 ? 3 : 2;
+  const int64_t work = (int64_t)row_blocks * chunks - (int64_t)pl.W * row_blocks * (row_blocks - 1) / 2;   // chunks of all rows
   // Rows from long to short fill two generations and more by themselves; fewer are cut into pieces, each an image to write
   // and sum.  Pieces are of about one length, so beyond one generation the time lies between what a slot has to do on the
-  // average and whole generations.
+  // average and whole generations.  The chip waits while this runs: workgroups are counted by piece, at most 64 terms, each a shift
+  // (grad_rows_with_piece); counting them by row block, a division
+  // each, took 10 us at n = 16384, t = 65 and 48 us at n = 43945, t = 17, and twice that with a second plan for the same block; now 3 us.
   constexpr double FIXED = 6.0;       // prologue and flush of a workgroup, in chunks
   double best = 1e300;
   for (int pieces = 1; pieces <= (row_blocks >= 2 * slots ? 1 : 64); ++pieces) {
     const int cps = (chunks + pieces - 1) / pieces;
     if (pieces > 1 && cps < 4) break;
-    int64_t all = 0, work = 0;
-    for (int rb = 0; rb < row_blocks; ++rb) {
-      const int len = chunks - rb * pl.W;
-      all += (len + cps - 1) / cps;
-      work += len;
-    }
+    int64_t all = 0;
+    for (int64_t left = chunks; left > 0; left -= cps) all += (left + pl.W - 1) >> shift;
     double cost = cps + FIXED;
     if (all > slots) {
       const double mean = ((double)work + FIXED * all) / slots, gens = (double)((all + slots - 1) / slots);
@@ -552,7 +551,8 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
   // blocks of PROBE_BLOCK probes, the last one with what is left
   const int first_block = s < PROBE_BLOCK ? s : PROBE_BLOCK, last_block = s > PROBE_BLOCK ? (s - 1) % PROBE_BLOCK + 1 : first_block;
   const int KTmax = 2 * grad_probe_steps(first_block);
-  const GradPlan first_plan = grad_plan(KTmax, (int)chunks, ctx->num_cu), last_plan = grad_plan(2 * grad_probe_steps(last_block), (int)chunks, ctx->num_cu);
+  const GradPlan first_plan = grad_plan(KTmax, (int)chunks, ctx->num_cu);
+  const GradPlan last_plan = last_block == first_block ? first_plan : grad_plan(2 * grad_probe_steps(last_block), (int)chunks, ctx->num_cu);
   const int JS = first_plan.pieces > last_plan.pieces ? first_plan.pieces : last_plan.pieces;
   // workgroups of the fp64 reduction: one step of 256 / (d + 2) rows each when n allows, so that
   // enough loads are in flight (the kernel is latency-bound at small n)
