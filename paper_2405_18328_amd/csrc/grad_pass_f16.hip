@@ -324,12 +324,16 @@ __global__ __launch_bounds__(64 * grad_waves(KT)) void grad_tile_f16_kernel(Grad
   }
 }
 
-// exponent e with m = f 2^e, f in [0.5, 1); dflt for m = 0
-__device__ __forceinline__ int exponent_of(float m, int dflt) {
-  if (!(m > 0.0f)) return dflt;
+// exponent e with m = f 2^e, f in [0.5, 1), for a positive finite m; of a column of zeros one that takes the other side's
+// values to zero too (they are scaled by 2^(alpha + e - C_TOP), alpha <= 113): nothing bounds them where their product is no part of the
+// bound alpha is chosen from, and an overflow to infinity would meet the zeros.  Infinities and NaN stay what they are.
+constexpr int ZERO_EXP = -400;
+__device__ __forceinline__ int exponent_of(float m) {
+  if (!(m > 0.0f)) return ZERO_EXP;
+  if (!(m < INFINITY)) return 0;
   int e;
   (void)frexpf(m, &e);
-  return e < -100 ? -100 : (e > 100 ? 100 : e);
+  return e;
 }
 
 // scales of one block of probe columns [c0, c0 + sb): scales[0] = exponent of alpha, scales[1 + m] = exponent e of
@@ -344,8 +348,8 @@ __global__ __launch_bounds__(PROBE_BLOCK) void grad_scales_kernel(const unsigned
   if (m < sb) {
     const float maxA = fabsf(probe_w) * __uint_as_float(cmV[c0 + m]);
     const float maxZ = __uint_as_float(cmB[c0 + m]);
-    scales[1 + m] = exponent_of(maxZ, C_TOP);
-    scales[1 + PROBE_BLOCK + m] = exponent_of(maxA, C_TOP);
+    scales[1 + m] = exponent_of(maxZ);
+    scales[1 + PROBE_BLOCK + m] = exponent_of(maxA);
     b = 2.0f * maxA * maxZ;
   }
   bound[m] = b;
@@ -354,8 +358,8 @@ __global__ __launch_bounds__(PROBE_BLOCK) void grad_scales_kernel(const unsigned
     const float maxY = __uint_as_float(cmV[0]);
     float ub = with_y ? 2.0f * half_w * maxY * maxY : 0.0f;
     for (int k = 0; k < sb; ++k) ub += bound[k];
-    // |u_ij| <= ub <= 2^e, so alpha = 2^(U_TOP - e) keeps alpha |u_ij| <= 2^U_TOP
-    scales[0] = (ub > 0.0f && ub < 3.0e38f) ? U_TOP - exponent_of(ub, U_TOP) : 0;
+    // |u_ij| <= ub <= 2^e, so alpha = 2^(U_TOP - e) keeps alpha |u_ij| <= 2^U_TOP; past 2^100 either way its inverse would leave fp32
+    scales[0] = (ub > 0.0f && ub < 3.0e38f) ? U_TOP - min(max(exponent_of(ub), -100), 100) : 0;
   }
 }
 

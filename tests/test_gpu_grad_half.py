@@ -17,11 +17,13 @@ from tests.gpu_util import Dev
 pytestmark = pytest.mark.gpu
 
 
-def _check(n, d, t, kind, seed):
+def _check(n, d, t, kind, seed, change=None):
     rng = np.random.default_rng(seed)
     X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
     V = rng.standard_normal((n, t)).astype(np.float32) * np.exp(rng.uniform(-3, 3, t)).astype(np.float32)
     B = rng.standard_normal((n, t)).astype(np.float32) * np.exp(rng.uniform(-3, 3, t)).astype(np.float32)
+    if change:
+        change(V, B)
     ell, a, sigma = rng.uniform(0.7, 1.3, d) * np.sqrt(d / 3.0), 1.2, 0.4
     V64, B64 = V.astype(np.float64), B.astype(np.float64)
     s = t - 1
@@ -67,3 +69,26 @@ def test_probes(t):
 def test_dimensions(d, t):
     print(f"[grad half] d={d} t={t}", flush=True)
     _check(290, d, t, "matern32", d)
+
+
+def _zero_columns(which, size):
+    def change(V, B):
+        V *= np.float32(size)
+        for k, M in (("V", V), ("B", B)):
+            if which == k:
+                M[:, 1] = 0.0
+            elif which == k + "*":
+                M[:, 1:] = 0.0
+        if which == "y":
+            V[:, 0] = 0.0
+    return change
+
+
+@pytest.mark.parametrize("which", ["V", "V*", "B", "B*", "y"])
+@pytest.mark.parametrize("size", [1e-3, 1e-12])
+@pytest.mark.parametrize("t", [3, 40, 66])
+def test_zero_columns(which, size, t):
+    """A column of zeros on one side takes no part in the bound the weights are scaled by; the other side's values, however
+    large next to the small solutions, must not overflow against it."""
+    print(f"[grad half] zero {which} size={size} t={t}", flush=True)
+    _check(256, 4, t, "matern32", t, _zero_columns(which, size))
