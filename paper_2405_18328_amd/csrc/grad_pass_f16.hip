@@ -32,7 +32,9 @@ namespace {
 
 constexpr int C_TOP = 7;                    // max |C'_c| in [2^6, 2^7)
 constexpr int U_TOP = 13;                   // alpha |u_ij| <= 2^13, so |U' psi| <= 3 2^13 < 2^15
-constexpr int PROBE_BLOCK = 64;             // probe columns per tile pass (two times 4 k-steps of 16)
+constexpr int PROBE_BLOCK = 80;             // most probe columns per tile pass (two times 5 k-steps of 16)
+constexpr int SCALE_THREADS = 128;          // of the kernel that scales them, a thread per probe
+static_assert(PROBE_BLOCK <= SCALE_THREADS, "a thread per probe");
 // A workgroup's waves, 32 rows each.  Two workgroups of four run past each other's barriers; from six k-steps of probes on a chunk's
 // operands are so many that eight waves should share them.  n = 16384, d = 26: t = 65 (8 k-steps) 254 us a gradient with four
 // waves, 239 with eight; n = 43945, d = 20, t = 17 (2 k-steps) 839 and 915.
@@ -339,10 +341,10 @@ __device__ __forceinline__ int exponent_of(float m) {
 // scales of one block of probe columns [c0, c0 + sb): scales[0] = exponent of alpha, scales[1 + m] = exponent e of
 // max |z_m| in [2^(e - 1), 2^e), scales[1 + PROBE_BLOCK + m] = the same of the weighted solutions a_m = probe_w v_m.
 // with_y: the y column's weights are in the bound too.  One workgroup, fixed-order sum.
-__global__ __launch_bounds__(PROBE_BLOCK) void grad_scales_kernel(const unsigned* __restrict__ cmV, const unsigned* __restrict__ cmB,
+__global__ __launch_bounds__(SCALE_THREADS) void grad_scales_kernel(const unsigned* __restrict__ cmV, const unsigned* __restrict__ cmB,
                                                                   int c0, int sb, int with_y, float half_w, float probe_w,
                                                                   int* __restrict__ scales) {
-  __shared__ float bound[PROBE_BLOCK];
+  __shared__ float bound[SCALE_THREADS];
   const int m = threadIdx.x;
   float b = 0.0f;
   if (m < sb) {
@@ -472,8 +474,9 @@ gradh_fn pick_kt_nt(int KT, int NT) {
     case 2: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 2, 1> : grad_tile_f16_kernel<KIND, KH, XP, 2, 2>;
     case 4: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 4, 1> : grad_tile_f16_kernel<KIND, KH, XP, 4, 2>;
     case 6: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 6, 1> : grad_tile_f16_kernel<KIND, KH, XP, 6, 2>;
+    case 8: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 8, 1> : grad_tile_f16_kernel<KIND, KH, XP, 8, 2>;
   }
-  return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 8, 1> : grad_tile_f16_kernel<KIND, KH, XP, 8, 2>;
+  return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 10, 1> : grad_tile_f16_kernel<KIND, KH, XP, 10, 2>;
 }
 
 template <int KIND, int XP>
@@ -497,6 +500,14 @@ gradh_fn pick_gradh(int kind, int KH, int XP, int KT, int NT) {
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 int grad_probe_steps(int s) { return s > 16 ? (s + 15) / 16 : 1; }
+
+// Probe columns of every block but the last: as few blocks as there can be, of about one size in whole k-steps.  A block works out
+// distances and kernel values again, so a last one of a few probes is dear: with blocks of 64, t = 80 took n = 16384, d = 26 385 us, now
+// 261; n = 43945, d = 96 11.5 ms, now 7.4; n = 2048, d = 60 137 us, now 93.
+int grad_probe_block(int s) {
+  const int blocks = s > 0 ? (s + PROBE_BLOCK - 1) / PROBE_BLOCK : 1;
+  return 16 * ((grad_probe_steps(s) + blocks - 1) / blocks);
+}
 
 // The work of one block of probes: workgroups of W waves, most chunks one of them takes, pieces of the longest rows (the first
 // ones), all workgroups.  `slots` workgroups run side by side.
@@ -552,8 +563,8 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
 
   const int64_t chunks = (n + 31) / 32;
   const int64_t chunks_pad = ctx->n_pad / 32;
-  // blocks of PROBE_BLOCK probes, the last one with what is left
-  const int first_block = s < PROBE_BLOCK ? s : PROBE_BLOCK, last_block = s > PROBE_BLOCK ? (s - 1) % PROBE_BLOCK + 1 : first_block;
+  const int block = grad_probe_block(s);
+  const int first_block = s < block ? s : block, last_block = s > block ? (s - 1) % block + 1 : first_block;
   const int KTmax = 2 * grad_probe_steps(first_block);
   const GradPlan first_plan = grad_plan(KTmax, (int)chunks, ctx->num_cu);
   const GradPlan last_plan = last_block == first_block ? first_plan : grad_plan(2 * grad_probe_steps(last_block), (int)chunks, ctx->num_cu);
@@ -626,12 +637,12 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
     a.slot_h = (k % 16) / 8;
     a.slot_e = k % 8;
   }
-  for (int c0 = 1; c0 == 1 || c0 < t; c0 += PROBE_BLOCK) {
-    const int sb = t - c0 < PROBE_BLOCK ? t - c0 : PROBE_BLOCK;       // 0 when y is the only column
+  for (int c0 = 1; c0 == 1 || c0 < t; c0 += block) {
+    const int sb = t - c0 < block ? t - c0 : block;       // 0 when y is the only column
     const int KTH = grad_probe_steps(sb), KT = 2 * KTH, with_y = c0 == 1;
     const GradPlan& pl = sb == first_block ? first_plan : last_plan;
     a.cps = pl.cps;
-    hipLaunchKernelGGL(grad_scales_kernel, dim3(1), dim3(PROBE_BLOCK), 0, st, (const unsigned*)cmV, (const unsigned*)cmB, c0, sb, with_y,
+    hipLaunchKernelGGL(grad_scales_kernel, dim3(1), dim3(SCALE_THREADS), 0, st, (const unsigned*)cmV, (const unsigned*)cmB, c0, sb, with_y,
                        half_w, probe_w, scales);
     GP_HIP(ctx, hipGetLastError());
     {

@@ -1,7 +1,7 @@
 """The gradient's tile pass over one half of the pairs, at the sizes where its rows, pieces and blocks of probes end.
 
 Rows: tiles of 32, workgroups of 4 or 8 of them (more than 32 probes: 8).  Columns: pieces of at least 4 tiles, several per row
-from n = 300 on.  Probes: 16 per step, 64 per pass, one step at least.  Bound, per component: the sum over all pairs of the
+from n = 300 on.  Probes: 16 per step, at most 80 per pass, passes of about one size, one step at least.  Bound, per component: the sum over all pairs of the
 terms' sizes times
 
     2^-22 (3 + 2 max |x|^2 + 2)   products of two split factors and G Q (three times 2^-22 at most, each piece being rounded to
@@ -59,13 +59,13 @@ def test_rows(n, t):
     _check(n, 4, t, "matern32" if n % 2 else "se", n + t)
 
 
-@pytest.mark.parametrize("t", [1, 2, 16, 17, 18, 33, 34, 49, 50, 65, 66, 81, 97, 129, 130])
+@pytest.mark.parametrize("t", [1, 2, 16, 17, 18, 33, 34, 49, 50, 65, 66, 80, 81, 82, 97, 98, 129, 130, 161, 162])
 def test_probes(t):
     print(f"[grad half] t={t}", flush=True)
     _check(413, 5, t, "se" if t % 2 else "matern32", t)
 
 
-@pytest.mark.parametrize("d,t", [(13, 20), (14, 70), (15, 40), (31, 20), (32, 70), (46, 33), (63, 65), (96, 66), (125, 65)])
+@pytest.mark.parametrize("d,t", [(13, 20), (14, 70), (15, 40), (31, 20), (32, 70), (46, 33), (63, 65), (96, 66), (125, 65), (13, 81), (46, 66), (96, 81), (125, 82)])
 def test_dimensions(d, t):
     print(f"[grad half] d={d} t={t}", flush=True)
     _check(290, d, t, "matern32", d)

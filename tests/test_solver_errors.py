@@ -20,11 +20,12 @@ RUNTIME = r"""
 #include <cstdlib>
 #include <cstring>
 static char* pinned;
-static int queued, until_failure, wide;
+static int queued, launched, until_failure, wide;
 static unsigned steps;
 static hipError_t fallible() { return until_failure > 0 && --until_failure == 0 ? hipErrorUnknown : hipSuccess; }
 extern "C" {
 int fake_queued() { return queued; }
+int fake_launched() { const int n = launched; launched = 0; return n; }      // since the last time it was asked
 int fake_wide() { return wide; }      // most workgroups of a launch with 1024 threads each
 int fake_fail(int k) { const int left = until_failure; until_failure = k; steps = 0; queued = 0; return left; }
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -38,6 +39,7 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* m, hipStream_t* s
 }
 hipError_t hipLaunchKernel(const void*, dim3 g, dim3 b, void**, size_t, hipStream_t) {
   ++queued;
+  ++launched;
   if (b.x == 1024 && (int)(g.x * g.y) > wide) wide = g.x * g.y;
   return hipSuccess;
 }
