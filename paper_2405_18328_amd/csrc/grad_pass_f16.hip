@@ -36,9 +36,15 @@ constexpr int PROBE_BLOCK = 80;             // most probe columns per tile pass 
 constexpr int SCALE_THREADS = 128;          // of the kernel that scales them, a thread per probe
 static_assert(PROBE_BLOCK <= SCALE_THREADS, "a thread per probe");
 // A workgroup's waves, 32 rows each.  Two workgroups of four run past each other's barriers; from six k-steps of probes on a chunk's
-// operands are so many that eight waves should share them.  n = 16384, d = 26: t = 65 (8 k-steps) 254 us a gradient with four
-// waves, 239 with eight; n = 43945, d = 20, t = 17 (2 k-steps) 839 and 915.
-constexpr int grad_waves(int KT) { return KT >= 6 ? 8 : 4; }
+// operands are so many that eight waves should share them.  n = 16384, d = 26: t = 65 (8 k-steps) 250 us a gradient with four
+// waves, 234 with eight; n = 43945, d = 20, t = 17 (2 k-steps) 839 and 915.  Not while there are too few rows for that: up to about
+// five workgroups of four waves to four compute units a gradient is the time of its chains, and those are shorter in a kernel that
+// may have 512 registers to a wave: of the eight-wave kernels with many distance operands, 37 of 144 keep some in scratch memory
+// (4 XP KH + 8 KT + 16 NT above 140).  Four and eight waves, t = 65: n = 2048, d = 60 86 and 90 us, d = 96 124 and 144,
+// with three pieces 135 and 186; n = 3500, d = 60 115 and 100, d = 96 191 and 170; n = 43945, d = 96 8.1 and 6.6 ms.
+int grad_waves(int KT, int64_t chunks, int cus) {
+  return KT >= 6 && chunks * (chunks + 4) / 32 > cus + cus / 4 ? 8 : 4;      // workgroups of four waves and four chunks
+}
 
 struct GradArgsH {
   const u32x4* XA[3];     // column-side distance pieces [(chunk*KH + kh)*64 + lane]
@@ -70,9 +76,8 @@ __host__ __device__ inline int grad_rows_with_piece(int js, int nchunks, int cps
 // A workgroup takes piece js of the columns of row block rb, from the row block's first chunk on.  Only pieces that are there
 // have a workgroup: with the others returning at once, as many pieces as compute units did not run side by side, the hardware
 // dealing workgroups to the eight dies in turn (n = 16384, d = 26, t = 65: compute units busy 46 % of the launch).
-template <int KIND, int KH, int XP, int KT, int NT>
-__global__ __launch_bounds__(64 * grad_waves(KT)) void grad_tile_f16_kernel(GradArgsH p) {
-  constexpr int W = grad_waves(KT);
+template <int KIND, int KH, int XP, int KT, int NT, int W>
+__global__ __launch_bounds__(64 * W) void grad_tile_f16_kernel(GradArgsH p) {
   constexpr int XA_G = XP * KH;          // groups of 64 16-byte units per stage
   constexpr int C_G = 2 * KT;
   constexpr int Q_G = 4 * NT;
@@ -468,33 +473,42 @@ __global__ __launch_bounds__(256) void grad_pack_q_f16_kernel(const float* __res
 
 typedef void (*gradh_fn)(GradArgsH);
 
-template <int KIND, int KH, int XP>
-gradh_fn pick_kt_nt(int KT, int NT) {
-  switch (KT) {
-    case 2: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 2, 1> : grad_tile_f16_kernel<KIND, KH, XP, 2, 2>;
-    case 4: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 4, 1> : grad_tile_f16_kernel<KIND, KH, XP, 4, 2>;
-    case 6: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 6, 1> : grad_tile_f16_kernel<KIND, KH, XP, 6, 2>;
-    case 8: return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 8, 1> : grad_tile_f16_kernel<KIND, KH, XP, 8, 2>;
+template <int KIND, int KH, int XP, int KT>
+gradh_fn pick_nt_w(int NT, int W) {
+  if constexpr (KT >= 6) {
+    if (W == 8) return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, KT, 1, 8> : grad_tile_f16_kernel<KIND, KH, XP, KT, 2, 8>;
   }
-  return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, 10, 1> : grad_tile_f16_kernel<KIND, KH, XP, 10, 2>;
+  return NT == 1 ? grad_tile_f16_kernel<KIND, KH, XP, KT, 1, 4> : grad_tile_f16_kernel<KIND, KH, XP, KT, 2, 4>;
 }
 
-template <int KIND, int XP>
-gradh_fn pick_kh(int KH, int KT, int NT) {
-  switch (KH) {
-    case 1: return pick_kt_nt<KIND, 1, XP>(KT, NT);
-    case 2: return pick_kt_nt<KIND, 2, XP>(KT, NT);
-    case 3: return pick_kt_nt<KIND, 3, XP>(KT, NT);
-    case 4: return pick_kt_nt<KIND, 4, XP>(KT, NT);
-    case 6: return pick_kt_nt<KIND, 6, XP>(KT, NT);
-    case 8: return pick_kt_nt<KIND, 8, XP>(KT, NT);
+template <int KIND, int KH, int XP>
+gradh_fn pick_kt(int KT, int NT, int W) {
+  switch (KT) {
+    case 2: return pick_nt_w<KIND, KH, XP, 2>(NT, W);
+    case 4: return pick_nt_w<KIND, KH, XP, 4>(NT, W);
+    case 6: return pick_nt_w<KIND, KH, XP, 6>(NT, W);
+    case 8: return pick_nt_w<KIND, KH, XP, 8>(NT, W);
+    case 10: return pick_nt_w<KIND, KH, XP, 10>(NT, W);
   }
   return nullptr;
 }
 
-gradh_fn pick_gradh(int kind, int KH, int XP, int KT, int NT) {
-  if (kind == GP_SE_ARD) return XP == 2 ? pick_kh<GP_SE_ARD, 2>(KH, KT, NT) : pick_kh<GP_SE_ARD, 3>(KH, KT, NT);
-  return XP == 2 ? pick_kh<GP_MATERN32_ARD, 2>(KH, KT, NT) : pick_kh<GP_MATERN32_ARD, 3>(KH, KT, NT);
+template <int KIND, int XP>
+gradh_fn pick_kh(int KH, int KT, int NT, int W) {
+  switch (KH) {
+    case 1: return pick_kt<KIND, 1, XP>(KT, NT, W);
+    case 2: return pick_kt<KIND, 2, XP>(KT, NT, W);
+    case 3: return pick_kt<KIND, 3, XP>(KT, NT, W);
+    case 4: return pick_kt<KIND, 4, XP>(KT, NT, W);
+    case 6: return pick_kt<KIND, 6, XP>(KT, NT, W);
+    case 8: return pick_kt<KIND, 8, XP>(KT, NT, W);
+  }
+  return nullptr;
+}
+
+gradh_fn pick_gradh(int kind, int KH, int XP, int KT, int NT, int W) {
+  if (kind == GP_SE_ARD) return XP == 2 ? pick_kh<GP_SE_ARD, 2>(KH, KT, NT, W) : pick_kh<GP_SE_ARD, 3>(KH, KT, NT, W);
+  return XP == 2 ? pick_kh<GP_MATERN32_ARD, 2>(KH, KT, NT, W) : pick_kh<GP_MATERN32_ARD, 3>(KH, KT, NT, W);
 }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -516,7 +530,7 @@ struct GradPlan {
 };
 GradPlan grad_plan(int KT, int chunks, int cus) {
   GradPlan pl;
-  pl.W = grad_waves(KT);
+  pl.W = grad_waves(KT, chunks, cus);
   const int slots = cus * 8 / pl.W, row_blocks = (chunks + pl.W - 1) / pl.W, shift = pl.W == 8 ? 3 : 2;
   const int64_t work = (int64_t)row_blocks * chunks - (int64_t)pl.W * row_blocks * (row_blocks - 1) / 2;   // chunks of all rows
   // Rows from long to short fill two generations and more by themselves; fewer are cut into pieces, each an image to write
@@ -665,7 +679,7 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
                            (const float*)ctx->dXs, n, d, (int)chunks, NT, a.col0, a.ncols, qshift, QP);
         GP_HIP(ctx, hipGetLastError());
       }
-      gradh_fn fn = pick_gradh(ctx->kernel, ctx->KH, ctx->XP, KT, NT);
+      gradh_fn fn = pick_gradh(ctx->kernel, ctx->KH, ctx->XP, KT, NT, pl.W);
       if (!fn) return gp_fail(ctx, GP_ERR_ARG, "gp_mll_grad: no fp16 kernel for KH=%d", ctx->KH);
       const bool pr = gp_prof_begin(ctx, GP_PROF_GRAD_TILE);
       hipLaunchKernelGGL(fn, dim3(pl.workgroups), dim3(64 * pl.W), 0, st, a);

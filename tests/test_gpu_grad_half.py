@@ -1,6 +1,6 @@
 """The gradient's tile pass over one half of the pairs, at the sizes where its rows, pieces and blocks of probes end.
 
-Rows: tiles of 32, workgroups of 4 or 8 of them (more than 32 probes: 8).  Columns: pieces of at least 4 tiles, several per row
+Rows: tiles of 32, workgroups of 4 or 8 of them (8 with more than 32 probes and from n = 3169 on).  Columns: pieces of at least 4 tiles, several per row
 from n = 300 on.  Probes: 16 per step, at most 80 per pass, passes of about one size, one step at least.  Bound, per component: the sum over all pairs of the
 terms' sizes times
 
@@ -92,3 +92,49 @@ def test_zero_columns(which, size, t):
     large next to the small solutions, must not overflow against it."""
     print(f"[grad half] zero {which} size={size} t={t}", flush=True)
     _check(256, 4, t, "matern32", t, _zero_columns(which, size))
+
+
+def _check_rows(n, d, t, kind, seed):
+    """As _check, at sizes where a dense n x n oracle takes too long: V is zero outside 96 rows, which leaves their terms only."""
+    rng = np.random.default_rng(seed)
+    X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
+    R = np.unique(np.concatenate([rng.choice(n, 88, replace=False), [0, 31, 32, 127, 128, 255, 256, n - 2, n - 1]]))
+    V = np.zeros((n, t), dtype=np.float32)
+    V[R] = rng.standard_normal((R.size, t))
+    B = rng.standard_normal((n, t)).astype(np.float32) * np.exp(rng.uniform(-3, 3, t)).astype(np.float32)
+    ell, a, sigma = rng.uniform(0.7, 1.3, d) * np.sqrt(d / 3.0), 1.2, 0.4
+    dv = Dev(X, kind, ell, a, sigma)
+    try:
+        got = np.array(dv.grad(dv.to(V), dv.to(B)))
+        assert (got == np.array(dv.grad(dv.to(V), dv.to(B)))).all()
+    finally:
+        dv.close()
+    ref = orc.mll_grad_hutchinson_rows(X, ell, a, sigma, kind, B, V, rows=R, row_block=32, workers=8)
+    A, C = V[R].astype(np.float64), B.astype(np.float64)
+    A[:, 0] *= 0.5
+    C[:, 0] = V[:, 0]
+    A[:, 1:] *= -0.5 / (t - 1)
+    W = np.abs(A) @ np.abs(C).T
+    xs = (X.astype(np.float64) - X.astype(np.float64).mean(0)) / ell
+    unit = 2.0 ** -22 * (5.0 + 2.0 * (xs ** 2).sum(1).max())
+    r2 = orc.scaled_sqdist(X[R], X, ell)
+    psi = np.exp(-0.5 * r2) if kind == "se" else 3.0 * np.exp(-np.sqrt(3.0 * r2))
+    size = a * a / ell * 2.0 * (((W * psi).sum(1)[:, None] * xs[R] ** 2).sum(0) + ((W * psi).sum(0)[:, None] * xs ** 2).sum(0))
+    size = np.append(size, [(W * 2.0 * orc.kernel_from_sqdist(r2, a, kind) / a).sum(), 2.0 * sigma * W[np.arange(R.size), R].sum()])
+    bad = np.abs(got - ref) > unit * size
+    assert not bad.any(), (got[bad], ref[bad], (unit * size)[bad])
+
+
+@pytest.mark.parametrize("n,d,t", [(3168, 5, 66), (3169, 5, 66), (3169, 26, 34), (3329, 13, 65), (3361, 14, 81), (3457, 31, 66), (3500, 46, 65),
+                                   (3200, 62, 81), (3169, 96, 65), (3329, 96, 66), (3329, 125, 81), (3329, 60, 98)])
+def test_eight_waves(n, d, t):
+    print(f"[grad half] n={n} d={d} t={t}", flush=True)
+    _check_rows(n, d, t, "matern32" if n % 2 else "se", n + d)
+
+
+@pytest.mark.parametrize("n,d,t", [(290, 5, 18), (290, 31, 50), (300, 46, 65), (290, 62, 66), (290, 96, 34), (310, 96, 81), (290, 125, 65),
+                                   (3169, 31, 50), (3329, 46, 66), (3200, 62, 65), (3329, 96, 34), (3169, 96, 66), (3329, 125, 81)])
+def test_three_pieces(monkeypatch, n, d, t):
+    monkeypatch.setenv("GPWS_PATH", "f16x3")
+    print(f"[grad half] three pieces n={n} d={d} t={t}", flush=True)
+    _check_rows(n, d, t, "matern32" if n % 2 else "se", n + d)
