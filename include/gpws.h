@@ -218,6 +218,9 @@ int gp_sgd_solve(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, fl
  *   t = s + 1 >= 1 (s = 0 leaves only the quadratic term).
  *   h_grad: out, d + 2 doubles: dL/d ell_1..ell_d, dL/da, dL/dsigma, with
  *   respect to the constrained parameters (a softplus chain rule is the caller's).
+ * Scratch of the context: 260 bytes per row and 256 more for every 16 probes (of 80 at most), and 4 (2 d + 2) bytes
+ * per row of partial sums, max(n, 2^19) of them at most.  Where the device does not have that, operands of 32 probes
+ * and max(n, 2^17) rows of partial sums do from then on, at the price of time.
  * Synchronises the stream.
  */
 int gp_mll_grad(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,

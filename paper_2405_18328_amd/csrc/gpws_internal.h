@@ -84,6 +84,7 @@ struct gp_ctx {
   // lazily grown scratch for split-column partial sums of gp_kmv / gp_mll_grad
   void* dScratch;
   size_t scratch_bytes;
+  bool grad_tight;        // the scratch of gp_mll_grad did not fit once: it makes do with less
   void* static_scratch;   // this device's address of the file-scope scratch gp_kmv_static uses (never freed)
   // small device + pinned host blocks for scalars
   double* dRed;           // reduction partials
@@ -284,13 +285,18 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
 // ---- grad_pass.hip
 int gp_grad_run(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,
                 double* h_grad);
-// fp64 reduction of one right-hand-side block's tile-pass output OUT[JS][n][nq] into acc[d + 2]
-// (part: G x (d + 2) workgroup partials); first_block adds the sigma component sum_i w_ii.  tri_rows > 0: only the tiles on
-// and above the diagonal were worked on, the columns of a row block of that many rows in pieces of at most tri_cps chunks,
-// one image of OUT each
-int gp_grad_reduce_launch(gp_ctx* ctx, const float* OUT, int64_t split_stride, int JS, int nq, const float* dV,
+// Row blocks of W chunks (the first ones) whose columns, from the block's own first chunk on, have more than js pieces of cps
+// chunks: row block rb has nchunks - rb W chunks.  W is 4 or 8.
+__host__ __device__ inline int gp_grad_rows_with_piece(int js, int nchunks, int cps, int W) {
+  return (nchunks - js * cps + W - 1) >> (W == 8 ? 3 : 2);
+}
+// fp64 reduction of one right-hand-side block's tile-pass output OUT into acc[d + 2] (part: G x (d + 2) workgroup
+// partials); first_block adds the sigma component sum_i w_ii.  tri_W = 0: OUT[JS][n][nq].  Else only the tiles on and
+// above the diagonal were worked on, the columns of a row block of tri_W chunks in pieces of at most tri_cps chunks, and
+// image k of OUT has the rows of the row blocks with that piece alone
+int gp_grad_reduce_launch(gp_ctx* ctx, const float* OUT, int JS, int nq, const float* dV,
                           int64_t ldv, const float* dB, int64_t ldb, int t, float half_w, float probe_w,
-                          int first_block, double* part, int G, double* acc, int tri_rows = 0, int tri_cps = 0);
+                          int first_block, double* part, int G, double* acc, int tri_W = 0, int tri_cps = 0);
 
 // ---- grad_pass_f16.hip
 int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int64_t ldb, int t,

@@ -229,13 +229,13 @@ __global__ void grad_pack_ac_kernel(const float* __restrict__ V, int64_t ldv, co
 }
 
 // per-workgroup fp64 partial sums of the d + 2 gradient components
-__global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ OUT, int64_t split_stride,
+__global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restrict__ OUT,
                                                           int JS, int64_t ldo, const float* __restrict__ Xs,
                                                           int64_t n, int d, const float* __restrict__ V,
                                                           int64_t ldv, const float* __restrict__ B, int64_t ldb,
                                                           int t, float half_w, float probe_w, int first_block,
                                                           double* __restrict__ part /* [grid][d+2] */,
-                                                          int tri_rows, int tri_cps, int chunks) {
+                                                          int tri_W, int tri_cps, int chunks) {
   extern __shared__ double sh[];   // [256]
   const int nq = 2 * d + 2;
   // thread <-> (row, component): consecutive threads take consecutive components of a row;
@@ -250,23 +250,29 @@ __global__ __launch_bounds__(256) void grad_reduce_kernel(const float* __restric
     double s = 0.0;
     if (rsub < rows_per_step) {
       for (int64_t i = (int64_t)blockIdx.x * rows_per_step + rsub; i < n; i += (int64_t)gridDim.x * rows_per_step) {
-        if (tri_rows) {
-          const int len = chunks - (int)(i / tri_rows) * (tri_rows / 32);
+        if (tri_W) {
+          const int len = chunks - (int)(i / (32 * tri_W)) * tri_W;
           JS = (len + tri_cps - 1) / tri_cps;
         }
+        int64_t at = i;      // where row i lies in image k
+        auto next = [&](int k) { at += tri_W ? (int64_t)gp_grad_rows_with_piece(k, chunks, tri_cps, tri_W) * 32 * tri_W : n; };
         if (comp < d) {
           float y = 0.f, t2 = 0.f, t1 = 0.f;
 #pragma unroll 4
           for (int k = 0; k < JS; ++k) {
-            const float* o = OUT + (int64_t)k * split_stride + i * ldo;
+            const float* o = OUT + at * ldo;
             y += o[comp]; t2 += o[d + comp]; t1 += o[2 * d];
+            next(k);
           }
           const double x = (double)Xs[i * d + comp];
           s += x * x * (double)t1 + (double)t2 - 2.0 * x * (double)y;
         } else {
           float ga = 0.f;
 #pragma unroll 4
-          for (int k = 0; k < JS; ++k) ga += OUT[(int64_t)k * split_stride + i * ldo + nq - 1];
+          for (int k = 0; k < JS; ++k) {
+            ga += OUT[at * ldo + nq - 1];
+            next(k);
+          }
           s += (double)ga;
         }
       }
@@ -354,13 +360,13 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
 
-int gp_grad_reduce_launch(gp_ctx* ctx, const float* OUT, int64_t split_stride, int JS, int nq, const float* dV,
+int gp_grad_reduce_launch(gp_ctx* ctx, const float* OUT, int JS, int nq, const float* dV,
                           int64_t ldv, const float* dB, int64_t ldb, int t, float half_w, float probe_w,
-                          int first_block, double* part, int G, double* acc, int tri_rows, int tri_cps) {
+                          int first_block, double* part, int G, double* acc, int tri_W, int tri_cps) {
   const int d = ctx->d;
-  hipLaunchKernelGGL(grad_reduce_kernel, dim3(G), dim3(256), 256 * sizeof(double), ctx->stream, OUT, split_stride, JS,
+  hipLaunchKernelGGL(grad_reduce_kernel, dim3(G), dim3(256), 256 * sizeof(double), ctx->stream, OUT, JS,
                      (int64_t)nq, (const float*)ctx->dXs, ctx->n, d, dV, ldv, dB, ldb, t, half_w, probe_w, first_block,
-                     part, tri_rows, tri_cps, (int)((ctx->n + 31) / 32));
+                     part, tri_W, tri_cps, (int)((ctx->n + 31) / 32));
   hipLaunchKernelGGL(grad_finalize_kernel, dim3(d + 2), dim3(256), 0, ctx->stream, (const double*)part, G, d + 2, acc);
   GP_HIP(ctx, hipGetLastError());
   return GP_OK;
@@ -470,7 +476,7 @@ int gp_grad_run(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, int6
       GP_HIP(ctx, hipGetLastError());
       c += a.ncols;
     }
-    rc = gp_grad_reduce_launch(ctx, OUT, a.split_stride, JS, nq, dV, ldv, dB, ldb, t, half_w, probe_w, t0 == 0 ? 1 : 0,
+    rc = gp_grad_reduce_launch(ctx, OUT, JS, nq, dV, ldv, dB, ldb, t, half_w, probe_w, t0 == 0 ? 1 : 0,
                                part, G, acc);
     if (rc < 0) return rc;
   }

@@ -35,6 +35,12 @@ constexpr int U_TOP = 13;                   // alpha |u_ij| <= 2^13, so |U' psi|
 constexpr int PROBE_BLOCK = 80;             // most probe columns per tile pass (two times 5 k-steps of 16)
 constexpr int SCALE_THREADS = 128;          // of the kernel that scales them, a thread per probe
 static_assert(PROBE_BLOCK <= SCALE_THREADS, "a thread per probe");
+// Rows of all images together, where they are more than one: 407 MB at d = 96.  Every row in pieces, n = 100000 would take 850000.
+// With half as many n = 43945 .. 125000 takes up to 10 % longer (d = 96, t = 65, n = 100000 33.6 -> 36.9 ms), with these 3 % at most.
+constexpr int64_t IMAGE_ROWS = 1 << 19;
+// the same, and probes per pass, of a context whose device did not have the memory
+constexpr int64_t IMAGE_ROWS_TIGHT = 1 << 17;
+constexpr int PROBE_BLOCK_TIGHT = 32;
 // A workgroup's waves, 32 rows each.  Two workgroups of four run past each other's barriers; from six k-steps of probes on a chunk's
 // operands are so many that eight waves should share them.  n = 16384, d = 26: t = 65 (8 k-steps) 250 us a gradient with four
 // waves, 234 with eight; n = 43945, d = 20, t = 17 (2 k-steps) 839 and 915.  Not while there are too few rows for that: up to about
@@ -54,9 +60,8 @@ struct GradArgsH {
   const u32x4* QP;        // Q' images of this column pass: [(((chunk*2 + mh)*NT + nt)*2 + part)*64 + lane]
   const float* VY;        // the y column, zero from n up to the end of its chunk; all zero in later blocks of probes
   const int* scales;      // [0] = exponent of alpha
-  float* OUT;             // [pieces of a row][n][ldo]
+  float* OUT;             // [workgroup][32 W][ldo]: an image per piece of a row, of the rows that have the piece
   int64_t ldo;
-  int64_t split_stride;
   int64_t n;
   int nchunks;
   int col0, ncols;        // Q columns of this pass
@@ -67,11 +72,6 @@ struct GradArgsH {
 };
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
-
-// row blocks (the first ones) whose columns have more than js pieces: row block rb has nchunks - rb W chunks
-__host__ __device__ inline int grad_rows_with_piece(int js, int nchunks, int cps, int W) {
-  return (nchunks - js * cps + W - 1) / W;
-}
 
 // A workgroup takes piece js of the columns of row block rb, from the row block's first chunk on.  Only pieces that are there
 // have a workgroup: with the others returning at once, as many pieces as compute units did not run side by side, the hardware
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(64 * W) void grad_tile_f16_kernel(GradArgsH p) {
   const int h = lane >> 5;
   const int li = lane & 31;
   int js = 0, rb = blockIdx.x;
-  for (int rows; rb >= (rows = grad_rows_with_piece(js, p.nchunks, p.cps, W)); ++js) rb -= rows;
+  for (int rows; rb >= (rows = gp_grad_rows_with_piece(js, p.nchunks, p.cps, W)); ++js) rb -= rows;
   const int sub0 = rb * W + wave;
   // The workgroup's column range [r_begin, r_end) is walked in segments [c_begin, c_end) of at most
   // GP_FLUSH_CHUNKS chunks; the accumulators are added into OUT after each segment (see flush below).
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * W) void grad_tile_f16_kernel(GradArgsH p) {
   const float oscale = row_sign * (KIND == GP_SE_ARD ? 1.0f : 3.0f) * ldexpf(1.0f, -alpha_exp - p.qshift);   // psi = 3 exp(-u) for Matern: the 3 is applied here
   const float vscale = row_sign * ldexpf(1.0f, -alpha_exp);
   const float yi = row_sign * ldexpf(sub0 < p.nchunks ? p.VY[(int64_t)sub0 * 32 + li] : 0.0f, alpha_exp);
-  float* out = p.OUT + (int64_t)js * p.split_stride;
+  float* out = p.OUT + (int64_t)(blockIdx.x - rb) * (32 * W) * p.ldo;      // this piece's image
   auto flush = [&](bool first) {
     // an opaque zero keeps the address arithmetic of the flush inside it: hoisted out of the segment
     // loop it would hold dozens of registers across the main loop
@@ -518,8 +518,8 @@ int grad_probe_steps(int s) { return s > 16 ? (s + 15) / 16 : 1; }
 // Probe columns of every block but the last: as few blocks as there can be, of about one size in whole k-steps.  A block works out
 // distances and kernel values again, so a last one of a few probes is dear: with blocks of 64, t = 80 took n = 16384, d = 26 385 us, now
 // 261; n = 43945, d = 96 11.5 ms, now 7.4; n = 2048, d = 60 137 us, now 93.
-int grad_probe_block(int s) {
-  const int blocks = s > 0 ? (s + PROBE_BLOCK - 1) / PROBE_BLOCK : 1;
+int grad_probe_block(int s, int most) {
+  const int blocks = s > 0 ? (s + most - 1) / most : 1;
   return 16 * ((grad_probe_steps(s) + blocks - 1) / blocks);
 }
 
@@ -527,16 +527,17 @@ int grad_probe_block(int s) {
 // ones), all workgroups.  `slots` workgroups run side by side.
 struct GradPlan {
   int W, cps, pieces, workgroups;
+  int64_t image_rows() const { return (int64_t)workgroups * 32 * W; }
 };
-GradPlan grad_plan(int KT, int chunks, int cus) {
+GradPlan grad_plan(int KT, int chunks, int cus, int64_t max_rows) {
   GradPlan pl;
   pl.W = grad_waves(KT, chunks, cus);
-  const int slots = cus * 8 / pl.W, row_blocks = (chunks + pl.W - 1) / pl.W, shift = pl.W == 8 ? 3 : 2;
+  const int slots = cus * 8 / pl.W, row_blocks = (chunks + pl.W - 1) / pl.W;
   const int64_t work = (int64_t)row_blocks * chunks - (int64_t)pl.W * row_blocks * (row_blocks - 1) / 2;   // chunks of all rows
   // Rows from long to short fill two generations and more by themselves; fewer are cut into pieces, each an image to write
   // and sum.  Pieces are of about one length, so beyond one generation the time lies between what a slot has to do on the
   // average and whole generations.  The chip waits while this runs: workgroups are counted by piece, at most 64 terms, each a shift
-  // (grad_rows_with_piece); counting them by row block, a division
+  // (gp_grad_rows_with_piece); counting them by row block, a division
   // each, took 10 us at n = 16384, t = 65 and 48 us at n = 43945, t = 17, and twice that with a second plan for the same block; now 3 us.
   constexpr double FIXED = 6.0;       // prologue and flush of a workgroup, in chunks
   double best = 1e300;
@@ -544,7 +545,8 @@ GradPlan grad_plan(int KT, int chunks, int cus) {
     const int cps = (chunks + pieces - 1) / pieces;
     if (pieces > 1 && cps < 4) break;
     int64_t all = 0;
-    for (int64_t left = chunks; left > 0; left -= cps) all += (left + pl.W - 1) >> shift;
+    for (int js = 0; (int64_t)js * cps < chunks; ++js) all += gp_grad_rows_with_piece(js, chunks, cps, pl.W);
+    if (pieces > 1 && all * 32 * pl.W > max_rows) break;
     double cost = cps + FIXED;
     if (all > slots) {
       const double mean = ((double)work + FIXED * all) / slots, gens = (double)((all + slots - 1) / slots);
@@ -559,7 +561,7 @@ GradPlan grad_plan(int KT, int chunks, int cus) {
   }
   pl.pieces = (chunks + pl.cps - 1) / pl.cps;
   pl.workgroups = 0;
-  for (int js = 0; js < pl.pieces; ++js) pl.workgroups += grad_rows_with_piece(js, chunks, pl.cps, pl.W);
+  for (int js = 0; js < pl.pieces; ++js) pl.workgroups += gp_grad_rows_with_piece(js, chunks, pl.cps, pl.W);
   return pl;
 }
 
@@ -577,12 +579,6 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
 
   const int64_t chunks = (n + 31) / 32;
   const int64_t chunks_pad = ctx->n_pad / 32;
-  const int block = grad_probe_block(s);
-  const int first_block = s < block ? s : block, last_block = s > block ? (s - 1) % block + 1 : first_block;
-  const int KTmax = 2 * grad_probe_steps(first_block);
-  const GradPlan first_plan = grad_plan(KTmax, (int)chunks, ctx->num_cu);
-  const GradPlan last_plan = last_block == first_block ? first_plan : grad_plan(2 * grad_probe_steps(last_block), (int)chunks, ctx->num_cu);
-  const int JS = first_plan.pieces > last_plan.pieces ? first_plan.pieces : last_plan.pieces;
   // workgroups of the fp64 reduction: one step of 256 / (d + 2) rows each when n allows, so that
   // enough loads are in flight (the kernel is latency-bound at small n)
   int G;
@@ -592,16 +588,34 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
     G = (int)(want < 8 * ctx->num_cu ? want : 8 * ctx->num_cu);
     if (G < 1) G = 1;
   }
-  const size_t op_bytes = align_up((size_t)chunks_pad * 2 * KTmax * 64 * 16, 256);
   const size_t q_bytes = align_up((size_t)chunks * 2 * 2 * 2 * 64 * 16, 256);
-  const size_t out_bytes = align_up((size_t)JS * n * nq * sizeof(float), 256);
   const size_t part_bytes = align_up((size_t)G * (d + 2) * sizeof(double), 256);
   const size_t acc_bytes = align_up((size_t)(d + 2) * sizeof(double), 256);
   const size_t cm_bytes = align_up((size_t)t * sizeof(unsigned), 256);
   const size_t sc_bytes = align_up((size_t)(1 + 2 * PROBE_BLOCK) * sizeof(int), 256);
   const size_t vy_bytes = align_up((size_t)chunks_pad * 32 * sizeof(float), 256);
-  int rc = gp_ensure_scratch(ctx, 2 * op_bytes + q_bytes + out_bytes + part_bytes + acc_bytes + 2 * cm_bytes + sc_bytes + vy_bytes);
-  if (rc < 0) return rc;
+  // Where the device does not have the memory, operands of fewer probes and fewer images do, from then on: a call's result does
+  // not depend on what else is allocated while it runs.
+  int block, first_block, rc;
+  GradPlan first_plan, last_plan;
+  size_t op_bytes, out_bytes;
+  for (;;) {
+    block = grad_probe_block(s, ctx->grad_tight ? PROBE_BLOCK_TIGHT : PROBE_BLOCK);
+    first_block = s < block ? s : block;
+    const int last_block = s > block ? (s - 1) % block + 1 : first_block;
+    const int KTmax = 2 * grad_probe_steps(first_block);
+    const int64_t max_rows = ctx->grad_tight ? IMAGE_ROWS_TIGHT : IMAGE_ROWS;
+    first_plan = grad_plan(KTmax, (int)chunks, ctx->num_cu, max_rows);
+    last_plan = last_block == first_block ? first_plan : grad_plan(2 * grad_probe_steps(last_block), (int)chunks, ctx->num_cu, max_rows);
+    const int64_t rows = first_plan.image_rows() > last_plan.image_rows() ? first_plan.image_rows() : last_plan.image_rows();
+    op_bytes = align_up((size_t)chunks_pad * 2 * KTmax * 64 * 16, 256);
+    out_bytes = align_up((size_t)rows * nq * sizeof(float), 256);
+    rc = gp_ensure_scratch(ctx, 2 * op_bytes + q_bytes + out_bytes + part_bytes + acc_bytes + 2 * cm_bytes + sc_bytes + vy_bytes);
+    if (rc >= 0) break;
+    if (ctx->grad_tight) return rc;
+    (void)hipGetLastError();      // of the failed allocation
+    ctx->grad_tight = true;
+  }
   char* w = (char*)ctx->dScratch;
   u32x4* CA = (u32x4*)w; w += op_bytes;
   u32x4* AB = (u32x4*)w; w += op_bytes;
@@ -640,7 +654,6 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
   a.scales = scales;
   a.OUT = OUT;
   a.ldo = nq;
-  a.split_stride = n * (int64_t)nq;
   a.n = n;
   a.nchunks = (int)chunks;
   a.qshift = qshift;
@@ -687,8 +700,8 @@ int gp_grad_run_f16(gp_ctx* ctx, const float* dV, int64_t ldv, const float* dB, 
       GP_HIP(ctx, hipGetLastError());
       c += a.ncols;
     }
-    rc = gp_grad_reduce_launch(ctx, OUT, a.split_stride, pl.pieces, nq, dV, ldv, dB, ldb, t, half_w, probe_w, with_y, part, G, acc,
-                               32 * pl.W, pl.cps);
+    rc = gp_grad_reduce_launch(ctx, OUT, pl.pieces, nq, dV, ldv, dB, ldb, t, half_w, probe_w, with_y, part, G, acc,
+                               pl.W, pl.cps);
     if (rc < 0) return rc;
   }
 

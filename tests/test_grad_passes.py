@@ -1,7 +1,8 @@
-"""Tile passes of a gradient over its probes, counted on the stand-in for the HIP runtime: as few as blocks of 80 allow.
+"""Tile passes and scratch of a gradient, counted on the stand-in for the HIP runtime.
 
-A pass works out distances and kernel values of all pairs again.  With 65 to 79 probes the time of a second pass, over no more
-than 16 of them, was up to that of the first."""
+Over the probes as few passes as blocks of 80 allow: a pass works out distances and kernel values of all pairs again, and with 65 to 79
+probes the time of a second one, over no more than 16 of them, was up to that of the first."""
+import os
 import subprocess
 import sys
 
@@ -38,3 +39,49 @@ def test_a_pass_for_every_eighty_probes(runtime, d):  # noqa: F811
     for t in ts:
         passes = max(1, -(-(t - 1) // 80))
         assert got[t] == got[1] + (passes - 1) * per_pass, (t, got)
+
+
+SCRATCH = r"""
+import ctypes as C, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+lib = C.CDLL(sys.argv[2])
+fake.fake_memory.restype, fake.fake_memory.argtypes = C.c_size_t, [C.c_size_t]
+lib.gp_last_error.restype = C.c_char_p
+n, d, t, i64, p = int(sys.argv[3]), int(sys.argv[4]), int(sys.argv[5]), C.c_int64, C.c_void_p
+ctx, X = p(), (C.c_float * (n * d))()
+assert lib.gp_create(C.byref(ctx), 1, i64(n), d, X, None) == 0
+assert lib.gp_set_theta(ctx, (C.c_double * d)(*[1.0] * d), C.c_double(1), C.c_double(0.5)) == 0
+g = (C.c_double * (d + 2))()
+V = (C.c_float * (n * t))()
+grad = lambda: lib.gp_mll_grad(ctx, V, i64(t), V, i64(t), t, g)
+up = lambda v, a: (v + a - 1) // a * a
+rest = 256 * up(n, 512) + 4 * up(n, 512) + (1 << 24) + 8 * 2048 * (d + 2)      # operands of the other side, y, sums
+size = lambda probes, rows: 256 * up(max(probes, 1), 16) * up(n, 512) + 4 * (2 * d + 2) * up(max(n, rows), 256) + rest
+few = size(min(t - 1, 32), 1 << 17)
+fake.fake_memory(few)                            # a device with as much and no more
+assert grad() == 0, lib.gp_last_error(ctx)
+tight = fake.fake_memory(1 << 40)
+assert tight <= few
+assert grad() == 0 and fake.fake_memory(1 << 40) == 0      # it goes on as it is
+assert lib.gp_destroy(ctx) == 0
+assert lib.gp_create(C.byref(ctx), 1, i64(n), d, X, None) == 0
+assert lib.gp_set_theta(ctx, (C.c_double * d)(*[1.0] * d), C.c_double(1), C.c_double(0.5)) == 0
+fake.fake_memory(1 << 40)
+assert grad() == 0
+full = fake.fake_memory(1 << 40)
+assert full <= size(min(t - 1, 80), 1 << 19), (full, size(min(t - 1, 80), 1 << 19))
+assert lib.gp_destroy(ctx) == 0
+print(full, tight)
+"""
+
+
+@pytest.mark.parametrize("n,d,t", [(3000, 96, 65), (43945, 96, 17), (43945, 20, 65), (100000, 60, 65), (100000, 60, 80), (131071, 5, 130),
+                                   (600000, 3, 9)])
+def test_scratch_is_bounded_and_gives_way(runtime, n, d, t):  # noqa: F811
+    """At most 2^19 rows of partial sums (or n); and on a device that has not the memory for them, what there was before rows were
+    cut into that many pieces is enough."""
+    r = subprocess.run([sys.executable, "-c", SCRATCH, runtime, LIB, str(n), str(d), str(t)], capture_output=True, text=True, timeout=300,
+                       env=dict(os.environ, OMP_NUM_THREADS="1"))
+    assert r.returncode == 0, r.stderr[-2000:]
+    full, tight = map(int, r.stdout.split())
+    assert tight <= full

@@ -43,7 +43,14 @@ hipError_t hipLaunchKernel(const void*, dim3 g, dim3 b, void**, size_t, hipStrea
   if (b.x == 1024 && (int)(g.x * g.y) > wide) wide = g.x * g.y;
   return hipSuccess;
 }
-hipError_t hipGetLastError() { return fallible(); }
+static size_t limit = ~(size_t)0, most;
+static hipError_t last_error = hipSuccess;
+size_t fake_memory(size_t l) { const size_t m = most; most = 0; limit = l; return m; }      // most bytes allocated at once since; limit on them
+hipError_t hipGetLastError() {
+  const hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e == hipSuccess ? fallible() : e;
+}
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return fallible(); }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
   if (fallible() != hipSuccess) return hipErrorUnknown;
@@ -60,7 +67,11 @@ hipError_t hipStreamQuery(hipStream_t) {
   return hipErrorNotReady;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { queued = 0; return hipSuccess; }
-hipError_t hipMalloc(void** p, size_t n) { *p = calloc(n, 1); return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) {
+  if (n > limit) return last_error = hipErrorOutOfMemory;
+  if (n > most) most = n;
+  *p = calloc(n, 1); return hipSuccess;
+}
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = pinned = (char*)calloc(n, 1); return hipSuccess; }
 hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
