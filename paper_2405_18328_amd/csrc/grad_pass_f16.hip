@@ -524,7 +524,9 @@ int grad_probe_block(int s, int most) {
 }
 
 // The work of one block of probes: workgroups of W waves, most chunks one of them takes, pieces of the longest rows (the first
-// ones), all workgroups.  `slots` workgroups run side by side.
+// ones), all workgroups.  `slots` workgroups are taken to run side by side, one of eight waves or two of four to a compute unit.
+// Not all kernels of four waves do: those with KH = 1, KT = 2 hold three (planned so, n = 16384, d = 3, t = 17 would take 125 us instead
+// of 138), those with three pieces of many dimensions one (n = 4000, d = 96, t = 33 172 instead of 211; from n = 16384 on nothing changes).
 struct GradPlan {
   int W, cps, pieces, workgroups;
   int64_t image_rows() const { return (int64_t)workgroups * 32 * W; }

@@ -314,17 +314,21 @@ def test_config5_two_million_rows_first_steps_of_ap_and_sgd():
 # ---------------------------------------------------------------------------------------------------
 # Column ranges longer than one accumulation segment.  Every tile kernel adds its fp32 accumulators into
 # its output after 1024 column chunks (32768 columns) and goes on; a workgroup walks more than one such
-# segment only when its column range is not split, i.e. from 65536 rows up.  The cases below run that
+# segment only when its column range is not split, or into pieces longer than that.  The cases below run that
 # loop in every tile kernel (K V and gradient, split-fp16 and fp32) under an oracle check.
 # ---------------------------------------------------------------------------------------------------
-LONG_N = 70001      # 2188 column chunks: three segments, a ragged last chunk, no column split
+LONG_N = 70001      # fp32 kernels, split up to 65536 rows: 2188 column chunks, three segments, a ragged last chunk
+# split-fp16 product: 2049 workgroups of 128 rows (1025 of 256) fill their generations without a split, 8194 chunks in nine segments
+LONG_N_F16 = 262177
+# split-fp16 gradient: rows are not cut from 131072 on, the first ones have 4098 chunks in five segments
+LONG_N_GRAD_F16 = 131105
 
 
 @pytest.mark.parametrize("name,kw,path", [
-    ("config4", dict(n=LONG_N, s=8), None),         # Matern-3/2, d = 90: six 16-wide k-steps of distance operands
+    ("config4", dict(n=LONG_N_F16, s=8), None),     # Matern-3/2, d = 90: six 16-wide k-steps of distance operands
     ("config4", dict(n=LONG_N, s=8), "fp32"),       # the same through the fp32 matrix-core kernel (KS = 46)
-    ("config2", dict(n=LONG_N, s=64), None),        # Matern-3/2, d = 26, t = 65 (two N-tiles + the y column)
-    ("config2", dict(n=LONG_N, s=8), "f16x3"),      # three fp16 pieces per distance operand
+    ("config2", dict(n=LONG_N_F16, s=64), None),    # Matern-3/2, d = 26, t = 65 (two N-tiles + the y column)
+    ("config2", dict(n=LONG_N_F16, s=8), "f16x3"),  # three fp16 pieces per distance operand
     ("config5", dict(n=LONG_N, s=8), "fp32"),       # SE, d = 11 through the fp32 kernel, two sub-tiles per wave
 ])
 def test_kmv_column_ranges_of_several_segments(monkeypatch, name, kw, path):
@@ -338,6 +342,7 @@ def test_kmv_column_ranges_of_several_segments(monkeypatch, name, kw, path):
         got = dv.kmv(w.B, 1)
         rows = np.random.default_rng(8).choice(w.n, size=160, replace=False)
         rows[:6] = [0, w.n - 1, 32767, 32768, 65535, 65536]
+        _note(f"{name} n = {w.n} path {path}")
         ref = _oracle_rows_threaded(w, w.ell, w.a, w.sigma, w.B, rows)
         err = relerr(got[rows], ref)
         _note(f"{name} {kw} path {path}: K V error on {rows.size} rows {err:.2e}")
@@ -350,28 +355,30 @@ def test_kmv_column_ranges_of_several_segments(monkeypatch, name, kw, path):
 _GRAD_REF = {}
 
 
-@pytest.mark.parametrize("name,path", [("config3", None), ("config3", "fp32"), ("config3", "f16x3"),
-                                       ("config2", None), ("config2", "fp32"), ("config2", "f16x3")])
-def test_gradient_column_ranges_of_several_segments(monkeypatch, name, path):
-    """gp_mll_grad at n = 70001 (SE d = 3 and Matern-3/2 d = 26, t = 9) on each arithmetic path.  The
+@pytest.mark.parametrize("name,path,s", [("config3", None, 8), ("config3", "fp32", 8), ("config3", "f16x3", 8),
+                                         ("config2", None, 8), ("config2", "fp32", 8), ("config2", "f16x3", 8),
+                                         ("config2", None, 64)])       # eight waves
+def test_gradient_column_ranges_of_several_segments(monkeypatch, name, path, s):
+    """gp_mll_grad (SE d = 3 and Matern-3/2 d = 26, t = 9 and 65) on each arithmetic path.  The
     oracle's estimator summed over rows (pinned to the dense one at small n) needs every row of every
-    derivative matrix, n^2 d entries, so V is given support on 1536 rows spread over the whole range:
+    derivative matrix, n^2 d entries, so V is given support on 1536 rows (768 of the longer set) spread over the whole range:
     the sum then has those rows' terms only and the oracle forms just them, against all n columns."""
     if path:
         monkeypatch.setenv("GPWS_PATH", path)
-    w = _make(name, n=LONG_N, s=8)
+    w = _make(name, n=LONG_N if path == "fp32" else LONG_N_GRAD_F16, s=s)
     a, sigma = 1.1, 0.3
     ell = w.ell * np.linspace(0.9, 1.4, w.d)
     rng = np.random.default_rng(17)
-    R = np.sort(rng.choice(w.n, size=1536, replace=False))
+    R = np.sort(rng.choice(w.n, size=1536 if path == "fp32" else 768, replace=False))
     R[:3], R[-3:] = [0, 1, 2], [w.n - 3, w.n - 2, w.n - 1]
     R = np.unique(np.concatenate([R, [32767, 32768, 65535, 65536]]))
     V = np.zeros(w.B.shape, dtype=np.float32)
     V[R] = (rng.standard_normal((R.size, w.s + 1)) * 0.3).astype(np.float32)
-    if name not in _GRAD_REF:
+    key = (name, w.n, s)
+    if key not in _GRAD_REF:
         _note(f"oracle estimator over {R.size} rows x {w.n} columns, d = {w.d}")
-        _GRAD_REF[name] = orc.mll_grad_hutchinson_rows(w.X, ell, a, sigma, w.kind, w.B, V, rows=R, row_block=32, workers=8)
-    ref = _GRAD_REF[name]
+        _GRAD_REF[key] = orc.mll_grad_hutchinson_rows(w.X, ell, a, sigma, w.kind, w.B, V, rows=R, row_block=32, workers=8)
+    ref = _GRAD_REF[key]
     dv = Dev(w.X, w.kind, ell, a, sigma)
     try:
         g = dv.grad(dv.to(V), dv.to(w.B))
