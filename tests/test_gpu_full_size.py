@@ -318,8 +318,8 @@ def test_config5_two_million_rows_first_steps_of_ap_and_sgd():
 # loop in every tile kernel (K V and gradient, split-fp16 and fp32) under an oracle check.
 # ---------------------------------------------------------------------------------------------------
 LONG_N = 70001      # fp32 kernels, split up to 65536 rows: 2188 column chunks, three segments, a ragged last chunk
-# split-fp16 product: 2049 workgroups of 128 rows (1025 of 256) fill their generations without a split, 8194 chunks in nine segments
-LONG_N_F16 = 262177
+# split-fp16 product: 2047 workgroups of 128 rows (1024 of 256) fill their generations without a split, 8188 chunks in eight segments
+LONG_N_F16 = 262001
 # split-fp16 gradient: rows are not cut from 131072 on, the first ones have 4098 chunks in five segments
 LONG_N_GRAD_F16 = 131105
 
