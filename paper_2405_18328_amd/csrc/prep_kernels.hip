@@ -73,7 +73,7 @@ struct PackArgs {
   u32x4* B[3];
   unsigned long long* max_norm;
   unsigned seq;
-  int64_t n;
+  int64_t n, chunk0;
   int d, KS, KH, is_se;
   float gamma;
 };
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
   float* norm = xs + 32 * ds;
   unsigned* top = reinterpret_cast<unsigned*>(norm + 32);
   const int tid = threadIdx.x;
-  const int64_t chunk = blockIdx.x, row0 = chunk * 32;
+  const int64_t chunk = p.chunk0 + blockIdx.x, row0 = chunk * 32;
   const int live = (int)(p.n - row0 < 0 ? 0 : p.n - row0 < 32 ? p.n - row0 : 32);
   if (tid == 0) *top = 0u;
   for (int e = tid; e < 32 * d; e += 256) {
@@ -181,10 +181,16 @@ int gp_launch_column_means(gp_ctx* ctx) {
 
 namespace {
 
-int launch_pack_points(gp_ctx* ctx, const PackArgs& p, int64_t n_pad) {
+int launch_pack_points(gp_ctx* ctx, PackArgs& p, int64_t n_pad) {
   const size_t lds = sizeof(float) * (32 * (size_t)(p.d | 1) + 33);
-  hipLaunchKernelGGL(pack_points_kernel, dim3((unsigned)(n_pad / 32)), dim3(256), lds, ctx->stream, p);
-  GP_HIP(ctx, hipGetLastError());
+  // all chunks in one launch would be more than the 2^32 threads it may have from 2^29 points on.  (Workgroups that walk over several
+  // chunks instead cost the usual sizes time: n = 500000, d = 3 41 -> 52 us for a gp_set_theta.)
+  constexpr int64_t MOST = 1 << 20;
+  for (p.chunk0 = 0; p.chunk0 < n_pad / 32; p.chunk0 += MOST) {
+    const int64_t left = n_pad / 32 - p.chunk0;
+    hipLaunchKernelGGL(pack_points_kernel, dim3((unsigned)(left < MOST ? left : MOST)), dim3(256), lds, ctx->stream, p);
+    GP_HIP(ctx, hipGetLastError());
+  }
   return GP_OK;
 }
 

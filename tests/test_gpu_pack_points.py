@@ -5,6 +5,7 @@ and up to the largest.  Bound: products of two split factors (3 2^-22) and r^2 f
 squared norms, taken four times for the steps of the chain that meet in it), against the sum of the terms' sizes."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import gp_oracle as orc
 from tests.gpu_util import Dev
@@ -71,5 +72,23 @@ def test_a_far_prediction_leaves_nothing_for_the_next():
             kmv = dv.kmv(V, 1)
             assert (dv.kmv(V, 1) == kmv).all()
         _check(dv, X, Xs, ell, 1.0, "matern32", V)
+    finally:
+        dv.close()
+
+
+def test_several_launches():
+    """2^20 chunks to a launch at most: 2^25 + 77 points, which repeat a short set, get that set's predictions again."""
+    print("[pack points] 2^25 + 77 points", flush=True)
+    rng = np.random.default_rng(25)
+    n, d, m, period = 100, 2, (1 << 25) + 77, 4099
+    X, Xs = rng.uniform(-1, 1, (n, d)).astype(np.float32), rng.uniform(-1, 1, (period, d)).astype(np.float32)
+    V = rng.standard_normal((n, 1)).astype(np.float32)
+    dv = Dev(X, "se", np.full(d, 1.0), 1.0, 0.3)
+    try:
+        few = torch.from_numpy(dv.predict(Xs, V).astype(np.float32)).to(dv.dev)
+        Xd, Vd, out = dv.to(Xs).repeat(m // period + 1, 1)[:m].contiguous(), dv.to(V), torch.empty(m, 1, device=dv.dev)
+        dv.gp.gp_predict(dv.ctx, Xd, m, Vd, 1, 1, out, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(out, few.repeat(m // period + 1, 1)[:m])
     finally:
         dv.close()

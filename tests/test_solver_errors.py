@@ -19,13 +19,17 @@ RUNTIME = r"""
 #include <hip/hip_runtime.h>
 #include <cstdlib>
 #include <cstring>
+#include <sys/mman.h>
 static char* pinned;
-static int queued, launched, until_failure, wide;
+static int queued, launched, until_failure, wide, posts, posting = 1;
+static unsigned long long threads;
 static unsigned steps;
 static hipError_t fallible() { return until_failure > 0 && --until_failure == 0 ? hipErrorUnknown : hipSuccess; }
 extern "C" {
 int fake_queued() { return queued; }
 int fake_launched() { const int n = launched; launched = 0; return n; }      // since the last time it was asked
+void fake_posting(int on) { posting = on; }      // off: norms are not posted, and the stream is idle
+unsigned long long fake_threads() { const unsigned long long m = threads; threads = 0; return m; }      // most in one dimension of a launch
 int fake_wide() { return wide; }      // most workgroups of a launch with 1024 threads each
 int fake_fail(int k) { const int left = until_failure; until_failure = k; steps = 0; queued = 0; return left; }
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -37,9 +41,12 @@ hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t) { gri
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* m, hipStream_t* s) {
   *g = grid; *b = block; *m = 0; *s = nullptr; return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void*, dim3 g, dim3 b, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void*, dim3 g, dim3 b, void** args, size_t, hipStream_t) {
   ++queued;
   ++launched;
+  if ((unsigned long long)g.x * b.x > threads) threads = (unsigned long long)g.x * b.x;
+  // a single thread posts the largest norm, under one tag after the other
+  if (g.x * b.x == 1 && posting) **(unsigned long long**)args[1] = (unsigned long long)++posts << 32;
   if (b.x == 1024 && (int)(g.x * g.y) > wide) wide = g.x * g.y;
   return hipSuccess;
 }
@@ -61,6 +68,7 @@ hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
   ++queued; memset(d, v, n); return hipSuccess;
 }
 hipError_t hipStreamQuery(hipStream_t) {
+  if (!posting) return hipSuccess;
   unsigned long long* post = (unsigned long long*)(pinned + 32768);
   ++steps;
   for (int k = 0; k < 16; ++k) post[k] = steps;
@@ -70,6 +78,10 @@ hipError_t hipStreamSynchronize(hipStream_t) { queued = 0; return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) {
   if (n > limit) return last_error = hipErrorOutOfMemory;
   if (n > most) most = n;
+  if (n >> 33) {      // never freed
+    *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    return *p == MAP_FAILED ? hipErrorOutOfMemory : hipSuccess;
+  }
   *p = calloc(n, 1); return hipSuccess;
 }
 hipError_t hipFree(void* p) { free(p); return hipSuccess; }
