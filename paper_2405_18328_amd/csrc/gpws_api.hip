@@ -252,7 +252,15 @@ int gp_predict(gp_ctx* ctx, const float* dXstar, int64_t m, const float* dV, int
   if ((rc = gp_ensure_scratch(ctx, pack_bytes + kmv_bytes)) < 0) return rc;
   KmvRows rows;
   if ((rc = gp_pack_rows(ctx, dXstar, m, ctx->dScratch, &rows)) < 0) return rc;
-  return gp_kmv_launch(ctx, dV, ldv, t, dOut, ldo, 0, (char*)ctx->dScratch + pack_bytes, kmv_bytes, nullptr, &rows);
+  const bool settled = rows.path != GP_PATH_PENDING;
+  rc = gp_kmv_launch(ctx, dV, ldv, t, dOut, ldo, 0, (char*)ctx->dScratch + pack_bytes, kmv_bytes, nullptr, &rows);
+  // dXstar is the caller's again when this returns: where the path did not have to wait for its packing, the call does
+  if (settled || rows.path == GP_PATH_PENDING) {
+    float norm;
+    const int waited = gp_wait_norm(ctx, "gp_predict", &norm);
+    if (rc >= 0) rc = waited;
+  }
+  return rc;
 }
 
 size_t gp_workspace_bytes(const gp_ctx* ctx, int t) {

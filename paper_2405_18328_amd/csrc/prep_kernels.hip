@@ -292,9 +292,9 @@ int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows
   p.XB = (float*)(w + L.off_xb);
   for (int pc = 0; pc < 3; ++pc) p.B[pc] = (u32x4*)(w + L.off_b[pc]);
   int rc;
-  if (ctx->f16_ok && (rc = next_norm_tag(ctx, p)) < 0) return rc;
+  if ((rc = next_norm_tag(ctx, p)) < 0) return rc;
   if ((rc = launch_pack_points(ctx, p, L.m_pad)) < 0) return rc;
-  if (ctx->f16_ok && (rc = post_norm(ctx)) < 0) return rc;
+  if ((rc = post_norm(ctx)) < 0) return rc;
   rows->m = m;
   rows->XB = p.XB;
   for (int pc = 0; pc < 3; ++pc) rows->XBh[pc] = p.B[pc];

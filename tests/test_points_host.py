@@ -3,6 +3,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 from paper_2405_18328_amd.build import LIB
 from tests.test_solver_errors import runtime  # noqa: F401
 
@@ -49,3 +51,20 @@ def test_no_launch_of_more_than_two_to_the_32_threads(runtime):  # noqa: F811
     """2^29 points and more have 2^24 chunks of 32: a workgroup of 256 for each is more than one launch may have."""
     _run(runtime, LARGE)
     _run(runtime, LARGE_PREDICT)
+
+
+WAITS = HEAD + r"""
+n, d, m = 300, int(sys.argv[3]), 70
+few = (C.c_float * (n * d))()
+ctx = create(0, n, d, few)
+fake.fake_posting(0)
+assert lib.gp_predict(ctx, few, i64(m), few, i64(1), 1, few, i64(1)) == -2
+assert b"not reported" in lib.gp_last_error(ctx), lib.gp_last_error(ctx)
+"""
+
+
+@pytest.mark.parametrize("d", [5, 126])
+def test_a_prediction_returns_behind_the_packing_of_its_points(runtime, d):  # noqa: F811
+    """X* is read during the call only: the call waits for the norm that is posted behind the packing (here: is told that there is
+    none), also where the path is settled without it, as in 126 dimensions."""
+    _run(runtime, WAITS, d)
