@@ -74,7 +74,7 @@ struct gp_ctx {
   bool f16_ok;            // false when d + 3 components do not fit the widest fp16 operand bucket (SE, d = 126)
   float max_norm;         // host copy of max_i |xs_i|^2
   unsigned* dColmax;      // GP_MAX_T words, zero between calls: column maxima of gp_kmv in accumulation
-  int colmax_dirty;       // how many of them a call that ended with an error may have left set
+  int colmax_dirty;       // how many of them may be set: a call ended with an error, or was a prediction that turned to the fp32 path
   double* dMean;          // d column means of X
   double* dTheta;         // device copy: 1/ell (d), then a, sigma
   bool theta_set;

@@ -298,7 +298,7 @@ int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows
   rows->m = m;
   rows->XB = p.XB;
   for (int pc = 0; pc < 3; ++pc) rows->XBh[pc] = p.B[pc];
-  rows->path = ctx->f16_ok ? GP_PATH_PENDING : GP_PATH_FP32;
+  rows->path = ctx->path == GP_PATH_FP32 ? GP_PATH_FP32 : GP_PATH_PENDING;     // farther rows do not bring it back from there
   return GP_OK;
 }
 

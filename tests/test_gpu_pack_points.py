@@ -92,3 +92,30 @@ def test_several_launches():
         assert torch.equal(out, few.repeat(m // period + 1, 1)[:m])
     finally:
         dv.close()
+
+
+@pytest.mark.parametrize("n,t", [(300, 70), (8300, 33)])
+def test_maxima_left_by_a_far_prediction(n, t):
+    """Longer V, or more columns than one pass: the maxima are accumulated in words of the context.  A prediction that turns to fp32 has
+    taken those of a much larger V and not cleared them; prediction and product of the first V have their bits from before."""
+    print(f"[pack points] maxima n={n} t={t}", flush=True)
+    rng = np.random.default_rng(n)
+    d, kind = 3, "matern32"
+    X, Xs = rng.uniform(-1, 1, (n, d)).astype(np.float32), rng.uniform(-1, 1, (40, d)).astype(np.float32)
+    V = rng.standard_normal((n, t)).astype(np.float32)
+    big = (1e6 * rng.standard_normal((n, t))).astype(np.float32)
+    ell, far = np.full(d, 1.0), (300.0 * Xs).astype(np.float32)
+    far[::4] = Xs[::4]              # some of them near, so that there is something to predict
+    dv = Dev(X, kind, ell, 1.0, 0.3)
+    try:
+        predicted, product = dv.predict(Xs, V), dv.kmv(V, 1)
+        for again in (lambda: (dv.predict(Xs, V) == predicted).all(), lambda: (dv.kmv(V, 1) == product).all()):
+            got = dv.predict(far, big)
+            ref = orc.cross_kmv(far, X, ell, 1.0, kind, big)
+            size = np.abs(big.astype(np.float64)).sum(0)
+            # fp32 throughout: r^2 from the expanded square of the near rows' coordinates, sums of n products
+            assert (np.abs(got - ref)[::4] <= 2.0 ** -22 * (5.0 + 8.0 * 3 * d) * size).all()
+            assert np.isfinite(got).all()
+            assert again()
+    finally:
+        dv.close()

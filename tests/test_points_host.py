@@ -68,3 +68,20 @@ def test_a_prediction_returns_behind_the_packing_of_its_points(runtime, d):  # n
     """X* is read during the call only: the call waits for the norm that is posted behind the packing (here: is told that there is
     none), also where the path is settled without it, as in 126 dimensions."""
     _run(runtime, WAITS, d)
+
+
+SETTLED = HEAD + r"""
+n, d, t = 9000, 5, 40
+X, V, O = (C.c_float * (n * d))(), (C.c_float * (n * t))(), (C.c_float * (n * t))()
+ctx = create(0, n, d, X)
+fake.fake_launched()
+assert lib.gp_kmv(ctx, V, i64(t), t, O, i64(t), 0) == 0
+square = fake.fake_launched()
+assert lib.gp_predict(ctx, X, i64(n), V, i64(t), t, O, i64(t)) == 0
+assert fake.fake_launched() == square + 2, square       # + points packed, norm posted
+"""
+
+
+def test_a_prediction_whose_path_is_settled_prepares_no_other(runtime):  # noqa: F811
+    """On the fp32 path of the training inputs neither the column maxima nor the fp16 operands of V are made."""
+    _run(runtime, SETTLED, GPWS_PATH="fp32")
