@@ -79,10 +79,12 @@ def cpu_baseline(w):
             "seconds": dt}
 
 
-def grad_flops(n, d, t, kind):
-    """Algorithmic flops of one gradient tile pass: per pair 2t for the weight w_ij, 2d for the distance
-    (dot form), 2d for the d lengthscale sums, and the kernel function (same convention as kmv_flops)."""
-    return float(n) * float(n) * (2 * t + 4 * d + (4 if kind == "se" else 8))
+def grad_flops(n, d, t, kind, half):
+    """Algorithmic flops of one gradient tile pass: per pair 2t for the weight w_ij, 2d for the distance (dot form), 2d for the d
+    lengthscale sums, and the kernel function (same convention as kmv_flops).  half: the fp16 kernels work on one of every
+    two mirrored pairs (the derivative matrices are symmetric), with the weight w_ij + w_ji, 4 (t - 1) + 2."""
+    rest = 4 * d + (4 if kind == "se" else 8)
+    return float(n) * float(n) * (0.5 * (4 * (t - 1) + 2 + rest) if half else 2 * t + rest)
 
 
 def config5_leg(cap=4, outer_steps=3, timed_products=3):
@@ -159,9 +161,10 @@ def config5_leg(cap=4, outer_steps=3, timed_products=3):
         out["cg_vector_kernels"] = vec
         g_launches, g_ms = gp.gp_profile_read_kind(opt.ctx, gp.GP_PROF_GRAD_TILE)
         if g_launches:
-            Fg = grad_flops(n, d, t, w.kind) * outer_steps / g_launches
+            Fg = grad_flops(n, d, t, w.kind, path != 0) * outer_steps / g_launches
             g_ach = Fg / (g_ms / 1e3 / g_launches) / 1e12
             out["grad_tile_kernel"] = {"launches": g_launches, "avg_launch_ms": g_ms / g_launches, "flops_per_launch": Fg,
+                                       "pairs": "all" if path == 0 else "one of every two mirrored ones, with the weights of both",
                                        "achieved": g_ach, "peak": peak, "unit": "TFLOP/s", "frac": g_ach / peak,
                                        "bound": "mfma", "grad_ms_per_step": float(np.mean([r.grad_ms for r in recs]))}
         gp.gp_profile(opt.ctx, 0)

@@ -16,9 +16,9 @@
 //   3. OUT_i   += G'[i][j] Q'_j      G' = U' psi split on the VALU, Q' = 2^qshift Q pre-split
 // The epilogue removes alpha and 2^qshift.  K and u are never stored.
 // Matrix instructions per pair of mirrored tiles, d = 26, t = 65: 42 instead of 66 (6 + 24 + 12 against twice 6 + 15 + 12), and half
-// the vector work; the matrix core and the vector port together bound it (48 % and 53 % of the cycles at n = 43945, d = 20, t = 17, at 1.86 GHz).
-// A gradient, all pairs -> half: n = 16384, d = 26, t = 65 (Matern) 327 -> 252 us; n = 43945, d = 20, t = 17 1491 -> 888 us;
-// n = 131072, d = 3, t = 65 (SE) 10.5 -> 7.9 ms; n = 20000, d = 60, t = 33 1065 -> 568 us.  Error against 64 bits, V a solution:
+// the vector work; the matrix core and the vector port together bound it (56 % and 39 % of the cycles at n = 43945, d = 26, t = 65, at 1.89 GHz).
+// A gradient, all pairs -> half: n = 16384, d = 26, t = 65 (Matern) 320 -> 234 us, d = 60 692 -> 471 us; n = 43945, d = 20, t = 17
+// 1468 -> 832 us; n = 140000, d = 3, t = 65 (SE) 14.0 -> 9.3 ms.  Error against 64 bits, V a solution:
 // n = 8192, d = 26, t = 65 1.05e-6 -> 2.3e-7; n = 8000, d = 9, t = 33 1.8e-6 -> 3.3e-7.
 #include <cstdlib>
 

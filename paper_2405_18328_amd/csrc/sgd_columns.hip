@@ -3,8 +3,8 @@
 // launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
 // context's packed operands; the gradient on the mini-batch rows is spread over the chip; momentum, iterate,
 // the stopping test and the packing of the iterate for the next product are per column (columns.h).
-// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: 78 -> 43 us per step (product 20.2, gradient 8.6, the rest
-// 10.7 us).  Bound by memory latency and by the 64 partial images of the product (16.6 MB written and read).
+// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: 78 -> 43 us per step (product 19.2, gradient 9.0, the rest
+// 11.0 us).  Bound by memory latency and by the 64 partial images of the product (16.6 MB written and read).
 #include "columns.h"
 
 namespace {
