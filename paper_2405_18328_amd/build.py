@@ -10,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgpws.so")
-SOURCES = ["gpws_api.hip", "prep_kernels.hip", "tile_pass.hip", "tile_pass_f16.hip", "cg_kernels.hip", "cg_columns.hip", "grad_pass.hip", "grad_pass_f16.hip", "ap_kernels.hip", "ap_columns.hip", "sgd_kernels.hip", "sgd_columns.hip"]
+# the ones that take longest first
+SOURCES = ["tile_se_x2.hip", "tile_se_x3.hip", "tile_matern32_x2.hip", "tile_matern32_x3.hip", "grad_pass_f16.hip", "gpws_api.hip", "prep_kernels.hip", "tile_pass.hip", "tile_pass_f16.hip", "cg_kernels.hip", "cg_columns.hip", "grad_pass.hip", "ap_kernels.hip", "ap_columns.hip", "sgd_kernels.hip", "sgd_columns.hip"]
 # packed FP32 VALU forms are kept off on purpose (some forms have miscomputed on the test machines)
 # MFMA accumulators are kept in ordinary VGPRs (vgpr-form): the tile kernels feed the result of one
 # MFMA chain through the VALU into the next chain, and the AGPR form costs a copy each way per value.

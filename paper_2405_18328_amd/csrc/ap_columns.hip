@@ -579,7 +579,7 @@ int gp_ap_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   const dim3 ugrid(L.parts, t);
   const bool small = (int64_t)((L.nb + L.parts - 1) / L.parts) * block <= 2 * CROWS;   // rows of a part
   hipLaunchKernelGGL((small ? apc_update_kernel<2, true> : apc_update_kernel<4, true>), ugrid, cblock, 0, st, s, dX0 ? 1 : 0);
-  if (dX0 && t % 32 > 1) clear(s.VP, (size_t)L.units * 16);   // the windows' operands are laid out anew
+  if (dX0 && padded_tiles(t)) clear(s.VP, (size_t)L.units * 16);   // the windows' operands are laid out anew
   if (failed(hipGetLastError())) return GP_ERR_HIP;
 
   const KmvBlock win = {&s.flags->pad, block, L.win_chunks};

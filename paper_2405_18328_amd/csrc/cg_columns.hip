@@ -338,7 +338,7 @@ int gp_cg_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX
   pk.ld = L.ld;
   if (failed(hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st))) return GP_ERR_HIP;
   hipLaunchKernelGGL(clear_units_kernel, dim3(1), dim3(256), 0, st, (u32x4*)s.flags, (int64_t)(sizeof(ColFlags) / 16));
-  if (t % 32 > 1) {   // the columns that pad the last tile are never written
+  if (padded_tiles(t)) {   // the columns that pad the last tile are never written
     int blocks = (int)((L.units + 255) / 256);
     if (blocks > 4 * ctx->num_cu) blocks = 4 * ctx->num_cu;
     hipLaunchKernelGGL(clear_units_kernel, dim3(blocks), dim3(256), 0, st, s.VP, L.units);

@@ -25,38 +25,38 @@ __device__ __forceinline__ int block_column(int t) {
   return (int)(blockIdx.x >> 3) < per && c < t ? c : -1;
 }
 
-// where the packed operands of column c lie: unit ((chunk*2 + mh)*NT + nt)*2 + part of its pass, lane c % 32 (+ 32)
+// where the packed operands of column c lie: unit (chunk*NT + nt)*2 + part of its pass, lanes c % 16 + 0, 16, 32, 48
 struct PackSpot {
   u32x4* base;       // NULL: the vector-ALU column, read as it is
   int NT, nt, lane;
 };
 __device__ __forceinline__ PackSpot pack_spot(u32x4* VP, int t, int64_t nchunks, int c) {
   PackSpot s;
-  const int c0 = t % 32 == 1 ? 1 : 0;
+  const int c0 = vec_columns(t);
   s.base = nullptr;
   s.NT = 1; s.nt = 0; s.lane = 0;
   if (c < c0) return s;
   const int pass = (c - c0) / 64, cc = (c - c0) % 64;   // every pass but the last is 64 columns wide
-  s.NT = t - c0 - 64 * pass > 32 ? 2 : 1;
-  s.nt = cc / 32;
-  s.lane = cc & 31;
+  s.NT = pass_tiles(t - c0 - 64 * pass);
+  s.nt = cc / 16;
+  s.lane = cc & 15;
   s.base = VP + (int64_t)pass * nchunks * 8 * 64;
   return s;
 }
 
 // Rows 4 k .. 4 k + 3 of a column as operands: scaled, split into fp16 halves, and written in the order of the
-// matrix instruction's accumulator layout.  The halves of quads k and k + 2 make up one 16-byte unit each,
-// so lanes two apart exchange theirs and every lane writes one whole unit.  The lanes of a group of eight must
+// matrix instruction's accumulator layout.  The halves of quads k and k + 4 make up one 16-byte unit each,
+// so lanes four apart exchange theirs and every lane writes one whole unit.  The lanes of a group of eight must
 // call it together.
 __device__ __forceinline__ void pack_quad(const PackSpot& s, int k, f32x4 v) {
   unsigned hi[2], lo[2];
   split_quad(v, hi, lo);
-  const bool up = (k & 2) != 0;          // this lane writes the low part
-  const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi[0] : lo[0]), 2);
-  const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi[1] : lo[1]), 2);
+  const bool up = (k & 4) != 0;          // this lane writes the low part
+  const unsigned x0 = (unsigned)__shfl_xor((int)(up ? hi[0] : lo[0]), 4);
+  const unsigned x1 = (unsigned)__shfl_xor((int)(up ? hi[1] : lo[1]), 4);
   const u32x4 unit = up ? u32x4{x0, x1, lo[0], lo[1]} : u32x4{hi[0], hi[1], x0, x1};
-  const int64_t g = (int64_t)(k >> 2) * s.NT + s.nt;   // (chunk*2 + mh)*NT + nt
-  s.base[(g * 2 + (up ? 1 : 0)) * 64 + s.lane + 32 * (k & 1)] = unit;
+  const int64_t g = (int64_t)(k >> 3) * s.NT + s.nt;   // chunk*NT + nt
+  s.base[(g * 2 + (up ? 1 : 0)) * 64 + s.lane + 16 * (k & 3)] = unit;
 }
 __device__ __forceinline__ float pack_scale(float max_abs) {
   return ldexpf(1.0f, V_TOP - column_exponent(__float_as_uint(max_abs)));

@@ -111,6 +111,21 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
       GP_HIP(ctx, hipMalloc(&ctx->dXBh[pc], units * 16));
     }
   }
+  {   // operands of the tile pass: one block
+    size_t size[6], total = 0;
+    for (int x = 0; x < 2; ++x) size[2 * x] = size[2 * x + 1] = gp_dist_bytes(ctx, x + 2, ctx->n_pad);
+    size[4] = sizeof(float) * ctx->n_pad;
+    size[5] = sizeof(unsigned short) * gp_dist_slots(ctx, nullptr);
+    for (size_t& v : size) total += v = (v + 255) / 256 * 256;
+    GP_HIP(ctx, hipMalloc(&ctx->dDist, total));
+    char* at = (char*)ctx->dDist;
+    for (int x = 0; x < 2; ++x) {
+      ctx->dDA[x] = at; at += size[2 * x];
+      ctx->dDB[x] = at; at += size[2 * x + 1];
+    }
+    ctx->dCI = (float*)at; at += size[4];
+    ctx->dDistSlots = at;
+  }
   GP_HIP(ctx, hipMalloc((void**)&ctx->dColmax, sizeof(unsigned) * GP_MAX_T));
   GP_HIP(ctx, hipMemsetAsync(ctx->dColmax, 0, sizeof(unsigned) * GP_MAX_T, ctx->stream));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dMean, sizeof(double) * d));
@@ -121,6 +136,10 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
   GP_HIP(ctx, hipHostMalloc(&ctx->hPinned, ctx->pinned_bytes, hipHostMallocDefault));
   GP_HIP(ctx, hipHostGetDevicePointer(&ctx->dPinned, ctx->hPinned, 0));
   memset(ctx->hPinned, 0, ctx->pinned_bytes);
+  // gp_launch_column_means waits for the stream before anything else is written to the block
+  unsigned short* slots = (unsigned short*)((char*)ctx->hPinned + GP_PIN_THETA);
+  const int count = gp_dist_slots(ctx, slots);
+  GP_HIP(ctx, hipMemcpyAsync(ctx->dDistSlots, slots, sizeof(unsigned short) * count, hipMemcpyHostToDevice, ctx->stream));
   return gp_launch_column_means(ctx);
 }
 
@@ -135,6 +154,7 @@ int gp_destroy(gp_ctx* ctx) {
     if (ctx->dXAh[pc]) (void)hipFree(ctx->dXAh[pc]);
     if (ctx->dXBh[pc]) (void)hipFree(ctx->dXBh[pc]);
   }
+  if (ctx->dDist) (void)hipFree(ctx->dDist);
   if (ctx->dColmax) (void)hipFree(ctx->dColmax);
   if (ctx->dMean) (void)hipFree(ctx->dMean);
   if (ctx->dTheta) (void)hipFree(ctx->dTheta);
@@ -193,6 +213,7 @@ int gp_set_theta(gp_ctx* ctx, const double* h_lengthscale, double signal_scale, 
   if (!ctx->f16_ok) path = GP_PATH_FP32;
   ctx->path = path;
   ctx->XP = path == GP_PATH_F16X3 ? 3 : 2;
+  if (ctx->XP == 3 && (rc = gp_pack_x3(ctx)) < 0) return rc;
   ctx->theta_set = true;
   return GP_OK;
 }
@@ -254,8 +275,8 @@ int gp_predict(gp_ctx* ctx, const float* dXstar, int64_t m, const float* dV, int
   if ((rc = gp_pack_rows(ctx, dXstar, m, ctx->dScratch, &rows)) < 0) return rc;
   const bool settled = rows.path != GP_PATH_PENDING;
   rc = gp_kmv_launch(ctx, dV, ldv, t, dOut, ldo, 0, (char*)ctx->dScratch + pack_bytes, kmv_bytes, nullptr, &rows);
-  // dXstar is the caller's again when this returns: where the path did not have to wait for its packing, the call does
-  if (settled || rows.path == GP_PATH_PENDING) {
+  // dXstar is the caller's again when this returns: where the path did not have to wait for its (last) packing, the call does
+  if (settled || rows.path == GP_PATH_PENDING || rows.reads_X) {
     float norm;
     const int waited = gp_wait_norm(ctx, "gp_predict", &norm);
     if (rc >= 0) rc = waited;

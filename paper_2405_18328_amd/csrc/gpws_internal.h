@@ -47,7 +47,7 @@ constexpr size_t GP_PIN_POST = 32768;     // flags the solvers' finalise kernels
 // Column splits already worked out for a shape of product: a solver asks for the same few thousands of times.
 struct SplitMemo {
   int64_t rows, chunks;
-  int t, XP, JS;
+  int t, XP, JS, CG;
 };
 
 struct gp_ctx {
@@ -63,7 +63,15 @@ struct gp_ctx {
   float* dXs;             // scaled centred inputs, row-major n x d (gradient pass)
   unsigned long long* dMaxNorm;   // a tag and below it the bit pattern of the largest |xs_i|^2 packed under it (device)
   unsigned norm_seq;      // the latest tag
-  // split-fp16 operands of the matrix-core path: three pieces (hi, mid, lo) per side, 16-byte units
+  // split-fp16 operands of the tile pass on two and three pieces (dist_f16.h), column and row side, 16-byte units
+  // [(16 points)*groups + group]*64 + lane: lane l holds slots 8 (l/16) .. + 7 of point l % 16
+  void* dDist;            // one block that holds them all
+  void* dDA[2];
+  void* dDB[2];
+  bool x3_packed;         // those on three pieces are there for the current theta (gp_pack_x3)
+  void* dDistSlots;       // what stands where in them (gp_dist_slots)
+  float* dCI;             // gamma |xs_i|^2, [n_pad]
+  // split-fp16 operands of the gradient pass: three pieces (hi, mid, lo) per side, 16-byte units
   // [(chunk*KH + kh)*64 + lane], element e of a unit = component 16 kh + 8 (lane/32) + e
   void* dXAh[3];
   void* dXBh[3];
@@ -109,7 +117,11 @@ struct gp_ctx {
 struct KmvRows {
   int64_t m;
   const float* XB;        // fp32 packed row operands, [m_pad/32][KS][64]
-  const void* XBh[3];     // fp16 pieces, [m_pad/32][KH][64] 16-byte units
+  const void* DB[2];      // fp16 row operands on two and three pieces, as in the context
+  const float* X;         // the points themselves, and whether a launch that reads them is behind the one their norm was posted by
+  bool reads_X;
+  const float* CI;
+  const int* gather;      // fp16 paths: row i is the row gather[i] of DB and CI, which hold the context's n points; NULL: i
   int path;               // GP_PATH_* to use (covers the norms of both point sets); GP_PATH_PENDING: gp_rows_path will tell
 };
 
@@ -158,14 +170,19 @@ int gp_ensure_scratch(gp_ctx* ctx, size_t bytes);
 // ---- prep_kernels.hip
 int gp_launch_column_means(gp_ctx* ctx);
 int gp_launch_pack(gp_ctx* ctx, bool want_norm);
+int gp_pack_x3(gp_ctx* ctx);     // the operands on three pieces, which gp_launch_pack leaves out
 // waits for the largest scaled squared norm of the latest packing that was asked for it
 int gp_wait_norm(gp_ctx* ctx, const char* who, float* norm);
 // packs m other points (device, row-major m x d) against the context's centring and theta into
 // caller-provided buffers sized by gp_pack_rows_bytes; fills rows.  The path follows from the larger of the two sets' scaled
 // norms: it stays pending until gp_rows_path waits for that norm, so that launches which do not depend on it go first
 size_t gp_pack_rows_bytes(const gp_ctx* ctx, int64_t m);
+constexpr int GP_DIST_LIST_EXTRA = 6;
+int gp_dist_slots(const gp_ctx* ctx, unsigned short* slots);     // fills (or NULL: counts) the table the packing kernel works from
+size_t gp_dist_bytes(const gp_ctx* ctx, int XP, int64_t rows);   // of one side's operands of the tile pass, rows a multiple of 32
 int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows);
 int gp_rows_path(gp_ctx* ctx, KmvRows* rows);
+int gp_rows_x3(gp_ctx* ctx, KmvRows* rows);      // operands on three pieces, of both sides
 
 // ---- tile_pass.hip
 struct KmvPlan {
@@ -189,9 +206,10 @@ int gp_kmv_launch(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut,
 
 // ---- tile_pass_f16.hip
 int gp_kh_bucket(int d, int kernel);
-// Number of equal ranges the column chunks are cut into, given the row blocks and the workgroups that run
-// side by side (see the definition): every row block is cut alike, so all rows share one summation tree.
-int gp_column_splits(int row_blocks, int64_t chunks, int slots, double image_cost, int max_splits);
+// Number of equal ranges the column chunks are cut into, given the row blocks, the workgroups a compute unit holds and the
+// waves that share a workgroup's rows (see the definition); *cost: about what the launch takes, in us.
+int gp_column_splits(int64_t row_blocks, int64_t chunks, int num_cu, int per_cu, int cg, double chunk_us, double stream_us, double image_us,
+                     int max_splits, double* cost);
 size_t gp_kmv_f16_scratch_bytes(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks = 0);
 size_t gp_kmv_f16_least_scratch_bytes(const gp_ctx* ctx, int t);   // square product with its rows in panels
 // GP_OK, an error, or GP_TO_FP32: the rows' path was pending and turned out to be the fp32 one (nothing is in OUT yet)
@@ -205,7 +223,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
 // multiple of 32 hold nothing of meaning.  f16 paths only.
 struct KmvPacked {
   const void* VP;          // operands of every column pass, one after the other (gp_packed_units 16-byte units)
-  const float* VY;         // the vector-ALU column (column 0 when t = 32 q + 1), zero up to the next multiple of 32 rows
+  const float* VY;         // the vector-ALU column (column 0 where vec_columns(t)), zero up to the next multiple of 32 rows
   const unsigned* colmax;  // bit patterns of the column maxima the operands were scaled by
   float* images;
   int64_t ld;              // rows per column, a multiple of 32

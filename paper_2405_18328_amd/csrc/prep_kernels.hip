@@ -4,6 +4,7 @@
 // shrinks |xs|^2 and with it the rounding of the dot-form r^2.
 #include <cstring>
 
+#include "dist_f16.h"
 #include "gpws_internal.h"
 #include "split_f16.h"
 
@@ -60,21 +61,26 @@ __device__ __forceinline__ void split3(float x, float& hi, float& mid, float& lo
 // workgroup per chunk keeps the scaled rows in LDS, so that inputs are read and operands written in whole lines; a thread per row
 // (256 to a workgroup) was a chain of strided loads on few compute units, and a second launch read its rows back: n = 16384,
 // d = 26 15.2 + 4.5 -> 8.7 us, 1500 rows 11.6 + 3.0 -> 6.9 us.
-// XA: NULL where only the row side is wanted (XB, B).  max_norm: the largest squared norm under the tag `seq` in the
+// XA: NULL where only the row side is wanted.  max_norm: the largest squared norm under the tag `seq` in the
 // upper half of the word, which makes whatever an earlier tag left there count as less; NULL where nobody asks.
 struct PackArgs {
   const float* X;         // [n][d]
   const double* mean;     // [d]
   const double* theta;    // [d] 1 / ell
-  float* XA;              // fp32 operands, both sides
+  float* XA;              // fp32 operands, both sides, or NULL
   float* XB;
   float* Xs;              // [n][d] scaled rows, or NULL
-  u32x4* A[3];            // fp16 pieces, both sides
+  u32x4* DA[2];           // operands of the tile pass on two and three pieces, both sides (DA: NULL where only the row side is wanted, DB: where none is)
+  u32x4* DB[2];
+  float* CI;              // gamma |xs|^2
+  u32x4* A[3];            // operands of the gradient pass, or NULL
   u32x4* B[3];
   unsigned long long* max_norm;
   unsigned seq;
   int64_t n, chunk0;
+  const unsigned short* slots;    // per layout and side (B, A): [group][32] places in a point's list of pieces
   int d, KS, KH, is_se;
+  int groups[2];
   float gamma;
 };
 __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
@@ -82,7 +88,11 @@ __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
   const int d = p.d, ds = d | 1;
   float* norm = xs + 32 * ds;
   unsigned* top = reinterpret_cast<unsigned*>(norm + 32);
+  _Float16* pieces = reinterpret_cast<_Float16*>(top + 1);    // [32][list]: see gp_dist_slots
+  const int list = (6 * d + GP_DIST_LIST_EXTRA) | 1;
+  __shared__ u32x4 slots[2 * 4 * (DIST_MOST_GROUPS_X2 + DIST_MOST_GROUPS_X3)];     // eight places each
   const int tid = threadIdx.x;
+  for (int e = tid; e < 8 * (p.groups[0] + p.groups[1]); e += 256) slots[e] = reinterpret_cast<const u32x4*>(p.slots)[e];
   const int64_t chunk = p.chunk0 + blockIdx.x, row0 = chunk * 32;
   const int live = (int)(p.n - row0 < 0 ? 0 : p.n - row0 < 32 ? p.n - row0 : 32);
   if (tid == 0) *top = 0u;
@@ -105,12 +115,23 @@ __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
     if ((tid & 7) == 0) {
       const float nf = (float)nrm;
       norm[r] = nf;
+      // with the bits that fp32 would round away: on three pieces the norms cancel against each other
+      const double g = r < live ? (double)p.gamma * nrm : p.gamma < 0.0f ? -(double)GP_PAD_NORM_H : (double)GP_PAD_NORM_H;   // padding: the kernel value is exactly 0
+      const float hi = (float)(_Float16)(float)g, mid = (float)(_Float16)(float)(g - hi);
+      _Float16* at = pieces + r * list + 6 * d;
+      at[0] = (_Float16)hi;
+      at[1] = (_Float16)mid;
+      at[2] = (_Float16)(float)(g - hi - mid);
+      at[3] = (_Float16)1.0f;
+      at[4] = (_Float16)(float)PHI_SHIFT;
+      at[5] = (_Float16)0.0f;
+      if (p.CI) p.CI[row0 + r] = r < live ? (float)g : 0.0f;
       if (p.max_norm && r < live) atomicMax(top, __float_as_uint(nf));     // non-negative floats order like unsigned ints
     }
   }
   __syncthreads();
   if (p.max_norm && tid == 0) atomicMax(p.max_norm, (unsigned long long)p.seq << 32 | *top);
-  for (int e = tid; e < p.KS * 64; e += 256) {
+  for (int e = tid; p.XB && e < p.KS * 64; e += 256) {
     const int k = 2 * (e >> 6) + ((e >> 5) & 1), r = e & 31;
     const bool ok = r < live;
     float va = 0.0f, vb = 0.0f;
@@ -121,6 +142,43 @@ __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
     if (p.XA) p.XA[chunk * p.KS * 64 + e] = va;
     p.XB[chunk * p.KS * 64 + e] = vb;
   }
+  const bool both = p.DA[0] || p.DA[1];
+  for (int e = tid; e < 32 * d; e += 256) {
+    const int r = e / d, k = e - r * d;
+    const float x = xs[r * ds + k], y = -2.0f * p.gamma * x;
+    float hi, mid, lo;
+    _Float16* at = pieces + r * list + k;
+    if (both) {
+      split3(x, hi, mid, lo);
+      at[0] = (_Float16)hi;
+      at[d] = (_Float16)mid;
+      at[2 * d] = (_Float16)lo;
+    }
+    split3(y, hi, mid, lo);
+    at[3 * d] = (_Float16)hi;
+    at[4 * d] = (_Float16)mid;
+    at[5 * d] = (_Float16)lo;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    if (!p.DB[x]) continue;
+    const int G = p.groups[x], units = 2 * G * 64;
+    for (int v = tid; v < (p.DA[x] ? 2 : 1) * units; v += 256) {
+      const int side = v >= units, u = side ? v - units : v;
+      const int lane = u & 63, jt = (u >> 6) >= G, g = (u >> 6) - (jt ? G : 0);
+      const u32x4 where = slots[((x ? 2 * p.groups[0] : 0) + side * G + g) * 4 + (lane >> 4)];
+      const _Float16* from = pieces + (16 * jt + (lane & 15)) * list;
+      u32x4 out;
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        const unsigned a = __builtin_bit_cast(unsigned short, from[where[e2] & 0xFFFFu]), b = __builtin_bit_cast(unsigned short, from[where[e2] >> 16]);
+        out[e2] = a | b << 16;
+      }
+      (side ? p.DA[x] : p.DB[x])[chunk * units + u] = out;
+    }
+  }
+  if (!p.B[0]) return;
   for (int u = tid; u < p.KH * 64; u += 256) {
     const int r = u & 31, k0 = 16 * (u >> 6) + 8 * ((u >> 5) & 1);
     const bool ok = r < live;
@@ -149,7 +207,7 @@ __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
     const int64_t at = chunk * p.KH * 64 + u;
 #pragma unroll
     for (int pc = 0; pc < 3; ++pc) {
-      if (p.A[pc]) p.A[pc][at] = a[pc];
+      p.A[pc][at] = a[pc];
       p.B[pc][at] = b[pc];
     }
   }
@@ -182,7 +240,7 @@ int gp_launch_column_means(gp_ctx* ctx) {
 namespace {
 
 int launch_pack_points(gp_ctx* ctx, PackArgs& p, int64_t n_pad) {
-  const size_t lds = sizeof(float) * (32 * (size_t)(p.d | 1) + 33);
+  const size_t lds = sizeof(float) * (32 * (size_t)(p.d | 1) + 33) + 32 * sizeof(_Float16) * ((6 * (size_t)p.d + GP_DIST_LIST_EXTRA) | 1);
   // all chunks in one launch would be more than the 2^32 threads it may have from 2^29 points on.  (Workgroups that walk over several
   // chunks instead cost the usual sizes time: n = 500000, d = 3 41 -> 52 us for a gp_set_theta.)
   constexpr int64_t MOST = 1 << 20;
@@ -202,6 +260,8 @@ PackArgs pack_args(const gp_ctx* ctx) {
   p.KS = ctx->KS;
   p.KH = ctx->KH;
   p.is_se = ctx->kernel == GP_SE_ARD ? 1 : 0;
+  for (int x = 0; x < 2; ++x) p.groups[x] = dist_groups(x + 2, dist_shape_of(x + 2, ctx->d, ctx->kernel == GP_SE_ARD));
+  p.slots = (const unsigned short*)ctx->dDistSlots;
   p.gamma = ctx->kernel == GP_SE_ARD ? (float)(-0.5 * 1.4426950408889634) : 3.0f;
   return p;
 }
@@ -257,17 +317,34 @@ int gp_launch_pack(gp_ctx* ctx, bool want_norm) {
     p.A[pc] = (u32x4*)ctx->dXAh[pc];
     p.B[pc] = (u32x4*)ctx->dXBh[pc];
   }
+  p.DA[0] = (u32x4*)ctx->dDA[0];
+  p.DB[0] = (u32x4*)ctx->dDB[0];
+  p.CI = ctx->dCI;
+  ctx->x3_packed = false;
   int rc;
   if (want_norm && (rc = next_norm_tag(ctx, p)) < 0) return rc;
   if ((rc = launch_pack_points(ctx, p, ctx->n_pad)) < 0) return rc;
   return want_norm ? post_norm(ctx) : GP_OK;
 }
 
+// The operands on three pieces: most thetas never ask for them (n = 16384, d = 26: 12.0 us for all operands, 9 for the others).
+int gp_pack_x3(gp_ctx* ctx) {
+  if (ctx->x3_packed) return GP_OK;
+  PackArgs p = pack_args(ctx);
+  p.X = ctx->dX;
+  p.n = ctx->n;
+  p.DA[1] = (u32x4*)ctx->dDA[1];
+  p.DB[1] = (u32x4*)ctx->dDB[1];
+  const int rc = launch_pack_points(ctx, p, ctx->n_pad);
+  ctx->x3_packed = rc >= 0;
+  return rc;
+}
+
 namespace {
 inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 struct RowBufs {
-  size_t off_xb, off_b[3], total;
+  size_t off_xb, off_ci, off_db[2], total;
   int64_t m_pad;
 };
 RowBufs row_bufs(const gp_ctx* ctx, int64_t m) {
@@ -275,11 +352,41 @@ RowBufs row_bufs(const gp_ctx* ctx, int64_t m) {
   L.m_pad = (m + GP_ROW_ALIGN - 1) / GP_ROW_ALIGN * GP_ROW_ALIGN;
   size_t o = 0;
   L.off_xb = o; o += up256(((size_t)(L.m_pad / 32) * ctx->KS * 64 + GP_PACK_SLACK) * sizeof(float));
-  for (int pc = 0; pc < 3; ++pc) { L.off_b[pc] = o; o += up256((size_t)(L.m_pad / 32) * ctx->KH * 64 * 16); }
+  L.off_ci = o; o += up256((size_t)L.m_pad * sizeof(float));
+  for (int x = 0; x < 2; ++x) { L.off_db[x] = o; o += up256(gp_dist_bytes(ctx, x + 2, L.m_pad)); }
   L.total = o;
   return L;
 }
 }  // namespace
+
+// Where every slot of both layouts and sides finds its piece in a point's list: x's pieces (hi, mid, lo, d each), those of -2 gamma x,
+// those of gamma |x|^2, then 1, 15 and 0.
+int gp_dist_slots(const gp_ctx* ctx, unsigned short* slots) {
+  const bool shift = ctx->kernel == GP_SE_ARD;
+  int n = 0;
+  for (int XP = 2; XP <= 3; ++XP) {
+    const int id = dist_shape_of(XP, ctx->d, shift), G = dist_groups(XP, id);
+    const DistShape s = dist_shape(XP, id);
+    for (int side = 0; side < 2; ++side)
+      for (int g = 0; g < G; ++g)
+        for (int k = 0; k < 32; ++k) {
+          const DistSlot t = dist_slot(XP, s.Q, s.R, ctx->d, shift, side != 0, g, k);
+          const int tail = 6 * ctx->d;
+          int at = tail + 5;
+          if (t.what == DIST_X) at = (side ? 0 : 3 * ctx->d) + t.piece * ctx->d + t.comp;
+          else if (t.what == DIST_NORM) at = tail + t.piece;
+          else if (t.what == DIST_ONE) at = tail + 3;
+          else if (t.what == DIST_SHIFT) at = tail + 4;
+          if (slots) slots[n] = (unsigned short)at;
+          ++n;
+        }
+  }
+  return n;
+}
+
+size_t gp_dist_bytes(const gp_ctx* ctx, int XP, int64_t rows) {
+  return (size_t)(rows / 16) * dist_groups(XP, dist_shape_of(XP, ctx->d, ctx->kernel == GP_SE_ARD)) * 64 * 16;
+}
 
 size_t gp_pack_rows_bytes(const gp_ctx* ctx, int64_t m) { return row_bufs(ctx, m).total; }
 
@@ -290,16 +397,37 @@ int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows
   p.X = dXstar;
   p.n = m;
   p.XB = (float*)(w + L.off_xb);
-  for (int pc = 0; pc < 3; ++pc) p.B[pc] = (u32x4*)(w + L.off_b[pc]);
+  p.CI = (float*)(w + L.off_ci);
+  for (int x = 0; x < 2; ++x) rows->DB[x] = w + L.off_db[x];
+  // farther rows do not bring the path back from where the context's own points have it: with its layout first
+  if (ctx->path != GP_PATH_FP32) p.DB[ctx->XP - 2] = (u32x4*)rows->DB[ctx->XP - 2];
   int rc;
   if ((rc = next_norm_tag(ctx, p)) < 0) return rc;
   if ((rc = launch_pack_points(ctx, p, L.m_pad)) < 0) return rc;
   if ((rc = post_norm(ctx)) < 0) return rc;
   rows->m = m;
+  rows->X = dXstar;
   rows->XB = p.XB;
-  for (int pc = 0; pc < 3; ++pc) rows->XBh[pc] = p.B[pc];
-  rows->path = ctx->path == GP_PATH_FP32 ? GP_PATH_FP32 : GP_PATH_PENDING;     // farther rows do not bring it back from there
+  rows->CI = p.CI;
+  rows->gather = nullptr;
+  rows->reads_X = false;
+  rows->path = ctx->path == GP_PATH_FP32 ? GP_PATH_FP32 : GP_PATH_PENDING;
   return GP_OK;
+}
+
+// Rows that need three pieces where the context's points need two: both sides once more.  The rows are read again, under a tag of their
+// own: gp_predict waits for it before the caller may have them back.
+int gp_rows_x3(gp_ctx* ctx, KmvRows* rows) {
+  int rc = gp_pack_x3(ctx);
+  if (rc < 0 || ctx->XP == 3 || rows->gather) return rc;
+  PackArgs p = pack_args(ctx);
+  p.X = rows->X;
+  p.n = rows->m;
+  p.DB[1] = (u32x4*)rows->DB[1];
+  if ((rc = next_norm_tag(ctx, p)) < 0) return rc;
+  if ((rc = launch_pack_points(ctx, p, (rows->m + GP_ROW_ALIGN - 1) / GP_ROW_ALIGN * GP_ROW_ALIGN)) < 0) return rc;
+  rows->reads_X = true;
+  return post_norm(ctx);
 }
 
 // the product path must cover the scaled norms of both point sets

@@ -372,7 +372,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
   pk.done = nullptr;
   if (failed(hipMemcpyAsync(s.tol, htol, sizeof(float) * t, hipMemcpyHostToDevice, st))) return GP_ERR_HIP;
   hipLaunchKernelGGL(clear_units_kernel, dim3(1), dim3(256), 0, st, (u32x4*)s.flags, (int64_t)(sizeof(ColFlags) / 16 + 1));
-  if (!dX0 || t % 32 > 1) {   // U = 0, or columns that pad the last tile: operands nobody writes before the product reads them
+  if (!dX0 || padded_tiles(t)) {   // U = 0, or columns that pad the last tile: operands nobody writes before the product reads them
     int blocks = (int)((L.units + 255) / 256);
     if (blocks > 4 * ctx->num_cu) blocks = 4 * ctx->num_cu;
     if (blocks > 0) hipLaunchKernelGGL(clear_units_kernel, dim3(blocks), dim3(256), 0, st, s.VP, L.units);

@@ -93,42 +93,22 @@ __global__ __launch_bounds__(256) void sgd_init_kernel(const float* __restrict__
   }
 }
 
-// packed row operands of the batch: slot s of the batch takes the place of row s.  fp32 operands:
-// float (chunk * KS + ks) * 64 + lane belongs to row 32 chunk + lane % 32; fp16 operands: 16-byte unit
-// (chunk * KH + kh) * 64 + lane likewise.  Slots past the batch repeat slot 0 (their output rows are
-// never stored).
+// fp32 path: packed row operands of the batch, slot s of the batch in the place of row s; float (chunk * KS + ks) * 64 + lane
+// belongs to row 32 chunk + lane % 32.  Slots past the batch repeat slot 0 (their output rows are never stored).  On the
+// fp16 paths the tile kernel gathers its rows itself.
 __global__ __launch_bounds__(256) void sgd_gather_kernel(const int* __restrict__ I, int b, int b_pad, int64_t n,
-                                                         const float* __restrict__ srcXB, int KS,
-                                                         const u32x4* __restrict__ s0, const u32x4* __restrict__ s1,
-                                                         const u32x4* __restrict__ s2, int KH,
-                                                         float* __restrict__ dstXB, u32x4* __restrict__ d0,
-                                                         u32x4* __restrict__ d1, u32x4* __restrict__ d2,
+                                                         const float* __restrict__ srcXB, int KS, float* __restrict__ dstXB,
                                                          const SgdFlags* __restrict__ flags, int* __restrict__ bad) {
   if (flags->all_done) return;
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t n32 = (int64_t)(b_pad / 32) * KS * 64;
-  const int64_t n16 = (int64_t)(b_pad / 32) * KH * 64;
-  if (gid < n32) {
-    const int lane = (int)(gid & 63);
-    const int64_t q = gid >> 6;
-    const int ks = (int)(q % KS);
-    const int chunk = (int)(q / KS);
-    const int slot = 32 * chunk + (lane & 31);
-    const int idx = clamp_index(I[slot < b ? slot : 0], n, bad);
-    dstXB[gid] = srcXB[((int64_t)(idx >> 5) * KS + ks) * 64 + (lane & 32) + (idx & 31)];
-  }
-  if (gid < n16) {
-    const int lane = (int)(gid & 63);
-    const int64_t q = gid >> 6;
-    const int kh = (int)(q % KH);
-    const int chunk = (int)(q / KH);
-    const int slot = 32 * chunk + (lane & 31);
-    const int idx = clamp_index(I[slot < b ? slot : 0], n, bad);
-    const int64_t src = ((int64_t)(idx >> 5) * KH + kh) * 64 + (lane & 32) + (idx & 31);
-    d0[gid] = s0[src];
-    d1[gid] = s1[src];
-    d2[gid] = s2[src];
-  }
+  if (gid >= (int64_t)(b_pad / 32) * KS * 64) return;
+  const int lane = (int)(gid & 63);
+  const int64_t q = gid >> 6;
+  const int ks = (int)(q % KS);
+  const int chunk = (int)(q / KS);
+  const int slot = 32 * chunk + (lane & 31);
+  const int idx = clamp_index(I[slot < b ? slot : 0], n, bad);
+  dstXB[gid] = srcXB[((int64_t)(idx >> 5) * KS + ks) * 64 + (lane & 32) + (idx & 31)];
 }
 
 // On the batch rows: G = (H U)[I] - B[I] with the product's result (column-split partials summed here
@@ -352,7 +332,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct SgdLayout {
   int GW, GB, b_pad;
-  size_t off_U, off_M, off_R, off_HX, off_OUT, off_Gs, off_xb, off_h[3], off_state, off_part, off_part2, off_kmv, total;
+  size_t off_U, off_M, off_R, off_HX, off_OUT, off_Gs, off_xb, off_state, off_part, off_part2, off_kmv, total;
   size_t kmv_bytes;
 };
 
@@ -372,7 +352,6 @@ SgdLayout sgd_layout(const gp_ctx* ctx, int t, int batch) {
   const size_t arr = align_up((size_t)ctx->n * t * sizeof(float), 256);
   const size_t barr = align_up((size_t)batch * t * sizeof(float), 256);
   const size_t p32 = align_up(((size_t)(L.b_pad / 32) * ctx->KS * 64 + GP_PACK_SLACK) * sizeof(float), 256);
-  const size_t p16 = align_up((size_t)(L.b_pad / 32) * ctx->KH * 64 * 16 + 4096, 256);
   size_t o = 0;
   L.off_U = o; o += arr;
   L.off_M = o; o += arr;
@@ -381,7 +360,6 @@ SgdLayout sgd_layout(const gp_ctx* ctx, int t, int batch) {
   L.off_OUT = o; o += barr;
   L.off_Gs = o; o += barr;
   L.off_xb = o; o += p32;
-  for (int pc = 0; pc < 3; ++pc) { L.off_h[pc] = o; o += p16; }
   L.off_state = o; o += align_up(sizeof(SgdFlags) + 64 + (size_t)t * (2 * sizeof(double) + 2 * sizeof(float) + 3 * sizeof(int)) + 256, 256);
   L.off_part = o; o += align_up((size_t)G * t * sizeof(double), 256);
   L.off_part2 = o; o += align_up((size_t)G * t * sizeof(double), 256);
@@ -424,8 +402,6 @@ int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, floa
   float* OUT = (float*)(w + L.off_OUT);
   float* Gs = (float*)(w + L.off_Gs);
   float* gXB = (float*)(w + L.off_xb);
-  u32x4* gH[3];
-  for (int pc = 0; pc < 3; ++pc) gH[pc] = (u32x4*)(w + L.off_h[pc]);
   SgdDev s;
   int* bad;
   {
@@ -496,13 +472,12 @@ int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, floa
   KmvRows rows;
   rows.m = batch;
   rows.XB = gXB;
-  for (int pc = 0; pc < 3; ++pc) rows.XBh[pc] = gH[pc];
+  for (int x = 0; x < 2; ++x) rows.DB[x] = ctx->dDB[x];
+  rows.CI = ctx->dCI;
   rows.path = ctx->path;
   const float sigma2 = (float)(ctx->sigma * ctx->sigma);
   const float step = (float)(lr / (double)batch);
-  const int64_t units32 = (int64_t)(L.b_pad / 32) * ctx->KS * 64;
-  const int64_t units16 = (int64_t)(L.b_pad / 32) * ctx->KH * 64;
-  const int64_t gunits = units32 > units16 ? units32 : units16;
+  const int64_t gunits = (int64_t)(L.b_pad / 32) * ctx->KS * 64;
   int sblocks = (int)(((int64_t)batch * t + 255) / 256);
   if (sblocks > 2 * ctx->num_cu) sblocks = 2 * ctx->num_cu;
 
@@ -512,10 +487,12 @@ int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, floa
   int it = 0;
   while (!hpost->all_done && it < max_iters) {
     const int* I = dBatches + (int64_t)it * batch;
-    hipLaunchKernelGGL(sgd_gather_kernel, dim3((unsigned)((gunits + 255) / 256)), dim3(256), 0, st, I, batch, L.b_pad, n,
-                       (const float*)ctx->dXB, ctx->KS, (const u32x4*)ctx->dXBh[0], (const u32x4*)ctx->dXBh[1],
-                       (const u32x4*)ctx->dXBh[2], ctx->KH, gXB, gH[0], gH[1], gH[2], (const SgdFlags*)s.flags, bad);
-    GP_HIP(ctx, hipGetLastError());
+    if (ctx->path == GP_PATH_FP32) {
+      hipLaunchKernelGGL(sgd_gather_kernel, dim3((unsigned)((gunits + 255) / 256)), dim3(256), 0, st, I, batch, L.b_pad, n,
+                         (const float*)ctx->dXB, ctx->KS, gXB, (const SgdFlags*)s.flags, bad);
+      GP_HIP(ctx, hipGetLastError());
+    }
+    rows.gather = I;
     KmvDeferred df = {nullptr, 0, 1};
     const int rc = gp_kmv_launch(ctx, U, t, t, OUT, t, 0, kmv_scratch, L.kmv_bytes, s.colmax, &rows, &df);
     if (rc < 0) return rc;

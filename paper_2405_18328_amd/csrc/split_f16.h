@@ -14,6 +14,16 @@ constexpr float LOG2E = 1.4426950408889634f;
 constexpr int PHI_SHIFT = 15;                   // phi' = 2^15 phi <= 32768 stays inside fp16's range
 constexpr int V_TOP = 14;                       // max |V'_c| in [2^13, 2^14)
 
+// Column passes of a product with t columns: up to four tiles of 16 columns each.  A lone column past whole tiles rides
+// on the vector ALU of the first pass instead of a tile used for 1/16 of its width, where that saves a tile.
+__host__ __device__ inline int pass_tiles(int rem) { return rem > 32 ? 4 : rem > 16 ? 2 : rem > 0 ? 1 : 0; }
+__host__ __device__ inline int vec_columns(int t) { return t % 64 == 1 || t % 64 == 17 || t % 64 == 33 ? 1 : 0; }
+// whether some tile of the last pass has columns that are not there
+__host__ __device__ inline bool padded_tiles(int t) {
+  const int rem = (t - vec_columns(t)) % 64;
+  return rem != 0 && rem != 16 * pass_tiles(rem);
+}
+
 // exponent e with max = f 2^e, f in [0.5, 1); 14 for an all-zero column (scale 1)
 __device__ __forceinline__ int column_exponent(unsigned max_bits) {
   const float m = __uint_as_float(max_bits);
