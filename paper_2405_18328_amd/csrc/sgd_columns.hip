@@ -1,10 +1,11 @@
 // Stochastic gradient descent with one workgroup per column, for n <= SGD_COLUMNS_FEW_N (SGD_COLUMNS_MAX_N with one or
-// more than 64 columns) on the split-fp16 product paths: the same step, stopping rule and freezing as the streaming kernels of sgd_kernels.hip, in three
+// more than 64 columns) on the split-fp16 product paths: the same step, stopping rule and freezing as the streaming kernels of sgd_kernels.hip, in two
 // launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
-// context's packed operands; the gradient on the mini-batch rows is spread over the chip; momentum, iterate,
-// the stopping test and the packing of the iterate for the next product are per column (columns.h).
-// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: 78 -> 43 us per step (product 19.2, gradient 9.0, the rest
-// 11.0 us).  Bound by memory latency and by the 64 partial images of the product (16.6 MB written and read).
+// context's packed operands; the gradient on the mini-batch rows, momentum, iterate, the stopping test and the packing of
+// the iterate for the next product are per column (columns.h).  For large mini-batches the gradient is spread over the chip in a launch of its own.
+// Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: a solve with the streaming kernels 78 us per step, with three launches 43, with the
+// gradient in the step's launch 38 (a whole marginal-likelihood step 6.60 -> 5.90 ms).  Bound by memory latency and by the
+// partial images of the product.
 #include "columns.h"
 
 namespace {
@@ -125,13 +126,17 @@ __global__ __launch_bounds__(GS / 4 * GG) void sgdc_grad_kernel(SgdCols s, const
   if (tid == 0) s.deltas[(int64_t)c * gridDim.x + blockIdx.x] = acc;
 }
 
-// The rest of a step of one column: stopping test, momentum, iterate, the operands of the next product.
+// A step of one column behind its product.  FUSED: the gradient on the mini-batch rows first, as in sgdc_grad_kernel but by the
+// workgroup that owns the column, so that it needs neither a launch nor a way through memory: four groups of threads share the
+// images, 1024 slots at a time.  Then stopping test, momentum, iterate, the operands of the next product.
 // Q > 0: ld <= 4096 Q; momentum and iterate are in registers from the start, the gradient is scattered over the
 // column in LDS.  Q = 0: momentum and iterate are streamed, the mini-batch rows corrected afterwards and the iterate
 // read again to be packed (the column maximum is then an upper bound, all its scaling needs).
-template <int Q>
+template <int Q, bool FUSED>
 __global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __restrict__ I, int slices) {
   __shared__ float shf[16];
+  __shared__ double shd[16];
+  __shared__ f32x4 part[FUSED ? 4 : 1][FUSED ? CT / 4 : 1];
   extern __shared__ float gcol[];     // [ld], Q > 0 only
   const int c = block_column(s.t);
   if (c < 0) return;
@@ -151,8 +156,10 @@ __global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __r
         m[j] = *reinterpret_cast<const f32x4*>(s.M + col + 4 * k);
       }
     }
-    i0 = I[min(tid, s.batch - 1)];
-    g0 = s.G[gcol0 + min(tid, s.batch - 1)];
+    if constexpr (!FUSED) {
+      i0 = I[min(tid, s.batch - 1)];
+      g0 = s.G[gcol0 + min(tid, s.batch - 1)];
+    }
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
       const int k = tid + CT * j;
@@ -162,13 +169,56 @@ __global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __r
   bool go = !s.frozen[c];
   const double rr0 = s.rr[c], bn2 = s.bn2[c];
   const float tol = s.tol[c];
-  int bad = *s.bad_index ? 2 : 0;
-  double delta = 0.0;      // every wave adds up all slices
-  for (int k = tid & 63; k < slices; k += 64) delta += s.deltas[(int64_t)c * slices + k];
+  int bad = !FUSED && *s.bad_index ? 2 : 0;
+  double delta = 0.0;
+  if constexpr (!FUSED)      // every wave adds up all slices
+    for (int k = tid & 63; k < slices; k += 64) delta += s.deltas[(int64_t)c * slices + k];
   if (s.flags->all_done) return;
+  if constexpr (!FUSED) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) delta += __shfl_xor(delta, off);
-  if constexpr (Q > 0) {
+    for (int off = 32; off > 0; off >>= 1) delta += __shfl_xor(delta, off);
+  }
+  if constexpr (FUSED) {
+    if (go) {
+      const int quad = tid % (CT / 4), grp = tid / (CT / 4);
+      int outside = 0;
+      for (int slot0 = 0; slot0 < s.batch; slot0 += CT) {
+        const int slot = slot0 + tid;
+        bool mine = slot < s.batch;
+        int64_t i = 0;
+        if (mine) {
+          i = I[slot];
+          if (i < 0 || i >= s.n) outside = 1, mine = false, i = 0;
+        }
+        const float ui = s.U[col + i], bi = s.B[col + i], old = s.R[col + i];
+        const float* at = s.images + gcol0 + min(slot0 + 4 * quad, (int)s.gld - 4);
+        f32x4 h = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = grp; k < s.JS; k += 32) {
+          f32x4 v[8];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] = *reinterpret_cast<const f32x4*>(at + (int64_t)min(k + 4 * x, s.JS - 1) * s.stride);
+#pragma unroll
+          for (int x = 0; x < 8; ++x)
+            if (k + 4 * x < s.JS) h += v[x];
+        }
+        if (slot0 > 0) __syncthreads();      // the sums of the slots before are read
+        part[grp][quad] = h;
+        __syncthreads();
+        if (mine) {
+          float hx = 0.0f;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) hx += part[k][tid / 4][tid % 4];
+          const float gr = fmaf(s.sigma2, ui, hx) - bi;
+          s.R[col + i] = -gr;
+          if constexpr (Q > 0) gcol[i] = s.step * gr;
+          else s.G[gcol0 + slot] = s.step * gr;
+          delta += (double)gr * (double)gr - (double)old * (double)old;
+        }
+      }
+      delta = column_sum(delta, shd);      // with barriers behind the scatter and behind every wave's reads above
+      bad = __syncthreads_or(outside) ? 2 : 0;
+    }
+  } else if constexpr (Q > 0) {
     if (go) {
       __syncthreads();
       if (tid < s.batch && i0 >= 0 && i0 < s.n) gcol[i0] = g0;
@@ -182,7 +232,7 @@ __global__ __launch_bounds__(CT) void sgdc_step_kernel(SgdCols s, const int* __r
   if (go) {
     // Thread 0 publishes below what every thread reads above (the column's stop, and through the last arrival all_done):
     // not before all waves have read it.  The register forms have a barrier around the scatter into LDS.
-    if constexpr (Q == 0) __syncthreads();
+    if constexpr (Q == 0 && !FUSED) __syncthreads();
     double rr = rr0 + delta;
     if (rr < 0.0) rr = 0.0;
     const double rel = sqrt(rr / bn2);
@@ -295,6 +345,10 @@ Layout layout(const gp_ctx* ctx, int t, int batch) {
 
 typedef void (*step_fn)(SgdCols, const int*, int);
 
+// Up to this many rows per mini-batch the step's workgroup takes the gradient along; one compute unit per column would be
+// longer over more than it takes to spread them and launch twice.
+constexpr int SGD_FUSED_BATCH = 2048;
+
 }  // namespace
 
 bool gp_sgd_by_columns(const gp_ctx* ctx, int t) {
@@ -392,8 +446,10 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
   pk.ld = L.gld;
   pk.done = &s.flags->all_done;
   s.stride = L.gld * (int64_t)t;
-  const step_fn step = L.ld <= CROWS ? sgdc_step_kernel<1> : L.ld <= 2 * CROWS ? sgdc_step_kernel<2> : L.ld <= 4 * CROWS ? sgdc_step_kernel<4>
-                                                                                                 : sgdc_step_kernel<0>;
+  const bool fused = batch <= SGD_FUSED_BATCH;
+  const int q = L.ld <= CROWS ? 1 : L.ld <= 2 * CROWS ? 2 : L.ld <= 4 * CROWS ? 4 : 0;
+  const step_fn step = fused ? (q == 1 ? sgdc_step_kernel<1, true> : q == 2 ? sgdc_step_kernel<2, true> : q == 4 ? sgdc_step_kernel<4, true> : sgdc_step_kernel<0, true>)
+                             : (q == 1 ? sgdc_step_kernel<1, false> : q == 2 ? sgdc_step_kernel<2, false> : q == 4 ? sgdc_step_kernel<4, false> : sgdc_step_kernel<0, false>);
   const size_t lds = L.ld <= 4 * CROWS ? (size_t)L.ld * sizeof(float) : 0;
   if (lds > 48 * 1024 && failed(hipFuncSetAttribute((const void*)step, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)))
     return GP_ERR_HIP;
@@ -416,7 +472,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
       const int* I = dBatches + (int64_t)queued * batch;
       const int rc = gp_kmv_packed(ctx, t, pk, I, batch, nullptr, &s.JS);
       if (rc < 0) return drained(rc);
-      hipLaunchKernelGGL(sgdc_grad_kernel, dim3(slices, t), dim3(GS / 4 * GG), 0, st, s, I);
+      if (!fused) hipLaunchKernelGGL(sgdc_grad_kernel, dim3(slices, t), dim3(GS / 4 * GG), 0, st, s, I);
       hipLaunchKernelGGL(step, grid, block, lds, st, s, I, slices);
       if (failed(hipGetLastError())) return GP_ERR_HIP;
     }
