@@ -272,7 +272,7 @@ int gp_predict(gp_ctx* ctx, const float* dXstar, int64_t m, const float* dV, int
   const size_t kmv_bytes = (gp_kmv_rect_scratch_bytes(ctx, t, m) + 255) / 256 * 256;
   if ((rc = gp_ensure_scratch(ctx, pack_bytes + kmv_bytes)) < 0) return rc;
   KmvRows rows;
-  if ((rc = gp_pack_rows(ctx, dXstar, m, ctx->dScratch, &rows)) < 0) return rc;
+  if ((rc = gp_pack_rows(ctx, dXstar, m, ctx->dScratch, &rows, dV, ldv, t, (char*)ctx->dScratch + pack_bytes)) < 0) return rc;
   const bool settled = rows.path != GP_PATH_PENDING;
   rc = gp_kmv_launch(ctx, dV, ldv, t, dOut, ldo, 0, (char*)ctx->dScratch + pack_bytes, kmv_bytes, nullptr, &rows);
   // dXstar is the caller's again when this returns: where the path did not have to wait for its (last) packing, the call does

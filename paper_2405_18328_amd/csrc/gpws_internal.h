@@ -120,6 +120,7 @@ struct KmvRows {
   const void* DB[2];      // fp16 row operands on two and three pieces, as in the context
   const float* X;         // the points themselves, and whether a launch that reads them is behind the one their norm was posted by
   bool reads_X;
+  bool v_prepared;        // the column maxima of V are in the context's words, or its one column is in the scratch
   const float* CI;
   const int* gather;      // fp16 paths: row i is the row gather[i] of DB and CI, which hold the context's n points; NULL: i
   int path;               // GP_PATH_* to use (covers the norms of both point sets); GP_PATH_PENDING: gp_rows_path will tell
@@ -180,7 +181,8 @@ size_t gp_pack_rows_bytes(const gp_ctx* ctx, int64_t m);
 constexpr int GP_DIST_LIST_EXTRA = 6;
 int gp_dist_slots(const gp_ctx* ctx, unsigned short* slots);     // fills (or NULL: counts) the table the packing kernel works from
 size_t gp_dist_bytes(const gp_ctx* ctx, int XP, int64_t rows);   // of one side's operands of the tile pass, rows a multiple of 32
-int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows);
+// dV, kmv_scratch: as gp_kmv_launch will get them; what V needs first is prepared in the same launch (rows->v_prepared)
+int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows, const float* dV, int64_t ldv, int t, void* kmv_scratch);
 int gp_rows_path(gp_ctx* ctx, KmvRows* rows);
 int gp_rows_x3(gp_ctx* ctx, KmvRows* rows);      // operands on three pieces, of both sides
 
@@ -242,6 +244,10 @@ int gp_packed_images(const gp_ctx* ctx, int t, int64_t rows, int64_t col_chunks 
 // gather: device, nrows indices of the context's points that are the rows of the product (NULL: all n, in order)
 int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, int64_t nrows, const KmvBlock* win, int* images);
 
+int gp_colmax_blocks(const gp_ctx* ctx, int t);
+int gp_clear_maxima(gp_ctx* ctx, int t);
+bool gp_short_pack(const gp_ctx* ctx, int t);
+size_t gp_vec_column_offset(const gp_ctx* ctx, int t);     // of the vector-ALU column in the scratch of a product
 // colmax[c] = bit pattern of max_i |V_ic| for c < t, stream-ordered; optionally the same for a second
 // n x t matrix in the same launch.  cleared = true: the caller has already zeroed the output words.
 int gp_launch_colmax(gp_ctx* ctx, const float* dV, int64_t ldv, int t, unsigned* colmax, const float* dV2 = nullptr,

@@ -78,6 +78,14 @@ struct PackArgs {
   unsigned long long* max_norm;
   unsigned seq;
   int64_t n, chunk0;
+  // Work beside the packing, by workgroups from pack_blocks on (0: none): the column maxima of V [nv][t] (colmax), or a copy of its
+  // one column with zeros up to vy_rows (VY).
+  unsigned pack_blocks;
+  const float* V;
+  int64_t ldv, nv, vy_rows;
+  int t;
+  unsigned* colmax;
+  float* VY;
   const unsigned short* slots;    // per layout and side (B, A): [group][32] places in a point's list of pieces
   int d, KS, KH, is_se;
   int groups[2];
@@ -85,6 +93,13 @@ struct PackArgs {
 };
 __global__ __launch_bounds__(256) void pack_points_kernel(PackArgs p) {
   extern __shared__ float xs[];        // [32][ds] rows, then 32 norms, then their maximum
+  if (p.pack_blocks && blockIdx.x >= p.pack_blocks) {
+    const int block = (int)(blockIdx.x - p.pack_blocks), blocks = (int)(gridDim.x - p.pack_blocks);
+    if (p.colmax) column_maxima(p.V, p.ldv, p.nv, p.t, block, blocks, reinterpret_cast<unsigned*>(xs), p.colmax);
+    else
+      for (int64_t i = (int64_t)block * 256 + threadIdx.x; i < p.vy_rows; i += (int64_t)blocks * 256) p.VY[i] = i < p.nv ? p.V[i * p.ldv] : 0.0f;
+    return;
+  }
   const int d = p.d, ds = d | 1;
   float* norm = xs + 32 * ds;
   unsigned* top = reinterpret_cast<unsigned*>(norm + 32);
@@ -239,14 +254,18 @@ int gp_launch_column_means(gp_ctx* ctx) {
 
 namespace {
 
-int launch_pack_points(gp_ctx* ctx, PackArgs& p, int64_t n_pad) {
-  const size_t lds = sizeof(float) * (32 * (size_t)(p.d | 1) + 33) + 32 * sizeof(_Float16) * ((6 * (size_t)p.d + GP_DIST_LIST_EXTRA) | 1);
+// beside: workgroups for the work beside it, in the first launch
+int launch_pack_points(gp_ctx* ctx, PackArgs& p, int64_t n_pad, int beside = 0) {
+  size_t lds = sizeof(float) * (32 * (size_t)(p.d | 1) + 33) + 32 * sizeof(_Float16) * ((6 * (size_t)p.d + GP_DIST_LIST_EXTRA) | 1);
+  if (beside && p.colmax && lds < sizeof(unsigned) * p.t) lds = sizeof(unsigned) * p.t;
   // all chunks in one launch would be more than the 2^32 threads it may have from 2^29 points on.  (Workgroups that walk over several
   // chunks instead cost the usual sizes time: n = 500000, d = 3 41 -> 52 us for a gp_set_theta.)
   constexpr int64_t MOST = 1 << 20;
   for (p.chunk0 = 0; p.chunk0 < n_pad / 32; p.chunk0 += MOST) {
     const int64_t left = n_pad / 32 - p.chunk0;
-    hipLaunchKernelGGL(pack_points_kernel, dim3((unsigned)(left < MOST ? left : MOST)), dim3(256), lds, ctx->stream, p);
+    const unsigned pack = (unsigned)(left < MOST ? left : MOST), more = p.chunk0 == 0 ? (unsigned)beside : 0u;
+    p.pack_blocks = more ? pack : 0u;
+    hipLaunchKernelGGL(pack_points_kernel, dim3(pack + more), dim3(256), lds, ctx->stream, p);
     GP_HIP(ctx, hipGetLastError());
   }
   return GP_OK;
@@ -390,7 +409,7 @@ size_t gp_dist_bytes(const gp_ctx* ctx, int XP, int64_t rows) {
 
 size_t gp_pack_rows_bytes(const gp_ctx* ctx, int64_t m) { return row_bufs(ctx, m).total; }
 
-int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows) {
+int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows, const float* dV, int64_t ldv, int t, void* kmv_scratch) {
   const RowBufs L = row_bufs(ctx, m);
   char* w = (char*)buf;
   PackArgs p = pack_args(ctx);
@@ -401,9 +420,26 @@ int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows
   for (int x = 0; x < 2; ++x) rows->DB[x] = w + L.off_db[x];
   // farther rows do not bring the path back from where the context's own points have it: with its layout first
   if (ctx->path != GP_PATH_FP32) p.DB[ctx->XP - 2] = (u32x4*)rows->DB[ctx->XP - 2];
-  int rc;
+  int rc, beside = 0;
+  // What V needs first has nothing to do with the rows: it goes along with their packing instead of into a launch behind it
+  rows->v_prepared = ctx->path != GP_PATH_FP32 && !gp_short_pack(ctx, t);
+  if (rows->v_prepared) {
+    p.V = dV;
+    p.ldv = ldv;
+    p.nv = ctx->n;
+    p.t = t;
+    if (t > 1) {
+      if ((rc = gp_clear_maxima(ctx, t)) < 0) return rc;
+      p.colmax = ctx->dColmax;
+      beside = gp_colmax_blocks(ctx, t);
+    } else {
+      p.VY = (float*)((char*)kmv_scratch + gp_vec_column_offset(ctx, t));
+      p.vy_rows = (ctx->n + 31) / 32 * 32;
+      beside = (int)((p.vy_rows + 1023) / 1024 < ctx->num_cu ? (p.vy_rows + 1023) / 1024 : ctx->num_cu);
+    }
+  }
   if ((rc = next_norm_tag(ctx, p)) < 0) return rc;
-  if ((rc = launch_pack_points(ctx, p, L.m_pad)) < 0) return rc;
+  if ((rc = launch_pack_points(ctx, p, L.m_pad, beside)) < 0) return rc;
   if ((rc = post_norm(ctx)) < 0) return rc;
   rows->m = m;
   rows->X = dXstar;

@@ -474,6 +474,7 @@ int gp_sgd_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* dX0, floa
   rows.XB = gXB;
   for (int x = 0; x < 2; ++x) rows.DB[x] = ctx->dDB[x];
   rows.CI = ctx->dCI;
+  rows.reads_X = rows.v_prepared = false;
   rows.path = ctx->path;
   const float sigma2 = (float)(ctx->sigma * ctx->sigma);
   const float step = (float)(lr / (double)batch);

@@ -33,6 +33,40 @@ __device__ __forceinline__ int column_exponent(unsigned max_bits) {
   return e < -60 ? -60 : e;
 }
 
+// colmax[c] = max_i |V_ic| as a bit pattern (non-negative floats order like unsigned ints), block's share of the rows, for
+// workgroups of 256 threads; smax: t words of LDS
+__device__ __forceinline__ void column_maxima(const float* __restrict__ V, int64_t ldv, int64_t n, int t, int block, int blocks,
+                                              unsigned* smax, unsigned* __restrict__ colmax) {
+  // a thread keeps one column (per group of 256 columns) and walks rows: consecutive threads read
+  // consecutive columns of a row, the running maximum stays in a register
+  for (int c = threadIdx.x; c < t; c += 256) smax[c] = 0u;
+  __syncthreads();
+  const int64_t rows_per_block = (n + blocks - 1) / blocks;
+  const int64_t r0 = (int64_t)block * rows_per_block;
+  const int64_t r1 = min(n, r0 + rows_per_block);
+  const int tw = t < 256 ? t : 256;        // columns handled side by side
+  const int lanes = 256 / tw;              // rows handled side by side
+  const int cl = threadIdx.x % tw, rl = threadIdx.x / tw;
+  if (rl < lanes) {
+    for (int c = cl; c < t; c += tw) {
+      float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, m3 = 0.0f;
+      int64_t i = r0 + rl;
+      for (; i + 3 * lanes < r1; i += 4 * lanes) {
+        m0 = fmaxf(m0, fabsf(V[i * ldv + c]));
+        m1 = fmaxf(m1, fabsf(V[(i + lanes) * ldv + c]));
+        m2 = fmaxf(m2, fabsf(V[(i + 2 * lanes) * ldv + c]));
+        m3 = fmaxf(m3, fabsf(V[(i + 3 * lanes) * ldv + c]));
+      }
+      for (; i < r1; i += lanes) m0 = fmaxf(m0, fabsf(V[i * ldv + c]));
+      m0 = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
+      atomicMax(&smax[c], __float_as_uint(m0));
+    }
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < t; c += 256)
+    if (smax[c]) atomicMax(&colmax[c], smax[c]);
+}
+
 // two values as fp16 halves of a word, rounded to nearest
 __device__ __forceinline__ unsigned pack_f16(float a, float b) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));

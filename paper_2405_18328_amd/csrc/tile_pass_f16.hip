@@ -6,45 +6,13 @@
 namespace {
 
 // ---- per-call operand preparation -------------------------------------------------------------
-// colmax[c] = max_i |V_ic| as a bit pattern (non-negative floats order like unsigned ints)
-// blockIdx.y = 1 does the same for a second matrix of the same shape.
+// colmax[c] = max_i |V_ic|; blockIdx.y = 1 does the same for a second matrix of the same shape.
 __global__ __launch_bounds__(256) void colmax_kernel(const float* __restrict__ V, int64_t ldv,
                                                      const float* __restrict__ V2, int64_t ldv2, int64_t n, int t,
                                                      unsigned* __restrict__ colmax, unsigned* __restrict__ colmax2) {
-  if (blockIdx.y) {
-    V = V2;
-    ldv = ldv2;
-    colmax = colmax2;
-  }
-  // a thread keeps one column (per group of 256 columns) and walks rows: consecutive threads read
-  // consecutive columns of a row, the running maximum stays in a register
   extern __shared__ unsigned smax[];   // [t]
-  for (int c = threadIdx.x; c < t; c += 256) smax[c] = 0u;
-  __syncthreads();
-  const int64_t rows_per_block = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-  const int64_t r1 = min(n, r0 + rows_per_block);
-  const int tw = t < 256 ? t : 256;        // columns handled side by side
-  const int lanes = 256 / tw;              // rows handled side by side
-  const int cl = threadIdx.x % tw, rl = threadIdx.x / tw;
-  if (rl < lanes) {
-    for (int c = cl; c < t; c += tw) {
-      float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, m3 = 0.0f;
-      int64_t i = r0 + rl;
-      for (; i + 3 * lanes < r1; i += 4 * lanes) {
-        m0 = fmaxf(m0, fabsf(V[i * ldv + c]));
-        m1 = fmaxf(m1, fabsf(V[(i + lanes) * ldv + c]));
-        m2 = fmaxf(m2, fabsf(V[(i + 2 * lanes) * ldv + c]));
-        m3 = fmaxf(m3, fabsf(V[(i + 3 * lanes) * ldv + c]));
-      }
-      for (; i < r1; i += lanes) m0 = fmaxf(m0, fabsf(V[i * ldv + c]));
-      m0 = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
-      atomicMax(&smax[c], __float_as_uint(m0));
-    }
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < t; c += 256)
-    if (smax[c]) atomicMax(&colmax[c], smax[c]);
+  if (blockIdx.y) column_maxima(V2, ldv2, n, t, blockIdx.x, gridDim.x, smax, colmax2);
+  else column_maxima(V, ldv, n, t, blockIdx.x, gridDim.x, smax, colmax);
 }
 
 // zeroes t words of one or two arrays (a kernel, not a memset command: memset nodes recorded into a
@@ -378,16 +346,34 @@ int gp_column_splits(int64_t row_blocks, int64_t chunks, int num_cu, int per_cu,
   return best;
 }
 
+// few workgroups: every one ends with t atomic maxima on the same t words
+int gp_colmax_blocks(const gp_ctx* ctx, int t) {
+  int blocks = (int)((ctx->n * (int64_t)t + 8191) / 8192);
+  if (blocks > 2 * ctx->num_cu) blocks = 2 * ctx->num_cu;
+  return blocks < 1 ? 1 : blocks;
+}
+
+// makes the context's words for column maxima in accumulation clear, for t columns
+int gp_clear_maxima(gp_ctx* ctx, int t) {
+  if (ctx->colmax_dirty) {
+    hipLaunchKernelGGL(clear_words_kernel, dim3((ctx->colmax_dirty + 255) / 256), dim3(256), 0, ctx->stream, ctx->dColmax, nullptr, ctx->colmax_dirty);
+    GP_HIP(ctx, hipGetLastError());
+  }
+  if (ctx->colmax_dirty < t) ctx->colmax_dirty = t;     // until the launch that clears them is on the stream
+  return GP_OK;
+}
+
+// operands of a short V are packed, maxima and all, in one launch
+bool gp_short_pack(const gp_ctx* ctx, int t) { return t > 1 && ctx->n <= 8192 && t - vec_columns(t) <= 64; }
+size_t gp_vec_column_offset(const gp_ctx* ctx, int t) { return scratch_layout(ctx, t, 1, 1).off_vy; }
+
 int gp_launch_colmax(gp_ctx* ctx, const float* dV, int64_t ldv, int t, unsigned* cm, const float* dV2, int64_t ldv2,
                      unsigned* cm2, bool cleared) {
   if (!cleared) {
     hipLaunchKernelGGL(clear_words_kernel, dim3((t + 255) / 256), dim3(256), 0, ctx->stream, cm, dV2 ? cm2 : nullptr, t);
     GP_HIP(ctx, hipGetLastError());
   }
-  // few workgroups: every one ends with t atomic maxima on the same t words
-  int blocks = (int)((ctx->n * (int64_t)t + 8191) / 8192);
-  if (blocks > 2 * ctx->num_cu) blocks = 2 * ctx->num_cu;
-  if (blocks < 1) blocks = 1;
+  const int blocks = gp_colmax_blocks(ctx, t);
   hipLaunchKernelGGL(colmax_kernel, dim3(blocks, dV2 ? 2 : 1), dim3(256), (size_t)t * sizeof(unsigned), ctx->stream, dV,
                      ldv, dV2, ldv2, ctx->n, t, cm, cm2);
   GP_HIP(ctx, hipGetLastError());
@@ -428,18 +414,13 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   // context that are zero between calls, copied by the first packing and zeroed again by the first tile pass; on the static
   // scratch in words of that scratch, cleared by a launch of their own: a captured gp_kmv_static may run beside other calls
   const bool y = vec_columns(t) != 0;
-  const bool small = !colmax_ready && !win && t > 1 && ctx->n <= 8192 && t - (y ? 1 : 0) <= 64;
+  const bool small = !colmax_ready && !win && gp_short_pack(ctx, t);
   const bool maxima = !colmax_ready && t > 1 && !small;       // a single vector is not scaled
   const bool accumulate = maxima && scratch != ctx->static_scratch;
   if (maxima) {
-    if (accumulate) {
-      if (ctx->colmax_dirty) {
-        hipLaunchKernelGGL(clear_words_kernel, dim3((ctx->colmax_dirty + 255) / 256), dim3(256), 0, st, ctx->dColmax, nullptr, ctx->colmax_dirty);
-        GP_HIP(ctx, hipGetLastError());
-      }
-      if (ctx->colmax_dirty < t) ctx->colmax_dirty = t;     // until the launch that clears them is on the stream
-    }
-    const int rc = gp_launch_colmax(ctx, dV, ldv, t, accumulate ? ctx->dColmax : (unsigned*)(w + L.off_colmax), nullptr, 0, nullptr, accumulate);
+    int rc = accumulate && !(rows && rows->v_prepared) ? gp_clear_maxima(ctx, t) : GP_OK;
+    if (rc >= 0 && !(rows && rows->v_prepared))
+      rc = gp_launch_colmax(ctx, dV, ldv, t, accumulate ? ctx->dColmax : (unsigned*)(w + L.off_colmax), nullptr, 0, nullptr, accumulate);
     if (rc < 0) return rc;
   }
 
@@ -470,7 +451,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   bool packed = false;
   if (rows && rows->path == GP_PATH_PENDING) {
     const int c = y ? 1 : 0, NT = pass_tiles(t - c);
-    int rc = pack_pass(NT, c, t - c < 16 * NT ? t - c : 16 * NT, y ? 0 : -1, true);
+    int rc = t == 1 && rows->v_prepared ? GP_OK : pack_pass(NT, c, t - c < 16 * NT ? t - c : 16 * NT, y ? 0 : -1, true);
     if (rc < 0 || (rc = gp_rows_path(ctx, rows)) < 0) return rc;
     if (rows->path == GP_PATH_FP32) return GP_TO_FP32;
     packed = true;
