@@ -125,11 +125,18 @@ __global__ __launch_bounds__(1024) void pack_small_kernel(const float* __restric
 // OUT = (add: OUT +) sum of the partial images, in order.  A chain of dependent loads bounded it (one element per thread, one image
 // after the other); now four consecutive elements per thread, eight images fetched at a time.  With the clearing launch
 // of the column maxima gone, gp_predict n = 13500, m = 1500, t = 65: 79 -> 70 us; n = 41157, m = 4573, t = 1: 85 -> 78 us.
+// GR > 1: that many groups of threads share the images of an element, a run of consecutive ones each, for the many images of few
+// elements: n = 41157, m = 4573, t = 1 (28 images, 4573 elements) 6.2 -> 4.6 us a launch.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int GR>
 __global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __restrict__ part, int64_t split_stride, int JS, int64_t n,
                                                              int t, int add, float* __restrict__ out, int64_t ldo) {
+  constexpr int Q = 256 / GR;        // quads of elements per workgroup
+  __shared__ f32x4 sums[GR][Q];
+  const int quad = threadIdx.x % Q, g = threadIdx.x / Q;
   const int64_t total = n * t;
-  for (int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; e < total; e += (int64_t)gridDim.x * 1024) {
+  for (int64_t e0 = (int64_t)blockIdx.x * Q * 4; e0 < total; e0 += (int64_t)gridDim.x * Q * 4) {
+    const int64_t e = e0 + 4 * quad;
     f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
     const int64_t at = e + 4 <= total || total < 4 ? e : total - 4;     // the last thread loads its neighbour's too
     auto each = [&](auto f) {       // this thread's elements
@@ -144,21 +151,31 @@ __global__ __launch_bounds__(256) void kmv_reduce_f16_kernel(const float* __rest
         }
       }
     };
-    if (add) each([&](int q, const float* o) { s[q] = *o; });
+    if (GR == 1 && add && e < total) each([&](int q, const float* o) { s[q] = *o; });
+    const int per = (JS + GR - 1) / GR, k0 = g * per, k1 = min(JS, k0 + per);
     if (total >= 4) {
-      for (int k = 0; k < JS; k += 8) {
+      for (int k = k0; k < k1; k += 8) {
         f32x4 v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f4u*>(part + (int64_t)min(k + u, JS - 1) * split_stride + at);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-          if (k + u < JS) s += v[u];
+          if (k + u < k1) s += v[u];
       }
-    } else {
+    } else if (e < total) {
       for (int q = 0; q < (int)total; ++q)
-        for (int k = 0; k < JS; ++k) s[q] += part[(int64_t)k * split_stride + q];
+        for (int k = k0; k < k1; ++k) s[q] += part[(int64_t)k * split_stride + q];
     }
-    each([&](int q, float* o) { *o = s[q]; });
+    if constexpr (GR > 1) {
+      sums[g][quad] = s;
+      __syncthreads();
+      if (g == 0) {
+#pragma unroll
+        for (int k = 1; k < GR; ++k) s += sums[k][quad];
+      }
+      __syncthreads();
+    }
+    if (g == 0 && e < total) each([&](int q, float* o) { *o = s[q]; });
   }
 }
 
@@ -502,9 +519,12 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
   a.diag_shift = 0;
 
   auto sum_images_of = [&](int64_t m, int width, bool add, float* out) {     // out = the sum of the images of m rows
-    int blocks = (int)((m * width + 1023) / 1024);
+    // the sums of a square product run in one order, whatever its images are cut into (gp_kmv_static)
+    const bool share = rows && a.JS >= 16 && m * width <= 65536;
+    const int64_t per = share ? 128 : 1024;
+    int blocks = (int)((m * width + per - 1) / per);
     if (blocks > 8 * ctx->num_cu) blocks = 8 * ctx->num_cu;
-    hipLaunchKernelGGL(kmv_reduce_f16_kernel, dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, a.JS, m, width, add ? 1 : 0,
+    hipLaunchKernelGGL((share ? kmv_reduce_f16_kernel<8> : kmv_reduce_f16_kernel<1>), dim3(blocks), dim3(256), 0, st, (const float*)part, a.split_stride, a.JS, m, width, add ? 1 : 0,
                        out, ldo);
   };
   int vcol = y ? 0 : -1;
