@@ -9,7 +9,7 @@
 #include "../../include/gpws.h"
 
 // ---------------------------------------------------------------------------
-// Geometry of the tile pass.  A wavefront (64 lanes) owns MI sub-tiles of 32
+// Geometry of the fp32 tile pass.  A wavefront (64 lanes) owns MI sub-tiles of 32
 // rows i and walks over the columns j in chunks of 32; one 32x32 tile of
 // pairs is one v_mfma_f32_32x32x2_f32 accumulator (16 VGPRs per lane).
 // ---------------------------------------------------------------------------
@@ -48,6 +48,7 @@ constexpr size_t GP_PIN_POST = 32768;     // flags the solvers' finalise kernels
 struct SplitMemo {
   int64_t rows, chunks;
   int t, XP, JS, CG;
+  bool wide;
 };
 
 struct gp_ctx {

@@ -62,10 +62,12 @@ constexpr int stage_chunks(int DS, int XP, int NT, bool y, int per_cu) {
     if (2 * per_cu * (c * chunk_units(DS, XP, NT) + (y ? 64 : 0)) * 16 <= LDS_BYTES) return c;
   return 1;
 }
-// Which kernel: four row tiles per wave, or two with this many waves per SIMD.  Four pay with 64 columns, where they halve the operands read
-// from LDS, and fit up to four groups of operands per tile.  With fewer columns two row tiles are as fast and cut rows finer: n = 43945, d = 20,
-// t = 17 (Matern) 625 us a product against 729, n = 65536, d = 11, t = 33 1517 against 1539.
+// Which kernel: four row tiles per wave, or two with this many waves per SIMD.  Four pay with 64 columns in long products (plan_h), where
+// they halve the operands read from LDS, and fit up to four groups of operands per tile.  With fewer columns two row tiles are as fast and
+// cut rows finer: n = 43945, d = 20, t = 17 (Matern) 625 us a product against 729, n = 65536, d = 11, t = 33 1517 against 1539.
 constexpr bool wide_tiles(int DS, int XP, int NT) { return NT == 4 && dist_groups(XP, DS) <= 4; }
+// which of those are built once per form
+constexpr bool wide_per_form(int DS, int XP) { return DS <= (XP == 2 ? 3 : 2); }
 constexpr int tile_waves(int DS, int XP, int NT) {
   return NT == 0 && dist_groups(XP, DS) <= 2 ? 8 : dist_groups(XP, DS) <= (NT == 0 ? 6 : 4) && NT < 4 ? 4 : 2;
 }
@@ -73,10 +75,10 @@ constexpr int tile_waves(int DS, int XP, int NT) {
 typedef void (*tileh_fn)(TileArgsH);
 
 // The kernel for operands of shape ds (dist_f16.h) and NT column tiles; y: with the vector-ALU column.  One translation unit for each
-// kind of kernel function and number of pieces, which compile side by side.
-tileh_fn gp_tile_se_x2(int ds, int NT, bool y, int form);
-tileh_fn gp_tile_se_x3(int ds, int NT, bool y, int form);
-tileh_fn gp_tile_matern32_x2(int ds, int NT, bool y, int form);
-tileh_fn gp_tile_matern32_x3(int ds, int NT, bool y, int form);
+// kind of kernel function and number of pieces, which compile side by side.  wide: with four row tiles where wide_tiles says there are.
+tileh_fn gp_tile_se_x2(int ds, int NT, bool y, int form, bool wide);
+tileh_fn gp_tile_se_x3(int ds, int NT, bool y, int form, bool wide);
+tileh_fn gp_tile_matern32_x2(int ds, int NT, bool y, int form, bool wide);
+tileh_fn gp_tile_matern32_x3(int ds, int NT, bool y, int form, bool wide);
 
 #endif

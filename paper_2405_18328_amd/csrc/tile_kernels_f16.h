@@ -446,8 +446,8 @@ tileh_fn pick_wide_form(int form) {
 // Shapes of few dimensions are built once per form: in one kernel with everything in it the 64-column one keeps 10 registers in
 // scratch memory (d = 26).
 template <int KIND, int DS, int XP, bool Y>
-tileh_fn pick_nt(int NT, int form) {
-  constexpr bool FEW = DS <= (XP == 2 ? 3 : 2);
+tileh_fn pick_nt(int NT, int form, bool wide) {
+  constexpr bool FEW = wide_per_form(DS, XP);
   if (NT == 1) {
     if constexpr (DS <= 2) return pick_form<KIND, DS, XP, 1, Y>(form);
     else return kmv_tile_f16_kernel<KIND, DS, XP, 1, Y, FORM_ANY>;
@@ -456,18 +456,19 @@ tileh_fn pick_nt(int NT, int form) {
     if constexpr (DS <= 2) return pick_form<KIND, DS, XP, 2, Y>(form);
     else return kmv_tile_f16_kernel<KIND, DS, XP, 2, Y, FORM_ANY>;
   }
+  if (!wide) return kmv_tile_f16_kernel<KIND, DS, XP, 4, Y, FORM_ANY>;
   if constexpr (FEW) return pick_wide_form<KIND, DS, XP, Y>(form);
   else if constexpr (wide_tiles(DS, XP, 4)) return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_ANY>;
   else return kmv_tile_f16_kernel<KIND, DS, XP, 4, Y, FORM_ANY>;
 }
 
 template <int KIND, int XP, int DS = 1>
-tileh_fn pick_shape(int ds, int NT, bool y, int form) {
+tileh_fn pick_shape(int ds, int NT, bool y, int form, bool wide) {
   if (ds == DS) {
     if (NT == 0) return kmv_tile_f16_kernel<KIND, DS, XP, 0, true, FORM_ANY>;
-    return y ? pick_nt<KIND, DS, XP, true>(NT, form) : pick_nt<KIND, DS, XP, false>(NT, form);
+    return y ? pick_nt<KIND, DS, XP, true>(NT, form, wide) : pick_nt<KIND, DS, XP, false>(NT, form, wide);
   }
-  if constexpr (DS < (XP == 2 ? DIST_SHAPES_X2 : DIST_SHAPES_X3)) return pick_shape<KIND, XP, DS + 1>(ds, NT, y, form);
+  if constexpr (DS < (XP == 2 ? DIST_SHAPES_X2 : DIST_SHAPES_X3)) return pick_shape<KIND, XP, DS + 1>(ds, NT, y, form, wide);
   else return nullptr;
 }
 

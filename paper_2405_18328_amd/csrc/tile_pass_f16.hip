@@ -184,26 +184,30 @@ struct TileKernelH {
   tileh_fn fn;
   int rows;                // of its waves
   int per_cu;              // workgroups that share a compute unit
+  bool wide;               // four row tiles per wave
   int most_cg;             // most waves that can share their rows: chunks of a stage
   double chunk_us;         // about what a chunk takes a compute unit for a workgroup whose waves have rows of their own
   double stream_us;        // and what bringing it from L2 takes
+  double start_us;         // what its launch takes more than that of a kernel with two row tiles
   int rows_per_wg(int cg) const { return rows * TILE_WAVES / cg; }
 };
 
 // form: FORM_PLAIN .. FORM_WINDOW (the shape does not depend on it)
-TileKernelH tile_kernel_h(const gp_ctx* ctx, int XP, int NT, bool y, int form) {
+TileKernelH tile_kernel_h(const gp_ctx* ctx, int XP, int NT, bool y, int form, bool most_rows) {
   TileKernelH k;
   const bool se = ctx->kernel == GP_SE_ARD;
   const int ds = dist_shape_of(XP, ctx->d, se), G = dist_groups(XP, ds);
-  const bool wide = wide_tiles(ds, XP, NT);
+  const bool wide = most_rows && wide_tiles(ds, XP, NT);
   auto* pick = XP == 2 ? (se ? gp_tile_se_x2 : gp_tile_matern32_x2) : se ? gp_tile_se_x3 : gp_tile_matern32_x3;
-  k.fn = pick(ds, NT, y, form);
+  k.fn = pick(ds, NT, y, form, wide);
+  k.wide = wide;
   k.rows = wide ? 64 : 32;
   k.per_cu = wide ? 1 : tile_waves(ds, XP, NT) / 2;
   k.most_cg = stage_chunks(ds, XP, NT, y, k.per_cu);
   // per 32x32 tile and SIMD, as measured: the vector work of phi and 14 ns per unit of matrix work (32x32 pairs, 16 slots or columns)
   const double tile_us = (se ? 0.145 : 0.23) + 0.014 * (2 * dist_products(XP, ds) + 3 * NT);
-  k.chunk_us = tile_us * k.rows / 32 * TILE_WAVES / 4;
+  k.chunk_us = tile_us * (wide_tiles(ds, XP, NT) && !wide ? 1.12 : 1.0) * k.rows / 32 * TILE_WAVES / 4;
+  k.start_us = !wide ? 0.0 : wide_per_form(ds, XP) ? 5.0 : 7.0;
   k.stream_us = (2 * G + 2 * NT) / 25.0;
   return k;
 }
@@ -214,6 +218,7 @@ dim3 tile_grid(const TileArgsH& a) { return dim3((unsigned)(((int64_t)a.row_bloc
 struct PlanH {
   int JS, cps;     // column-range splits, chunks per split
   int CG;          // waves of a workgroup that share its rows
+  bool wide;       // four row tiles per wave where there is such a kernel
 };
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -245,11 +250,11 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
     if (m.JS && m.rows == rows && m.chunks == chunks && m.t == t && m.XP == XP) {
       pl.JS = m.JS;
       pl.CG = m.CG;
+      pl.wide = m.wide;
       pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
       return pl;
     }
   const int y = vec_columns(t);
-  const TileKernelH k = tile_kernel_h(ctx, XP, pass_tiles(t - y), y, FORM_PLAIN);
   // a partial image is written and read once, at about 4 TB/s
   const double image = (double)rows * t * sizeof(float);
   // images of more than 2 GB in all would not pay for their memory
@@ -258,19 +263,33 @@ PlanH plan_h(const gp_ctx* ctx, int64_t rows, int64_t col_chunks, int t, int XP)
   // Up to 128 columns are never cut: there is nothing to gain, and such a product gives a row the same bits whatever rows are beside it.
   constexpr int MIN_CHUNKS = 4;
   double best = 1e300;
-  for (int cg = 1; cg <= (chunks > MIN_CHUNKS ? k.most_cg : 1); cg *= 2) {
-    const int64_t row_blocks = (rows + k.rows_per_wg(cg) - 1) / k.rows_per_wg(cg);
-    double cost;
-    const int js = gp_column_splits(row_blocks, chunks, ctx->num_cu, k.per_cu, cg, k.chunk_us, k.stream_us, 2.0 * image / 4.0e6, chunks > MIN_CHUNKS ? max_js : 1, &cost);
-    if (cost < best * (1.0 - 1e-9)) {
-      best = cost;
-      pl.JS = js;
-      pl.CG = cg;
+  // Of the two kernels for 64 columns the one with two row tiles has half the code and half the rows to fetch, set up and write, the one
+  // with four reads half the operands per pair.  One product, four row tiles -> two: n = 1000, t = 65 (Matern), d = 26 22.1 -> 16.2 us,
+  // d = 50 28.0 -> 16.7; n = 4000 32.2 -> 28.6, 44.8 -> 30.0; n = 9000 72 -> 69, 87 -> 74; n = 14000 128 -> 137, 151 -> 148; n = 30000
+  // 475 -> 504, 542 -> 564.
+  const int first = pass_tiles(t - y);
+  int tiles = first;
+  for (int c = y + 16 * first; c < t; c += 16 * pass_tiles(t - c)) tiles += pass_tiles(t - c);
+  const double image_us = 2.0 * image / 4.0e6 * (first ? (double)first / tiles : 1.0);     // against the time of the first pass
+  for (int w = 0; w < 2; ++w) {
+    const TileKernelH k = tile_kernel_h(ctx, XP, first, y, FORM_PLAIN, w == 1);
+    if (w == 1 && (!k.wide || chunks <= MIN_CHUNKS)) continue;
+    for (int cg = 1; cg <= (chunks > MIN_CHUNKS ? k.most_cg : 1); cg *= 2) {
+      const int64_t row_blocks = (rows + k.rows_per_wg(cg) - 1) / k.rows_per_wg(cg);
+      double cost;
+      const int js = gp_column_splits(row_blocks, chunks, ctx->num_cu, k.per_cu, cg, k.chunk_us, k.stream_us, image_us, chunks > MIN_CHUNKS ? max_js : 1, &cost);
+      cost += k.start_us;
+      if (cost < best * (1.0 - 1e-9)) {
+        best = cost;
+        pl.JS = js;
+        pl.CG = cg;
+        pl.wide = w == 1;
+      }
     }
   }
   pl.cps = (int)((chunks + pl.JS - 1) / pl.JS);
   gp_ctx* memo = const_cast<gp_ctx*>(ctx);   // a context belongs to one host thread at a time
-  memo->split_memo[memo->split_next] = SplitMemo{rows, chunks, t, XP, pl.JS, pl.CG};
+  memo->split_memo[memo->split_next] = SplitMemo{rows, chunks, t, XP, pl.JS, pl.CG, pl.wide};
   memo->split_next = (memo->split_next + 1) % 4;
   return pl;
 }
@@ -294,7 +313,7 @@ size_t panel_images_at(const ScratchH& L, int group, const PlanH& pl) {
 // n = 200000 d = 5 24.2 -> 20.7 ms (19.6), n = 240000 d = 5 28.4 -> 29.8 ms (26.8).
 PanelsH plan_panels(const gp_ctx* ctx, int64_t nrows, int t, int XP, const PlanH& pl, const ScratchH& L, size_t scratch_bytes) {
   const int y = vec_columns(t);
-  const TileKernelH k = tile_kernel_h(ctx, XP, pass_tiles(t - y), y, FORM_PLAIN);
+  const TileKernelH k = tile_kernel_h(ctx, XP, pass_tiles(t - y), y, FORM_PLAIN, pl.wide);
   const int64_t unit = PANEL_ROWS / k.rows_per_wg(pl.CG), slots = (int64_t)k.per_cu * ctx->num_cu;
   const int64_t units = (nrows + PANEL_ROWS - 1) / PANEL_ROWS;
   const size_t per_unit = (size_t)(t < 65 ? t : 65) * sizeof(float) * PANEL_ROWS;     // images of the columns of one pass
@@ -545,7 +564,7 @@ int gp_kmv_launch_f16(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* d
     packed = false;
     a.clear = accumulate && first_pass ? ctx->dColmax : nullptr;
     a.clear_n = t;
-    const TileKernelH k = tile_kernel_h(ctx, XP, NT, a.vcol >= 0, a.gather ? FORM_ANY : FORM_PLAIN);
+    const TileKernelH k = tile_kernel_h(ctx, XP, NT, a.vcol >= 0, a.gather ? FORM_ANY : FORM_PLAIN, pl.wide);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for d=%d", ctx->d);
     const int col = a.vcol >= 0 ? a.vcol : a.col0, width = a.ncols + (a.vcol >= 0 ? 1 : 0);   // the pass's columns
     const int64_t panel = pn.rows ? pn.rows : nrows;
@@ -656,7 +675,7 @@ int gp_kmv_packed(gp_ctx* ctx, int t, const KmvPacked& pk, const int* gather, in
     a.ncols = rem < 16 * NT ? rem : 16 * NT;
     a.vcol = vcol;
     vcol = -1;
-    const TileKernelH k = tile_kernel_h(ctx, ctx->XP, NT, a.vcol >= 0, gather ? FORM_GATHER : win ? FORM_WINDOW : FORM_COLUMNS);
+    const TileKernelH k = tile_kernel_h(ctx, ctx->XP, NT, a.vcol >= 0, gather ? FORM_GATHER : win ? FORM_WINDOW : FORM_COLUMNS, pl.wide);
     if (!k.fn) return gp_fail(ctx, GP_ERR_ARG, "gp_kmv: no fp16 kernel for d=%d", ctx->d);
     a.row_blocks = (int)((nrows + k.rows_per_wg(pl.CG) - 1) / k.rows_per_wg(pl.CG));
     const dim3 grid = tile_grid(a);

@@ -1,4 +1,4 @@
 // Tile pass kernels: SE, three fp16 pieces per point.
 #include "tile_kernels_f16.h"
 
-tileh_fn gp_tile_se_x3(int ds, int NT, bool y, int form) { return pick_shape<GP_SE_ARD, 3>(ds, NT, y, form); }
+tileh_fn gp_tile_se_x3(int ds, int NT, bool y, int form, bool wide) { return pick_shape<GP_SE_ARD, 3>(ds, NT, y, form, wide); }

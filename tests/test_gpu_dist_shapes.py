@@ -51,6 +51,21 @@ def test_every_number_of_column_tiles(t):
         dv.close()
 
 
+@pytest.mark.parametrize("d", [3, 18, 26, 40, 50, 61])
+def test_four_row_tiles_in_long_products(d):
+    """The layouts that have a kernel with four row tiles per wave, at a size where it is chosen; 64 rows are checked.  Rows add up 30011
+    terms in ranges of at most 1024 chunks: an fp32 chain of partial sums adds below 1e-6 normwise."""
+    n, t, kind = 30011, 65, "se" if d % 4 else "matern32"
+    X, V, ell = _case(n, d, t, d)
+    rows = np.r_[0:8, n // 2: n // 2 + 24, n - 32: n]
+    dv = Dev(X, kind, ell, 1.2, 0.4)
+    try:
+        ref = orc.cross_kmv(X[rows], X, ell, 1.2, kind, V) + 0.4 ** 2 * V[rows].astype(np.float64)
+        assert relerr(dv.kmv(V, 1)[rows], ref) <= KMV_TOL
+    finally:
+        dv.close()
+
+
 @pytest.mark.parametrize("d,t", [(4, 17), (26, 65), (90, 40)])
 def test_rows_and_chunks_around_the_cuts(d, t):
     """129 to 1100 points: from 5 chunks of columns on, waves share rows and columns are cut into ranges."""
