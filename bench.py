@@ -26,12 +26,13 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E
 # HBM bytes per launch of the tile kernel: NOT measured by this script.  They come from separate
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script whose summary is the file named here, keyed
 # by (workload, n); the JSON line repeats the source next to the number.
+# They were taken of the tile kernel on 32x32x16 matrix products, which read and wrote the same operands and images.
 TRAFFIC = {("config2", 16384): 43.4e6, ("config5", 2000000): 742e9}
-TRAFFIC_SOURCE = "profiles/kmv_tile_f16_hbm_traffic_pmc.md (rocprofv3 --pmc runs, not this run)"
+TRAFFIC_SOURCE = "profiles/kmv_tile_f16_hbm_traffic_pmc.md (rocprofv3 --pmc runs of the 32x32x16 kernel, not this run)"
 # Engine clock under the tile kernel (GRBM_GUI_ACTIVE over the kernel's duration), likewise from separate
 # counter runs: the published peaks assume 2.4 GHz, the chip holds less under this kernel's load.
 ENGINE_CLOCK_GHZ = {"config2": 1.98, "config5": 1.74}
-ENGINE_CLOCK_SOURCE = "profiles/kmv_tile_f16_engine_clock_under_load.md (rocprofv3 --pmc runs, not this run; peak assumes 2.4 GHz)"
+ENGINE_CLOCK_SOURCE = "profiles/kmv_tile_f16_engine_clock_under_load.md (rocprofv3 --pmc runs of the 32x32x16 kernel, not this run; peak assumes 2.4 GHz)"
 
 
 def kmv_flops(n, d, t, kind):
@@ -39,8 +40,9 @@ def kmv_flops(n, d, t, kind):
 
 
 def executed_mfma_flops(n, d, t, kind, path, rows=None):
-    """Matrix-core flops the tile kernel really issues per K V product (padding of the contraction
-    lengths and the extra products of the fp16 splitting included), as opposed to kmv_flops."""
+    """Matrix-core flops per K V product with the extra products of the fp16 splitting and the padding of the contraction
+    lengths to steps of 16, as opposed to kmv_flops.  The fp16 tile kernel issues the products of V as counted here; the
+    distance's slots it packs into steps of 32 (d = 26: 192 flops a pair, as counted; d = 11 with SE 128, counted 96)."""
     nt = (t // 32) if t % 32 == 1 and t > 1 else -(-t // 32)     # a lone 33rd column goes through the vector ALU
     if path == 0:
         ks = next(b for b in (4, 7, 10, 14, 24, 46, 64) if 2 * b >= d + 2)
@@ -50,6 +52,14 @@ def executed_mfma_flops(n, d, t, kind, path, rows=None):
         kh = next(b for b in (1, 2, 3, 4, 6, 8) if 16 * b >= slots)
         per_pair = (3 if path == 1 else 6) * 2 * 16 * kh + 3 * 2 * 32 * nt
     return float(n) * float(rows if rows else n) * per_pair
+
+
+def tile_kernel_name(d, t, path):
+    """The kernel of a product's passes of 64 columns, or of its only one: the fp32 kernel, or the fp16 one with four row tiles
+    per wave (more than 33 columns and a distance of few dimensions) or with two."""
+    if path == 0:
+        return "kmv_tile_kernel"
+    return "kmv_tile_f16_wide_kernel" if t > 33 and d <= (61 if path == 1 else 29) else "kmv_tile_f16_kernel"
 
 
 def cpu_baseline(w):
@@ -138,7 +148,7 @@ def config5_leg(cap=4, outer_steps=3, timed_products=3):
                                    "frac": achieved / peak, "traffic": TRAFFIC.get(("config5", n)),
                                    "traffic_source": TRAFFIC_SOURCE, "engine_clock_ghz": ENGINE_CLOCK_GHZ["config5"],
                                    "engine_clock_source": ENGINE_CLOCK_SOURCE,
-                                   "kernel": "kmv_tile_kernel" if path == 0 else "kmv_tile_f16_kernel",
+                                   "kernel": tile_kernel_name(d, t, path),
                                    "product_path": PATH_NAMES[path], "peak_dtype": "fp32" if path == 0 else "fp16",
                                    "launches": int(launches), "avg_launch_ms": avg_s * 1e3, "flops_per_launch": F_launch,
                                    "executed_mfma_tflops": executed, "executed_mfma_frac_of_peak": executed / peak,
@@ -451,7 +461,7 @@ def main():
                          "traffic_source": TRAFFIC_SOURCE if args.solver == "cg" and not args.predict and (args.workload, n) in TRAFFIC else None,
                          "engine_clock_ghz": ENGINE_CLOCK_GHZ.get(args.workload) if (args.workload, n) in TRAFFIC else None,
                          "engine_clock_source": ENGINE_CLOCK_SOURCE if (args.workload, n) in TRAFFIC else None,
-                         "kernel": "kmv_tile_kernel" if path == 0 else "kmv_tile_f16_kernel",
+                         "kernel": tile_kernel_name(d, t, path),
                          "product_path": PATH_NAMES[path], "peak_dtype": "fp32" if path == 0 else "fp16",
                          "launches": int(launches), "avg_launch_ms": avg_kern_s * 1e3,
                          "flops_per_launch": F_launch,
