@@ -19,7 +19,7 @@ struct TileArgsH {
   int64_t ldo;
   int64_t split_stride;
   int64_t n;               // rows of the output (the context's n, or m for a rectangular product)
-  int diag;                // square product: the pair (i, i) gets r^2 = 0 exactly
+  int diag;                // square product: the pair (i, i) counts with r^2 = 0, as 2^15 V'_i (all pieces of V')
   int diag_shift;          // chunk of the first row minus the first chunk of the contraction
   int nchunks;             // column chunks (always the context's points)
   int col0, ncols, vcol;

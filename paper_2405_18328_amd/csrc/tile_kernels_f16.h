@@ -169,8 +169,10 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
     return fmaf(u, ex, ex);
   };
 
-  // The pair (i, i) of a square product counts with r^2 = 0 exactly.  The loop takes it as it comes, with the rounding of its distance, and
-  // the accumulators start with what is missing: (phi(0) - phi(S_ii)) V_i, S_ii worked out here by the same instructions.  A
+  // The pair (i, i) of a square product counts with r^2 = 0 exactly: with 2^15 V'_i.  The loop takes it as it comes, with the rounding of its
+  // distance, as hi V'_i + lo Vh_i (phi(S_ii) in two pieces, V' = Vh + Vl), and the accumulators start with what that is short of:
+  // (2^15 - hi - lo) V'_i + lo Vl_i, S_ii worked out here by the same instructions.  (Short of phi(S_ii) itself the split's own rounding and the
+  // dropped product would stay in: K = a^2 I came out 1.1e-7 off instead of 4.4e-8, which is what V' has.)  A
   // special case inside the loop would put a branch between distances and phi, across which nothing is scheduled.
   const int own = tile0 / 2 + p.diag_shift;      // the chunk that holds the first row tile's own points
   if (p.diag && cg == 0 && own + RT / 2 > r_begin && own < r_end) {
@@ -198,13 +200,24 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
       const bool here = own + it / 2 >= r_begin && own + it / 2 < r_end;
       const f32x4 S = distance(xa[it], it);
       const float s = li & 2 ? (li & 1 ? S[3] : S[2]) : li & 1 ? S[1] : S[0];
-      const float miss = here && q == li >> 2 ? (float)(1 << PHI_SHIFT) - phi(s) : 0.0f;     // of row li, in lane 20 (li/4) + li%4
-      if (Y) accv[it] = miss * vy[it];
+      const bool mine = here && q == li >> 2;      // lane 20 (li/4) + li%4 holds row li's
+      const float f = phi(s);
+      if (Y) accv[it] = mine ? ((float)(1 << PHI_SHIFT) - f) * vy[it] : 0.0f;
+      if constexpr (NT > 0) {
+        unsigned hi, lo;
+        split_pair_positive(mine ? f : (float)(1 << PHI_SHIFT), 0.0f, hi, lo);
+        const int both = (int)(hi | lo << 16);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float m = __shfl(miss, 20 * q + r);
+        for (int r = 0; r < 4; ++r) {
+          const unsigned of_row = (unsigned)__shfl(both, 20 * q + r);
+          const float h = (float)__builtin_bit_cast(_Float16, (unsigned short)of_row);
+          const float l = (float)__builtin_bit_cast(_Float16, (unsigned short)(of_row >> 16)), m = ((float)(1 << PHI_SHIFT) - h) - l;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[it][nt][r] = m * ((float)vh[it / 2][nt][4 * jt + r] + (float)vl[it / 2][nt][4 * jt + r]);
+          for (int nt = 0; nt < NT; ++nt) {
+            const float v0 = (float)vh[it / 2][nt][4 * jt + r], v1 = (float)vl[it / 2][nt][4 * jt + r];
+            acc[it][nt][r] = fmaf(m, v0 + v1, l * v1);
+          }
+        }
       }
     }
   }
