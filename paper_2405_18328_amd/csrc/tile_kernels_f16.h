@@ -202,7 +202,8 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
       const float s = li & 2 ? (li & 1 ? S[3] : S[2]) : li & 1 ? S[1] : S[0];
       const bool mine = here && q == li >> 2;      // lane 20 (li/4) + li%4 holds row li's
       const float f = phi(s);
-      if (Y) accv[it] = mine ? ((float)(1 << PHI_SHIFT) - f) * vy[it] : 0.0f;
+      // an infinite V_i is infinite in the loop; what is missing of it would make a NaN of that
+      if (Y) accv[it] = mine && __builtin_isfinite(vy[it]) ? ((float)(1 << PHI_SHIFT) - f) * vy[it] : 0.0f;
       if constexpr (NT > 0) {
         unsigned hi, lo;
         split_pair_positive(mine ? f : (float)(1 << PHI_SHIFT), 0.0f, hi, lo);

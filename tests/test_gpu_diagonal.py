@@ -42,3 +42,20 @@ def test_k_of_points_far_apart_is_the_identity(monkeypatch, path, kind, n, d, t)
     err = got - want
     assert np.abs(err / want).max() <= 2.0 ** -23
     assert np.linalg.norm(err) <= 2.0 ** -25 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("kind", ["se", "matern32"])
+@pytest.mark.parametrize("n,d,t", [(300, 5, 1), (300, 26, 17), (300, 90, 65), (300, 5, 33)])
+def test_an_infinity_stays_one(kind, n, d, t):
+    """The vector-ALU column is multiplied in fp32 as it is: where every entry of K is positive, an infinity in it is one in every row."""
+    rng = np.random.default_rng(n + t)
+    X = rng.uniform(-1.0, 1.0, size=(n, d)).astype(np.float32)
+    V = rng.standard_normal((n, t)).astype(np.float32)
+    V[[7, 100, 299], 0] = np.inf
+    dv = Dev(X, kind, np.full(d, 0.6 * np.sqrt(d)), 1.0, 0.3)
+    try:
+        got = dv.kmv(V, 1)
+    finally:
+        dv.close()
+    assert np.isposinf(got[:, 0]).all()
+    assert np.isfinite(got[:, 1:]).all()
