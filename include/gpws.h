@@ -58,7 +58,8 @@ enum {
 /*
  * Create a context for n training inputs of dimension d (paper Section 2: the
  * inputs x of the regression model).  dX: device, row-major n x d fp32; it is
- * read at every gp_set_theta and must stay valid and unchanged until
+ * read at every gp_set_theta, and by a gp_predict whose test inputs need other
+ * arithmetic than the training inputs, and must stay valid and unchanged until
  * gp_destroy.  hip_stream: a hipStream_t (NULL = the default stream).
  * kernel: GP_SE_ARD      k = a^2 exp(-r^2/2)
  *         GP_MATERN32_ARD k = a^2 (1 + sqrt(3) r) exp(-sqrt(3) r)
@@ -81,7 +82,10 @@ int gp_destroy(gp_ctx* ctx);
  * the largest scaled squared norm.  Waits for earlier work on the stream (a
  * pinned staging block is reused); the packing itself is left running unless
  * the norm has to be read back, which happens only when a bound kept on the
- * host does not already settle the choice.  Must be called before any of the
+ * host does not already settle the choice.  The first theta (or gp_predict) that
+ * needs other arithmetic than two fp16 pieces allocates its operands, which the
+ * context then keeps (d = 11: 448 bytes per point for three pieces, 112 for fp32,
+ * beside 430 of every context; d = 90: 1536 and 736 beside 1900).  Must be called before any of the
  * calls below.  Errors: GP_ERR_ARG for non-positive or non-finite values, or
  * inputs that are not finite after scaling.
  */

@@ -98,32 +98,22 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
     return gp_fail(ctx, GP_ERR_HIP, "libgpws is built for gfx950 only, device is %s", prop.gcnArchName);
   GP_HIP(ctx, static_scratch_on(dev, &ctx->static_scratch));
 
-  const size_t packed = ((size_t)(ctx->n_pad / GP_CHUNK) * ctx->KS * 64 + GP_PACK_SLACK) * sizeof(float);
-  GP_HIP(ctx, hipMalloc((void**)&ctx->dXA, packed));
-  GP_HIP(ctx, hipMalloc((void**)&ctx->dXB, packed));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dXs, (size_t)n * d * sizeof(float)));
   GP_HIP(ctx, hipMalloc((void**)&ctx->dMaxNorm, 256));
   GP_HIP(ctx, hipMemsetAsync(ctx->dMaxNorm, 0, 256, ctx->stream));
-  {
-    const size_t units = (size_t)(ctx->n_pad / GP_CHUNK) * ctx->KH * 64;
-    for (int pc = 0; pc < 3; ++pc) {
-      GP_HIP(ctx, hipMalloc(&ctx->dXAh[pc], units * 16));
-      GP_HIP(ctx, hipMalloc(&ctx->dXBh[pc], units * 16));
-    }
+  for (int pc = 0; pc < 2; ++pc) {
+    GP_HIP(ctx, hipMalloc(&ctx->dXAh[pc], gp_grad_piece_bytes(ctx)));
+    GP_HIP(ctx, hipMalloc(&ctx->dXBh[pc], gp_grad_piece_bytes(ctx)));
   }
-  {   // operands of the tile pass: one block
-    size_t size[6], total = 0;
-    for (int x = 0; x < 2; ++x) size[2 * x] = size[2 * x + 1] = gp_dist_bytes(ctx, x + 2, ctx->n_pad);
-    size[4] = sizeof(float) * ctx->n_pad;
-    size[5] = sizeof(unsigned short) * gp_dist_slots(ctx, nullptr);
+  {   // operands of the tile pass on two pieces: one block
+    size_t size[4] = {gp_dist_bytes(ctx, 2, ctx->n_pad), gp_dist_bytes(ctx, 2, ctx->n_pad), sizeof(float) * ctx->n_pad,
+                      sizeof(unsigned short) * gp_dist_slots(ctx, nullptr)}, total = 0;
     for (size_t& v : size) total += v = (v + 255) / 256 * 256;
     GP_HIP(ctx, hipMalloc(&ctx->dDist, total));
     char* at = (char*)ctx->dDist;
-    for (int x = 0; x < 2; ++x) {
-      ctx->dDA[x] = at; at += size[2 * x];
-      ctx->dDB[x] = at; at += size[2 * x + 1];
-    }
-    ctx->dCI = (float*)at; at += size[4];
+    ctx->dDA[0] = at; at += size[0];
+    ctx->dDB[0] = at; at += size[1];
+    ctx->dCI = (float*)at; at += size[2];
     ctx->dDistSlots = at;
   }
   GP_HIP(ctx, hipMalloc((void**)&ctx->dColmax, sizeof(unsigned) * GP_MAX_T));
@@ -140,20 +130,22 @@ int gp_create(gp_ctx** out, int kernel, int64_t n, int d, const float* dX, void*
   unsigned short* slots = (unsigned short*)((char*)ctx->hPinned + GP_PIN_THETA);
   const int count = gp_dist_slots(ctx, slots);
   GP_HIP(ctx, hipMemcpyAsync(ctx->dDistSlots, slots, sizeof(unsigned short) * count, hipMemcpyHostToDevice, ctx->stream));
-  return gp_launch_column_means(ctx);
+  const int rc = gp_launch_column_means(ctx);
+  ctx->created = rc >= 0;
+  return rc;
 }
 
 int gp_destroy(gp_ctx* ctx) {
   if (!ctx) return GP_OK;
   (void)hipStreamSynchronize(ctx->stream);
   if (ctx->dXA) (void)hipFree(ctx->dXA);
-  if (ctx->dXB) (void)hipFree(ctx->dXB);
   if (ctx->dXs) (void)hipFree(ctx->dXs);
   if (ctx->dMaxNorm) (void)hipFree(ctx->dMaxNorm);
-  for (int pc = 0; pc < 3; ++pc) {
+  for (int pc = 0; pc < 2; ++pc) {
     if (ctx->dXAh[pc]) (void)hipFree(ctx->dXAh[pc]);
     if (ctx->dXBh[pc]) (void)hipFree(ctx->dXBh[pc]);
   }
+  if (ctx->dDA[1]) (void)hipFree(ctx->dDA[1]);
   if (ctx->dDist) (void)hipFree(ctx->dDist);
   if (ctx->dColmax) (void)hipFree(ctx->dColmax);
   if (ctx->dMean) (void)hipFree(ctx->dMean);
@@ -172,7 +164,7 @@ int gp_destroy(gp_ctx* ctx) {
 
 int gp_set_theta(gp_ctx* ctx, const double* h_lengthscale, double signal_scale, double noise_scale) {
   if (!ctx) return GP_ERR_ARG;
-  if (!ctx->dXA) return gp_fail(ctx, GP_ERR_ARG, "gp_set_theta: context was not created successfully");
+  if (!ctx->created) return gp_fail(ctx, GP_ERR_ARG, "gp_set_theta: context was not created successfully");
   if (!h_lengthscale) return gp_fail(ctx, GP_ERR_ARG, "gp_set_theta: NULL lengthscales");
   for (int k = 0; k < ctx->d; ++k)
     if (!(h_lengthscale[k] > 0.0) || !std::isfinite(h_lengthscale[k]))
@@ -192,6 +184,10 @@ int gp_set_theta(gp_ctx* ctx, const double* h_lengthscale, double signal_scale, 
   stage[ctx->d + 1] = noise_scale;
   ctx->a = signal_scale;
   ctx->sigma = noise_scale;
+  auto not_set = [&](int rc) {      // the operands are neither the last theta's nor this one's
+    ctx->theta_set = false;
+    return rc;
+  };
   GP_HIP(ctx, hipMemcpyAsync(ctx->dTheta, stage, sizeof(double) * (ctx->d + 2), hipMemcpyHostToDevice, ctx->stream));
   // The largest scaled squared norm decides which product path holds the error budget.  The host-side
   // bound sum_k (xabs_k / ell_k)^2 >= max_i |xs_i|^2 settles the common case (two fp16 pieces) without a
@@ -201,19 +197,24 @@ int gp_set_theta(gp_ctx* ctx, const double* h_lengthscale, double signal_scale, 
   bound *= 1.0 + 1e-5;   // fp32 rounding of the scaled inputs
   const bool settled = bound <= (double)GP_NORM_X2_MAX && ctx->path_forced < 0;
   ctx->max_norm = (float)bound;
-  int rc = gp_launch_pack(ctx, !settled);
-  if (rc < 0) return rc;
-  if (!settled && (rc = gp_wait_norm(ctx, "gp_set_theta", &ctx->max_norm)) < 0) return rc;
+  auto path_of = [&](double norm) {
+    int path = norm <= GP_NORM_X2_MAX ? GP_PATH_F16X2 : norm <= GP_NORM_X3_MAX ? GP_PATH_F16X3 : GP_PATH_FP32;
+    if (ctx->path_forced >= 0 && !(ctx->path_forced != GP_PATH_FP32 && norm > GP_NORM_X3_MAX)) path = ctx->path_forced;
+    return ctx->f16_ok ? path : GP_PATH_FP32;
+  };
+  // What is packed first is for the path of the least the largest norm can be; where that is not the one, the other follows
+  double least = 0.0;
+  for (int k = 0; k < ctx->d; ++k) least += ctx->xvar[k] / (ctx->ell[k] * ctx->ell[k]);
+  for (int k = 0; k < ctx->d; ++k) least = fmax(least, (ctx->xabs[k] / ctx->ell[k]) * (ctx->xabs[k] / ctx->ell[k]));
+  int rc = gp_launch_pack(ctx, path_of(settled ? bound : least * (1.0 - 1e-5)), !settled);
+  if (rc < 0) return not_set(rc);
+  if (!settled && (rc = gp_wait_norm(ctx, "gp_set_theta", &ctx->max_norm)) < 0) return not_set(rc);
   if (!std::isfinite(ctx->max_norm))
     return gp_fail(ctx, GP_ERR_ARG, "gp_set_theta: inputs scaled by the lengthscales are not finite");
-  int path = ctx->max_norm <= GP_NORM_X2_MAX ? GP_PATH_F16X2
-             : ctx->max_norm <= GP_NORM_X3_MAX ? GP_PATH_F16X3 : GP_PATH_FP32;
-  if (ctx->path_forced >= 0 && !(ctx->path_forced != GP_PATH_FP32 && ctx->max_norm > GP_NORM_X3_MAX))
-    path = ctx->path_forced;
-  if (!ctx->f16_ok) path = GP_PATH_FP32;
+  const int path = path_of(ctx->max_norm);
+  if ((rc = gp_need_path(ctx, path)) < 0) return not_set(rc);
   ctx->path = path;
   ctx->XP = path == GP_PATH_F16X3 ? 3 : 2;
-  if (ctx->XP == 3 && (rc = gp_pack_x3(ctx)) < 0) return rc;
   ctx->theta_set = true;
   return GP_OK;
 }

@@ -59,23 +59,24 @@ struct gp_ctx {
   int64_t n_pad;          // n rounded up to GP_ROW_ALIGN
   hipStream_t stream;
   const float* dX;        // caller-owned
-  float* dXA;             // packed, n_pad/32 * KS * 64
+  unsigned packed;        // bit 1 << GP_PATH_*: what that path reads is packed for the current theta
+  float* dXA;             // fp32 path: n_pad/32 * KS * 64; one block with dXB, NULL until a theta or a prediction asks for that path
   float* dXB;
   float* dXs;             // scaled centred inputs, row-major n x d (gradient pass)
   unsigned long long* dMaxNorm;   // a tag and below it the bit pattern of the largest |xs_i|^2 packed under it (device)
   unsigned norm_seq;      // the latest tag
   // split-fp16 operands of the tile pass on two and three pieces (dist_f16.h), column and row side, 16-byte units
   // [(16 points)*groups + group]*64 + lane: lane l holds slots 8 (l/16) .. + 7 of point l % 16
-  void* dDist;            // one block that holds them all
-  void* dDA[2];
+  void* dDist;            // one block: those on two pieces, dDistSlots and dCI
+  void* dDA[2];           // [1]: NULL until a theta or a prediction asks for three pieces; one block with dDB[1], dXAh[2] and dXBh[2]
   void* dDB[2];
-  bool x3_packed;         // those on three pieces are there for the current theta (gp_pack_x3)
   void* dDistSlots;       // what stands where in them (gp_dist_slots)
   float* dCI;             // gamma |xs_i|^2, [n_pad]
-  // split-fp16 operands of the gradient pass: three pieces (hi, mid, lo) per side, 16-byte units
+  // split-fp16 operands of the gradient pass: two or three pieces (hi, mid, lo) per side, 16-byte units
   // [(chunk*KH + kh)*64 + lane], element e of a unit = component 16 kh + 8 (lane/32) + e
   void* dXAh[3];
   void* dXBh[3];
+  int grad_pieces;        // how many of them are packed for the current theta
   int KH;                 // 16-wide k-steps of the fp16 distance chain, bucketed
   int XP;                 // pieces used per operand of the distance chain (2 or 3)
   int path;               // GP_PATH_* chosen by gp_set_theta
@@ -86,8 +87,9 @@ struct gp_ctx {
   int colmax_dirty;       // how many of them may be set: a call ended with an error, or was a prediction that turned to the fp32 path
   double* dMean;          // d column means of X
   double* dTheta;         // device copy: 1/ell (d), then a, sigma
-  bool theta_set;
+  bool created, theta_set;
   double xabs[GP_MAX_D];  // max_i |x_ik - mean_k| per dimension (host copy, fixed at gp_create)
+  double xvar[GP_MAX_D];  // mean_i (x_ik - mean_k)^2
   double ell[GP_MAX_D];
   double a, sigma;
   // lazily grown scratch for split-column partial sums of gp_kmv / gp_mll_grad
@@ -171,8 +173,8 @@ int gp_ensure_scratch(gp_ctx* ctx, size_t bytes);
 
 // ---- prep_kernels.hip
 int gp_launch_column_means(gp_ctx* ctx);
-int gp_launch_pack(gp_ctx* ctx, bool want_norm);
-int gp_pack_x3(gp_ctx* ctx);     // the operands on three pieces, which gp_launch_pack leaves out
+int gp_launch_pack(gp_ctx* ctx, int path, bool want_norm);     // for a new theta: what `path` reads
+int gp_need_path(gp_ctx* ctx, int path);                       // and another one too, unless it is there
 // waits for the largest scaled squared norm of the latest packing that was asked for it
 int gp_wait_norm(gp_ctx* ctx, const char* who, float* norm);
 // packs m other points (device, row-major m x d) against the context's centring and theta into
@@ -182,6 +184,7 @@ size_t gp_pack_rows_bytes(const gp_ctx* ctx, int64_t m);
 constexpr int GP_DIST_LIST_EXTRA = 6;
 int gp_dist_slots(const gp_ctx* ctx, unsigned short* slots);     // fills (or NULL: counts) the table the packing kernel works from
 size_t gp_dist_bytes(const gp_ctx* ctx, int XP, int64_t rows);   // of one side's operands of the tile pass, rows a multiple of 32
+size_t gp_grad_piece_bytes(const gp_ctx* ctx);                   // of one piece of one side's operands of the gradient pass
 // dV, kmv_scratch: as gp_kmv_launch will get them; what V needs first is prepared in the same launch (rows->v_prepared)
 int gp_pack_rows(gp_ctx* ctx, const float* dXstar, int64_t m, void* buf, KmvRows* rows, const float* dV, int64_t ldv, int t, void* kmv_scratch);
 int gp_rows_path(gp_ctx* ctx, KmvRows* rows);

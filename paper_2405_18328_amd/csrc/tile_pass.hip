@@ -348,6 +348,8 @@ int gp_kmv_launch(gp_ctx* ctx, const float* dV, int64_t ldv, int t, float* dOut,
   if ((rows ? rows->path : ctx->path) != GP_PATH_FP32) {
     const int rc = gp_kmv_launch_f16(ctx, dV, ldv, t, dOut, ldo, add_noise, scratch, scratch_bytes, colmax, rows, defer, win);
     if (rc != GP_TO_FP32) return rc;
+    const int packed = gp_need_path(ctx, GP_PATH_FP32);      // test inputs farther out than fp16 reaches
+    if (packed < 0) return packed;
   }
   const int64_t nrows = rows ? rows->m : ctx->n;
   const KmvPlan pl = gp_plan_kmv(ctx, nrows, win ? win->nchunks : 0);
