@@ -1,8 +1,9 @@
 // Stochastic gradient descent with one workgroup per column, for n <= SGD_COLUMNS_FEW_N (SGD_COLUMNS_MAX_N with one or
 // more than 64 columns) on the split-fp16 product paths: the same step, stopping rule and freezing as the streaming kernels of sgd_kernels.hip, in two
-// launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
+// or three launches per step instead of seven.  The product's rows are gathered by the tile kernel itself from the
 // context's packed operands; the gradient on the mini-batch rows, momentum, iterate, the stopping test and the packing of
-// the iterate for the next product are per column (columns.h).  For large mini-batches the gradient is spread over the chip in a launch of its own.
+// the iterate for the next product are per column (columns.h).  With few columns the gradient is spread over the chip in a launch of its own
+// (with_gradient).
 // Measured on MI355X, n = 16384 d = 26 t = 65, batch 1000: a solve with the streaming kernels 78 us per step, with three launches 43, with the
 // gradient in the step's launch 38 (a whole marginal-likelihood step 6.60 -> 5.90 ms).  Bound by memory latency and by the
 // partial images of the product.
@@ -345,9 +346,13 @@ Layout layout(const gp_ctx* ctx, int t, int batch) {
 
 typedef void (*step_fn)(SgdCols, const int*, int);
 
-// Up to this many rows per mini-batch the step's workgroup takes the gradient along; one compute unit per column would be
-// longer over more than it takes to spread them and launch twice.
-constexpr int SGD_FUSED_BATCH = 2048;
+// Whether the step's workgroups take the gradient along.  One of them reads all images of its column, batch x ranges, on one compute unit;
+// a launch of its own spreads them over the chip, which costs 3 to 4 us with few columns and 9 with 65.  Below 49 columns the launch is the
+// faster way, and so it is for mini-batches of a few images' lines and of more rows than four rounds of a workgroup.  A step, d = 26,
+// launch -> taken along: n = 16384, batch 1000 t = 9 27.7 -> 28.5 us, 17 30.4 -> 31.1, 33 35.3 -> 34.5, 49 39.0 -> 36.7, 65 41.3 -> 37.9,
+// 97 57.4 -> 52.9; n = 8192 t = 1 19.7 -> 22.6, 33 27.6 -> 27.6, 65 34.9 -> 31.4; t = 65, n = 8192 batch 100 24.2 -> 24.6, 500 27.7 -> 25.2,
+// 2048 41.8 -> 39.2, 4000 53.2 -> 53.9; n = 30000 57.2 -> 55.1 (1000), 80.7 -> 80.7 (2048), 124.3 -> 128.2 (4000).
+bool with_gradient(int t, int batch) { return t > 48 && batch >= 200 && batch <= 2048; }
 
 }  // namespace
 
@@ -446,7 +451,7 @@ int gp_sgd_columns_run(gp_ctx* ctx, const float* dB, int64_t ldb, const float* d
   pk.ld = L.gld;
   pk.done = &s.flags->all_done;
   s.stride = L.gld * (int64_t)t;
-  const bool fused = batch <= SGD_FUSED_BATCH;
+  const bool fused = with_gradient(t, batch);
   const int q = L.ld <= CROWS ? 1 : L.ld <= 2 * CROWS ? 2 : L.ld <= 4 * CROWS ? 4 : 0;
   const step_fn step = fused ? (q == 1 ? sgdc_step_kernel<1, true> : q == 2 ? sgdc_step_kernel<2, true> : q == 4 ? sgdc_step_kernel<4, true> : sgdc_step_kernel<0, true>)
                              : (q == 1 ? sgdc_step_kernel<1, false> : q == 2 ? sgdc_step_kernel<2, false> : q == 4 ? sgdc_step_kernel<4, false> : sgdc_step_kernel<0, false>);
