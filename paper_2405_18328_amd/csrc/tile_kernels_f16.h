@@ -306,17 +306,18 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
   float* out = p.OUT + (int64_t)js * p.split_stride;
   auto flush = [&](bool first) {
     const bool noise = first && p.add_noise && js == 0;
-    // an opaque zero keeps the address arithmetic of the flush inside it: hoisted out of the segment
-    // loop it would hold dozens of registers across the main loop
+    // an opaque zero keeps the address arithmetic of the flush inside it, that of rows and that of columns: hoisted out of the segment
+    // loop it would hold dozens of registers across the main loop, or be stored to scratch memory in front of it
     int zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
     const bool mine = cg == 0;
+    const int li0 = li + zero, q0 = q + zero;
     const int64_t ibase = (int64_t)tile0 * 16 + zero;
     const bool columns = FORM == FORM_ANY ? p.cm_ld != 0 : FORM != FORM_PLAIN;
     float oscale[NT > 0 ? NT : 1];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-      oscale[nt] = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(16 * nt + li, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
+      oscale[nt] = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(16 * nt + li0, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
     const float yscale = p.a2 * ldexpf(1.0f, -PHI_SHIFT);
 #pragma unroll
     for (int it = 0; it < RT; ++it) {
@@ -329,22 +330,22 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
         if (mine && i0 < p.cm_ld) {
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt) {
-            const int c = 16 * nt + li;
+            const int c = 16 * nt + li0;
             f32x4 v = oscale[nt] * acc[it][nt];
             if (c < p.ncols) {
-              f32x4* d = reinterpret_cast<f32x4*>(out + (int64_t)(p.col0 + c) * p.cm_ld + i0 + 4 * q);
+              f32x4* d = reinterpret_cast<f32x4*>(out + (int64_t)(p.col0 + c) * p.cm_ld + i0 + 4 * q0);
               if (!first) v += *d;
               *d = v;
             }
           }
-          if (Y && q == 0) {
-            float* o = out + (int64_t)p.vcol * p.cm_ld + i0 + li;
+          if (Y && q0 == 0) {
+            float* o = out + (int64_t)p.vcol * p.cm_ld + i0 + li0;
             const float v = yscale * accv[it];
             *o = first ? v : *o + v;
           }
         }
       } else if (mine) {
-        auto row = [&](int r) { return i0 + 4 * q + r; };
+        auto row = [&](int r) { return i0 + 4 * q0 + r; };
         float v[NT > 0 ? NT : 1][4];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
@@ -355,7 +356,7 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) w[nt][r] = from[min(row(r), p.n - 1) * ld + p.col0 + min(16 * nt + li, p.ncols - 1)];
+            for (int r = 0; r < 4; ++r) w[nt][r] = from[min(row(r), p.n - 1) * ld + p.col0 + min(16 * nt + li0, p.ncols - 1)];
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -367,9 +368,9 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (16 * nt + li < p.ncols && row(r) < p.n) out[row(r) * p.ldo + p.col0 + 16 * nt + li] = v[nt][r];
-        if (Y && q == 0 && i0 + li < p.n) {
-          const int64_t i = i0 + li;
+            if (16 * nt + li0 < p.ncols && row(r) < p.n) out[row(r) * p.ldo + p.col0 + 16 * nt + li0] = v[nt][r];
+        if (Y && q0 == 0 && i0 + li0 < p.n) {
+          const int64_t i = i0 + li0;
           float v1 = yscale * accv[it];
           if (noise) v1 = fmaf(p.sigma2, p.V[i * p.ldv + p.vcol], v1);
           if (!first) v1 += out[i * p.ldo + p.vcol];
