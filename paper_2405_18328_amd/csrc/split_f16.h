@@ -16,8 +16,8 @@ constexpr int V_TOP = 14;                       // max |V'_c| in [2^13, 2^14)
 
 // Column passes of a product with t columns: up to four tiles of 16 columns each.  A lone column past whole tiles rides
 // on the vector ALU of the first pass instead of a tile used for 1/16 of its width, where that saves a tile.
-__host__ __device__ inline int pass_tiles(int rem) { return rem > 32 ? 4 : rem > 16 ? 2 : rem > 0 ? 1 : 0; }
-__host__ __device__ inline int vec_columns(int t) { return t % 64 == 1 || t % 64 == 17 || t % 64 == 33 ? 1 : 0; }
+__host__ __device__ inline int pass_tiles(int rem) { return rem > 48 ? 4 : rem > 0 ? (rem + 15) / 16 : 0; }
+__host__ __device__ inline int vec_columns(int t) { return t % 16 == 1 ? 1 : 0; }
 // whether some tile of the last pass has columns that are not there
 __host__ __device__ inline bool padded_tiles(int t) {
   const int rem = (t - vec_columns(t)) % 64;

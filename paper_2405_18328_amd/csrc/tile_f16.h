@@ -38,8 +38,7 @@ struct TileArgsH {
   const int* done;         // a non-zero value there turns the launch into a no-op; NULL: always runs
 };
 
-// What a tile kernel is compiled for, besides the row-major product of gp_kmv and gp_predict (FORM_PLAIN).  Shapes that come
-// close to the end of the register file may be built once per form instead of with all options in one kernel.
+// What a tile kernel is compiled for, besides the row-major product of gp_kmv and gp_predict (FORM_PLAIN).
 enum {
   FORM_PLAIN,
   FORM_COLUMNS,   // the solvers' products: column-major images, early return
@@ -62,14 +61,13 @@ constexpr int stage_chunks(int DS, int XP, int NT, bool y, int per_cu) {
     if (2 * per_cu * (c * chunk_units(DS, XP, NT) + (y ? 64 : 0)) * 16 <= LDS_BYTES) return c;
   return 1;
 }
-// Which kernel: four row tiles per wave, or two with this many waves per SIMD.  Four pay with 64 columns in long products (plan_h), where
+// Which kernel: four row tiles per wave, or two with this many waves per SIMD.  Four pay with 48 and 64 columns in long products (plan_h), where
 // they halve the operands read from LDS, and fit up to four groups of operands per tile.  With fewer columns two row tiles are as fast and
 // cut rows finer: n = 43945, d = 20, t = 17 (Matern) 625 us a product against 729, n = 65536, d = 11, t = 33 1517 against 1539.
-constexpr bool wide_tiles(int DS, int XP, int NT) { return NT == 4 && dist_groups(XP, DS) <= 4; }
-// which of those are built once per form
-constexpr bool wide_per_form(int DS, int XP) { return DS <= (XP == 2 ? 3 : 2); }
+constexpr bool wide_tiles(int DS, int XP, int NT) { return NT >= 3 && dist_groups(XP, DS) <= 4; }
+// Three column tiles leave four waves 28 registers short, two have them all: n = 5000, d = 26, t = 49 1.2 times faster, level from n = 14000 on.
 constexpr int tile_waves(int DS, int XP, int NT) {
-  return NT == 0 && dist_groups(XP, DS) <= 2 ? 8 : dist_groups(XP, DS) <= (NT == 0 ? 6 : 4) && NT < 4 ? 4 : 2;
+  return NT == 0 && dist_groups(XP, DS) <= 2 ? 8 : dist_groups(XP, DS) <= (NT == 0 ? 6 : 4) && NT < 3 ? 4 : 2;
 }
 
 typedef void (*tileh_fn)(TileArgsH);

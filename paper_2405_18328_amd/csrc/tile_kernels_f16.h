@@ -316,8 +316,7 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
     const bool columns = FORM == FORM_ANY ? p.cm_ld != 0 : FORM != FORM_PLAIN;
     float oscale[NT > 0 ? NT : 1];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      oscale[nt] = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(16 * nt + li0, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
+    for (int nt = 0; nt < NT; ++nt) oscale[nt] = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(16 * nt + li0, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
     const float yscale = p.a2 * ldexpf(1.0f, -PHI_SHIFT);
 #pragma unroll
     for (int it = 0; it < RT; ++it) {
@@ -426,61 +425,46 @@ __global__ __launch_bounds__(64 * TILE_WAVES) __attribute__((amdgpu_waves_per_eu
   tile_pass<KIND, DS, XP, NT, 2, Y, FORM, SC>(p, lds);
 }
 
-// Four row tiles per wave and up to 64 columns (NT counts 32 of them): every operand read from LDS serves 64 rows, two waves per SIMD, one
+// Four row tiles per wave and 48 or 64 columns: every operand read from LDS serves 64 rows, two waves per SIMD, one
 // workgroup per compute unit.  Against four waves per SIMD with two row tiles, n = 131072, loops of the main part: d = 26, t = 65 (Matern) 478 and
 // 498 ns per 32x32 tile and SIMD, d = 11 (SE) 375 and 392, d = 3 (SE) 347 and 364.
 template <int KIND, int DS, int XP, int NT, bool Y, int FORM>
 __global__ __launch_bounds__(64 * TILE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void kmv_tile_f16_wide_kernel(TileArgsH p) {
-  constexpr int SC = stage_chunks(DS, XP, 2 * NT, Y, 1);
-  __shared__ u32x4 lds[2 * (SC * chunk_units(DS, XP, 2 * NT) + (Y ? 64 : 0))];
-  tile_pass<KIND, DS, XP, 2 * NT, 4, Y, FORM, SC>(p, lds);
+  constexpr int SC = stage_chunks(DS, XP, NT, Y, 1);
+  __shared__ u32x4 lds[2 * (SC * chunk_units(DS, XP, NT) + (Y ? 64 : 0))];
+  tile_pass<KIND, DS, XP, NT, 4, Y, FORM, SC>(p, lds);
 }
 
+// Two row tiles: built once per form where a short product or step may take them, whose time is to a good part that of the code in front of the
+// loop and behind it (one kernel with everything in it: n = 1000, d = 3, t = 17 6 % longer, n = 5000 1 %, level from 16384 on).
 template <int KIND, int DS, int XP, int NT, bool Y>
-tileh_fn pick_form(int form) {
-  switch (form) {
-    case FORM_PLAIN: return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_PLAIN>;
-    case FORM_COLUMNS: return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_COLUMNS>;
-    case FORM_GATHER: return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_GATHER>;
-    case FORM_WINDOW: return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_WINDOW>;
+tileh_fn pick_rows(int form, bool wide) {
+  if constexpr (wide_tiles(DS, XP, NT)) {
+    if (wide) return kmv_tile_f16_wide_kernel<KIND, DS, XP, NT, Y, FORM_ANY>;
+  }
+  if (form == FORM_PLAIN) return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_PLAIN>;
+  if (form == FORM_COLUMNS) return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_COLUMNS>;
+  if constexpr (NT > 0 && NT <= 2 && DS <= 2) {
+    if (form == FORM_GATHER) return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_GATHER>;
+    if (form == FORM_WINDOW) return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_WINDOW>;
   }
   return kmv_tile_f16_kernel<KIND, DS, XP, NT, Y, FORM_ANY>;
 }
 
 template <int KIND, int DS, int XP, bool Y>
-tileh_fn pick_wide_form(int form) {
-  switch (form) {
-    case FORM_PLAIN: return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_PLAIN>;
-    case FORM_COLUMNS: return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_COLUMNS>;
-    case FORM_GATHER: return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_GATHER>;
-    case FORM_WINDOW: return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_WINDOW>;
-  }
-  return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_ANY>;
-}
-
-// Shapes of few dimensions are built once per form: in one kernel with everything in it the 64-column one keeps 10 registers in
-// scratch memory (d = 26).
-template <int KIND, int DS, int XP, bool Y>
 tileh_fn pick_nt(int NT, int form, bool wide) {
-  constexpr bool FEW = wide_per_form(DS, XP);
-  if (NT == 1) {
-    if constexpr (DS <= 2) return pick_form<KIND, DS, XP, 1, Y>(form);
-    else return kmv_tile_f16_kernel<KIND, DS, XP, 1, Y, FORM_ANY>;
+  switch (NT) {
+    case 1: return pick_rows<KIND, DS, XP, 1, Y>(form, wide);
+    case 2: return pick_rows<KIND, DS, XP, 2, Y>(form, wide);
+    case 3: return pick_rows<KIND, DS, XP, 3, Y>(form, wide);
   }
-  if (NT == 2) {
-    if constexpr (DS <= 2) return pick_form<KIND, DS, XP, 2, Y>(form);
-    else return kmv_tile_f16_kernel<KIND, DS, XP, 2, Y, FORM_ANY>;
-  }
-  if (!wide) return kmv_tile_f16_kernel<KIND, DS, XP, 4, Y, FORM_ANY>;
-  if constexpr (FEW) return pick_wide_form<KIND, DS, XP, Y>(form);
-  else if constexpr (wide_tiles(DS, XP, 4)) return kmv_tile_f16_wide_kernel<KIND, DS, XP, 2, Y, FORM_ANY>;
-  else return kmv_tile_f16_kernel<KIND, DS, XP, 4, Y, FORM_ANY>;
+  return pick_rows<KIND, DS, XP, 4, Y>(form, wide);
 }
 
 template <int KIND, int XP, int DS = 1>
 tileh_fn pick_shape(int ds, int NT, bool y, int form, bool wide) {
   if (ds == DS) {
-    if (NT == 0) return kmv_tile_f16_kernel<KIND, DS, XP, 0, true, FORM_ANY>;
+    if (NT == 0) return pick_rows<KIND, DS, XP, 0, true>(form, wide);
     return y ? pick_nt<KIND, DS, XP, true>(NT, form, wide) : pick_nt<KIND, DS, XP, false>(NT, form, wide);
   }
   if constexpr (DS < (XP == 2 ? DIST_SHAPES_X2 : DIST_SHAPES_X3)) return pick_shape<KIND, XP, DS + 1>(ds, NT, y, form, wide);

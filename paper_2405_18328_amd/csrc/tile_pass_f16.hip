@@ -207,7 +207,7 @@ TileKernelH tile_kernel_h(const gp_ctx* ctx, int XP, int NT, bool y, int form, b
   // per 32x32 tile and SIMD, as measured: the vector work of phi and 14 ns per unit of matrix work (32x32 pairs, 16 slots or columns)
   const double tile_us = (se ? 0.145 : 0.23) + 0.014 * (2 * dist_products(XP, ds) + 3 * NT);
   k.chunk_us = tile_us * (wide_tiles(ds, XP, NT) && !wide ? 1.12 : 1.0) * k.rows / 32 * TILE_WAVES / 4;
-  k.start_us = !wide ? 0.0 : wide_per_form(ds, XP) ? 5.0 : 7.0;
+  k.start_us = wide ? 6.0 : 0.0;
   k.stream_us = (2 * G + 2 * NT) / 25.0;
   return k;
 }
