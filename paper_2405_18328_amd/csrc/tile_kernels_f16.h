@@ -129,6 +129,18 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
     start[it] = f32x4{c, c, c, c};
   }
 
+  // What the output is scaled with goes out with the first loads and waits in registers, where there are some: fetched behind the loop, a
+  // short product waits for it again (t <= 48: n = 1000 1 to 2 %, n = 2200 0.5 %; level from n = 16384 on).
+  constexpr bool SCALES = RT == 2;
+  unsigned top[SCALES && NT > 0 ? NT : 1];
+  float scales[SCALES && NT > 0 ? NT : 1];
+  auto column_top = [&](int nt, int of) { return p.colmax[p.col0 + min(16 * nt + of, p.ncols - 1)]; };
+  auto out_scale = [&](unsigned max_bits) { return p.a2 * ldexpf(1.0f, column_exponent(max_bits) - V_TOP - PHI_SHIFT); };
+  if constexpr (SCALES) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) top[nt] = column_top(nt, li);
+  }
+
   f32x4 acc[RT][NT > 0 ? NT : 1];
   float accv[RT];
 #pragma unroll
@@ -316,7 +328,7 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
     const bool columns = FORM == FORM_ANY ? p.cm_ld != 0 : FORM != FORM_PLAIN;
     float oscale[NT > 0 ? NT : 1];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) oscale[nt] = p.a2 * ldexpf(1.0f, column_exponent(p.colmax[p.col0 + min(16 * nt + li0, p.ncols - 1)]) - V_TOP - PHI_SHIFT);
+    for (int nt = 0; nt < NT; ++nt) oscale[nt] = SCALES ? scales[SCALES ? nt : 0] : out_scale(column_top(nt, li0));
     const float yscale = p.a2 * ldexpf(1.0f, -PHI_SHIFT);
 #pragma unroll
     for (int it = 0; it < RT; ++it) {
@@ -388,6 +400,10 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
   // The row operands are waited for here, where the compiler sees it: it would otherwise wait for them at their first use,
   // inside the loop, and there drain the stage in flight too.
   __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+  if constexpr (SCALES) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) scales[nt] = out_scale(top[nt]);
+  }
   if (over) return;                       // nothing is in flight any more
   bool first = true;
   if (empty) {
