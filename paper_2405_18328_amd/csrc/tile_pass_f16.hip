@@ -208,7 +208,8 @@ TileKernelH tile_kernel_h(const gp_ctx* ctx, int XP, int NT, bool y, int form, b
   const double tile_us = (se ? 0.145 : 0.23) + 0.014 * (2 * dist_products(XP, ds) + 3 * NT);
   k.chunk_us = tile_us * (wide_tiles(ds, XP, NT) && !wide ? 1.12 : 1.0) * k.rows / 32 * TILE_WAVES / 4;
   k.start_us = wide ? 6.0 : 0.0;
-  k.stream_us = (2 * G + 2 * NT) / 25.0;
+// a workgroup that has its compute unit to itself brings 36 KB in a us, with others beside it 25
+  k.stream_us = (2 * G + 2 * NT) / (k.per_cu == 1 ? 36.0 : 25.0);
   return k;
 }
 
@@ -353,12 +354,15 @@ int gp_kh_bucket(int d, int kernel) {
 
 // Compute units take workgroups in turn; the busiest one ends the launch, and a last turn of a few workgroups costs as much as a full
 // one.  A workgroup's time is its chunks and what its prologue and flush cost; waves that share rows pass fewer chunks between two
-// barriers, which costs them 4 % for every doubling (n = 65536, d = 26, t = 65: 2157, 2238, 2374 us a product with 1, 2, 4 of them).
+// barriers, which costs them 6 % for every doubling (n = 65536, d = 26, t = 65: 2157, 2238, 2374 us a product with 1, 2, 4 of them).
 // Every further cut adds one partial image of the output to write and read (image_us).
+// Against every plan of 336 products (n = 1000 .. 14000, d = 3 .. 90, t = 1 .. 97; up to 60 plans each) the one priced lowest is 1.4 % behind the fastest in the
+// mean, 2 % behind it when an unshared compute unit was priced at 25 KB a us too and a doubling at 4 %, which kept short products from sharing rows:
+// n = 1800, d = 26, t = 65 20.1 -> 18.4 us.
 int gp_column_splits(int64_t row_blocks, int64_t chunks, int num_cu, int per_cu, int cg, double chunk_us, double stream_us, double image_us,
                      int max_splits, double* cost) {
   constexpr double FIXED = 6.0;       // prologue and flush of a workgroup, in us
-  const double shared = chunk_us / cg * (cg == 1 ? 1.0 : cg == 2 ? 1.04 : cg == 4 ? 1.08 : 1.12);
+  const double shared = chunk_us / cg * (cg == 1 ? 1.0 : cg == 2 ? 1.06 : cg == 4 ? 1.12 : 1.18);
   const double per_chunk = shared > stream_us ? shared : stream_us;
   auto price = [&](int64_t cps, int64_t parts) {
     const int64_t turns = (row_blocks * parts + num_cu - 1) / num_cu;
