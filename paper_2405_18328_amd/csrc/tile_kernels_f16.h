@@ -183,7 +183,7 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
 
   // The pair (i, i) of a square product counts with r^2 = 0 exactly: with 2^15 V'_i.  The loop takes it as it comes, with the rounding of its
   // distance, as hi V'_i + lo Vh_i (phi(S_ii) in two pieces, V' = Vh + Vl), and the accumulators start with what that is short of:
-  // (2^15 - hi - lo) V'_i + lo Vl_i, S_ii worked out here by the same instructions.  (Short of phi(S_ii) itself the split's own rounding and the
+  // (2^15 - hi - lo) Vh_i + (2^15 - hi) Vl_i, S_ii worked out here by the same instructions.  (Short of phi(S_ii) itself the split's own rounding and the
   // dropped product would stay in: K = a^2 I came out 1.1e-7 off instead of 4.4e-8, which is what V' has.)  A
   // special case inside the loop would put a branch between distances and phi, across which nothing is scheduled.
   const int own = tile0 / 2 + p.diag_shift;      // the chunk that holds the first row tile's own points
@@ -213,23 +213,21 @@ __device__ __forceinline__ void tile_pass(const TileArgsH& p, u32x4* lds) {
       const f32x4 S = distance(xa[it], it);
       const float s = li & 2 ? (li & 1 ? S[3] : S[2]) : li & 1 ? S[1] : S[0];
       const bool mine = here && q == li >> 2;      // lane 20 (li/4) + li%4 holds row li's
-      const float f = phi(s);
-      // an infinite V_i is infinite in the loop; what is missing of it would make a NaN of that
-      if (Y) accv[it] = mine && __builtin_isfinite(vy[it]) ? ((float)(1 << PHI_SHIFT) - f) * vy[it] : 0.0f;
+      const float f = mine ? phi(s) : (float)(1 << PHI_SHIFT);
+      // An infinite V_i is infinite in the loop; what is missing of it would make a NaN of that.  (With `mine` in this condition the load of
+      // V_i would move behind it, to be waited for on its own.)
+      if (Y) accv[it] = __builtin_isfinite(vy[it]) ? ((float)(1 << PHI_SHIFT) - f) * vy[it] : 0.0f;
       if constexpr (NT > 0) {
         unsigned hi, lo;
-        split_pair_positive(mine ? f : (float)(1 << PHI_SHIFT), 0.0f, hi, lo);
+        split_pair_positive(f, 0.0f, hi, lo);
         const int both = (int)(hi | lo << 16);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const unsigned of_row = (unsigned)__shfl(both, 20 * q + r);
-          const float h = (float)__builtin_bit_cast(_Float16, (unsigned short)of_row);
-          const float l = (float)__builtin_bit_cast(_Float16, (unsigned short)(of_row >> 16)), m = ((float)(1 << PHI_SHIFT) - h) - l;
+          const float less_hi = minus_half<0>(of_row, (float)(1 << PHI_SHIFT)), less_both = minus_half<1>(of_row, less_hi);
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const float v0 = (float)vh[it / 2][nt][4 * jt + r], v1 = (float)vl[it / 2][nt][4 * jt + r];
-            acc[it][nt][r] = fmaf(m, v0 + v1, l * v1);
-          }
+          for (int nt = 0; nt < NT; ++nt)
+            acc[it][nt][r] = fmaf((float)vh[it / 2][nt][4 * jt + r], less_both, (float)vl[it / 2][nt][4 * jt + r] * less_hi);
         }
       }
     }
