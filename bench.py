@@ -26,40 +26,47 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E
 # HBM bytes per launch of the tile kernel: NOT measured by this script.  They come from separate
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this script whose summary is the file named here, keyed
 # by (workload, n); the JSON line repeats the source next to the number.
-# They were taken of the tile kernel on 32x32x16 matrix products, which read and wrote the same operands and images.
-TRAFFIC = {("config2", 16384): 43.4e6, ("config5", 2000000): 742e9}
-TRAFFIC_SOURCE = "profiles/kmv_tile_f16_hbm_traffic_pmc.md (rocprofv3 --pmc runs of the 32x32x16 kernel, not this run)"
+TRAFFIC = {("config2", 16384): 43.1e6, ("config5", 2000000): 173e9}
+TRAFFIC_SOURCE = "profiles/kmv_tile_f16_hbm_traffic_pmc.md (rocprofv3 --pmc runs, not this run)"
 # Engine clock under the tile kernel (GRBM_GUI_ACTIVE over the kernel's duration), likewise from separate
 # counter runs: the published peaks assume 2.4 GHz, the chip holds less under this kernel's load.
-ENGINE_CLOCK_GHZ = {"config2": 1.98, "config5": 1.74}
-ENGINE_CLOCK_SOURCE = "profiles/kmv_tile_f16_engine_clock_under_load.md (rocprofv3 --pmc runs of the 32x32x16 kernel, not this run; peak assumes 2.4 GHz)"
+ENGINE_CLOCK_GHZ = {"config2": 2.23, "config5": 2.16}
+ENGINE_CLOCK_SOURCE = "profiles/kmv_tile_f16_engine_clock_under_load.md (rocprofv3 --pmc runs, not this run; peak assumes 2.4 GHz)"
 
 
 def kmv_flops(n, d, t, kind):
     return float(n) * float(n) * (2 * d + 2 * t + (4 if kind == "se" else 8))
 
 
+def distance_products(d, kind, pieces):
+    """32-wide matrix instructions of the distance per pair of 16x16 tiles, from the shapes in csrc/dist_f16.h."""
+    import re
+    with open(os.path.join(ROOT, "paper_2405_18328_amd", "csrc", "dist_f16.h")) as f:
+        table = re.search(r"DIST_X%d\[\] = \{(.*?)\};" % pieces, f.read(), re.S).group(1)
+    for Q, R, most, most_shift in (map(int, m) for m in re.findall(r"\{(\d+), (\d+), (\d+), (\d+)\}", table)):
+        if d <= (most_shift if kind == "se" else most):
+            return (3 if pieces == 2 else 6) * Q + R
+    raise ValueError(d)
+
+
 def executed_mfma_flops(n, d, t, kind, path, rows=None):
-    """Matrix-core flops per K V product with the extra products of the fp16 splitting and the padding of the contraction
-    lengths to steps of 16, as opposed to kmv_flops.  The fp16 tile kernel issues the products of V as counted here; the
-    distance's slots it packs into steps of 32 (d = 26: 192 flops a pair, as counted; d = 11 with SE 128, counted 96)."""
-    nt = (t // 32) if t % 32 == 1 and t > 1 else -(-t // 32)     # a lone 33rd column goes through the vector ALU
+    """Matrix-core flops per K V product as issued, as opposed to kmv_flops.  fp16 paths: per pair and pass of up to 64 columns the
+    distance's instructions of 32 slots each, and three products for every column of the tiles of 16; a lone column past whole tiles
+    goes through the vector ALU.  fp32 path: contraction lengths padded to the kernel's."""
     if path == 0:
+        nt = (t // 32) if t % 32 == 1 and t > 1 else -(-t // 32)     # a lone 33rd column goes through the vector ALU
         ks = next(b for b in (4, 7, 10, 14, 24, 46, 64) if 2 * b >= d + 2)
         per_pair = 2 * 2 * ks + 2 * 32 * nt
     else:
-        slots = d + 2 + (1 if kind == "se" else 0)
-        kh = next(b for b in (1, 2, 3, 4, 6, 8) if 16 * b >= slots)
-        per_pair = (3 if path == 1 else 6) * 2 * 16 * kh + 3 * 2 * 32 * nt
+        columns = t - (t % 16 == 1)
+        passes = max(1, -(-columns // 64))
+        per_pair = passes * 2 * 32 * distance_products(d, kind, 2 if path == 1 else 3) + 3 * 2 * 16 * -(-columns // 16)
     return float(n) * float(rows if rows else n) * per_pair
 
 
-def tile_kernel_name(d, t, path):
-    """The kernel of a product's passes of 64 columns, or of its only one: the fp32 kernel, or the fp16 one with four row tiles
-    per wave (more than 33 columns and a distance of few dimensions) or with two."""
-    if path == 0:
-        return "kmv_tile_kernel"
-    return "kmv_tile_f16_wide_kernel" if t > 33 and d <= (61 if path == 1 else 29) else "kmv_tile_f16_kernel"
+def tile_kernel_name(path):
+    """The kernels that serve a product.  On the fp16 paths the library chooses by price whether a wave has two or four row tiles."""
+    return "kmv_tile_kernel" if path == 0 else "kmv_tile_f16_kernel or kmv_tile_f16_wide_kernel"
 
 
 def cpu_baseline(w):
@@ -148,7 +155,7 @@ def config5_leg(cap=4, outer_steps=3, timed_products=3):
                                    "frac": achieved / peak, "traffic": TRAFFIC.get(("config5", n)),
                                    "traffic_source": TRAFFIC_SOURCE, "engine_clock_ghz": ENGINE_CLOCK_GHZ["config5"],
                                    "engine_clock_source": ENGINE_CLOCK_SOURCE,
-                                   "kernel": tile_kernel_name(d, t, path),
+                                   "kernel": tile_kernel_name(path),
                                    "product_path": PATH_NAMES[path], "peak_dtype": "fp32" if path == 0 else "fp16",
                                    "launches": int(launches), "avg_launch_ms": avg_s * 1e3, "flops_per_launch": F_launch,
                                    "executed_mfma_tflops": executed, "executed_mfma_frac_of_peak": executed / peak,
@@ -168,6 +175,9 @@ def config5_leg(cap=4, outer_steps=3, timed_products=3):
                 vec[name] = {"launches": k_launches, "avg_launch_ms": k_ms / k_launches, "array_passes": passes,
                              "bytes_per_launch": passes * nt_bytes, "achieved": gbs, "peak": HBM_PEAK_GBS,
                              "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "bound": "hbm"}
+        if "cg_dot" in vec:
+            vec["cg_dot"]["note"] = ("a lower bound: where the product's columns are cut into ranges, this launch also reads a partial image "
+                                     "for each and writes their sum, one array pass for each")
         out["cg_vector_kernels"] = vec
         g_launches, g_ms = gp.gp_profile_read_kind(opt.ctx, gp.GP_PROF_GRAD_TILE)
         if g_launches:
@@ -461,7 +471,7 @@ def main():
                          "traffic_source": TRAFFIC_SOURCE if args.solver == "cg" and not args.predict and (args.workload, n) in TRAFFIC else None,
                          "engine_clock_ghz": ENGINE_CLOCK_GHZ.get(args.workload) if (args.workload, n) in TRAFFIC else None,
                          "engine_clock_source": ENGINE_CLOCK_SOURCE if (args.workload, n) in TRAFFIC else None,
-                         "kernel": tile_kernel_name(d, t, path),
+                         "kernel": tile_kernel_name(path),
                          "product_path": PATH_NAMES[path], "peak_dtype": "fp32" if path == 0 else "fp16",
                          "launches": int(launches), "avg_launch_ms": avg_kern_s * 1e3,
                          "flops_per_launch": F_launch,

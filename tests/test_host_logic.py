@@ -68,8 +68,10 @@ def test_flop_accounting_of_the_benchmark():
     # reporting convention: 2d + 2t + c_phi per pair, c = 4 (SE) / 8 (Matern-3/2)
     assert b.kmv_flops(16384, 26, 65, "matern32") == 16384.0 ** 2 * 190
     assert b.kmv_flops(2_000_000, 11, 65, "se") == 4.0e12 * 156
-    # matrix-core flops really issued: 3 fp16 products per product, k padded to 16, columns to 32
+    # matrix-core flops really issued: on fp16 paths distances in instructions of 32 slots, 3 products per column of the tiles of 16
     assert b.executed_mfma_flops(16384, 26, 65, "matern32", 1) == 16384.0 ** 2 * (3 * 2 * 32 + 3 * 2 * 64)
     assert b.executed_mfma_flops(1000, 11, 65, "se", 2) == 1.0e6 * (6 * 2 * 16 + 3 * 2 * 64)
-    assert b.executed_mfma_flops(1000, 11, 65, "se", 1, rows=10) == 1.0e4 * (3 * 2 * 16 + 3 * 2 * 64)
+    assert b.executed_mfma_flops(1000, 11, 65, "se", 1, rows=10) == 1.0e4 * (2 * 2 * 32 + 3 * 2 * 64)
+    assert b.executed_mfma_flops(1000, 8, 17, "se", 1) == 1.0e6 * (1 * 2 * 32 + 3 * 2 * 16)
+    assert b.executed_mfma_flops(1000, 26, 113, "matern32", 1) == 1.0e6 * (2 * 3 * 2 * 32 + 3 * 2 * 112)
     assert b.executed_mfma_flops(2048, 8, 17, "se", 0) == 2048.0 ** 2 * (2 * 2 * 7 + 2 * 32)
