@@ -13,6 +13,9 @@
 // out like that ("diagonal": group k of A meets group k of B), smallest products first; else a group per piece again.  In units of
 // 32x32 pairs and 16 slots, on two pieces: d = 3, 8 and 9 take 2 (3 with whole pieces in instructions of 16 slots), d = 20 4 (6),
 // d = 26 6 (6), d = 64 16 (18), d = 90 18 (18), d = 96 24 (24); only 11 <= d <= 14 take 4 instead of 3.
+// They cost those dimensions more than the instruction saves where little else is issued (a product, instructions of 16 slots and 32x32x16 -> now,
+// d = 11, n = 131072: t = 1 SE 2.01 -> 2.17 ms, Matern 3.52 -> 3.63; d = 12, t = 17 and more columns gain).  v_mfma_f32_16x16x16_f16 for half a group takes
+// 0.86 of a whole one's time.
 // What is rounded where: v_mfma_f32_16x16x32_f16 adds eight slots at a time to its accumulator, slots 0-7 first; all nine terms are
 // cut off 24 bits below the largest of them, and the sum is an fp32 number before the next eight (probed with single products).
 // So the largest terms come last, and the shift, larger than all of them, stands in the last slot of the last group, where there

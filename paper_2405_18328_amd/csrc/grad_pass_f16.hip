@@ -9,7 +9,7 @@
 // half a matrix of pairs is all there is to it.
 // All three contractions of a 32x32 tile of pairs run on v_mfma_f32_32x32x16_f16 with operands split
 // into two fp16 pieces rounded to nearest (three products per fp32 product, fp32 accumulation):
-//   1. S[j][i]  = XA_j . XB_i        the distance chain of the K V pass (same packed operands)
+//   1. S[j][i]  = XA_j . XB_i        the distance chain, on operands of its own (the K V pass packs its slots otherwise: dist_f16.h)
 //   2. U'[j][i] = C'_j . A'_i        the probes' part of u; every column-side component is scaled to max in [2^6, 2^7),
 //                                    the row side carries the inverse scales and a global power of two alpha chosen so
 //                                    that |U' psi| < 2^15 (from the sum over the components of max|row| max|column| >= |u_ij|)
